@@ -13,7 +13,48 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
+typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
+
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
+
+// Direct-to-LDS loads that the compiler does not track.  It orders every LDS
+// read behind all direct-to-LDS loads that may have written the same object, so
+// a double-buffered tile in one array costs a wait for the NEXT tile's loads in
+// front of the current tile's first read.  These forms are for kernels that
+// place the waits themselves: s_waitcnt vmcnt before the barrier that publishes
+// the tile (the loads complete in order; the compiler's own waits can only be
+// stricter for not knowing them).
+// Buffer descriptor of `bytes` bytes at p (raw, bounds-checked: reads past the
+// end return zeros).
+__device__ __forceinline__ i32x4 buffer_desc(const void* p, uint32_t bytes)
+{
+    const uint64_t a = (uint64_t)p;
+    const i32x4 d = {(int32_t)(uint32_t)a, (int32_t)((uint32_t)(a >> 32) & 0xffffu),
+                     (int32_t)bytes, 0x00020000};
+    return d;
+}
+// Byte address of an LDS object inside the workgroup's allocation.
+__device__ __forceinline__ uint32_t lds_address(const void* p)
+{
+    return (uint32_t)(uintptr_t)LDS_PTR(void, p);
+}
+// (M0 holds the LDS address; the compiler warns that it may not preserve such a
+// register, which is the point of naming it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// Lane l: 16 bytes from rsrc[voff + soff] to LDS lds + 16 l (lds, soff uniform).
+__device__ __forceinline__ void load_lds_16(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+// Lane l: 4 bytes from rsrc[voff + soff] to LDS lds + 4 l.
+__device__ __forceinline__ void load_lds_4(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+#pragma clang diagnostic pop
 
 // Exchange with the lane 32 away (lanes l < 32 get the value of l + 32 and
 // vice versa).
