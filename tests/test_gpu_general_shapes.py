@@ -1,0 +1,67 @@
+"""GPU parity of the general-shape kernels at the sizes where their tiling can go
+wrong: block sizes around the 32-row wavefront tile and the 256-row workgroup,
+key sequences around the 32- and 64-key tiles (block boundaries inside a tile,
+a last tile of one key), lists around the 64 blocks that are sorted and the
+1,024 that the LDS table holds."""
+import numpy as np
+import pytest
+import torch
+
+from inputs.fields import round_to_bf16
+from tests.helpers import rand_qkv, random_selection, shape_ns
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_util
+    return gpu_util
+
+
+SHAPES = [
+    # H, W, bh, bw, D, n
+    (8, 12, 1, 1, 32, 7),        # b = 1: every key its own block
+    (9, 12, 3, 3, 64, 6),        # b = 9: 63 keys, a tile minus one
+    (10, 13, 5, 1, 128, 12),     # b = 5: 65 keys, a last tile of one key
+    (10, 9, 2, 3, 64, 15),       # n = m: everything, b = 6, grid no multiple of 8
+    (31, 8, 31, 1, 64, 2),       # b = 31: one wavefront with an idle row
+    (22, 33, 11, 3, 32, 3),      # b = 33: two wavefronts, one row in the second
+    (16, 30, 8, 15, 128, 3),     # b = 120
+    (14, 57, 7, 19, 64, 4),      # b = 133: five wavefronts
+    (32, 40, 16, 20, 32, 1),     # b = 320: two workgroups of five wavefronts per block
+    (34, 60, 17, 30, 64, 2),     # b = 510: two workgroups of eight, two idle rows
+    (20, 26, 2, 2, 64, 63),      # 64 attended blocks: the last list that is sorted
+    (20, 26, 2, 2, 64, 64),      # 65: kept in the given order
+    (46, 48, 1, 2, 32, 1030),    # more listed blocks than the LDS table holds
+]
+
+
+def inputs_of(cfg, seed):
+    q, k, v = rand_qkv(cfg, seed)
+    if cfg.dtype == "bf16":
+        q, k, v = (round_to_bf16(x) for x in (q, k, v))
+    return q, k, v
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("H,W,bh,bw,D,n", SHAPES)
+def test_general_forward(G, oracle, dtype, H, W, bh, bw, D, n):
+    """fp32: 1e-5 of the largest output, lse likewise.  bf16: the output is one
+    rounding (half an ulp: at most 2^-8 of the value) of a sum whose weights are
+    kept as two bf16 terms (truncated to 2^-7, the rest rounded to 2^-8 of itself:
+    2^-15 of the largest value; twice that covers the fp32 sums as well)."""
+    cfg = shape_ns(1, 2, H, W, bh, bw, D, min(n, (H // bh) * (W // bw) - 1), dtype)
+    q, k, v = inputs_of(cfg, 40 + H + W + D)
+    s = oracle.shape_of(cfg)
+    idx = random_selection(cfg, 7)
+    out_ref, lse_ref = oracle.fwd(s, q, k, v, idx)
+    out, lse = G.gpu_fwd(cfg, q, k, v, idx)
+    err = np.abs(out - out_ref)
+    if dtype == "fp32":
+        assert err.max() <= 1e-5 * np.abs(out_ref).max()
+    else:
+        assert (err <= 2.0 ** -8 * np.abs(out_ref) + 2.0 ** -14 * np.abs(v).max()).all()
+    assert np.abs(lse - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
