@@ -89,7 +89,7 @@ size_t select_workspace(const Checked& c)
     return 2 * pooled_bytes(c) + align_up(bsa::select_scratch_bytes(c.g.n_blocks, c.D, c.BH, c.BKV));
 }
 
-// delta | lse * log2(e) | connection map (the last two: matrix-core path only)
+// delta | lse * log2(e) | connection map
 size_t bwd_rows_bytes(const Checked& c)
 {
     return align_up((size_t)c.BH * (size_t)c.g.n_tokens * sizeof(float));
@@ -348,8 +348,8 @@ hipError_t backward(const Checked& c, const bsa::Geom& g, const void* q, const v
     return bsa::bwd_mfma_supported(c.is_bf16, g, c.D)
                ? bsa::launch_bwd_mfma(q, k, v, out, lse, dout, lists, dq, dk, dv, delta, lse2,
                                       conn, g, c.D, c.BH, stream)
-               : bsa::launch_bwd(c.is_bf16, q, k, v, out, lse, dout, lists, dq, dk, dv, delta, g,
-                                 c.D, c.BH, stream);
+               : bsa::launch_bwd(c.is_bf16, q, k, v, out, lse, dout, lists, dq, dk, dv, delta, lse2,
+                                 conn, g, c.D, c.BH, stream);
 }
 
 }  // namespace

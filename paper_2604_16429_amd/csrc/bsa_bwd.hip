@@ -10,321 +10,499 @@
 // top-n choice (Appendix, kernel design paragraph: the backward pass walks, for
 // every key/value block, the query blocks connected to it).
 //
-// Three kernels, general in tile shape, head dim (32/64/128) and element type,
-// fp32 vector arithmetic throughout:
-//   bwd_delta_kernel  delta per query row (workspace, fp32 [B, heads, N]);
-//   bwd_dq_kernel     one workgroup per 64 query rows; walks the n+1 attended
-//                     blocks like the forward pass;
-//   bwd_dkdv_kernel   one workgroup per 64 key rows of a key/value block j; it
-//                     first lists, in ascending order, the query blocks i that
-//                     attend to j (i == j, or j in sel_idx[i]) by scanning the
-//                     selection of its (batch, head), then walks that list.
-//                     The order of the list fixes the summation order: results
-//                     are reproducible run to run, and there are no
-//                     floating-point atomics.
-// In the two main kernels four adjacent lanes share a row, each holding a
-// quarter of the channels; the two dot products per (query, key) pair are
-// completed with two DPP steps inside the quad.
+// Here: the preparation that both backward paths share (delta, the base-2
+// log-sum-exps, the reverse map of the selection) and the general-shape kernels on
+// the matrix cores (fp32 and bf16, head dim 32, 64 or 128, any tile of up to 1024
+// tokens), with the tiles, products and precision of the general forward: the
+// rows of the other side are walked as one flat sequence (bsa_flat_rows.h).
+//   bwd_generic_dq    a wavefront owns 32 query rows, walks the attended keys:
+//                     S^T = K Q^T and dP^T = V dO^T (a lane holds one query: lse
+//                     and delta are scalars of the lane, -delta is the accumulator
+//                     that dP^T starts from), dQ^T += K^T dS^T.
+//   bwd_generic_dkdv  a wavefront owns 32 rows of a key block, walks the rows of
+//                     the query blocks connected to it: S = Q K^T, dP = dO V^T,
+//                     dV^T += dO^T P, dK^T += Q^T dS.  The blocks are listed in
+//                     ascending order per query head, heads of a group ascending:
+//                     the summation order is fixed, there are no floating-point
+//                     atomics and results are the same from run to run.
+// Measured against the vector-ALU kernels that they replace (a row per four lanes,
+// the other side's rows broadcast from LDS): 1.5 degree grid, batch 2, 8 heads,
+// head dim 64, bf16, tiles of 10 x 10, 9 blocks: dQ 2.76 -> 0.33 ms, dK and dV
+// 4.38 -> 0.57 ms; fp32, batch 1, tiles of 8 x 8: dQ 0.81 -> 0.51 ms, dK and dV 1.55
+// -> 1.37 ms.  delta: 233 -> 21 us and 113 -> 20 us (one thread walked a row).
 #include "bsa_device.h"
+#include "bsa_flat_rows.h"
 #include "bsa_launch.h"
+#include "bsa_mfma_common.h"
 
 namespace bsa {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// delta_l = dO_l . O_l and lse_l * log2(e).  A row is read by LPR adjacent lanes,
+// 16 bytes each, so a wavefront's loads cover whole lines; the partial dot products
+// are summed inside the lane group with DPP steps (32 lanes, fp32 rows of 128
+// channels: one more exchange).
 template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v)
+__device__ __forceinline__ float dpp_add(float v)
 {
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+    return v + __int_as_float(
+                   __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 
-// Sum over the four lanes of a quad (all lanes receive the sum).
-__device__ __forceinline__ float quad_sum(float x)
+__device__ __forceinline__ float dot16(const uint16_t* a_row, const uint16_t* b_row)
 {
-    x += dpp_f<0xB1>(x);    // quad_perm [1,0,3,2]
-    x += dpp_f<0x4E>(x);    // quad_perm [2,3,0,1]
-    return x;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_delta_kernel(const T* __restrict__ out,
-                                                        const T* __restrict__ dout,
-                                                        float* __restrict__ delta,
-                                                        int64_t rows, int D)
-{
-    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (row >= rows) return;
-    const T* o = out + row * D;
-    const T* g = dout + row * D;
+    const uint4 a = *(const uint4*)a_row, b = *(const uint4*)b_row;
+    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
     float acc = 0.0f;
-    for (int d = 0; d < D; d += 4) {
-        const float4 a = load4(o + d), b = load4(g + d);
-        acc = fmaf(a.x, b.x, acc);
-        acc = fmaf(a.y, b.y, acc);
-        acc = fmaf(a.z, b.z, acc);
-        acc = fmaf(a.w, b.w, acc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        acc = fmaf(__uint_as_float(aw[e] << 16), __uint_as_float(bw[e] << 16), acc);
+        acc = fmaf(__uint_as_float(aw[e] & 0xffff0000u), __uint_as_float(bw[e] & 0xffff0000u),
+                   acc);
     }
-    delta[row] = acc;
+    return acc;
 }
-
-// Stage `cnt` token rows (tile positions tau0 .. tau0+cnt-1 of block beta) of
-// two tensors into LDS as fp32 [cnt][D].
-template <typename T, int D>
-__device__ __forceinline__ void stage_rows(const Geom& g, const T* __restrict__ a,
-                                           const T* __restrict__ b, int64_t base, int beta,
-                                           int tau0, int cnt, float* a_s, float* b_s)
+__device__ __forceinline__ float dot16(const float* a_row, const float* b_row)
 {
-    for (int item = threadIdx.x; item < cnt * (D / 4); item += blockDim.x) {
-        const int t = item / (D / 4), d = (item - t * (D / 4)) * 4;
-        const int64_t tok = token_of(g, beta, tau0 + t);
-        *(float4*)(a_s + t * D + d) = load4(a + base + tok * D + d);
-        *(float4*)(b_s + t * D + d) = load4(b + base + tok * D + d);
-    }
+    const float4 a = *(const float4*)a_row, b = *(const float4*)b_row;
+    return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)));
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_dq_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-    const T* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
-    const int32_t* __restrict__ sel_idx, T* __restrict__ dq, Geom g, int row_chunks)
+__global__ __launch_bounds__(256) void bwd_prep_kernel(const T* __restrict__ out,
+                                                       const T* __restrict__ dout,
+                                                       const float* __restrict__ lse,
+                                                       float* __restrict__ delta,
+                                                       float* __restrict__ lse2, int64_t rows)
 {
-    constexpr int CPT = D / 4;                     // channels per lane
-    constexpr int KC = 32;                         // keys staged per chunk
-    __shared__ __attribute__((aligned(16))) float k_s[KC * D];
-    __shared__ __attribute__((aligned(16))) float v_s[KC * D];
+    constexpr int VEC = 16 / (int)sizeof(T), LPR = D / VEC;      // 4, 8, 16 or 32 lanes per row
+    const int sub = threadIdx.x % LPR;
+    int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LPR;
+    const bool valid = row < rows;
+    if (!valid) row = rows - 1;                     // keep the lane group whole for the sums
+    float acc = dot16(out + row * D + VEC * sub, dout + row * D + VEC * sub);
+    acc = dpp_add<0xB1>(acc);                       // quad_perm [1,0,3,2]
+    acc = dpp_add<0x4E>(acc);                       // quad_perm [2,3,0,1]
+    if (LPR >= 8) acc = dpp_add<0x141>(acc);        // row_half_mirror: 8 lanes
+    if (LPR >= 16) acc = dpp_add<0x140>(acc);       // row_mirror: 16 lanes
+    if (LPR == 32) acc += __shfl_xor(acc, 16);
+    if (valid && sub == 0) {
+        delta[row] = acc;
+        lse2[row] = lse[row] * kLog2e;
+    }
+}
 
-    // blockIdx.x = (batch*head * m + block) * row_chunks + chunk
-    const int rc = blockIdx.x % row_chunks;
-    const int64_t blk = blockIdx.x / row_chunks;
-    const int i = (int)(blk % g.n_blocks);
-    const int64_t bh_idx = blk / g.n_blocks;
+template <typename T, int D>
+static hipError_t launch_prep_t(const void* out, const void* dout, const float* lse, float* delta,
+                                float* lse2, int64_t rows, hipStream_t stream)
+{
+    const int64_t threads = rows * (D * (int)sizeof(T) / 16);
+    bwd_prep_kernel<T, D><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream>>>(
+        (const T*)out, (const T*)dout, lse, delta, lse2, rows);
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
+                           float* delta, float* lse2, int64_t rows, int D, hipStream_t stream)
+{
+#define BSA_CASE(DD)                                                                              \
+    case DD:                                                                                      \
+        return is_bf16 ? launch_prep_t<uint16_t, DD>(out, dout, lse, delta, lse2, rows, stream)   \
+                       : launch_prep_t<float, DD>(out, dout, lse, delta, lse2, rows, stream);
+    switch (D) {
+        BSA_CASE(32)
+        BSA_CASE(64)
+        BSA_CASE(128)
+    }
+#undef BSA_CASE
+    return hipErrorInvalidValue;
+}
+
+// The reverse map of the selection ("the query blocks connected to a key/value
+// block", Appendix, kernel design paragraph) as a bit matrix: bit i of row
+// [query slice][key block j] says that query block i attends to block j.  One
+// thread per (query slice, query block) sets the bits of its row of sel_idx
+// (and its own block's, unless only the lists count) with integer atomic ORs:
+// the final state does not depend on their order.  A dK/dV workgroup then reads
+// its m bits instead of scanning all m * n entries of the slice, and walking
+// the set bits upwards is the fixed summation order.
+__global__ __launch_bounds__(256) void bwd_connect_clear_kernel(uint32_t* __restrict__ conn,
+                                                                int64_t n_words)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n_words) conn[t] = 0u;
+}
+
+__global__ __launch_bounds__(256) void bwd_connect_kernel(const int32_t* __restrict__ sel_idx,
+                                                          uint32_t* __restrict__ conn, Geom g,
+                                                          int64_t rows)
+{
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;    // slice * m + i
+    if (row >= rows) return;
+    const int m = g.n_blocks, n = g.n_select, words = (m + 31) >> 5;
+    const int64_t bh_idx = row / m;
+    const int i = (int)(row - bh_idx * m);
+    uint32_t* base = conn + bh_idx * (int64_t)m * words + (i >> 5);
+    const uint32_t bit = 1u << (i & 31);
+    if (!g.list_only) atomicOr(base + (int64_t)i * words, bit);
+    const int32_t* r = sel_idx + row * n;
+    for (int a = 0; a < n; ++a) {
+        const int j = r[a];
+        if ((unsigned)j < (unsigned)m) atomicOr(base + (int64_t)j * words, bit);
+    }
+}
+
+hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, const Geom& g, int64_t BH,
+                              hipStream_t stream)
+{
+    const int64_t rows = BH * g.n_blocks, n_words = bwd_connection_words(g.n_blocks, BH);
+    bwd_connect_clear_kernel<<<dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, stream>>>(
+        conn, n_words);
+    bwd_connect_kernel<<<dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream>>>(sel_idx, conn,
+                                                                                      g, rows);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// dQ
+// ---------------------------------------------------------------------------
+// Launch bounds: workgroups of up to 4 wavefronts at head dim 128 (the stationary
+// rows and accumulators need more registers than two wavefronts per SIMD have), up
+// to 8 below.
+template <int D> struct BwdLimits {
+    static constexpr int MAX_WAVES = D == 128 ? 4 : 8;
+    static constexpr int PER_SIMD = D == 128 ? 1 : 2;
+};
+
+template <typename T, int D, int NL>
+__global__ __launch_bounds__(NL == 4 ? 64 * BwdLimits<D>::MAX_WAVES : NL == 2 ? 192 : 64,
+                             NL == 1 ? 1 : BwdLimits<D>::PER_SIMD)
+void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                    const T* __restrict__ dout, const float* __restrict__ lse2,
+                    const float* __restrict__ delta, const int32_t* __restrict__ sel_idx,
+                    T* __restrict__ dq, Geom g, uint32_t n_units, int row_chunks, int chunk_rows)
+{
+    using Tile = FlatTile<T, D>;
+    constexpr int KT = Tile::KT;
+    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][Tile::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_lds[2][Tile::TILE_BYTES];
+    extern __shared__ __attribute__((aligned(16))) uint32_t tables_s[];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
     const int b = g.block_tokens;
-    const int quarter = threadIdx.x & 3;
-    const int tau_q = rc * 64 + (threadIdx.x >> 2);
-    const bool valid = tau_q < b;
+
+    int item;
+    int64_t bh_idx;
+    map_workgroup(g, blockIdx.x, (uint32_t)(g.n_blocks * row_chunks), n_units, bh_idx, item);
+    const int i = item / row_chunks;
+    const int row0 = (item - i * row_chunks) * chunk_rows;
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
-    const int64_t tok_q = token_of(g, i, valid ? tau_q : 0);
-    // The attended blocks: block i itself followed by its selected blocks, or,
-    // in list-only mode, exactly the listed blocks.
-    const int list_only = g.list_only;
-    const int32_t* sel_row = sel_idx + (bh_idx * g.n_blocks + i) * g.n_select + list_only;
-    const int first = list_only ? sel_row[-1] : i;
-    const int n = g.n_select - list_only;        // blocks after the first
-    const float c2 = g.scale * kLog2e;
 
-    float qr[CPT], gr[CPT], acc[CPT];
+    AttendedKeys<T, D, NL> keys;
+    keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave);
+
+    const int tau_q = row0 + 32 * wave + l32;
+    const bool valid = tau_q < min(b, row0 + chunk_rows);
+    const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
+    typename RowFrag<T, D>::type qf[RowFrag<T, D>::N], dof[RowFrag<T, D>::N];
 #pragma unroll
-    for (int d = 0; d < CPT; d += 4) {
-        const float4 a = load4(q + base + tok_q * D + quarter * CPT + d);
-        const float4 c = load4(dout + base + tok_q * D + quarter * CPT + d);
-        qr[d] = a.x; qr[d + 1] = a.y; qr[d + 2] = a.z; qr[d + 3] = a.w;
-        gr[d] = c.x; gr[d + 1] = c.y; gr[d + 2] = c.z; gr[d + 3] = c.w;
-        acc[d] = acc[d + 1] = acc[d + 2] = acc[d + 3] = 0.0f;
+    for (int s = 0; s < RowFrag<T, D>::N; ++s) {
+        load_row(q + base + q_tok * D, qf[s], s, half);
+        load_row(dout + base + q_tok * D, dof[s], s, half);
     }
-    const float lse2 = lse[bh_idx * g.n_tokens + tok_q] * kLog2e;
-    const float dl = delta[bh_idx * g.n_tokens + tok_q];
+    const float neg_l2 = -lse2[bh_idx * g.n_tokens + q_tok];
+    const float neg_delta = -delta[bh_idx * g.n_tokens + q_tok];
+    const float c2 = g.scale * kLog2e;
+    f32x16 acc[D / 32], dp0;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) acc[dt] = zero_tile();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dp0[r] = neg_delta;
 
-    for (int c = 0; c <= n; ++c) {
-        const int beta = (c == 0) ? first : sel_row[c - 1];
-        for (int k0 = 0; k0 < b; k0 += KC) {
-            const int kcnt = min(KC, b - k0);
-            __syncthreads();
-            stage_rows<T, D>(g, k, v, kv_base, beta, k0, kcnt, k_s, v_s);
-            __syncthreads();
-            for (int t = 0; t < kcnt; ++t) {
-                const float* kr = k_s + t * D + quarter * CPT;
-                const float* vr = v_s + t * D + quarter * CPT;
-                float s = 0.0f, dp = 0.0f;
+    __syncthreads();                                 // tables
+    const unsigned char* kb = (const unsigned char*)(k + kv_base);
+    const unsigned char* vb = (const unsigned char*)(v + kv_base);
+    const uint32_t k_dst = lds_address(k_lds), v_dst = lds_address(v_lds);
+    if (wave < NL) keys.gather_next(kb, vb, k_dst, v_dst);
+    for (int c = 0; c < keys.tiles; ++c) {
+        // tile c has landed and everyone is done with the other buffer
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const int buf = c & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
+        if (wave < NL && c + 1 < keys.tiles) keys.gather_next(kb, vb, k_dst + other, v_dst + other);
 #pragma unroll
-                for (int d = 0; d < CPT; ++d) {
-                    s = fmaf(qr[d], kr[d], s);
-                    dp = fmaf(gr[d], vr[d], dp);
-                }
-                s = quad_sum(s);
-                dp = quad_sum(dp);
-                const float p = __builtin_amdgcn_exp2f(fmaf(s, c2, -lse2));
-                const float ds = p * (dp - dl);
+        for (int hh = 0; hh < KT / 32; ++hh) {
+            const unsigned char* kt = k_lds[buf] + 32 * hh * Tile::ROW_BYTES;
+            const unsigned char* vt = v_lds[buf] + 32 * hh * Tile::ROW_BYTES;
+            const int left = keys.total - (KT * c + 32 * hh);
+            if (left <= 0) break;
+            f32x16 s = dot_tile<D>(kt, qf, zero_tile(), l32, half);
+            f32x16 dp = dot_tile<D>(vt, dof, dp0, l32, half);
+            if (left < 32)
 #pragma unroll
-                for (int d = 0; d < CPT; ++d) acc[d] = fmaf(ds, kr[d], acc[d]);
-            }
+                for (int r = 0; r < 16; ++r)
+                    if (past_end(r, half, left)) s[r] = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dp[r] *= __builtin_amdgcn_exp2f(fmaf(s[r], c2, neg_l2));
+            weighted_rows<D>((const T*)nullptr, kt, dp, acc, lane);
         }
     }
 
     if (valid) {
         const float inv_b = 1.0f / (float)b;
-        const float* extra =
-            g.add_dq ? g.add_dq + (bh_idx * g.n_blocks + i) * D + quarter * CPT : nullptr;
-#pragma unroll
-        for (int d = 0; d < CPT; d += 4)
-            store4_or_add(dq + base + tok_q * D + quarter * CPT + d,
-                          make_float4(acc[d] * g.scale, acc[d + 1] * g.scale, acc[d + 2] * g.scale,
-                                      acc[d + 3] * g.scale),
-                          extra ? extra + d : nullptr, inv_b);
+        const float* extra = g.add_dq ? g.add_dq + (bh_idx * g.n_blocks + i) * D : nullptr;
+        store_column<T, D>(dq + base + q_tok * D, acc, g.scale, extra, inv_b, half);
     }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_dkdv_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-    const T* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
-    const int32_t* __restrict__ sel_idx, T* __restrict__ dk, T* __restrict__ dv, Geom g,
-    int row_chunks)
+// ---------------------------------------------------------------------------
+// dK, dV
+// ---------------------------------------------------------------------------
+// The list of connected query blocks holds up to kConnCap of them; it is filled
+// 1024 blocks (32 words of the reverse map) at a time while it has room for all of
+// them, and walked whenever it is full or the map is exhausted.
+constexpr int kConnCap = 2048;
+
+template <typename T, int D, int NL>
+__global__ __launch_bounds__(NL == 4 ? 64 * BwdLimits<D>::MAX_WAVES : NL == 2 ? 192 : 64,
+                             NL == 1 ? 1 : BwdLimits<D>::PER_SIMD)
+void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                      const T* __restrict__ dout, const float* __restrict__ lse2,
+                      const float* __restrict__ delta, const uint32_t* __restrict__ conn,
+                      T* __restrict__ dk, T* __restrict__ dv, Geom g, uint32_t n_units,
+                      int row_chunks, int chunk_rows)
 {
-    constexpr int CPT = D / 4;
-    constexpr int QC = 32;                         // query rows staged per chunk
-    constexpr int SCAN = 256;                      // query blocks examined per scan round
-    __shared__ __attribute__((aligned(16))) float q_s[QC * D];
-    __shared__ __attribute__((aligned(16))) float g_s[QC * D];
-    __shared__ float lse_s[QC], delta_s[QC];
-    __shared__ int list_s[SCAN];
-    __shared__ int wave_cnt[4];
+    using Tile = FlatTile<T, D>;
+    constexpr int KT = Tile::KT, MINE = Tile::SLABS / NL;
+    __shared__ __attribute__((aligned(1024))) unsigned char q_lds[2][Tile::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char g_lds[2][Tile::TILE_BYTES];
+    __shared__ __attribute__((aligned(256))) float l_lds[2][64];
+    __shared__ __attribute__((aligned(256))) float d_lds[2][64];
+    __shared__ uint32_t list_s[kConnCap];             // first token (in the group's rows) per block
+    __shared__ int state_s[2];                        // blocks listed, words left
+    extern __shared__ __attribute__((aligned(16))) uint32_t pos_s[];        // [b]
 
-    const int rc = blockIdx.x % row_chunks;
-    const int64_t blk = blockIdx.x / row_chunks;
-    const int j = (int)(blk % g.n_blocks);
-    const int64_t kv_idx = blk / g.n_blocks;          // key/value slice
-    const int b = g.block_tokens, n = g.n_select, m = g.n_blocks;
-    const int quarter = threadIdx.x & 3;
-    const int tau_k = rc * 64 + (threadIdx.x >> 2);
-    const bool valid = tau_k < b;
-    const int64_t base = kv_idx * g.n_tokens * D;
-    const int64_t tok_k = token_of(g, j, valid ? tau_k : 0);
-    // the query slices that share this key/value slice are consecutive
-    const int64_t kv_heads = g.heads / g.kv_group;
-    const int64_t bh_first = (kv_idx / kv_heads) * g.heads + (kv_idx % kv_heads) * g.kv_group;
-    const float c2 = g.scale * kLog2e;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int m = g.n_blocks, b = g.block_tokens;
+    const int words = (m + 31) >> 5;                  // of a key block's row of the reverse map
 
-    float kr[CPT], vr[CPT], acck[CPT], accv[CPT];
-#pragma unroll
-    for (int d = 0; d < CPT; d += 4) {
-        const float4 a = load4(k + base + tok_k * D + quarter * CPT + d);
-        const float4 c = load4(v + base + tok_k * D + quarter * CPT + d);
-        kr[d] = a.x; kr[d + 1] = a.y; kr[d + 2] = a.z; kr[d + 3] = a.w;
-        vr[d] = c.x; vr[d + 1] = c.y; vr[d + 2] = c.z; vr[d + 3] = c.w;
-        acck[d] = acck[d + 1] = acck[d + 2] = acck[d + 3] = 0.0f;
-        accv[d] = accv[d + 1] = accv[d + 2] = accv[d + 3] = 0.0f;
+    // workgroup -> (key/value slice, key block, row chunk), slices dealt to the 8
+    // XCDs whole; the query slices that share the key/value slice are consecutive
+    uint32_t unit, item;
+    map_unit(blockIdx.x, (uint32_t)(m * row_chunks), n_units, unit, item);
+    const int j = (int)item / row_chunks;
+    const int row0 = ((int)item - j * row_chunks) * chunk_rows;
+    const int64_t base = (int64_t)unit * g.n_tokens * D;
+    int64_t bh_first;
+    {
+        const uint32_t kv_heads = (uint32_t)(g.heads / g.kv_group);
+        const uint32_t e = unit / kv_heads, a = unit - e * kv_heads;
+        bh_first = (int64_t)e * g.heads + (int64_t)a * g.kv_group;
     }
+    const unsigned char* qb = (const unsigned char*)(q + bh_first * g.n_tokens * D);
+    const unsigned char* gb = (const unsigned char*)(dout + bh_first * g.n_tokens * D);
+    const float* lb = lse2 + bh_first * g.n_tokens;
+    const float* db = delta + bh_first * g.n_tokens;
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // query heads in ascending order, then query blocks in ascending order:
-    // the summation order is fixed
-    for (int gq = 0; gq < g.kv_group; ++gq) {
-    const int64_t bh_idx = bh_first + gq;
-    const int64_t q_base = bh_idx * g.n_tokens * D;
-    const int32_t* sel_bh = sel_idx + bh_idx * (int64_t)m * n;
-    for (int i0 = 0; i0 < m; i0 += SCAN) {
-        // ---- which of the query blocks i0 .. i0+SCAN-1 attend to block j?
-        // ascending order, so the summation order below is fixed
-        const int i_mine = i0 + threadIdx.x;
-        bool hit = false;
-        if (i_mine < m) {
-            hit = i_mine == j && !g.list_only;    // list-only mode: the lists say it all
-            const int32_t* row = sel_bh + (int64_t)i_mine * n;
-            for (int r = 0; r < n; ++r) hit |= row[r] == j;
-        }
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
-        __syncthreads();                      // previous round's list fully consumed
-        if (lane == 0) wave_cnt[wave] = __builtin_popcountll(mask);
-        __syncthreads();
-        int offset = 0;
-        for (int w = 0; w < wave; ++w) offset += wave_cnt[w];
-        const int total = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-        if (hit) list_s[offset + __builtin_popcountll(mask & ((1ull << lane) - 1))] = i_mine;
-        __syncthreads();
+    fill_position_table(g, pos_s);
 
-        // ---- walk the connected query blocks
-        for (int e = 0; e < total; ++e) {
-            const int i = list_s[e];
-            for (int r0 = 0; r0 < b; r0 += QC) {
-                const int qcnt = min(QC, b - r0);
-                __syncthreads();
-                stage_rows<T, D>(g, q, dout, q_base, i, r0, qcnt, q_s, g_s);
-                if ((int)threadIdx.x < qcnt) {
-                    const int64_t tok = token_of(g, i, r0 + threadIdx.x);
-                    lse_s[threadIdx.x] = lse[bh_idx * g.n_tokens + tok] * kLog2e;
-                    delta_s[threadIdx.x] = delta[bh_idx * g.n_tokens + tok];
-                }
-                __syncthreads();
-                for (int l = 0; l < qcnt; ++l) {
-                    const float* qr = q_s + l * D + quarter * CPT;
-                    const float* gr = g_s + l * D + quarter * CPT;
-                    float s = 0.0f, dp = 0.0f;
+    // this wavefront's 32 key rows.  V enters negated: the accumulator that starts
+    // from delta then ends as delta - dP without an instruction per element, and
+    // dK is stored with the sign turned.
+    const int tau_k = row0 + 32 * wave + l32;
+    const bool valid = tau_k < min(b, row0 + chunk_rows);
+    const int64_t k_tok = token_of(g, j, valid ? tau_k : 0);
+    typename RowFrag<T, D>::type kf[RowFrag<T, D>::N], vf[RowFrag<T, D>::N];
 #pragma unroll
-                    for (int d = 0; d < CPT; ++d) {
-                        s = fmaf(kr[d], qr[d], s);
-                        dp = fmaf(vr[d], gr[d], dp);
-                    }
-                    s = quad_sum(s);
-                    dp = quad_sum(dp);
-                    const float p = __builtin_amdgcn_exp2f(fmaf(s, c2, -lse_s[l]));
-                    const float ds = p * (dp - delta_s[l]);
+    for (int s = 0; s < RowFrag<T, D>::N; ++s) {
+        load_row(k + base + k_tok * D, kf[s], s, half);
+        load_row(v + base + k_tok * D, vf[s], s, half);
+        vf[s] = negated(vf[s]);
+    }
+    const float c2 = g.scale * kLog2e;
+    f32x16 acck[D / 32], accv[D / 32];
 #pragma unroll
-                    for (int d = 0; d < CPT; ++d) {
-                        accv[d] = fmaf(p, gr[d], accv[d]);
-                        acck[d] = fmaf(ds, qr[d], acck[d]);
-                    }
+    for (int dt = 0; dt < D / 32; ++dt) acck[dt] = accv[dt] = zero_tile();
+
+    const uint32_t q_dst = lds_address(q_lds), g_dst = lds_address(g_lds);
+    const uint32_t l_dst = lds_address(l_lds), d_dst = lds_address(d_lds);
+    const int step_q = KT / b, step_r = KT - step_q * b;
+
+    // the map's words of the group's heads, head-major: one flat sequence
+    const int all_words = g.kv_group * words;
+    int next_word = 0;                                // wavefront 0 only
+    for (;;) {
+        __syncthreads();                              // the previous list is used up
+        if (wave == 0) {
+            int count = 0;
+            while (next_word < all_words && count <= kConnCap - 1024) {
+                const int w = next_word + lane;
+                uint32_t bits = 0;
+                int gq = 0, wi = 0;
+                if (lane < 32 && w < all_words) {
+                    gq = w / words;
+                    wi = w - gq * words;
+                    bits = conn[((bh_first + gq) * m + j) * words + wi];
                 }
+                const int mine = __builtin_popcount(bits);
+                int upto = mine;                      // inclusive prefix sum over the lanes
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int t = __shfl_up(upto, off);
+                    upto += lane >= off ? t : 0;
+                }
+                int at = count + upto - mine;
+                while (bits) {
+                    const int i = 32 * wi + __builtin_ctz(bits);
+                    bits &= bits - 1;
+                    list_s[at++] = (uint32_t)gq * (uint32_t)g.n_tokens + block_first_token(g, i);
+                }
+                count += __builtin_amdgcn_readlane(upto, 63);
+                next_word += 32;
+            }
+            if (lane == 0) {
+                state_s[0] = count;
+                state_s[1] = next_word < all_words ? 1 : 0;
             }
         }
-    }
+        __syncthreads();
+        const int listed = __builtin_amdgcn_readfirstlane(state_s[0]);
+        const bool more = __builtin_amdgcn_readfirstlane(state_s[1]) != 0;
+        const int total = listed * b;
+        const int tiles = (total + KT - 1) / KT;
+
+        // this lane's rows of a tile (slab wave + NL jj), and for the loads of lse and
+        // delta row `lane`
+        FlatRow at[MINE], at_row;
+        uint32_t chunk_off[MINE];
+#pragma unroll
+        for (int jj = 0; jj < MINE; ++jj) {
+            const int row = Tile::RPS * (wave + NL * jj) + lane / Tile::LPR;
+            at[jj].start(row, b);
+            chunk_off[jj] = (uint32_t)Tile::swz(row, lane % Tile::LPR) * 16u;
+        }
+        at_row.start(lane, b);
+        auto row_of = [&](const FlatRow& r) -> uint32_t {   // past the end: the last row
+            const bool past = r.blk >= listed;
+            return list_s[past ? listed - 1 : r.blk] + pos_s[past ? b - 1 : r.tau];
+        };
+        auto gather_next = [&](int buf) {
+#pragma unroll
+            for (int jj = 0; jj < MINE; ++jj) {
+                const uint64_t off = (uint64_t)row_of(at[jj]) * Tile::ROW_BYTES + chunk_off[jj];
+                const uint32_t dst = (uint32_t)buf * Tile::TILE_BYTES +
+                                     (uint32_t)(wave + NL * jj) * 1024u;
+                load_lds_16_at(qb + off, q_dst + dst);
+                load_lds_16_at(gb + off, g_dst + dst);
+                at[jj].advance(step_q, step_r, b);
+            }
+            if (wave == 0) {
+                const uint32_t row = row_of(at_row);
+                load_lds_4_at(lb + row, l_dst + (uint32_t)buf * 256u);
+                load_lds_4_at(db + row, d_dst + (uint32_t)buf * 256u);
+                at_row.advance(step_q, step_r, b);
+            }
+        };
+        if (wave < NL && tiles > 0) gather_next(0);
+        for (int c = 0; c < tiles; ++c) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            const int buf = c & 1;
+            if (wave < NL && c + 1 < tiles) gather_next(buf ^ 1);
+#pragma unroll
+            for (int hh = 0; hh < KT / 32; ++hh) {
+                const unsigned char* qt = q_lds[buf] + 32 * hh * Tile::ROW_BYTES;
+                const unsigned char* gt = g_lds[buf] + 32 * hh * Tile::ROW_BYTES;
+                const int left = total - (KT * c + 32 * hh);
+                if (left <= 0) break;
+                f32x16 p = dot_tile<D>(qt, kf, zero_tile(), l32, half);
+                f32x16 dp;
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const float4 d4 = *(const float4*)(d_lds[buf] + 32 * hh + 8 * r4 + 4 * half);
+                    dp[4 * r4] = d4.x; dp[4 * r4 + 1] = d4.y;
+                    dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
+                }
+                dp = dot_tile<D>(gt, vf, dp, l32, half);
+                if (left < 32)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (past_end(r, half, left)) p[r] = -INFINITY;
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const float4 l4 = *(const float4*)(l_lds[buf] + 32 * hh + 8 * r4 + 4 * half);
+                    p[4 * r4] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4], c2, -l4.x));
+                    p[4 * r4 + 1] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 1], c2, -l4.y));
+                    p[4 * r4 + 2] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 2], c2, -l4.z));
+                    p[4 * r4 + 3] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 3], c2, -l4.w));
+                }
+                weighted_rows<D>((const T*)nullptr, gt, p, accv, lane);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) dp[r] *= p[r];
+                weighted_rows<D>((const T*)nullptr, qt, dp, acck, lane);
+            }
+        }
+        if (!more) break;
     }
 
     if (valid) {
         const float inv_b = 1.0f / (float)b;
-        const int64_t pooled_row = (kv_idx * g.n_blocks + j) * D + quarter * CPT;
-        const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
-        const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
-#pragma unroll
-        for (int d = 0; d < CPT; d += 4) {
-            store4_or_add(dk + base + tok_k * D + quarter * CPT + d,
-                          make_float4(acck[d] * g.scale, acck[d + 1] * g.scale,
-                                      acck[d + 2] * g.scale, acck[d + 3] * g.scale),
-                          extra_k ? extra_k + d : nullptr, inv_b);
-            store4_or_add(dv + base + tok_k * D + quarter * CPT + d,
-                          make_float4(accv[d], accv[d + 1], accv[d + 2], accv[d + 3]),
-                          extra_v ? extra_v + d : nullptr, inv_b);
-        }
+        const int64_t pooled_row = ((int64_t)unit * m + j) * D;
+        store_column<T, D>(dk + base + k_tok * D, acck, -g.scale,
+                           g.add_dk ? g.add_dk + pooled_row : nullptr, inv_b, half);
+        store_column<T, D>(dv + base + k_tok * D, accv, 1.0f,
+                           g.add_dv ? g.add_dv + pooled_row : nullptr, inv_b, half);
     }
 }
 
 template <typename T, int D>
-static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void* out,
-                               const float* lse, const void* dout, const int32_t* sel_idx,
-                               void* dq, void* dk, void* dv, float* delta, const Geom& g,
-                               int64_t BH, hipStream_t stream)
+static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void* dout,
+                               const int32_t* sel_idx, void* dq, void* dk, void* dv,
+                               const float* delta, const float* lse2, const uint32_t* conn,
+                               const Geom& g, int64_t BH, hipStream_t stream)
 {
-    const int64_t rows = BH * g.n_tokens;
-    hipLaunchKernelGGL((bwd_delta_kernel<T>), dim3((unsigned)((rows + 255) / 256)), dim3(256), 0,
-                       stream, (const T*)out, (const T*)dout, delta, rows, D);
-    hipError_t e = hipGetLastError();
+    const RowSplit rows(g.block_tokens, BwdLimits<D>::MAX_WAVES);
+    const int nw = rows.waves;
+    const int64_t BKV = BH / g.kv_group;
+    if (BH * g.n_blocks * rows.chunks >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    const dim3 block(64 * nw), grid((unsigned)(BH * g.n_blocks * rows.chunks)),
+        grid_kv((unsigned)(BKV * g.n_blocks * rows.chunks));
+    auto dq_kernel = nw >= 4 ? bwd_generic_dq<T, D, 4>
+                     : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
+    dq_kernel<<<grid, block, flat_table_bytes(g), stream>>>(
+        (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, sel_idx, (T*)dq, g,
+        (uint32_t)BKV, rows.chunks, 32 * nw);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int row_chunks = (g.block_tokens + 63) / 64;
-    dim3 grid((unsigned)(BH * g.n_blocks * row_chunks));
-    hipLaunchKernelGGL((bwd_dq_kernel<T, D>), grid, dim3(256), 0, stream, (const T*)q,
-                       (const T*)k, (const T*)v, (const T*)dout, lse, delta, sel_idx, (T*)dq, g,
-                       row_chunks);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    dim3 grid_kv((unsigned)(BH / g.kv_group * g.n_blocks * row_chunks));
-    hipLaunchKernelGGL((bwd_dkdv_kernel<T, D>), grid_kv, dim3(256), 0, stream, (const T*)q,
-                       (const T*)k, (const T*)v, (const T*)dout, lse, delta, sel_idx, (T*)dk,
-                       (T*)dv, g, row_chunks);
+    auto kv_kernel = nw >= 4 ? bwd_generic_dkdv<T, D, 4>
+                     : nw >= 2 ? bwd_generic_dkdv<T, D, 2> : bwd_generic_dkdv<T, D, 1>;
+    kv_kernel<<<grid_kv, block, sizeof(uint32_t) * (size_t)g.block_tokens, stream>>>(
+        (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, conn, (T*)dk, (T*)dv, g,
+        (uint32_t)BKV, rows.chunks, 32 * nw);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v, const void* out,
                       const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
-                      void* dk, void* dv, float* delta, const Geom& g, int D, int64_t BH,
-                      hipStream_t stream)
+                      void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, const Geom& g,
+                      int D, int64_t BH, hipStream_t stream)
 {
+    hipError_t e = launch_bwd_connect(sel_idx, conn, g, BH, stream);
+    if (e != hipSuccess) return e;
+    e = launch_bwd_prep(is_bf16, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
+    if (e != hipSuccess) return e;
 #define BSA_CASE(DD)                                                                             \
     case DD:                                                                                     \
-        return is_bf16 ? launch_bwd_t<uint16_t, DD>(q, k, v, out, lse, dout, sel_idx, dq, dk,    \
-                                                    dv, delta, g, BH, stream)                    \
-                       : launch_bwd_t<float, DD>(q, k, v, out, lse, dout, sel_idx, dq, dk, dv,   \
-                                                 delta, g, BH, stream);
+        return is_bf16 ? launch_bwd_t<uint16_t, DD>(q, k, v, dout, sel_idx, dq, dk, dv, delta,   \
+                                                    lse2, conn, g, BH, stream)                   \
+                       : launch_bwd_t<float, DD>(q, k, v, dout, sel_idx, dq, dk, dv, delta,      \
+                                                 lse2, conn, g, BH, stream);
     switch (D) {
         BSA_CASE(32)
         BSA_CASE(64)

@@ -658,84 +658,6 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
 
 }  // namespace bwdm
 
-// delta_l = dO_l . O_l and lse_l * log2(e).  A row (D bf16 = 128 or 256 bytes)
-// is read by D/8 adjacent lanes, 16 bytes each, so a wavefront's loads cover
-// whole lines; the partial dot products are summed inside the lane group with
-// DPP steps.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v)
-{
-    return v + __int_as_float(
-                   __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void bwd_mfma_prep_kernel(const uint16_t* __restrict__ out,
-                                                            const uint16_t* __restrict__ dout,
-                                                            const float* __restrict__ lse,
-                                                            float* __restrict__ delta,
-                                                            float* __restrict__ lse2,
-                                                            int64_t rows)
-{
-    constexpr int LPR = D / 8;                      // lanes per row: 8 or 16
-    const int sub = threadIdx.x % LPR;
-    int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LPR;
-    const bool valid = row < rows;
-    if (!valid) row = rows - 1;                     // keep the lane group whole for the DPP sums
-    const uint4 a = *(const uint4*)(out + row * D + 8 * sub);
-    const uint4 b = *(const uint4*)(dout + row * D + 8 * sub);
-    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-    float acc = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        acc = fmaf(__uint_as_float(aw[e] << 16), __uint_as_float(bw[e] << 16), acc);
-        acc = fmaf(__uint_as_float(aw[e] & 0xffff0000u), __uint_as_float(bw[e] & 0xffff0000u),
-                   acc);
-    }
-    acc = dpp_add<0xB1>(acc);                       // quad_perm [1,0,3,2]
-    acc = dpp_add<0x4E>(acc);                       // quad_perm [2,3,0,1]
-    acc = dpp_add<0x141>(acc);                      // row_half_mirror: 8 lanes
-    if (LPR == 16) acc = dpp_add<0x140>(acc);       // row_mirror: 16 lanes
-    if (valid && sub == 0) {
-        delta[row] = acc;
-        lse2[row] = lse[row] * bwdm::kLog2e;
-    }
-}
-
-// The reverse map of the selection ("the query blocks connected to a key/value
-// block", Appendix, kernel design paragraph) as a bit matrix: bit i of row
-// [query slice][key block j] says that query block i attends to block j.  One
-// thread per (query slice, query block) sets the bits of its row of sel_idx
-// (and its own block's, unless only the lists count) with integer atomic ORs:
-// the final state does not depend on their order.  A dK/dV workgroup then reads
-// its m bits instead of scanning all m * n entries of the slice, and walking
-// the set bits upwards is the fixed summation order.
-__global__ __launch_bounds__(256) void bwd_connect_clear_kernel(uint32_t* __restrict__ conn,
-                                                                int64_t n_words)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n_words) conn[t] = 0u;
-}
-
-__global__ __launch_bounds__(256) void bwd_connect_kernel(const int32_t* __restrict__ sel_idx,
-                                                          uint32_t* __restrict__ conn, Geom g,
-                                                          int64_t rows)
-{
-    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;    // slice * m + i
-    if (row >= rows) return;
-    const int m = g.n_blocks, n = g.n_select, words = (m + 31) >> 5;
-    const int64_t bh_idx = row / m;
-    const int i = (int)(row - bh_idx * m);
-    uint32_t* base = conn + bh_idx * (int64_t)m * words + (i >> 5);
-    const uint32_t bit = 1u << (i & 31);
-    if (!g.list_only) atomicOr(base + (int64_t)i * words, bit);
-    const int32_t* r = sel_idx + row * n;
-    for (int a = 0; a < n; ++a) {
-        const int j = r[a];
-        if ((unsigned)j < (unsigned)m) atomicOr(base + (int64_t)j * words, bit);
-    }
-}
-
 // plain kernels per (head dim, wavefronts per workgroup); the bodies are templates
 #define BSA_BWD_KERNELS(D, NW)                                                                    \
     __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dq_d##D##_w##NW(                       \
@@ -799,27 +721,9 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
                            void* dk, void* dv, float* delta, float* lse2, uint32_t* conn,
                            const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
-    {
-        const int64_t crows = BH * g.n_blocks, n_words = crows * ((g.n_blocks + 31) >> 5);
-        bwd_connect_clear_kernel<<<dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, stream>>>(
-            conn, n_words);
-        bwd_connect_kernel<<<dim3((unsigned)((crows + 255) / 256)), dim3(256), 0, stream>>>(
-            sel_idx, conn, g, crows);
-        const hipError_t ce = hipGetLastError();
-        if (ce != hipSuccess) return ce;
-    }
-    const int64_t rows = BH * g.n_tokens;
-    {
-        const int64_t threads = rows * (D / 8);
-        const dim3 pgrid((unsigned)((threads + 255) / 256));
-        if (D == 64)
-            bwd_mfma_prep_kernel<64><<<pgrid, dim3(256), 0, stream>>>(
-                (const uint16_t*)out, (const uint16_t*)dout, lse, delta, lse2, rows);
-        else
-            bwd_mfma_prep_kernel<128><<<pgrid, dim3(256), 0, stream>>>(
-                (const uint16_t*)out, (const uint16_t*)dout, lse, delta, lse2, rows);
-    }
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_bwd_connect(sel_idx, conn, g, BH, stream);
+    if (e != hipSuccess) return e;
+    e = launch_bwd_prep(true, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
     if (e != hipSuccess) return e;
     const int nw = g.block_tokens / 32;
     const uint32_t sx = (uint32_t)(BH / g.kv_group);           // key/value slices

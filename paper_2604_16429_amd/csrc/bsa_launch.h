@@ -38,7 +38,7 @@ hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float*
                               float* kbar, void* scratch, int32_t* sel_idx, const Geom& g, int D,
                               int64_t BH, hipStream_t stream);
 
-// Any tile shape / head dim in {32, 64, 128} / dtype; fp32 vector arithmetic.
+// Any tile shape / head dim in {32, 64, 128} / dtype.
 hipError_t launch_fwd_generic(bool is_bf16, const void* q, const void* k, const void* v,
                               const int32_t* sel_idx, void* out, float* lse, const Geom& g, int D,
                               int64_t BH, hipStream_t stream);
@@ -56,18 +56,26 @@ hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v,
                                 const int32_t* sel_idx, void* out, float* lse, const Geom& g,
                                 int64_t BH, hipStream_t stream);
 
-// Backward with the selection fixed; `delta` is fp32 scratch of B*heads*N floats.
+// What both backward paths need first: delta_l = dO_l . O_l and lse_l * log2(e)
+// (fp32, `rows` of each), and the reverse map of the selection in `conn`.
+hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
+                           float* delta, float* lse2, int64_t rows, int D, hipStream_t stream);
+hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, const Geom& g, int64_t BH,
+                              hipStream_t stream);
+
+// Backward with the selection fixed, any tile shape / head dim in {32, 64, 128} /
+// dtype.  `delta` and `lse2` are fp32 scratch of B*heads*N floats each, `conn`
+// scratch of bwd_connection_words(...) 32-bit words (the reverse map of the
+// selection: one bit per (query slice, key block, query block)).
+inline int64_t bwd_connection_words(int m, int64_t BH) { return BH * m * (int64_t)((m + 31) >> 5); }
 hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v, const void* out,
                       const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
-                      void* dk, void* dv, float* delta, const Geom& g, int D, int64_t BH,
-                      hipStream_t stream);
+                      void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, const Geom& g,
+                      int D, int64_t BH, hipStream_t stream);
 
-// bf16 MFMA backward (head dim 64 or 128, blocks of 64, 128 or 256 tokens);
-// `delta` and `lse2` are fp32 scratch of B*heads*N floats each, `conn` scratch of
-// bwd_connection_words(...) 32-bit words (the reverse map of the selection: one
-// bit per (query slice, key block, query block)).
+// bf16 MFMA backward (head dim 64 or 128, blocks of 64, 128 or 256 tokens), same
+// scratch.
 bool bwd_mfma_supported(bool is_bf16, const Geom& g, int D);
-inline int64_t bwd_connection_words(int m, int64_t BH) { return BH * m * (int64_t)((m + 31) >> 5); }
 hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const void* out,
                            const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
                            void* dk, void* dv, float* delta, float* lse2, uint32_t* conn,

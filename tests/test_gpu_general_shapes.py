@@ -65,3 +65,31 @@ def test_general_forward(G, oracle, dtype, H, W, bh, bw, D, n):
     else:
         assert (err <= 2.0 ** -8 * np.abs(out_ref) + 2.0 ** -14 * np.abs(v).max()).all()
     assert np.abs(lse - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
+
+
+@pytest.mark.parametrize("dtype,kv_heads", [("fp32", 0), ("bf16", 0), ("fp32", 1), ("bf16", 1)])
+@pytest.mark.parametrize("H,W,bh,bw,D,n", SHAPES)
+def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
+    """fp32: 1e-4 of the largest entry, the bound of the other fp32 backward tests.
+    bf16: the stored gradient is off by half an ulp (2^-8 of its value, 4e-3) and
+    delta = dO . O by the rounding of O (2^-8 of O, D zero-mean terms: about 2^-8
+    sqrt(D) |dO| |O| <= 0.01 here, which enters dS weighted with P <= 1 and the
+    softmax scale): 1e-2 of max(1, largest entry) covers both.  Reruns are bitwise
+    identical."""
+    cfg = shape_ns(1, 2, H, W, bh, bw, D, min(n, (H // bh) * (W // bw) - 1), dtype, kv_heads)
+    rng = np.random.default_rng(90 + H + W + D)
+    shape = (1, 2, H * W, D)
+    q, dout = (rng.standard_normal(shape).astype(np.float32) for _ in range(2))
+    k, v = (rng.standard_normal((1, kv_heads or 2, H * W, D)).astype(np.float32) for _ in range(2))
+    if dtype == "bf16":
+        q, k, v, dout = (round_to_bf16(x) for x in (q, k, v, dout))
+    s = oracle.shape_of(cfg)
+    idx = random_selection(cfg, 8)
+    ref = (oracle.bwd_gqa if kv_heads else oracle.bwd)(s, q, k, v, dout, idx)
+    got = G.gpu_bwd(cfg, q, k, v, dout, idx)
+    for name, x, r in zip(("dq", "dk", "dv"), got, ref):
+        tol = 1e-4 * np.abs(r).max() if dtype == "fp32" else 1e-2 * max(1.0, np.abs(r).max())
+        err = np.abs(x - r).max()
+        assert err <= tol, f"{name}: max error {err} > {tol}"
+    again = G.gpu_bwd(cfg, q, k, v, dout, idx)
+    assert all(np.array_equal(x, y) for x, y in zip(got, again))
