@@ -24,8 +24,8 @@
 //                lists, in ascending order, the query blocks that attend to
 //                its block (the paper's "query blocks connected to a key/value
 //                block"), from a reverse map of the selection that a small
-//                kernel builds first: a bit matrix, one bit per (key block,
-//                query block).  No floating-point atomics: the ascending list
+//                kernel builds first (bsa_bwd.hip): a bit matrix, one bit per
+//                (key block, query block).  No floating-point atomics: the ascending list
 //                fixes the summation order.  It then walks their Q/dO
 //                sub-tiles.  Per 32-query tile: S = Q K^T and dP = dO V^T (rows
 //                are queries now: lse and delta come from LDS per row), and
@@ -465,6 +465,7 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
                                           const float* __restrict__ lse2,
                                           const float* __restrict__ delta,
                                           const uint32_t* __restrict__ conn,
+                                          const int32_t* __restrict__ order,
                                           uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                           const Geom& g, uint32_t n_units)
 {
@@ -493,7 +494,7 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
     {
         uint32_t unit, r;
         map_unit(blockIdx.x, (uint32_t)m, n_units, unit, r);
-        j = (int)r;
+        j = order[(int64_t)unit * m + r];
         kv_unit = unit;
         base = (int64_t)unit * g.n_tokens * D;
         const uint32_t kv_heads = (uint32_t)(g.heads / g.kv_group);
@@ -539,7 +540,7 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
     // order within each: the summation order is fixed
     for (int gq = 0; gq < g.kv_group; ++gq) {
     const int64_t bh_idx = bh_first + gq;
-    const uint32_t* conn_row = conn + (bh_idx * (int64_t)m + j) * words;
+    const uint32_t* conn_col = conn + bh_idx * (int64_t)words * m + j;
     const i32x4 q_rsrc = buffer_desc(q + bh_idx * g.n_tokens * D, slice_bytes);
     const i32x4 g_rsrc = buffer_desc(dout + bh_idx * g.n_tokens * D, slice_bytes);
     const i32x4 l_rsrc = buffer_desc(lse2 + bh_idx * g.n_tokens, (uint32_t)(g.n_tokens * 4));
@@ -560,7 +561,7 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
         // bit each in the connection map; ascending order, so the summation
         // order below is fixed
         const int i_mine = i0 + (int)threadIdx.x;
-        const bool hit = i_mine < m && ((conn_row[i_mine >> 5] >> (i_mine & 31)) & 1u) != 0;
+        const bool hit = i_mine < m && ((conn_col[(int64_t)(i_mine >> 5) * m] >> (i_mine & 31)) & 1u) != 0;
         const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
         __syncthreads();                      // previous round's list and tiles fully consumed
         if (lane == 0) wave_cnt[wave] = __builtin_popcountll(mask);
@@ -669,18 +670,18 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
     }                                                                                             \
     __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dv_d##D##_w##NW(                       \
         const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dout,            \
-        const float* lse2, const float* delta, const uint32_t* conn, uint16_t* dk,                \
+        const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order, uint16_t* dk, \
         uint16_t* dv, Geom g, uint32_t n_units)                                                 \
     {                                                                                             \
-        bwdm::dkdv_body<D, NW, bwdm::PASS_DV>(q, k, v, dout, lse2, delta, conn, dk, dv, g,        \
+        bwdm::dkdv_body<D, NW, bwdm::PASS_DV>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g,        \
                                               n_units);                                        \
     }                                                                                             \
     __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dk_d##D##_w##NW(                       \
         const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dout,            \
-        const float* lse2, const float* delta, const uint32_t* conn, uint16_t* dk,                \
+        const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order, uint16_t* dk, \
         uint16_t* dv, Geom g, uint32_t n_units)                                                 \
     {                                                                                             \
-        bwdm::dkdv_body<D, NW, bwdm::PASS_DK>(q, k, v, dout, lse2, delta, conn, dk, dv, g,        \
+        bwdm::dkdv_body<D, NW, bwdm::PASS_DK>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g,        \
                                               n_units);                                        \
     }
 BSA_BWD_KERNELS(64, 2)
@@ -690,11 +691,11 @@ BSA_BWD_KERNELS(64, 8)
 #define BSA_BWD_FUSED(NW)                                                                         \
     __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dkdv_d64_w##NW(                        \
         const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dout,            \
-        const float* lse2, const float* delta, const uint32_t* conn, uint16_t* dk,                \
+        const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order, uint16_t* dk, \
         uint16_t* dv, Geom g, uint32_t n_units)                                                 \
     {                                                                                             \
         bwdm::dkdv_body<64, NW, bwdm::PASS_DV | bwdm::PASS_DK>(q, k, v, dout, lse2, delta,        \
-                                                               conn, dk, dv, g, n_units);      \
+                                                               conn, order, dk, dv, g, n_units);      \
     }
 BSA_BWD_FUSED(2)
 BSA_BWD_FUSED(4)
@@ -718,10 +719,10 @@ bool bwd_mfma_supported(bool is_bf16, const Geom& g, int D)
 
 hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const void* out,
                            const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
-                           void* dk, void* dv, float* delta, float* lse2, uint32_t* conn,
+                           void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
                            const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
-    hipError_t e = launch_bwd_connect(sel_idx, conn, g, BH, stream);
+    hipError_t e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
     if (e != hipSuccess) return e;
     e = launch_bwd_prep(true, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
     if (e != hipSuccess) return e;
@@ -736,11 +737,11 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
         if ((e = hipGetLastError()) != hipSuccess) return e;                                      \
         bwd_mfma_dv_d##D_##_w##NW_<<<grid_kv, block, 0, stream>>>(                                   \
             (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, conn, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
+            lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                      \
         bwd_mfma_dk_d##D_##_w##NW_<<<grid_kv, block, 0, stream>>>(                                   \
             (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, conn, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
+            lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
         return hipGetLastError();                                                                 \
     }
 #define BSA_LAUNCH_FUSED(NW_)                                                                     \
@@ -751,7 +752,7 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
         if ((e = hipGetLastError()) != hipSuccess) return e;                                      \
         bwd_mfma_dkdv_d64_w##NW_<<<grid_kv, block, 0, stream>>>(                                     \
             (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, conn, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
+            lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
         return hipGetLastError();                                                                 \
     }
     BSA_LAUNCH_FUSED(2)

@@ -57,11 +57,13 @@ hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v,
                                 int64_t BH, hipStream_t stream);
 
 // What both backward paths need first: delta_l = dO_l . O_l and lse_l * log2(e)
-// (fp32, `rows` of each), and the reverse map of the selection in `conn`.
+// (fp32, `rows` of each), the reverse map of the selection in `conn` and, in
+// `order` (int32, key/value slices x m), the order in which the key blocks of each
+// key/value slice are worked on.
 hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
                            float* delta, float* lse2, int64_t rows, int D, hipStream_t stream);
-hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, const Geom& g, int64_t BH,
-                              hipStream_t stream);
+hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,
+                              int64_t BH, hipStream_t stream);
 
 // Backward with the selection fixed, any tile shape / head dim in {32, 64, 128} /
 // dtype.  `delta` and `lse2` are fp32 scratch of B*heads*N floats each, `conn`
@@ -70,15 +72,15 @@ hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, const Geom
 inline int64_t bwd_connection_words(int m, int64_t BH) { return BH * m * (int64_t)((m + 31) >> 5); }
 hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v, const void* out,
                       const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
-                      void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, const Geom& g,
-                      int D, int64_t BH, hipStream_t stream);
+                      void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
+                      const Geom& g, int D, int64_t BH, hipStream_t stream);
 
 // bf16 MFMA backward (head dim 64 or 128, blocks of 64, 128 or 256 tokens), same
 // scratch.
 bool bwd_mfma_supported(bool is_bf16, const Geom& g, int D);
 hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const void* out,
                            const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
-                           void* dk, void* dv, float* delta, float* lse2, uint32_t* conn,
+                           void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
                            const Geom& g, int D, int64_t BH, hipStream_t stream);
 
 // Three-branch output: coarse branch (softmax over all pooled key blocks times
