@@ -92,14 +92,96 @@ __device__ __forceinline__ void pool_block(const T* __restrict__ q, const T* __r
     }
 }
 
-template <typename T, int VEC>
-__global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ q,
-                                                   const T* __restrict__ k,
-                                                   float* __restrict__ qbar,
-                                                   float* __restrict__ kbar, Geom g, int D,
-                                                   int64_t BH, int wgs_per_slice)
+// Pooling as a launch of its own (little to pool, or nothing to rank beside it):
+// the same sums with more loads in flight.  A thread owns VEC channels of a tile and
+// walks the tile's tokens BATCH at a time, over row ends, all loads of a batch
+// before the adds.  VEC is chosen by the launcher: 16 bytes per load where that
+// fills the chip, less where it would leave too few wavefronts: what bounds a
+// small call is the number of memory latencies in a thread's chain.
+// Measured against pool_block in a launch of its own (16-byte loads, 8 in flight):
+// 25 slices of 24 tiles of 128 tokens (10 MB) 12.1 -> 6.5 us; 32 slices of 288 tiles
+// of 10 x 10 (118 MB) 24.3 -> 23.3 us, which is the memory's rate, as is 10.8 us for
+// 59 MB.
+template <typename T, int VEC> struct PoolPiece { T x[VEC]; };
+
+template <int VEC>
+__device__ __forceinline__ void add_piece(const PoolPiece<uint16_t, VEC>& p, float (&acc)[VEC])
 {
-    pool_block<T, VEC>(q, k, qbar, kbar, nullptr, g, D, 0, BH, 0, wgs_per_slice, blockIdx.x);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = acc[e] + bf16_to_f32(p.x[e]);
+}
+template <int VEC>
+__device__ __forceinline__ void add_piece(const PoolPiece<float, VEC>& p, float (&acc)[VEC])
+{
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = acc[e] + p.x[e];
+}
+
+// A tensor of `slices` slices and where its means go (il: second copy of the means,
+// per slice [D/4][m][4], or null).
+struct PoolTensor {
+    const void* x;
+    float *xbar, *xbar_il;
+    uint32_t slices;
+};
+
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void pool_kernel(PoolTensor t0, PoolTensor t1, PoolTensor t2,
+                                                   Geom g, int D, uint32_t wgs_per_slice)
+{
+    typedef uint32_t word __attribute__((ext_vector_type(VEC * (int)sizeof(T) / 4)));
+    constexpr int BATCH = 16;
+    uint32_t slice = blockIdx.x / wgs_per_slice;
+    const uint32_t chunk = blockIdx.x - slice * wgs_per_slice;
+    PoolTensor t = t0;
+    if (slice >= t.slices) {
+        slice -= t.slices;
+        t = t1;
+        if (slice >= t.slices) { slice -= t.slices; t = t2; }
+    }
+    const int groups = D / VEC;
+    const int item = (int)(chunk * 256 + threadIdx.x);
+    const int beta = item / groups;
+    if (beta >= g.n_blocks) return;
+    const int ch = (item - beta * groups) * VEC;
+    const int tile_row = beta / g.blocks_per_row, tile_col = beta - tile_row * g.blocks_per_row;
+    const T* at = (const T*)t.x + (int64_t)slice * g.n_tokens * D +
+                  ((int64_t)tile_row * g.block_h * g.grid_w + (int64_t)tile_col * g.block_w) * D + ch;
+    const int64_t row_jump = (int64_t)(g.grid_w - g.block_w) * D;
+    const int b = g.block_tokens;
+    float acc[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = 0.0f;
+    int col = 0;                                     // wave-uniform: position in the tile row
+    auto next = [&] {
+        const T* here = at;
+        at += D;
+        if (++col == g.block_w) { col = 0; at += row_jump; }
+        return here;
+    };
+    int tau = 0;
+    for (; tau + BATCH <= b; tau += BATCH) {
+        word w[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const word* src = (const word*)next();
+            // 16-byte pieces: much to read, once
+            w[u] = sizeof(word) == 16 ? __builtin_nontemporal_load(src) : *src;
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) add_piece(__builtin_bit_cast(PoolPiece<T, VEC>, w[u]), acc);
+    }
+    for (; tau < b; ++tau)
+        add_piece(__builtin_bit_cast(PoolPiece<T, VEC>, *(const word*)next()), acc);
+    const float inv_b = 1.0f / (float)b;
+    float* dst = t.xbar + ((int64_t)slice * g.n_blocks + beta) * D + ch;
+    float* il = t.xbar_il ? t.xbar_il + (int64_t)slice * g.n_blocks * D : nullptr;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        const float mean = acc[e] * inv_b;
+        dst[e] = mean;
+        if (il) il[((int64_t)((ch + e) >> 2) * g.n_blocks + beta) * 4 + ((ch + e) & 3)] = mean;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -500,40 +582,51 @@ int select_group_size(int m, int D)
 }
 
 template <typename T, int VEC>
-static hipError_t launch_pool_t(const void* q, const void* k, float* qbar, float* kbar,
-                                const Geom& g, int D, int64_t BH, hipStream_t stream)
+static hipError_t launch_pool_t(const PoolTensor (&t)[3], const Geom& g, int D, hipStream_t stream)
 {
-    const int items = g.n_blocks * (D / VEC);
-    const int wgs_per_slice = (items + 255) / 256;
-    dim3 grid((unsigned)((BH + BH / g.kv_group) * wgs_per_slice));
-    hipLaunchKernelGGL((pool_kernel<T, VEC>), grid, dim3(256), 0, stream, (const T*)q,
-                       (const T*)k, qbar, kbar, g, D, BH, wgs_per_slice);
+    const int64_t slices = (int64_t)t[0].slices + t[1].slices + t[2].slices;
+    const int64_t wgs_per_slice = ((int64_t)g.n_blocks * (D / VEC) + 255) / 256;
+    if (slices * wgs_per_slice >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    pool_kernel<T, VEC><<<dim3((unsigned)(slices * wgs_per_slice)), dim3(256), 0, stream>>>(
+        t[0], t[1], t[2], g, D, (uint32_t)wgs_per_slice);
     return hipGetLastError();
+}
+
+// Pools up to three tensors.  16-byte loads when that gives every CU two
+// workgroups of 256 threads, else 8 or 4 bytes.
+static hipError_t launch_pool_tensors(bool is_bf16, const PoolTensor (&t)[3], const Geom& g, int D,
+                                      hipStream_t stream)
+{
+    const int64_t slices = (int64_t)t[0].slices + t[1].slices + t[2].slices;
+    const int64_t channels = slices * g.n_blocks * D;
+    const int64_t fill = (int64_t)2 * 256 * 256;             // threads
+    const int per16 = is_bf16 ? 8 : 4;
+    if (channels / per16 >= fill)
+        return is_bf16 ? launch_pool_t<uint16_t, 8>(t, g, D, stream)
+                       : launch_pool_t<float, 4>(t, g, D, stream);
+    if (2 * channels / per16 >= fill)
+        return is_bf16 ? launch_pool_t<uint16_t, 4>(t, g, D, stream)
+                       : launch_pool_t<float, 2>(t, g, D, stream);
+    return is_bf16 ? launch_pool_t<uint16_t, 2>(t, g, D, stream)
+                   : launch_pool_t<float, 1>(t, g, D, stream);
 }
 
 hipError_t launch_pool(bool is_bf16, const void* q, const void* k, float* qbar, float* kbar,
                        const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
-    return is_bf16 ? launch_pool_t<uint16_t, 8>(q, k, qbar, kbar, g, D, BH, stream)
-                   : launch_pool_t<float, 4>(q, k, qbar, kbar, g, D, BH, stream);
+    const PoolTensor t[3] = {{q, qbar, nullptr, (uint32_t)BH},
+                             {k, kbar, nullptr, (uint32_t)(BH / g.kv_group)},
+                             {nullptr, nullptr, nullptr, 0}};
+    return launch_pool_tensors(is_bf16, t, g, D, stream);
 }
 
 hipError_t launch_pool_one(bool is_bf16, const void* x, float* xbar, const Geom& g, int D,
                            int64_t slices, hipStream_t stream)
 {
-    // the pooling kernel with no query slices: every slice is a "key" slice
-    const int items = g.n_blocks * (D / (is_bf16 ? 8 : 4));
-    const int wgs_per_slice = (items + 255) / 256;
-    dim3 grid((unsigned)(slices * wgs_per_slice));
-    if (is_bf16)
-        hipLaunchKernelGGL((pool_kernel<uint16_t, 8>), grid, dim3(256), 0, stream,
-                           (const uint16_t*)nullptr, (const uint16_t*)x, (float*)nullptr, xbar, g,
-                           D, (int64_t)0, wgs_per_slice);
-    else
-        hipLaunchKernelGGL((pool_kernel<float, 4>), grid, dim3(256), 0, stream,
-                           (const float*)nullptr, (const float*)x, (float*)nullptr, xbar, g, D,
-                           (int64_t)0, wgs_per_slice);
-    return hipGetLastError();
+    const PoolTensor t[3] = {{x, xbar, nullptr, (uint32_t)slices},
+                             {nullptr, nullptr, nullptr, 0},
+                             {nullptr, nullptr, nullptr, 0}};
+    return launch_pool_tensors(is_bf16, t, g, D, stream);
 }
 
 size_t select_scratch_bytes(int m, int D, int64_t BH, int64_t BKV)
@@ -543,14 +636,26 @@ size_t select_scratch_bytes(int m, int D, int64_t BH, int64_t BKV)
     return (size_t)BKV * (size_t)m * (size_t)D * 4;
 }
 
-#ifndef BSA_SELECT_PARTS
-#define BSA_SELECT_PARTS 4
-#endif
-#ifndef BSA_POOLERS
-#define BSA_POOLERS 256
-#endif
 // pooling workgroups that stay resident beside the ranking (one per CU)
-constexpr int64_t kPoolers = BSA_POOLERS;
+constexpr int64_t kPoolers = 256;
+
+// Parts of the batch: as many as leave each about 128 MiB to pool, at most 4.  A
+// part costs a launch that the GPU drains before the next one (8 us and more),
+// and what it buys is the shorter of pooling and ranking of a part.  Measured with
+// 1 / 2 / 4 parts: 59 MB (1.5 degree grid, 8 heads) 28 / 40 / 63 us, 118 MB 36 / 44
+// / 67, 252 MB 79 / 73 / 84, 944 MB 237 / 229 / 203, 2.8 GB (24 members) 862 / 749
+// / 705.
+constexpr int64_t kPartBytes = (int64_t)128 << 20;
+constexpr int64_t kMaxParts = 4;
+
+static int select_parts(int64_t BH, int64_t BKV, const Geom& g, int D, size_t element)
+{
+    const int64_t bytes = (BH + BKV) * g.n_tokens * D * (int64_t)element;
+    int64_t parts = (bytes + kPartBytes / 2) / kPartBytes;
+    if (parts > kMaxParts) parts = kMaxParts;
+    if (parts > BKV) parts = BKV;
+    return parts < 1 ? 1 : (int)parts;
+}
 
 bool select_interleaves_keys(int m) { (void)m; return true; }
 
@@ -560,8 +665,12 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
                                        int64_t BH, hipStream_t stream)
 {
     const int m = g.n_blocks;
-    const int G = select_group_size(m, D);
+    int G = select_group_size(m, D);
     if (G == 0) return hipErrorInvalidValue;
+    // few query blocks: fewer per workgroup, down to a workgroup each, until there
+    // are two workgroups per CU (ranking 480 blocks 9.8 -> 5.1 us, 3,600 blocks 15.9
+    // -> 13.4 us, 64 blocks 6.3 -> 3.9 us)
+    while (G > 1 && BH * ((m + G - 1) / G) < 512) G >>= 1;
     const size_t lds = select_lds_bytes(G, m, D);
     // the attribute is per device; setting it twice (two host threads racing) is harmless
     static bool attr_set[64] = {};
@@ -575,11 +684,19 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
         attr_set[dev] = true;
     }
     const int64_t BKV = BH / g.kv_group;
-    const int parts = (int)(BKV < BSA_SELECT_PARTS ? BKV : BSA_SELECT_PARTS);
+    const int parts = select_parts(BH, BKV, g, D, sizeof(T));
     const int wgs_per_slice = (m * (D / VEC) + 255) / 256;
     const int groups = (m + G - 1) / G;
+    // one part: pooled by a launch of its own
+    if (parts == 1) {
+        const PoolTensor tensors[3] = {{q, qbar, nullptr, (uint32_t)BH},
+                                       {k, kbar, kbar_il, (uint32_t)BKV},
+                                       {nullptr, nullptr, nullptr, 0}};
+        const hipError_t e = launch_pool_tensors(sizeof(T) == 2, tensors, g, D, stream);
+        if (e != hipSuccess) return e;
+    }
     // launch t pools part t and ranks part t - 1
-    for (int t = 0; t <= parts; ++t) {
+    for (int t = parts == 1 ? 1 : 0; t <= parts; ++t) {
         int64_t pq0 = 0, pnq = 0, pk0 = 0, n_pool = 0, sel_first = 0, n_sel = 0;
         if (t < parts) {
             pk0 = BKV * t / parts;
