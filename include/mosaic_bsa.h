@@ -179,10 +179,10 @@ int mosaic_bsa_fwd(const mosaic_bsa_params *params, const void *q, const void *k
  *                            mosaic_bsa_workspace_bytes(.., OP_BWD) bytes; on
  *                            return its start holds delta_l = dout_l . out_l,
  *                            fp32 [B, heads, N] (the rest is scratch: the
- *                            log-sum-exps in base 2, the reverse map of the
+ *                            log-sum-exps in base 2 and the reverse map of the
  *                            selection, one bit per (query slice, query
- *                            block, key block), and the order in which the key
- *                            blocks are worked on).
+ *                            block, key block)).  dq serves as scratch before it
+ *                            is written.
  * dk/dv of a key block are reduced over the query blocks that attend to it in
  * a fixed order (no floating-point atomics): results are run-to-run identical.
  */

@@ -7,6 +7,7 @@
 
 #include <mutex>
 
+#include "bsa_coarse.h"
 #include "bsa_launch.h"
 
 // Device memory of mosaic_bsa_select_static, which may not take a workspace from
@@ -89,21 +90,16 @@ size_t select_workspace(const Checked& c)
     return 2 * pooled_bytes(c) + align_up(bsa::select_scratch_bytes(c.g.n_blocks, c.D, c.BH, c.BKV));
 }
 
-// delta | lse * log2(e) | connection map | order of the key blocks
+// delta | lse * log2(e) | connection map
 size_t bwd_rows_bytes(const Checked& c)
 {
     return align_up((size_t)c.BH * (size_t)c.g.n_tokens * sizeof(float));
 }
 
-size_t bwd_map_bytes(const Checked& c)
-{
-    return align_up((size_t)bsa::bwd_connection_words(c.g.n_blocks, c.BH) * sizeof(uint32_t));
-}
-
 size_t bwd_workspace(const Checked& c)
 {
-    return 2 * bwd_rows_bytes(c) + bwd_map_bytes(c) +
-           align_up((size_t)c.BKV * (size_t)c.g.n_blocks * sizeof(int32_t));
+    return 2 * bwd_rows_bytes(c) +
+           align_up((size_t)bsa::bwd_connection_words(c.g.n_blocks, c.BH) * sizeof(uint32_t));
 }
 
 }  // namespace
@@ -194,17 +190,16 @@ extern "C" int mosaic_bsa_select_static(const mosaic_bsa_params* params, const v
 
 namespace {
 
-// The attention forward for geometry g (which may differ from the checked one
-// in its block lists): matrix-core kernels where they apply.
-hipError_t forward(const Checked& c, const bsa::Geom& g, const void* q, const void* k,
-                   const void* v, const int32_t* lists, void* out, float* lse,
-                   hipStream_t stream)
+// The attention forward of one or two jobs (lists, output) over the same q, k, v:
+// matrix-core kernels specialised for a shape where there are.
+hipError_t forward(const Checked& c, const void* q, const void* k, const void* v,
+                   const bsa::FwdJob* jobs, int n_jobs, hipStream_t stream)
 {
-    if (bsa::fwd_mfma_supported(c.is_bf16, g, c.D))
-        return bsa::launch_fwd_mfma(q, k, v, lists, out, lse, g, c.D, c.BH, stream);
-    if (bsa::fwd_mfma_d128_supported(c.is_bf16, g, c.D))
-        return bsa::launch_fwd_mfma_d128(q, k, v, lists, out, lse, g, c.BH, stream);
-    return bsa::launch_fwd_generic(c.is_bf16, q, k, v, lists, out, lse, g, c.D, c.BH, stream);
+    if (bsa::fwd_mfma_supported(c.is_bf16, c.g, c.D))
+        return bsa::launch_fwd_mfma(q, k, v, jobs, n_jobs, c.g, c.D, c.BH, stream);
+    if (bsa::fwd_mfma_d128_supported(c.is_bf16, c.g, c.D))
+        return bsa::launch_fwd_mfma_d128(q, k, v, jobs, n_jobs, c.g, c.BH, stream);
+    return bsa::launch_fwd_generic(c.is_bf16, q, k, v, jobs, n_jobs, c.g, c.D, c.BH, stream);
 }
 
 }  // namespace
@@ -222,7 +217,8 @@ extern "C" int mosaic_bsa_fwd(const mosaic_bsa_params* params, const void* q, co
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out))
         return MOSAIC_BSA_ERR_ALIGN;
 
-    return forward(c, c.g, q, k, v, sel_idx, out, lse, (hipStream_t)hip_stream) == hipSuccess
+    const bsa::FwdJob job = {sel_idx, out, lse, c.g.n_select, 0};
+    return forward(c, q, k, v, &job, 1, (hipStream_t)hip_stream) == hipSuccess
                ? MOSAIC_BSA_OK
                : MOSAIC_BSA_ERR_LAUNCH;
 }
@@ -309,28 +305,19 @@ extern "C" int mosaic_bsa_fwd_three_branch(const mosaic_bsa_params* params, int3
     void* o_fg = ws + w.o_fg;
     void* o_l = ws + w.o_l;
 
-    // compression (pooled q, k, v), the coarse branch, and the ranking it shares
-    // with the selection branch
-    if (bsa::launch_pool_select(c.is_bf16, q, k, qbar, kbar, ws + w.keys, sel_idx, c.g, c.D, c.BH,
-                                stream) != hipSuccess)
+    // compression (pooled q, k, v), the ranking, the coarse branch, the local lists
+    if (bsa::launch_blocks_three_branch(c.is_bf16, q, k, v, qbar, kbar, vbar,
+                                        (float*)(ws + w.keys), sel_idx, obar, lists, local_h,
+                                        local_w, c.g, c.D, c.BH, stream) != hipSuccess)
         return MOSAIC_BSA_ERR_LAUNCH;
-    if (bsa::launch_pool_one(c.is_bf16, v, vbar, c.g, c.D, c.BKV, stream) != hipSuccess ||
-        bsa::launch_coarse(qbar, kbar,
-                           bsa::select_interleaves_keys(c.g.n_blocks) ? (const float*)(ws + w.keys)
-                                                                      : nullptr,
-                           vbar, obar, c.g, c.D, c.BH, stream) != hipSuccess)
-        return MOSAIC_BSA_ERR_LAUNCH;
-    // selection branch: one softmax over the selected blocks only
-    bsa::Geom g_fg = c.g;
-    g_fg.list_only = 1;
-    if (forward(c, g_fg, q, k, v, sel_idx, o_fg, (float*)(ws + w.lse_fg), stream) != hipSuccess)
-        return MOSAIC_BSA_ERR_LAUNCH;
-    // local branch: the tile and the other tiles of its large block
-    bsa::Geom g_l = c.g;
-    g_l.n_select = local_tiles - 1;
-    if (bsa::launch_local_lists(lists, c.g, local_h, local_w, c.BH, stream) != hipSuccess ||
-        forward(c, g_l, q, k, v, lists, o_l, (float*)(ws + w.lse_l), stream) != hipSuccess)
-        return MOSAIC_BSA_ERR_LAUNCH;
+    // selection branch: one softmax over the selected blocks only; local branch:
+    // the tile and the other tiles of its large block.  The one with more blocks
+    // goes first.
+    const bsa::FwdJob fg = {sel_idx, o_fg, (float*)(ws + w.lse_fg), c.g.n_select, 1};
+    const bsa::FwdJob loc = {lists, o_l, (float*)(ws + w.lse_l), local_tiles - 1, 0};
+    const bool fg_first = c.g.n_select >= local_tiles;
+    const bsa::FwdJob jobs[2] = {fg_first ? fg : loc, fg_first ? loc : fg};
+    if (forward(c, q, k, v, jobs, 2, stream) != hipSuccess) return MOSAIC_BSA_ERR_LAUNCH;
     // gated sum
     if (bsa::launch_combine(c.is_bf16, obar, o_fg, o_l, gates, out, c.g, c.D, c.BH, stream) !=
         hipSuccess)
@@ -341,16 +328,16 @@ extern "C" int mosaic_bsa_fwd_three_branch(const mosaic_bsa_params* params, int3
 namespace {
 
 // The attention backward for geometry g (selection or lists held fixed);
-// scratch: bwd_workspace(c) bytes.
+// scratch: bwd_workspace(c) bytes; order: int32 per key block of every key/value
+// slice (dK and dV are done before dQ is touched, so dq may serve).
 hipError_t backward(const Checked& c, const bsa::Geom& g, const void* q, const void* k,
                     const void* v, const void* out, const float* lse, const void* dout,
                     const int32_t* lists, void* dq, void* dk, void* dv, void* scratch,
-                    hipStream_t stream)
+                    int32_t* order, hipStream_t stream)
 {
     float* delta = (float*)scratch;
     float* lse2 = (float*)((char*)scratch + bwd_rows_bytes(c));
     uint32_t* conn = (uint32_t*)((char*)scratch + 2 * bwd_rows_bytes(c));
-    int32_t* order = (int32_t*)((char*)conn + bwd_map_bytes(c));
     return bsa::bwd_mfma_supported(c.is_bf16, g, c.D)
                ? bsa::launch_bwd_mfma(q, k, v, out, lse, dout, lists, dq, dk, dv, delta, lse2,
                                       conn, order, g, c.D, c.BH, stream)
@@ -375,7 +362,7 @@ extern "C" int mosaic_bsa_bwd(const mosaic_bsa_params* params, const void* q, co
     if (!workspace || workspace_bytes < bwd_workspace(c)) return MOSAIC_BSA_ERR_WORKSPACE;
 
     return backward(c, c.g, q, k, v, out, lse, dout, sel_idx, dq, dk, dv, workspace,
-                    (hipStream_t)hip_stream) == hipSuccess
+                    (int32_t*)dq, (hipStream_t)hip_stream) == hipSuccess
                ? MOSAIC_BSA_OK
                : MOSAIC_BSA_ERR_LAUNCH;
 }
@@ -384,7 +371,7 @@ namespace {
 
 // Workspace of the three-branch backward: 256-byte aligned parts in this order.
 struct ThreeBranchBwdLayout {
-    size_t attn, do_fg, do_l, dobar, a_mat, ds_mat, dqbar, dkbar, dvbar, total;
+    size_t attn, order, do_fg, do_l, dobar, a_mat, ds_mat, dqbar, dkbar, dvbar, total;
     int chunk_rows;        // query blocks per pass of the coarse branch's backward
 };
 
@@ -413,6 +400,7 @@ ThreeBranchBwdLayout three_branch_bwd_layout(const Checked& c)
         return start;
     };
     w.attn = take(bwd_workspace(c));                 // scratch of the attention backward kernels
+    w.order = take((size_t)c.BKV * m * sizeof(int32_t));
     w.do_fg = take((size_t)c.BH * N * c.D * esz);
     w.do_l = take((size_t)c.BH * N * c.D * esz);
     w.dobar = take((size_t)c.BH * m * c.D * 4);
@@ -480,12 +468,11 @@ extern "C" int mosaic_bsa_bwd_three_branch(const mosaic_bsa_params* params, int3
     bsa::Geom g_fg = c.g;
     g_fg.list_only = 1;
     if (backward(c, g_fg, q, k, v, fw + f.o_fg, (const float*)(fw + f.lse_fg), ws + w.do_fg,
-                 sel_idx, dq, dk, dv, ws + w.attn, stream) != hipSuccess)
+                 sel_idx, dq, dk, dv, ws + w.attn, (int32_t*)(ws + w.order), stream) != hipSuccess)
         return MOSAIC_BSA_ERR_LAUNCH;
     // coarse branch on the pooled tensors
     if (bsa::launch_coarse_bwd(qbar, kbar,
-                               bsa::select_interleaves_keys(c.g.n_blocks)
-                                   ? (const float*)(fw + f.keys) : nullptr,
+                               (const float*)(fw + f.keys),
                                vbar, dobar, (float*)(ws + w.a_mat),
                                (float*)(ws + w.ds_mat), (float*)(ws + w.dqbar),
                                (float*)(ws + w.dkbar), (float*)(ws + w.dvbar), c.g, c.D, c.BH,
@@ -499,7 +486,7 @@ extern "C" int mosaic_bsa_bwd_three_branch(const mosaic_bsa_params* params, int3
     g_l.add_dk = (const float*)(ws + w.dkbar);
     g_l.add_dv = (const float*)(ws + w.dvbar);
     if (backward(c, g_l, q, k, v, fw + f.o_l, (const float*)(fw + f.lse_l), ws + w.do_l, lists,
-                 dq, dk, dv, ws + w.attn, stream) != hipSuccess)
+                 dq, dk, dv, ws + w.attn, (int32_t*)(ws + w.order), stream) != hipSuccess)
         return MOSAIC_BSA_ERR_LAUNCH;
     return MOSAIC_BSA_OK;
 }

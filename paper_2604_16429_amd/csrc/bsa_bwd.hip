@@ -285,15 +285,17 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
 
+    TileReader<T, D> rd;
+    rd.init(lane);
     AttendedKeys<T, D, NL> keys;
     keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave);
 
     const int tau_q = row0 + 32 * wave + l32;
     const bool valid = tau_q < min(b, row0 + chunk_rows);
     const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
-    typename RowFrag<T, D>::type qf[RowFrag<T, D>::N], dof[RowFrag<T, D>::N];
+    typename RowPieces<T, D>::type qf[RowPieces<T, D>::N], dof[RowPieces<T, D>::N];
 #pragma unroll
-    for (int s = 0; s < RowFrag<T, D>::N; ++s) {
+    for (int s = 0; s < RowPieces<T, D>::N; ++s) {
         load_row(q + base + q_tok * D, qf[s], s, half);
         load_row(dout + base + q_tok * D, dof[s], s, half);
     }
@@ -310,28 +312,34 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     const unsigned char* kb = (const unsigned char*)(k + kv_base);
     const unsigned char* vb = (const unsigned char*)(v + kv_base);
     const uint32_t k_dst = lds_address(k_lds), v_dst = lds_address(v_lds);
-    if (wave < NL) keys.gather_next(kb, vb, k_dst, v_dst);
+    if (wave < NL) {
+        keys.look_up();
+        keys.gather_next(kb, vb, k_dst, v_dst);
+    }
     for (int c = 0; c < keys.tiles; ++c) {
         // tile c has landed and everyone is done with the other buffer
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        wait_gathers();
         __syncthreads();
         const int buf = c & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
         if (wave < NL && c + 1 < keys.tiles) keys.gather_next(kb, vb, k_dst + other, v_dst + other);
 #pragma unroll
         for (int hh = 0; hh < KT / 32; ++hh) {
-            const unsigned char* kt = k_lds[buf] + 32 * hh * Tile::ROW_BYTES;
-            const unsigned char* vt = v_lds[buf] + 32 * hh * Tile::ROW_BYTES;
+            const uint32_t kt = k_dst + (uint32_t)buf * Tile::TILE_BYTES;
+            const uint32_t vt = v_dst + (uint32_t)buf * Tile::TILE_BYTES;
+            constexpr int HALF = 32 * Tile::ROW_BYTES;
             const int left = keys.total - (KT * c + 32 * hh);
             if (left <= 0) break;
-            f32x16 s = dot_tile<D>(kt, qf, zero_tile(), l32, half);
-            f32x16 dp = dot_tile<D>(vt, dof, dp0, l32, half);
+            f32x16 s = zero_tile(), dp = dp0;
+            dot_tiles(rd, kt, vt, hh * HALF, qf, dof, s, dp);
+            ColumnPieces<T, D> k0;
+            read_columns(rd, kt, hh * HALF, 0, k0);
             if (left < 32)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     if (past_end(r, half, left)) s[r] = -INFINITY;
 #pragma unroll
             for (int r = 0; r < 16; ++r) dp[r] *= __builtin_amdgcn_exp2f(fmaf(s[r], c2, neg_l2));
-            weighted_rows<D>((const T*)nullptr, kt, dp, acc, lane);
+            weighted_rows(rd, kt, hh * HALF, k0, dp, acc);
         }
     }
 
@@ -395,6 +403,8 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     const float* db = delta + bh_first * g.n_tokens;
 
     fill_position_table(g, pos_s);
+    TileReader<T, D> rd;
+    rd.init(lane);
 
     // this wavefront's 32 key rows.  V enters negated: the accumulator that starts
     // from delta then ends as delta - dP without an instruction per element, and
@@ -402,9 +412,9 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     const int tau_k = row0 + 32 * wave + l32;
     const bool valid = tau_k < min(b, row0 + chunk_rows);
     const int64_t k_tok = token_of(g, j, valid ? tau_k : 0);
-    typename RowFrag<T, D>::type kf[RowFrag<T, D>::N], vf[RowFrag<T, D>::N];
+    typename RowPieces<T, D>::type kf[RowPieces<T, D>::N], vf[RowPieces<T, D>::N];
 #pragma unroll
-    for (int s = 0; s < RowFrag<T, D>::N; ++s) {
+    for (int s = 0; s < RowPieces<T, D>::N; ++s) {
         load_row(k + base + k_tok * D, kf[s], s, half);
         load_row(v + base + k_tok * D, vf[s], s, half);
         vf[s] = negated(vf[s]);
@@ -464,7 +474,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
         // this lane's rows of a tile (slab wave + NL jj), and for the loads of lse and
         // delta row `lane`
         FlatRow at[MINE], at_row;
-        uint32_t chunk_off[MINE];
+        uint32_t chunk_off[MINE], tok[MINE], tok_row = 0;
 #pragma unroll
         for (int jj = 0; jj < MINE; ++jj) {
             const int row = Tile::RPS * (wave + NL * jj) + lane / Tile::LPR;
@@ -476,44 +486,59 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
             const bool past = r.blk >= listed;
             return list_s[past ? listed - 1 : r.blk] + pos_s[past ? b - 1 : r.tau];
         };
+        // rows of the next tile, looked up a tile before they are used
+        auto look_up = [&] {
+#pragma unroll
+            for (int jj = 0; jj < MINE; ++jj) {
+                tok[jj] = row_of(at[jj]);
+                at[jj].advance(step_q, step_r, b);
+            }
+            if (wave == 0) {
+                tok_row = row_of(at_row);
+                at_row.advance(step_q, step_r, b);
+            }
+        };
         auto gather_next = [&](int buf) {
 #pragma unroll
             for (int jj = 0; jj < MINE; ++jj) {
-                const uint64_t off = (uint64_t)row_of(at[jj]) * Tile::ROW_BYTES + chunk_off[jj];
+                const uint64_t off = (uint64_t)tok[jj] * Tile::ROW_BYTES + chunk_off[jj];
                 const uint32_t dst = (uint32_t)buf * Tile::TILE_BYTES +
                                      (uint32_t)(wave + NL * jj) * 1024u;
                 load_lds_16_at(qb + off, q_dst + dst);
                 load_lds_16_at(gb + off, g_dst + dst);
-                at[jj].advance(step_q, step_r, b);
             }
             if (wave == 0) {
-                const uint32_t row = row_of(at_row);
-                load_lds_4_at(lb + row, l_dst + (uint32_t)buf * 256u);
-                load_lds_4_at(db + row, d_dst + (uint32_t)buf * 256u);
-                at_row.advance(step_q, step_r, b);
+                load_lds_4_at(lb + tok_row, l_dst + (uint32_t)buf * 256u);
+                load_lds_4_at(db + tok_row, d_dst + (uint32_t)buf * 256u);
             }
+            look_up();
         };
-        if (wave < NL && tiles > 0) gather_next(0);
+        if (wave < NL && tiles > 0) {
+            look_up();
+            gather_next(0);
+        }
         for (int c = 0; c < tiles; ++c) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            wait_gathers();
             __syncthreads();
             const int buf = c & 1;
             if (wave < NL && c + 1 < tiles) gather_next(buf ^ 1);
 #pragma unroll
             for (int hh = 0; hh < KT / 32; ++hh) {
-                const unsigned char* qt = q_lds[buf] + 32 * hh * Tile::ROW_BYTES;
-                const unsigned char* gt = g_lds[buf] + 32 * hh * Tile::ROW_BYTES;
+                const uint32_t qt = q_dst + (uint32_t)buf * Tile::TILE_BYTES;
+                const uint32_t gt = g_dst + (uint32_t)buf * Tile::TILE_BYTES;
+                constexpr int HALF = 32 * Tile::ROW_BYTES;
                 const int left = total - (KT * c + 32 * hh);
                 if (left <= 0) break;
-                f32x16 p = dot_tile<D>(qt, kf, zero_tile(), l32, half);
-                f32x16 dp;
+                f32x16 p = zero_tile(), dp;
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     const float4 d4 = *(const float4*)(d_lds[buf] + 32 * hh + 8 * r4 + 4 * half);
                     dp[4 * r4] = d4.x; dp[4 * r4 + 1] = d4.y;
                     dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
                 }
-                dp = dot_tile<D>(gt, vf, dp, l32, half);
+                dot_tiles(rd, qt, gt, hh * HALF, kf, vf, p, dp);
+                ColumnPieces<T, D> c0;
+                read_columns(rd, gt, hh * HALF, 0, c0);
                 if (left < 32)
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
@@ -526,10 +551,11 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                     p[4 * r4 + 2] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 2], c2, -l4.z));
                     p[4 * r4 + 3] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 3], c2, -l4.w));
                 }
-                weighted_rows<D>((const T*)nullptr, gt, p, accv, lane);
+                weighted_rows(rd, gt, hh * HALF, c0, p, accv);
+                read_columns(rd, qt, hh * HALF, 0, c0);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) dp[r] *= p[r];
-                weighted_rows<D>((const T*)nullptr, qt, dp, acck, lane);
+                weighted_rows(rd, qt, hh * HALF, c0, dp, acck);
             }
         }
         if (!more) break;
@@ -557,17 +583,18 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
     if (BH * g.n_blocks * rows.chunks >= (int64_t)1 << 31) return hipErrorInvalidValue;
     const dim3 block(64 * nw), grid((unsigned)(BH * g.n_blocks * rows.chunks)),
         grid_kv((unsigned)(BKV * g.n_blocks * rows.chunks));
-    auto dq_kernel = nw >= 4 ? bwd_generic_dq<T, D, 4>
-                     : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
-    dq_kernel<<<grid, block, flat_table_bytes(g), stream>>>(
-        (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, sel_idx, (T*)dq, g,
-        (uint32_t)BKV, rows.chunks, 32 * nw);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    // dK and dV first: `order` may lie where dQ goes
     auto kv_kernel = nw >= 4 ? bwd_generic_dkdv<T, D, 4>
                      : nw >= 2 ? bwd_generic_dkdv<T, D, 2> : bwd_generic_dkdv<T, D, 1>;
     kv_kernel<<<grid_kv, block, sizeof(uint32_t) * (size_t)g.block_tokens, stream>>>(
         (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, conn, order, (T*)dk, (T*)dv, g,
+        (uint32_t)BKV, rows.chunks, 32 * nw);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    auto dq_kernel = nw >= 4 ? bwd_generic_dq<T, D, 4>
+                     : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
+    dq_kernel<<<grid, block, flat_table_bytes(g, g.n_select + 1), stream>>>(
+        (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, sel_idx, (T*)dq, g,
         (uint32_t)BKV, rows.chunks, 32 * nw);
     return hipGetLastError();
 }

@@ -729,31 +729,27 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
     const int nw = g.block_tokens / 32;
     const uint32_t sx = (uint32_t)(BH / g.kv_group);           // key/value slices
     const dim3 grid((unsigned)(BH * g.n_blocks)), grid_kv(sx * (unsigned)g.n_blocks), block(64 * nw);
+    // dK and dV first: `order` may lie where dQ goes
+#define BSA_DKDV(KERNEL)                                                                          \
+    KERNEL<<<grid_kv, block, 0, stream>>>(                                                        \
+        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2,  \
+        delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                                 \
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+#define BSA_DQ(KERNEL)                                                                            \
+    KERNEL<<<grid, block, 0, stream>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
+                                       (const uint16_t*)dout, lse2, delta, sel_idx, (uint16_t*)dq, \
+                                       g, sx);                                                    \
+    return hipGetLastError();
 #define BSA_LAUNCH(D_, NW_)                                                                       \
     if (D == D_ && nw == NW_) {                                                                   \
-        bwd_mfma_dq_d##D_##_w##NW_<<<grid, block, 0, stream>>>(                                   \
-            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, sel_idx, (uint16_t*)dq, g, sx);                                          \
-        if ((e = hipGetLastError()) != hipSuccess) return e;                                      \
-        bwd_mfma_dv_d##D_##_w##NW_<<<grid_kv, block, 0, stream>>>(                                   \
-            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
-        if ((e = hipGetLastError()) != hipSuccess) return e;                                      \
-        bwd_mfma_dk_d##D_##_w##NW_<<<grid_kv, block, 0, stream>>>(                                   \
-            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
-        return hipGetLastError();                                                                 \
+        BSA_DKDV(bwd_mfma_dv_d##D_##_w##NW_)                                                      \
+        BSA_DKDV(bwd_mfma_dk_d##D_##_w##NW_)                                                      \
+        BSA_DQ(bwd_mfma_dq_d##D_##_w##NW_)                                                        \
     }
 #define BSA_LAUNCH_FUSED(NW_)                                                                     \
     if (D == 64 && nw == NW_) {                                                                   \
-        bwd_mfma_dq_d64_w##NW_<<<grid, block, 0, stream>>>(                                       \
-            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, sel_idx, (uint16_t*)dq, g, sx);                                          \
-        if ((e = hipGetLastError()) != hipSuccess) return e;                                      \
-        bwd_mfma_dkdv_d64_w##NW_<<<grid_kv, block, 0, stream>>>(                                     \
-            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,    \
-            lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                              \
-        return hipGetLastError();                                                                 \
+        BSA_DKDV(bwd_mfma_dkdv_d64_w##NW_)                                                        \
+        BSA_DQ(bwd_mfma_dq_d64_w##NW_)                                                            \
     }
     BSA_LAUNCH_FUSED(2)
     BSA_LAUNCH_FUSED(4)
@@ -762,6 +758,8 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
     BSA_LAUNCH(128, 4)
     BSA_LAUNCH(128, 8)
 #undef BSA_LAUNCH
+#undef BSA_DKDV
+#undef BSA_DQ
     return hipErrorInvalidValue;
 }
 

@@ -33,6 +33,29 @@ struct Geom {
     const float* add_dv;
 };
 
+// What a forward launch computes over its q, k, v: one or two sets of block lists,
+// each with its own output (the selection and the local branch of the three-branch
+// form run side by side: two small launches would leave the chip half empty twice).
+// Workgroups below n_first belong to job 0, the others to job 1.
+struct FwdJob {
+    const int32_t* lists;   // int32 [slices, m, n_select]
+    void* out;
+    float* lse;             // or null
+    int32_t n_select, list_only;    // see Geom
+};
+// The jobs as kernel arguments: the pointers one by one (behind a struct the compiler
+// no longer knows them as global memory and uses flat accesses, which count as LDS
+// accesses in the waits).
+struct FwdShape {
+    int32_t n_select[2], list_only[2];
+    uint32_t n_first;
+};
+#define BSA_FWD_JOB_PARAMS(T)                                                                   \
+    const int32_t *__restrict__ lists0, const int32_t *__restrict__ lists1,                     \
+        T *__restrict__ out0, T *__restrict__ out1, float *__restrict__ lse0,                   \
+        float *__restrict__ lse1, FwdShape jobs
+#define BSA_FWD_JOB_ARGS lists0, lists1, out0, out1, lse0, lse1, jobs
+
 // out = v, or in accumulate mode (extra != null) out = old + v + extra[0..3] * inv_b
 template <typename T>
 __device__ __forceinline__ void store4_or_add(T* p, float4 v, const float* extra, float inv_b);

@@ -17,11 +17,9 @@ namespace bsa {
 
 constexpr int kListTable = 1024;           // listed blocks the LDS table holds
 
-// LDS of both tables for the attended blocks of one query block (at most 8 KiB:
-// b <= 1024)
-inline size_t flat_table_bytes(const Geom& g)
+// LDS of both tables for `listed` attended blocks (at most 8 KiB: b <= 1024)
+inline size_t flat_table_bytes(const Geom& g, int listed)
 {
-    const int listed = g.n_select + 1;
     return sizeof(uint32_t) * (size_t)(g.block_tokens + (listed < kListTable ? listed : kListTable));
 }
 
@@ -112,108 +110,247 @@ __device__ __forceinline__ f32x16 zero_tile()
     return z;
 }
 
-// acc + X Y^T for 32 tile rows X and 32 stationary rows Y: this lane's column is
-// its stationary row yf (bf16: B operands of the 16-channel steps; fp32: the
-// channels 8 j + 4 half + 0..3), register r is tile row 8 (r/4) + 4 half + r%4.
-template <int D>
-__device__ __forceinline__ f32x16 dot_tile(const unsigned char* x_rows, const bf16x8 (&yf)[D / 16],
-                                           f32x16 acc, int l32, int half)
+// Where a lane reads a 32-row tile in LDS.  The swizzle leaves few distinct
+// addresses per lane: everything else is a constant that goes into the read's
+// offset field.  (Written out because the compiler otherwise keeps an address
+// register per read, which at 64 fp32 channels no longer fits: it spilled them, and
+// a reload from scratch memory waits for every gather in flight.)
+template <typename T, int D> struct TileReader;
+
+template <typename V>
+__device__ __forceinline__ V lds_read(uint32_t addr, int imm)
 {
-    using Tile = FlatTile<uint16_t, D>;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-        const bf16x8 xf = *(const bf16x8*)(x_rows + l32 * Tile::ROW_BYTES +
-                                           Tile::swz(l32, 2 * ks + half) * 16);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, yf[ks], acc, 0, 0, 0);
-    }
-    return acc;
-}
-template <int D>
-__device__ __forceinline__ f32x16 dot_tile(const unsigned char* x_rows, const float4 (&yf)[D / 8],
-                                           f32x16 acc, int l32, int half)
-{
-    using Tile = FlatTile<float, D>;
-#pragma unroll
-    for (int j = 0; j < D / 8; ++j) {
-        const float4 xf = *(const float4*)(x_rows + l32 * Tile::ROW_BYTES +
-                                           Tile::swz(l32, 2 * j + half) * 16);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.x, yf[j].x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.y, yf[j].y, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.z, yf[j].z, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.w, yf[j].w, acc, 0, 0, 0);
-    }
-    return acc;
+    return *(const __attribute__((address_space(3))) V*)(uintptr_t)(addr + (uint32_t)imm);
 }
 
-// acc^T += X^T W^T for 32 tile rows X: channels x this lane's column; w: the
-// column's weights of the 32 rows in the accumulator layout of dot_tile, which is
-// the B operand as it stands.
-template <int D>
-__device__ __forceinline__ void weighted_rows(const uint16_t*, const unsigned char* x_rows,
-                                              const f32x16& w, f32x16 (&acc)[D / 32], int lane)
-{
+template <int D> struct TileReader<uint16_t, D> {
     using Tile = FlatTile<uint16_t, D>;
-    const int s16 = lane & 15, gq = lane >> 4;
+    static constexpr int STEPS = D / 16, BASES = STEPS < 4 ? STEPS : 4;
+    static constexpr int WBASES = D == 32 ? 1 : 2;
+    uint32_t row[BASES];        // chunk 2 s + half of row l32, s < BASES
+    uint32_t trans[WBASES];     // transposing read of channels 32 dt, dt < WBASES
+    __device__ __forceinline__ void init(int lane)
+    {
+        const int l32 = lane & 31, half = lane >> 5, s16 = lane & 15, gq = lane >> 4;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        uint32_t hi[4], lo[4];
+        for (int s = 0; s < BASES; ++s)
+            row[s] = (uint32_t)(l32 * Tile::ROW_BYTES + Tile::swz(l32, 2 * s + half) * 16);
+        // source lane s16 of 16-lane group gq supplies 8 bytes of row
+        // 4 (gq/2) + s16/4 (+ 16 h + 8 rd), channel 16 (gq%2) + 4 (s16%4) + 32 dt
+        const int r = 4 * (gq >> 1) + (s16 >> 2);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            split_bf16(w[8 * h + 2 * e], w[8 * h + 2 * e + 1], hi[e], lo[e]);
-        const bf16x8 w_hi = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
-        const bf16x8 w_lo = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt) {
-            // transposing read: source lane s of 16-lane group gq supplies 8 bytes
-            // of X[16 h + 8 rd + 4 (gq/2) + s/4][32 dt + 16 (gq%2) + 4 (s%4)]
+        for (int dt = 0; dt < WBASES; ++dt) {
             const int col = 16 * (gq & 1) + 4 * (s16 & 3) + 32 * dt;
-            bf16x4 part[2];
-#pragma unroll
-            for (int rd = 0; rd < 2; ++rd) {
-                const int row = 16 * h + 8 * rd + 4 * (gq >> 1) + (s16 >> 2);
-                const unsigned char* src = x_rows + row * Tile::ROW_BYTES +
-                                           Tile::swz(row, col >> 3) * 16 + (col & 7) * 2;
-                part[rd] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, src));
-            }
-            const bf16x8 xf = __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
-            acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, w_hi, acc[dt], 0, 0, 0);
-            acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, w_lo, acc[dt], 0, 0, 0);
+            trans[dt] = (uint32_t)(r * Tile::ROW_BYTES + Tile::swz(r, col >> 3) * 16 + (col & 7) * 2);
         }
+    }
+};
+template <int D> struct TileReader<float, D> {
+    using Tile = FlatTile<float, D>;
+    static constexpr int BASES = 4;
+    uint32_t row[BASES];        // chunk 2 s + half of row l32, s < 4
+    uint32_t col[4];            // channel l32 of row 4 half + r, r < 4
+    __device__ __forceinline__ void init(int lane)
+    {
+        const int l32 = lane & 31, half = lane >> 5;
+#pragma unroll
+        for (int s = 0; s < BASES; ++s)
+            row[s] = (uint32_t)(l32 * Tile::ROW_BYTES + Tile::swz(l32, 2 * s + half) * 16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int rr = 4 * half + r;
+            col[r] = (uint32_t)(rr * Tile::ROW_BYTES + Tile::swz(rr, l32 >> 2) * 16 + (l32 & 3) * 4);
+        }
+    }
+};
+
+// Products of a 32-row tile.  LDS reads are issued a group ahead of the matrix
+// instructions that use them, and held there (sched_barrier): the compiler would
+// reuse one group's registers and expose the read latency between groups.
+//
+// Row products, acc + X Y^T: this lane's column is its stationary row (y: its
+// pieces), accumulator register r is tile row 8 (r/4) + 4 half + r%4.  A piece is 16
+// channels in bf16, 8 in fp32 (channels 8 s + 4 half + 0..3 of each lane).
+template <typename T, int D> struct RowPieces;
+template <int D> struct RowPieces<uint16_t, D> {
+    typedef bf16x8 type;
+    static constexpr int N = D / 16, GROUP = N < 4 ? N : 4;
+};
+template <int D> struct RowPieces<float, D> {
+    typedef f32x4 type;
+    static constexpr int N = D / 8, GROUP = 4;
+};
+
+template <typename T, int D>
+__device__ __forceinline__ void read_rows(const TileReader<T, D>& rd, uint32_t tile, int imm, int group,
+                                          typename RowPieces<T, D>::type (&x)[RowPieces<T, D>::GROUP])
+{
+    typedef typename RowPieces<T, D>::type V;
+#pragma unroll
+    for (int u = 0; u < RowPieces<T, D>::GROUP; ++u) {
+        const int s = group * RowPieces<T, D>::GROUP + u;
+        x[u] = lds_read<V>(rd.row[s % rd.BASES] + tile, imm + (s / rd.BASES) * 128);
+    }
+}
+__device__ __forceinline__ f32x16 mul_piece(bf16x8 x, bf16x8 y, f32x16 acc)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mul_piece(f32x4 x, f32x4 y, f32x16 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc, 0, 0, 0);
+}
+
+// acc + X Y^T.  tile: LDS address of the tile (uniform), imm: constant to add.
+template <typename T, int D>
+__device__ __forceinline__ f32x16 dot_tile(
+    const TileReader<T, D>& rd, uint32_t tile, int imm,
+    const typename RowPieces<T, D>::type (&y)[RowPieces<T, D>::N], f32x16 acc)
+{
+    constexpr int G = RowPieces<T, D>::GROUP, GROUPS = RowPieces<T, D>::N / G;
+    typename RowPieces<T, D>::type x[2][G];
+    read_rows(rd, tile, imm, 0, x[0]);
+#pragma unroll
+    for (int gr = 0; gr < GROUPS; ++gr) {
+        if (gr + 1 < GROUPS) read_rows(rd, tile, imm, gr + 1, x[(gr + 1) & 1]);
+        if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < G; ++u) acc = mul_piece(x[gr & 1][u], y[gr * G + u], acc);
+        if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+    }
+    return acc;
+}
+// Two row products side by side (two independent accumulation chains).
+template <typename T, int D>
+__device__ __forceinline__ void dot_tiles(
+    const TileReader<T, D>& rd, uint32_t tile_a, uint32_t tile_b, int imm,
+    const typename RowPieces<T, D>::type (&ya)[RowPieces<T, D>::N],
+    const typename RowPieces<T, D>::type (&yb)[RowPieces<T, D>::N], f32x16& acc_a, f32x16& acc_b)
+{
+    constexpr int G = RowPieces<T, D>::GROUP, GROUPS = RowPieces<T, D>::N / G;
+    typename RowPieces<T, D>::type a[2][G], b[2][G];
+    read_rows(rd, tile_a, imm, 0, a[0]);
+    read_rows(rd, tile_b, imm, 0, b[0]);
+#pragma unroll
+    for (int gr = 0; gr < GROUPS; ++gr) {
+        if (gr + 1 < GROUPS) {
+            read_rows(rd, tile_a, imm, gr + 1, a[(gr + 1) & 1]);
+            read_rows(rd, tile_b, imm, gr + 1, b[(gr + 1) & 1]);
+        }
+        if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            acc_a = mul_piece(a[gr & 1][u], ya[gr * G + u], acc_a);
+            acc_b = mul_piece(b[gr & 1][u], yb[gr * G + u], acc_b);
+        }
+        if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Weighted row sums, acc^T += X^T W^T: channels x this lane's column; w: the
+// column's weights of the 32 rows in the accumulator layout of dot_tile, which is
+// the B operand as it stands.  Groups: 16 rows in bf16, 8 in fp32.  The caller
+// reads group 0 (read_columns) before it computes the weights.
+template <typename T, int D> struct ColumnPieces;
+template <int D> struct ColumnPieces<uint16_t, D> {
+    static constexpr int GROUPS = 2;
+    bf16x8 x[D / 32];                       // A operand: channels 32 dt .. x 16 rows
+};
+template <int D> struct ColumnPieces<float, D> {
+    static constexpr int GROUPS = 4;
+    float x[4][D / 32];                     // row 4 half + r, channel 32 dt + l32
+};
+template <int D>
+__device__ __forceinline__ void read_columns(const TileReader<uint16_t, D>& rd, uint32_t tile, int imm,
+                                             int group, ColumnPieces<uint16_t, D>& c)
+{
+    constexpr int ROW = FlatTile<uint16_t, D>::ROW_BYTES;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+        bf16x4 part[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+            part[r] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                (__attribute__((address_space(3))) bf16x4*)(uintptr_t)(
+                    rd.trans[dt % rd.WBASES] + tile +
+                    (uint32_t)(imm + (16 * group + 8 * r) * ROW + (dt / rd.WBASES) * 128)));
+        c.x[dt] = __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
     }
 }
 template <int D>
-__device__ __forceinline__ void weighted_rows(const float*, const unsigned char* x_rows,
-                                              const f32x16& w, f32x16 (&acc)[D / 32], int lane)
+__device__ __forceinline__ void read_columns(const TileReader<float, D>& rd, uint32_t tile, int imm,
+                                             int group, ColumnPieces<float, D>& c)
 {
-    using Tile = FlatTile<float, D>;
-    const int l32 = lane & 31, half = lane >> 5;
+    constexpr int ROW = FlatTile<float, D>::ROW_BYTES;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r >> 2) + 4 * half + (r & 3);
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt) {
-            const int chunk = 8 * dt + (l32 >> 2);
-            const float x = *(const float*)(x_rows + row * Tile::ROW_BYTES +
-                                            Tile::swz(row, chunk) * 16 + (l32 & 3) * 4);
-            acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, w[r], acc[dt], 0, 0, 0);
-        }
+        for (int dt = 0; dt < D / 32; ++dt)
+            c.x[r][dt] = lds_read<float>(rd.col[r] + tile, imm + 8 * group * ROW + 128 * dt);
+}
+template <int D>
+__device__ __forceinline__ void add_columns(const ColumnPieces<uint16_t, D>& c, const f32x16& w,
+                                            int group, f32x16 (&acc)[D / 32])
+{
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        split_bf16(w[8 * group + 2 * e], w[8 * group + 2 * e + 1], hi[e], lo[e]);
+    const bf16x8 w_hi = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+    const bf16x8 w_lo = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.x[dt], w_hi, acc[dt], 0, 0, 0);
+        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.x[dt], w_lo, acc[dt], 0, 0, 0);
     }
+}
+template <int D>
+__device__ __forceinline__ void add_columns(const ColumnPieces<float, D>& c, const f32x16& w, int group,
+                                            f32x16 (&acc)[D / 32])
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+            acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(c.x[r][dt], w[4 * group + r], acc[dt], 0, 0,
+                                                           0);
+}
+template <typename T, int D>
+__device__ __forceinline__ void weighted_rows(const TileReader<T, D>& rd, uint32_t tile, int imm,
+                                              ColumnPieces<T, D>& first, const f32x16& w,
+                                              f32x16 (&acc)[D / 32])
+{
+    constexpr int GROUPS = ColumnPieces<T, D>::GROUPS;
+    ColumnPieces<T, D> second;
+#pragma unroll
+    for (int gr = 0; gr < GROUPS; ++gr) {
+        ColumnPieces<T, D>&cur = gr & 1 ? second : first, &nxt = gr & 1 ? first : second;
+        if (gr + 1 < GROUPS) read_columns(rd, tile, imm, gr + 1, nxt);
+        if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+        add_columns(cur, w, gr, acc);
+        if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Waits for this wavefront's direct-to-LDS loads in a form that the compiler
+// accounts for: it then knows that loads it issued itself are done as well and
+// does not wait for them (and for the gathers issued since) inside the loop.
+__device__ __forceinline__ void wait_gathers()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
 }
 
 __device__ __forceinline__ void load_row(const uint16_t* row, bf16x8& f, int step, int half)
 {
     f = *(const bf16x8*)(row + 16 * step + 8 * half);
 }
-__device__ __forceinline__ void load_row(const float* row, float4& f, int step, int half)
+__device__ __forceinline__ void load_row(const float* row, f32x4& f, int step, int half)
 {
-    f = *(const float4*)(row + 8 * step + 4 * half);
+    f = *(const f32x4*)(row + 8 * step + 4 * half);
 }
-
-// A stationary row as the operand of dot_tile: 16-byte pieces of the lane's half.
-template <typename T, int D> struct RowFrag;
-template <int D> struct RowFrag<uint16_t, D> { typedef bf16x8 type; static constexpr int N = D / 16; };
-template <int D> struct RowFrag<float, D> { typedef float4 type; static constexpr int N = D / 8; };
-
 
 // Padding of the last tile: register r of a 32-row tile with `left` rows is a row
 // past the end.
@@ -228,9 +365,9 @@ __device__ __forceinline__ bf16x8 negated(bf16x8 x)
     u.x ^= 0x80008000u; u.y ^= 0x80008000u; u.z ^= 0x80008000u; u.w ^= 0x80008000u;
     return __builtin_bit_cast(bf16x8, u);
 }
-__device__ __forceinline__ float4 negated(float4 x)
+__device__ __forceinline__ f32x4 negated(f32x4 x)
 {
-    return make_float4(-x.x, -x.y, -x.z, -x.w);
+    return -x;
 }
 
 // Stores this lane's column of D channels (accumulators of weighted_rows), scaled
@@ -266,7 +403,8 @@ struct AttendedKeys {
     int b, n, step_q, step_r, wave;
     const int32_t* sel_row;
     const uint32_t *pos_s, *first_s;
-    FlatRow at[MINE];               // this lane's row of slab wave + NL j of the next tile
+    FlatRow at[MINE];               // this lane's row of slab wave + NL j of the tile after
+    uint32_t tok[MINE];             // token of its row of the next tile
     uint32_t chunk_off[MINE];
 
     // Fills the LDS tables (flat_table_bytes); a barrier has to follow.
@@ -310,24 +448,36 @@ struct AttendedKeys {
         }
     }
 
-    // Gathers the next tile of both tensors (kb, vb: their slices; k_dst, v_dst: LDS
-    // addresses of the tiles) and moves on.  Rows past the end repeat the last row;
-    // they carry no weight.
-    __device__ __forceinline__ void gather_next(const unsigned char* kb, const unsigned char* vb,
-                                                uint32_t k_dst, uint32_t v_dst)
+    // Looks up the rows of the next tile and moves on: once after the barrier, then
+    // from gather_next, i.e. a whole tile before the tokens are used.  Rows past the
+    // end repeat the last row; they carry no weight.
+    __device__ __forceinline__ void look_up()
     {
 #pragma unroll
         for (int j = 0; j < MINE; ++j) {
             const bool past = at[j].blk > n;
             const int blk = past ? n : at[j].blk, tau = past ? b - 1 : at[j].tau;
-            const uint32_t org = blk < kListTable ? first_s[blk]
-                                                  : block_first_token(*geom, sel_row[blk - 1]);
-            const uint64_t off = (uint64_t)(org + pos_s[tau]) * Tile::ROW_BYTES + chunk_off[j];
+            const uint32_t org = n < kListTable || blk < kListTable
+                                     ? first_s[blk]
+                                     : block_first_token(*geom, sel_row[blk - 1]);
+            tok[j] = org + pos_s[tau];
+            at[j].advance(step_q, step_r, b);
+        }
+    }
+
+    // Gathers the next tile of both tensors (kb, vb: their slices; k_dst, v_dst: LDS
+    // addresses of the tiles).
+    __device__ __forceinline__ void gather_next(const unsigned char* kb, const unsigned char* vb,
+                                                uint32_t k_dst, uint32_t v_dst)
+    {
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const uint64_t off = (uint64_t)tok[j] * Tile::ROW_BYTES + chunk_off[j];
             const uint32_t dst = (uint32_t)(wave + NL * j) * 1024u;
             load_lds_16_at(kb + off, k_dst + dst);
             load_lds_16_at(vb + off, v_dst + dst);
-            at[j].advance(step_q, step_r, b);
         }
+        look_up();
     }
 
 private:

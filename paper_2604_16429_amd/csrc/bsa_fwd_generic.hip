@@ -41,10 +41,16 @@ namespace bsa {
 template <typename T, int D, int NL>
 __global__ __launch_bounds__(NL == 4 ? 512 : NL == 2 ? 192 : 64, NL == 1 || (NL == 2 && D == 128) ? 1 : D == 32 ? 4 : 2)
 void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                        const int32_t* __restrict__ sel_idx, T* __restrict__ out,
-                        float* __restrict__ lse, Geom g, uint32_t n_units, int row_chunks,
-                        int chunk_rows)
+                        BSA_FWD_JOB_PARAMS(T), Geom g, uint32_t n_units, int row_chunks, int chunk_rows)
 {
+    // this workgroup's job, and its number inside the job
+    const bool second_job = blockIdx.x >= jobs.n_first;
+    const uint32_t wg = second_job ? blockIdx.x - jobs.n_first : blockIdx.x;
+    const int32_t* __restrict__ sel_idx = second_job ? lists1 : lists0;
+    T* __restrict__ out = second_job ? out1 : out0;
+    float* __restrict__ lse = second_job ? lse1 : lse0;
+    g.n_select = jobs.n_select[second_job ? 1 : 0];
+    g.list_only = jobs.list_only[second_job ? 1 : 0];
     using Tile = FlatTile<T, D>;
     constexpr int KT = Tile::KT;
     __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][Tile::TILE_BYTES];
@@ -58,11 +64,13 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 
     int item;
     int64_t bh_idx;
-    map_workgroup(g, blockIdx.x, (uint32_t)(g.n_blocks * row_chunks), n_units, bh_idx, item);
+    map_workgroup(g, wg, (uint32_t)(g.n_blocks * row_chunks), n_units, bh_idx, item);
     const int i = item / row_chunks;
     const int row0 = (item - i * row_chunks) * chunk_rows;
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
+    TileReader<T, D> rd;
+    rd.init(lane);
     AttendedKeys<T, D, NL> keys;
     keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave);
 
@@ -70,15 +78,18 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     const int tau_q = row0 + 32 * wave + l32;
     const bool valid = tau_q < min(b, row0 + chunk_rows);
     const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
-    typename RowFrag<T, D>::type qf[RowFrag<T, D>::N];
+    typename RowPieces<T, D>::type qf[RowPieces<T, D>::N];
 #pragma unroll
-    for (int s = 0; s < RowFrag<T, D>::N; ++s) load_row(q + base + q_tok * D, qf[s], s, half);
+    for (int s = 0; s < RowPieces<T, D>::N; ++s) load_row(q + base + q_tok * D, qf[s], s, half);
     __syncthreads();                                 // tables
 
     const unsigned char* kb = (const unsigned char*)(k + kv_base);
     const unsigned char* vb = (const unsigned char*)(v + kv_base);
     const uint32_t k_dst = lds_address(k_lds), v_dst = lds_address(v_lds);
-    if (wave < NL) keys.gather_next(kb, vb, k_dst, v_dst);
+    if (wave < NL) {
+        keys.look_up();
+        keys.gather_next(kb, vb, k_dst, v_dst);
+    }
 
     const float c2 = g.scale * 1.4426950408889634f;
     f32x16 oacc[D / 32];
@@ -88,15 +99,14 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 
     for (int c = 0; c < keys.tiles; ++c) {
         // tile c has landed and everyone is done with the other buffer
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        wait_gathers();
         __syncthreads();
         const int buf = c & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
         if (wave < NL && c + 1 < keys.tiles) keys.gather_next(kb, vb, k_dst + other, v_dst + other);
-        const unsigned char* kt = k_lds[buf];
-        const unsigned char* vt = v_lds[buf];
+        const uint32_t at = (uint32_t)buf * Tile::TILE_BYTES;
 #pragma unroll
         for (int hh = 0; hh < KT / 32; ++hh) {
-            f32x16 s = dot_tile<D>(kt + 32 * hh * Tile::ROW_BYTES, qf, zero_tile(), l32, half);
+            f32x16 s = dot_tile(rd, k_dst + at, 32 * hh * Tile::ROW_BYTES, qf, zero_tile());
             const int left = keys.total - (KT * c + 32 * hh);     // keys from this half tile on
             if (left < 32) {
                 if (left <= 0) break;
@@ -104,6 +114,8 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 for (int r = 0; r < 16; ++r)
                     if (past_end(r, half, left)) s[r] = -INFINITY;
             }
+            ColumnPieces<T, D> v0;
+            read_columns(rd, v_dst + at, 32 * hh * Tile::ROW_BYTES, 0, v0);
             f32x16 p;
             float rs0 = 0.0f, rs1 = 0.0f;
 #pragma unroll
@@ -136,7 +148,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 }
             }
             l_run += rs;
-            weighted_rows<D>((const T*)nullptr, vt + 32 * hh * Tile::ROW_BYTES, p, oacc, lane);
+            weighted_rows(rd, v_dst + at, 32 * hh * Tile::ROW_BYTES, v0, p, oacc);
         }
     }
 
@@ -151,28 +163,33 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 }
 
 template <typename T, int D>
-static hipError_t launch_t(const void* q, const void* k, const void* v, const int32_t* sel_idx,
-                           void* out, float* lse, const Geom& g, int64_t BH, hipStream_t stream)
+static hipError_t launch_t(const void* q, const void* k, const void* v, const FwdJob* jobs,
+                           int n_jobs, const Geom& g, int64_t BH, hipStream_t stream)
 {
     const RowSplit rows(g.block_tokens, 8);
     const int nw = rows.waves;
-    if (BH * g.n_blocks * rows.chunks >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(BH * g.n_blocks * rows.chunks)), block(64 * nw);
     auto kernel = nw >= 4 ? fwd_generic_kernel<T, D, 4>
                   : nw >= 2 ? fwd_generic_kernel<T, D, 2> : fwd_generic_kernel<T, D, 1>;
-    kernel<<<grid, block, flat_table_bytes(g), stream>>>((const T*)q, (const T*)k, (const T*)v, sel_idx, (T*)out, lse,
-                                       g, (uint32_t)(BH / g.kv_group), rows.chunks, 32 * nw);
-    return hipGetLastError();
+    int listed = 0;
+    for (int j = 0; j < n_jobs; ++j)
+        listed = jobs[j].n_select + 1 > listed ? jobs[j].n_select + 1 : listed;
+    return launch_jobs(jobs, n_jobs, BH * g.n_blocks * rows.chunks, 64 * nw,
+                       [&](const FwdJob& a, const FwdJob& b, const FwdShape& j, unsigned grid) {
+                           kernel<<<dim3(grid), dim3(64 * nw), flat_table_bytes(g, listed), stream>>>(
+                               (const T*)q, (const T*)k, (const T*)v, a.lists, b.lists, (T*)a.out,
+                               (T*)b.out, a.lse, b.lse, j, g,
+                               (uint32_t)(BH / g.kv_group), rows.chunks, 32 * nw);
+                       });
 }
 
 hipError_t launch_fwd_generic(bool is_bf16, const void* q, const void* k, const void* v,
-                              const int32_t* sel_idx, void* out, float* lse, const Geom& g, int D,
-                              int64_t BH, hipStream_t stream)
+                              const FwdJob* jobs, int n_jobs, const Geom& g, int D, int64_t BH,
+                              hipStream_t stream)
 {
-#define BSA_CASE(DD)                                                                          \
-    case DD:                                                                                  \
-        return is_bf16 ? launch_t<uint16_t, DD>(q, k, v, sel_idx, out, lse, g, BH, stream)    \
-                       : launch_t<float, DD>(q, k, v, sel_idx, out, lse, g, BH, stream);
+#define BSA_CASE(DD)                                                                    \
+    case DD:                                                                            \
+        return is_bf16 ? launch_t<uint16_t, DD>(q, k, v, jobs, n_jobs, g, BH, stream)   \
+                       : launch_t<float, DD>(q, k, v, jobs, n_jobs, g, BH, stream);
     switch (D) {
         BSA_CASE(32)
         BSA_CASE(64)

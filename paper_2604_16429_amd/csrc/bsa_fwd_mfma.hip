@@ -222,11 +222,17 @@ template <int S> struct SetTag { static constexpr int value = S; };
 template <int NW, int DEPTH>
 __device__ __forceinline__ void fwd_mfma_d64_body(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-    const uint16_t* __restrict__ v, const int32_t* __restrict__ sel_idx,
-    uint16_t* __restrict__ out, float* __restrict__ lse, const Geom& g, uint32_t n_units,
-    int subs)
+    const uint16_t* __restrict__ v, BSA_FWD_JOB_PARAMS(uint16_t), Geom g, uint32_t n_units, int subs)
 {
     constexpr int D = 64;
+    // this workgroup's job, and its number inside the job
+    const bool second_job = blockIdx.x >= jobs.n_first;
+    const uint32_t wg = second_job ? blockIdx.x - jobs.n_first : blockIdx.x;
+    const int32_t* __restrict__ sel_idx = second_job ? lists1 : lists0;
+    uint16_t* __restrict__ out = second_job ? out1 : out0;
+    float* __restrict__ lse = second_job ? lse1 : lse0;
+    g.n_select = jobs.n_select[second_job ? 1 : 0];
+    g.list_only = jobs.list_only[second_job ? 1 : 0];
     static_assert(NW == 1 || NW == 2 || NW == 4, "8 loads per refill step, split between waves");
     auto wg_barrier = [] { if (NW > 1) __builtin_amdgcn_s_barrier(); };
     static_assert(DEPTH == 1 || (DEPTH == 2 && NW > 1), "one K/V tile in LDS, or two (even pair counts only)");
@@ -277,7 +283,7 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
     {
         const int groups = subs / NW;
         int item;
-        map_workgroup(g, blockIdx.x, (uint32_t)(g.n_blocks * groups), n_units, bh_idx, item);
+        map_workgroup(g, wg, (uint32_t)(g.n_blocks * groups), n_units, bh_idx, item);
         i = item / groups;
         qsub = (item - i * groups) * NW + wave;
     }
@@ -616,11 +622,10 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
 #define BSA_FWD_D64_KERNEL(NAME, NW, DEPTH)                                                       \
     __global__ __launch_bounds__(64 * NW, 2) void NAME(                                           \
         const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,                           \
-        const uint16_t* __restrict__ v, const int32_t* __restrict__ sel_idx,                      \
-        uint16_t* __restrict__ out, float* __restrict__ lse, Geom g, uint32_t n_units,            \
+        const uint16_t* __restrict__ v, BSA_FWD_JOB_PARAMS(uint16_t), Geom g, uint32_t n_units,   \
         int subs)                                                                                 \
     {                                                                                             \
-        fwd_mfma_d64_body<NW, DEPTH>(q, k, v, sel_idx, out, lse, g, n_units, subs);               \
+        fwd_mfma_d64_body<NW, DEPTH>(q, k, v, BSA_FWD_JOB_ARGS, g, n_units, subs);                \
     }
 BSA_FWD_D64_KERNEL(fwd_mfma_b64_d64_kernel, 1, 1)
 BSA_FWD_D64_KERNEL(fwd_mfma_d64_wg2_kernel, 2, 2)
@@ -638,22 +643,23 @@ bool fwd_mfma_supported(bool is_bf16, const Geom& g, int D)
            g.n_tokens * D * 2 < ((int64_t)1 << 31);
 }
 
-hipError_t launch_fwd_mfma(const void* q, const void* k, const void* v, const int32_t* sel_idx,
-                           void* out, float* lse, const Geom& g, int D, int64_t BH,
-                           hipStream_t stream)
+hipError_t launch_fwd_mfma(const void* q, const void* k, const void* v, const FwdJob* jobs,
+                           int n_jobs, const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
     (void)D;
     const int subs = g.block_tokens / 64;
     // the sub-blocks of a query block share their K/V tiles in LDS, four or two
     // to a workgroup when the count allows
     const int nw = subs % 4 == 0 ? 4 : subs % 2 == 0 ? 2 : 1;
-    dim3 grid((unsigned)(BH * g.n_blocks * (subs / nw)));
     auto kernel = nw == 4 ? fwd_mfma_d64_wg4_kernel
                   : nw == 2 ? fwd_mfma_d64_wg2_kernel : fwd_mfma_b64_d64_kernel;
-    kernel<<<grid, dim3(64 * nw), 0, stream>>>((const uint16_t*)q, (const uint16_t*)k,
-                                               (const uint16_t*)v, sel_idx, (uint16_t*)out, lse, g,
-                                               (uint32_t)(BH / g.kv_group), subs);
-    return hipGetLastError();
+    return launch_jobs(jobs, n_jobs, BH * g.n_blocks * (subs / nw), 64 * nw,
+                       [&](const FwdJob& a, const FwdJob& b, const FwdShape& j, unsigned grid) {
+                           kernel<<<dim3(grid), dim3(64 * nw), 0, stream>>>(
+                               (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, a.lists,
+                               b.lists, (uint16_t*)a.out, (uint16_t*)b.out, a.lse, b.lse, j, g,
+                               (uint32_t)(BH / g.kv_group), subs);
+                       });
 }
 
 }  // namespace bsa

@@ -67,10 +67,17 @@ __device__ __forceinline__ int swz(int row, int chunk)
 template <int D, int NW>
 __device__ __forceinline__ void fwd_mfma_q32_body(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-    const uint16_t* __restrict__ v, const int32_t* __restrict__ sel_idx,
-    uint16_t* __restrict__ out, float* __restrict__ lse, const Geom& g, uint32_t n_units)
+    const uint16_t* __restrict__ v, BSA_FWD_JOB_PARAMS(uint16_t), Geom g, uint32_t n_units)
 {
     using namespace q32;
+    // this workgroup's job, and its number inside the job
+    const bool second_job = blockIdx.x >= jobs.n_first;
+    const uint32_t wg = second_job ? blockIdx.x - jobs.n_first : blockIdx.x;
+    const int32_t* __restrict__ sel_idx = second_job ? lists1 : lists0;
+    uint16_t* __restrict__ out = second_job ? out1 : out0;
+    float* __restrict__ lse = second_job ? lse1 : lse0;
+    g.n_select = jobs.n_select[second_job ? 1 : 0];
+    g.list_only = jobs.list_only[second_job ? 1 : 0];
     constexpr int ROW_BYTES = D * 2;               // one token row of K or V in LDS
     constexpr int HALF_BYTES = 32 * ROW_BYTES;
     constexpr int KS = D / 16;                     // k-steps of S^T = K Q^T
@@ -97,7 +104,7 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
     // the XCDs whole (map_workgroup).
     int i;
     int64_t bh_idx;
-    map_workgroup(g, blockIdx.x, (uint32_t)g.n_blocks, n_units, bh_idx, i);
+    map_workgroup(g, wg, (uint32_t)g.n_blocks, n_units, bh_idx, i);
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
     // The attended blocks: block i itself followed by its selected blocks, or,
@@ -477,10 +484,9 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
 #define BSA_FWD_D128_KERNEL(NAME, NW_)                                                            \
     __global__ __launch_bounds__(64 * NW_, 2) void NAME(                                          \
         const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,                           \
-        const uint16_t* __restrict__ v, const int32_t* __restrict__ sel_idx,                      \
-        uint16_t* __restrict__ out, float* __restrict__ lse, Geom g, uint32_t n_units)            \
+        const uint16_t* __restrict__ v, BSA_FWD_JOB_PARAMS(uint16_t), Geom g, uint32_t n_units)   \
     {                                                                                             \
-        fwd_mfma_q32_body<128, NW_>(q, k, v, sel_idx, out, lse, g, n_units);                      \
+        fwd_mfma_q32_body<128, NW_>(q, k, v, BSA_FWD_JOB_ARGS, g, n_units);                       \
     }
 BSA_FWD_D128_KERNEL(fwd_mfma_d128_kernel, 4)
 BSA_FWD_D128_KERNEL(fwd_mfma_d128_w2_kernel, 2)
@@ -498,18 +504,19 @@ bool fwd_mfma_d128_supported(bool is_bf16, const Geom& g, int D)
            (g.block_w & (g.block_w - 1)) == 0 && g.block_w >= 4 && g.n_tokens * D * 2 < ((int64_t)1 << 31);
 }
 
-hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v,
-                                const int32_t* sel_idx, void* out, float* lse, const Geom& g,
-                                int64_t BH, hipStream_t stream)
+hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v, const FwdJob* jobs,
+                                int n_jobs, const Geom& g, int64_t BH, hipStream_t stream)
 {
-    dim3 grid((unsigned)(BH * g.n_blocks));
     const int nw = g.block_tokens / 32;
     auto kernel = nw == 4 ? fwd_mfma_d128_kernel
                   : nw == 2 ? fwd_mfma_d128_w2_kernel : fwd_mfma_d128_w8_kernel;
-    kernel<<<grid, dim3(64 * nw), 0, stream>>>(
-        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, sel_idx, (uint16_t*)out, lse, g,
-        (uint32_t)(BH / g.kv_group));
-    return hipGetLastError();
+    return launch_jobs(jobs, n_jobs, BH * g.n_blocks, 64 * nw,
+                       [&](const FwdJob& a, const FwdJob& b, const FwdShape& j, unsigned grid) {
+                           kernel<<<dim3(grid), dim3(64 * nw), 0, stream>>>(
+                               (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, a.lists,
+                               b.lists, (uint16_t*)a.out, (uint16_t*)b.out, a.lse, b.lse, j, g,
+                               (uint32_t)(BH / g.kv_group));
+                       });
 }
 
 }  // namespace bsa

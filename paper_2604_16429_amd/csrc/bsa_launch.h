@@ -21,45 +21,57 @@ hipError_t launch_pool(bool is_bf16, const void* q, const void* k, float* qbar, 
 hipError_t launch_check_selection(const int32_t* sel_idx, int32_t* n_bad, const Geom& g,
                                   bool own_ok, int64_t BH, hipStream_t stream);
 
-// Pooled means of one key/value-shaped tensor (slices = batch * kv_heads).
-hipError_t launch_pool_one(bool is_bf16, const void* x, float* xbar, const Geom& g, int D,
-                           int64_t slices, hipStream_t stream);
-
 // Pooling of Q and K, block scores and top-n as one sequence of launches in
 // which the pooling of one part of the batch runs beside the ranking of the part
 // before.  The scores of a query block stay in LDS; `scratch` is device memory
 // of select_scratch_bytes(...) bytes (BKV = batch * kv_heads): a second copy of
 // the pooled keys, per slice [D/4][m][4], which the ranking's threads (one key
 // block each) read as consecutive 16-byte groups and launch_pool_select leaves
-// there (select_interleaves_keys(m)).
+// there.
 size_t select_scratch_bytes(int m, int D, int64_t BH, int64_t BKV);
-bool select_interleaves_keys(int m);
 hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float* qbar,
                               float* kbar, void* scratch, int32_t* sel_idx, const Geom& g, int D,
                               int64_t BH, hipStream_t stream);
 
+// Launches one or two forward jobs of `wgs` workgroups each as one grid (two, where
+// one would exceed the 2^32 work items of a launch); launch(job 0, job 1, shape,
+// grid) does it.
+template <class F>
+inline hipError_t launch_jobs(const FwdJob* jobs, int n_jobs, int64_t wgs, int threads, F launch)
+{
+    const bool together = n_jobs == 2 && 2 * wgs * threads < (int64_t)1 << 32;
+    if (wgs >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    for (int j = 0; j < n_jobs; j += together ? 2 : 1) {
+        const FwdJob &a = jobs[j], &b = together ? jobs[1] : jobs[j];
+        launch(a, b,
+               FwdShape{{a.n_select, b.n_select}, {a.list_only, b.list_only}, (uint32_t)wgs},
+               (unsigned)(together ? 2 * wgs : wgs));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // Any tile shape / head dim in {32, 64, 128} / dtype.
 hipError_t launch_fwd_generic(bool is_bf16, const void* q, const void* k, const void* v,
-                              const int32_t* sel_idx, void* out, float* lse, const Geom& g, int D,
-                              int64_t BH, hipStream_t stream);
+                              const FwdJob* jobs, int n_jobs, const Geom& g, int D, int64_t BH,
+                              hipStream_t stream);
 
 // bf16 MFMA forward; covers the shapes fwd_mfma_supported() accepts.
 bool fwd_mfma_supported(bool is_bf16, const Geom& g, int D);
-hipError_t launch_fwd_mfma(const void* q, const void* k, const void* v, const int32_t* sel_idx,
-                           void* out, float* lse, const Geom& g, int D, int64_t BH,
-                           hipStream_t stream);
+hipError_t launch_fwd_mfma(const void* q, const void* k, const void* v, const FwdJob* jobs,
+                           int n_jobs, const Geom& g, int D, int64_t BH, hipStream_t stream);
 
 // bf16 MFMA forward for head dim 128 (query blocks of 64, 128 or 256 tokens, one
 // workgroup of 2, 4 or 8 wavefronts each, K/V tiles shared through LDS).
 bool fwd_mfma_d128_supported(bool is_bf16, const Geom& g, int D);
-hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v,
-                                const int32_t* sel_idx, void* out, float* lse, const Geom& g,
-                                int64_t BH, hipStream_t stream);
+hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v, const FwdJob* jobs,
+                                int n_jobs, const Geom& g, int64_t BH, hipStream_t stream);
 
 // What both backward paths need first: delta_l = dO_l . O_l and lse_l * log2(e)
 // (fp32, `rows` of each), the reverse map of the selection in `conn` and, in
 // `order` (int32, key/value slices x m), the order in which the key blocks of each
-// key/value slice are worked on.
+// key/value slice are worked on.  It is read before dQ is written: dq may serve.
 hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
                            float* delta, float* lse2, int64_t rows, int D, hipStream_t stream);
 hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,
@@ -83,17 +95,20 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
                            void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
                            const Geom& g, int D, int64_t BH, hipStream_t stream);
 
-// Three-branch output: coarse branch (softmax over all pooled key blocks times
-// pooled values, fp32 [B*heads, m, D]), the block lists of the local branch
-// (int32 [B*heads, m, local_h*local_w - 1]) and the gated sum of the branches.
-// kbar_il: the channel-interleaved copy of the pooled keys that
-// launch_pool_select leaves in its scratch for m <= 512, or NULL.
-int coarse_group_size(int m, int D);
-hipError_t launch_coarse(const float* qbar, const float* kbar, const float* kbar_il,
-                         const float* vbar, float* obar, const Geom& g, int D, int64_t BH,
-                         hipStream_t stream);
-hipError_t launch_local_lists(int32_t* lists, const Geom& g, int local_h, int local_w,
-                              int64_t BH, hipStream_t stream);
+// The block-level part of the three-branch output: pooled q, k, v, the selection
+// (as launch_pool_select), the coarse branch (softmax over all pooled key blocks
+// times pooled values, fp32 [B*heads, m, D]) and the block lists of the local branch
+// (int32 [B*heads, m, local_h*local_w - 1]).  kbar_il: the channel-interleaved copy
+// of the pooled keys (the scratch of launch_pool_select).
+hipError_t launch_blocks_three_branch(bool is_bf16, const void* q, const void* k, const void* v,
+                                      float* qbar, float* kbar, float* vbar, float* kbar_il,
+                                      int32_t* sel_idx, float* obar, int32_t* lists, int local_h,
+                                      int local_w, const Geom& g, int D, int64_t BH,
+                                      hipStream_t stream);
+hipError_t launch_coarse(const float* qbar, const float* kbar_il, const float* vbar, float* obar,
+                         const Geom& g, int D, int64_t BH, hipStream_t stream);
+
+// The gated sum of the three branches.
 hipError_t launch_combine(bool is_bf16, const float* obar, const void* o_fg, const void* o_l,
                           const float* gates, void* out, const Geom& g, int D, int64_t BH,
                           hipStream_t stream);

@@ -16,6 +16,7 @@
 // ranked by (score descending, block index ascending) and the query block
 // itself is never a candidate.  MFMA is deliberately not used here: its
 // internal accumulation order cannot be reproduced by such a loop.
+#include "bsa_coarse.h"
 #include "bsa_device.h"
 #include "bsa_launch.h"
 
@@ -125,12 +126,41 @@ struct PoolTensor {
     uint32_t slices;
 };
 
+// Block lists of the local branch: lists[bh, i, c], c = 0 .. local_h*local_w - 2, the
+// other tiles of the aligned group of local_h x local_w tiles that contains tile i,
+// ascending.  Written by the workgroups of a pooling launch from first_wg on.
+struct LocalLists {
+    int32_t* lists;
+    int32_t local_h, local_w;
+    int64_t total;          // entries
+    uint32_t first_wg;
+};
+
+__device__ __forceinline__ void write_local_list(const LocalLists& ll, const Geom& g)
+{
+    const int64_t e = (int64_t)(blockIdx.x - ll.first_wg) * 256 + threadIdx.x;
+    if (e >= ll.total) return;
+    const int nl = ll.local_h * ll.local_w - 1;
+    const int c = (int)(e % nl);
+    const int i = (int)((e / nl) % g.n_blocks);
+    const int r = i / g.blocks_per_row, col = i - r * g.blocks_per_row;
+    const int r0 = r - r % ll.local_h, c0 = col - col % ll.local_w;
+    const int own = (r - r0) * ll.local_w + (col - c0);    // position of tile i in its group
+    const int pos = c < own ? c : c + 1;
+    ll.lists[e] = (r0 + pos / ll.local_w) * g.blocks_per_row + c0 + pos % ll.local_w;
+}
+
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void pool_kernel(PoolTensor t0, PoolTensor t1, PoolTensor t2,
-                                                   Geom g, int D, uint32_t wgs_per_slice)
+                                                   Geom g, int D, uint32_t wgs_per_slice,
+                                                   LocalLists ll)
 {
     typedef uint32_t word __attribute__((ext_vector_type(VEC * (int)sizeof(T) / 4)));
     constexpr int BATCH = 16;
+    if (blockIdx.x >= ll.first_wg) {
+        write_local_list(ll, g);
+        return;
+    }
     uint32_t slice = blockIdx.x / wgs_per_slice;
     const uint32_t chunk = blockIdx.x - slice * wgs_per_slice;
     PoolTensor t = t0;
@@ -327,8 +357,7 @@ __device__ __forceinline__ void topn_of_row_in_registers(const uint32_t* keys,
 // (batch, head).
 //   phase 1: thread t owns key block j = t, t + 256, ..., holds kbar_j in
 //            registers (loaded from the channel-interleaved copy of the pooled
-//            keys where there is one: consecutive lanes then read consecutive
-//            16-byte groups) and runs the pinned fma chain against each of the
+//            keys: consecutive lanes read consecutive 16-byte groups) and runs the pinned fma chain against each of the
 //            G pooled queries (wave-uniform: scalar loads, scalar operands); the
 //            ranking keys of all m candidates of each query land in LDS.
 //   phase 2: one wavefront per query block extracts the n best candidates by
@@ -340,7 +369,6 @@ __device__ __forceinline__ void topn_of_row_in_registers(const uint32_t* keys,
 // count must not cost the common case its occupancy).
 template <int D, bool BIG>
 __device__ __forceinline__ void select_block(const float* __restrict__ qbar,
-                                             const float* __restrict__ kbar,
                                              const float* __restrict__ kbar_il,
                                              int32_t* __restrict__ sel_idx, const Geom& g, int G,
                                              uint32_t vblock)
@@ -355,20 +383,15 @@ __device__ __forceinline__ void select_block(const float* __restrict__ qbar,
     const int i0 = (int)(vblock - (uint32_t)bh_idx * (uint32_t)groups) * G;
     const int rows = min(G, m - i0);
     qbar += (bh_idx * m + i0) * D;
-    kbar += kv_slice_of(g, bh_idx) * m * D;
-
-    if (kbar_il) kbar_il += kv_slice_of(g, bh_idx) * m * D;   // per slice [D/4][m][4]
+    kbar_il += kv_slice_of(g, bh_idx) * m * D;       // per slice [D/4][m][4]
 
     // ---- phase 1: scores.  The pooled queries are wave-uniform and are fetched
     // with scalar loads straight into the fma's scalar operand.
     auto load_key = [&](int j, float (&kr)[D]) {
-        // the interleaved copy where there is one, else the key block's row
-        const float4* ksrc = kbar_il ? (const float4*)kbar_il + j
-                                     : (const float4*)(kbar + (int64_t)j * D);
-        const int64_t kstep = kbar_il ? (int64_t)m : 1;
+        const float4* ksrc = (const float4*)kbar_il + j;
 #pragma unroll
         for (int d4 = 0; d4 < D / 4; ++d4) {
-            const float4 v = ksrc[d4 * kstep];
+            const float4 v = ksrc[(int64_t)d4 * m];
             kr[4 * d4 + 0] = v.x; kr[4 * d4 + 1] = v.y;
             kr[4 * d4 + 2] = v.z; kr[4 * d4 + 3] = v.w;
         }
@@ -495,25 +518,40 @@ __device__ __forceinline__ void select_block(const float* __restrict__ qbar,
 // workgroups rank (virtual ids from select_first on).  No workgroup waits for
 // another: what a ranking workgroup reads was written by an earlier launch.
 // The pooled means are passed twice: written through qbar_w / kbar_w / kbar_il_w
-// (the part being pooled), read through qbar_r / kbar_r / kbar_il_r (the part
+// (the part being pooled), read through qbar_r / kbar_il_r (the part
 // being ranked).
 template <typename T, int VEC, int D, bool BIG>
 __global__ __launch_bounds__(256) void pool_select_kernel(
     const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ qbar_w,
     float* __restrict__ kbar_w, float* __restrict__ kbar_il_w, const float* __restrict__ qbar_r,
-    const float* __restrict__ kbar_r, const float* __restrict__ kbar_il_r,
+    const float* __restrict__ kbar_il_r,
     int32_t* __restrict__ sel_idx, Geom g, int G,
     int64_t pool_q_first, int64_t pool_n_q, int64_t pool_k_first, int wgs_per_slice,
     uint32_t n_pool_blocks, uint32_t n_poolers, uint32_t select_first)
 {
     if (blockIdx.x >= n_poolers) {
-        select_block<D, BIG>(qbar_r, kbar_r, kbar_il_r, sel_idx, g, G,
+        select_block<D, BIG>(qbar_r, kbar_il_r, sel_idx, g, G,
                         select_first + (blockIdx.x - n_poolers));
         return;
     }
     for (uint32_t v = blockIdx.x; v < n_pool_blocks; v += n_poolers)
         pool_block<T, VEC>(q, k, qbar_w, kbar_w, kbar_il_w, g, D, pool_q_first, pool_n_q, pool_k_first,
                            wgs_per_slice, v);
+}
+
+// The ranking beside the coarse branch, for a batch that is pooled by a launch of its
+// own: both read only pooled means, and apart each would leave most of the chip idle
+// (of a small batch).  Workgroups below n_rank rank.
+template <int D, bool BIG>
+__global__ __launch_bounds__(256) void rank_coarse_kernel(
+    const float* __restrict__ qbar, const float* __restrict__ kbar_il,
+    const float* __restrict__ vbar, float* __restrict__ obar, int32_t* __restrict__ sel_idx, Geom g,
+    int G, int G_coarse, uint32_t n_rank)
+{
+    if (blockIdx.x < n_rank)
+        select_block<D, BIG>(qbar, kbar_il, sel_idx, g, G, blockIdx.x);
+    else
+        coarse_block<D>(qbar, kbar_il, vbar, obar, g, G_coarse, blockIdx.x - n_rank);
 }
 
 // ---------------------------------------------------------------------------
@@ -582,33 +620,36 @@ int select_group_size(int m, int D)
 }
 
 template <typename T, int VEC>
-static hipError_t launch_pool_t(const PoolTensor (&t)[3], const Geom& g, int D, hipStream_t stream)
+static hipError_t launch_pool_t(const PoolTensor (&t)[3], LocalLists ll, const Geom& g, int D,
+                                hipStream_t stream)
 {
     const int64_t slices = (int64_t)t[0].slices + t[1].slices + t[2].slices;
     const int64_t wgs_per_slice = ((int64_t)g.n_blocks * (D / VEC) + 255) / 256;
-    if (slices * wgs_per_slice >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    pool_kernel<T, VEC><<<dim3((unsigned)(slices * wgs_per_slice)), dim3(256), 0, stream>>>(
-        t[0], t[1], t[2], g, D, (uint32_t)wgs_per_slice);
+    const int64_t wgs = slices * wgs_per_slice, list_wgs = (ll.total + 255) / 256;
+    if (wgs + list_wgs >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    ll.first_wg = (uint32_t)wgs;
+    pool_kernel<T, VEC><<<dim3((unsigned)(wgs + list_wgs)), dim3(256), 0, stream>>>(
+        t[0], t[1], t[2], g, D, (uint32_t)wgs_per_slice, ll);
     return hipGetLastError();
 }
 
 // Pools up to three tensors.  16-byte loads when that gives every CU two
 // workgroups of 256 threads, else 8 or 4 bytes.
-static hipError_t launch_pool_tensors(bool is_bf16, const PoolTensor (&t)[3], const Geom& g, int D,
-                                      hipStream_t stream)
+static hipError_t launch_pool_tensors(bool is_bf16, const PoolTensor (&t)[3], const LocalLists& ll,
+                                      const Geom& g, int D, hipStream_t stream)
 {
     const int64_t slices = (int64_t)t[0].slices + t[1].slices + t[2].slices;
     const int64_t channels = slices * g.n_blocks * D;
     const int64_t fill = (int64_t)2 * 256 * 256;             // threads
     const int per16 = is_bf16 ? 8 : 4;
     if (channels / per16 >= fill)
-        return is_bf16 ? launch_pool_t<uint16_t, 8>(t, g, D, stream)
-                       : launch_pool_t<float, 4>(t, g, D, stream);
+        return is_bf16 ? launch_pool_t<uint16_t, 8>(t, ll, g, D, stream)
+                       : launch_pool_t<float, 4>(t, ll, g, D, stream);
     if (2 * channels / per16 >= fill)
-        return is_bf16 ? launch_pool_t<uint16_t, 4>(t, g, D, stream)
-                       : launch_pool_t<float, 2>(t, g, D, stream);
-    return is_bf16 ? launch_pool_t<uint16_t, 2>(t, g, D, stream)
-                   : launch_pool_t<float, 1>(t, g, D, stream);
+        return is_bf16 ? launch_pool_t<uint16_t, 4>(t, ll, g, D, stream)
+                       : launch_pool_t<float, 2>(t, ll, g, D, stream);
+    return is_bf16 ? launch_pool_t<uint16_t, 2>(t, ll, g, D, stream)
+                   : launch_pool_t<float, 1>(t, ll, g, D, stream);
 }
 
 hipError_t launch_pool(bool is_bf16, const void* q, const void* k, float* qbar, float* kbar,
@@ -617,16 +658,7 @@ hipError_t launch_pool(bool is_bf16, const void* q, const void* k, float* qbar, 
     const PoolTensor t[3] = {{q, qbar, nullptr, (uint32_t)BH},
                              {k, kbar, nullptr, (uint32_t)(BH / g.kv_group)},
                              {nullptr, nullptr, nullptr, 0}};
-    return launch_pool_tensors(is_bf16, t, g, D, stream);
-}
-
-hipError_t launch_pool_one(bool is_bf16, const void* x, float* xbar, const Geom& g, int D,
-                           int64_t slices, hipStream_t stream)
-{
-    const PoolTensor t[3] = {{x, xbar, nullptr, (uint32_t)slices},
-                             {nullptr, nullptr, nullptr, 0},
-                             {nullptr, nullptr, nullptr, 0}};
-    return launch_pool_tensors(is_bf16, t, g, D, stream);
+    return launch_pool_tensors(is_bf16, t, LocalLists{}, g, D, stream);
 }
 
 size_t select_scratch_bytes(int m, int D, int64_t BH, int64_t BKV)
@@ -657,7 +689,15 @@ static int select_parts(int64_t BH, int64_t BKV, const Geom& g, int D, size_t el
     return parts < 1 ? 1 : (int)parts;
 }
 
-bool select_interleaves_keys(int m) { (void)m; return true; }
+// Few query blocks: fewer per workgroup, down to a workgroup each, until there are
+// two workgroups per CU (ranking 480 blocks 9.8 -> 5.1 us, 3,600 blocks 15.9 -> 13.4
+// us, 64 blocks 6.3 -> 3.9 us).
+static int select_group_for(int m, int D, int64_t BH)
+{
+    int G = select_group_size(m, D);
+    while (G > 1 && BH * ((m + G - 1) / G) < 512) G >>= 1;
+    return G;
+}
 
 template <typename T, int VEC, int D, bool BIG>
 static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar, float* kbar,
@@ -665,12 +705,8 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
                                        int64_t BH, hipStream_t stream)
 {
     const int m = g.n_blocks;
-    int G = select_group_size(m, D);
+    const int G = select_group_for(m, D, BH);
     if (G == 0) return hipErrorInvalidValue;
-    // few query blocks: fewer per workgroup, down to a workgroup each, until there
-    // are two workgroups per CU (ranking 480 blocks 9.8 -> 5.1 us, 3,600 blocks 15.9
-    // -> 13.4 us, 64 blocks 6.3 -> 3.9 us)
-    while (G > 1 && BH * ((m + G - 1) / G) < 512) G >>= 1;
     const size_t lds = select_lds_bytes(G, m, D);
     // the attribute is per device; setting it twice (two host threads racing) is harmless
     static bool attr_set[64] = {};
@@ -692,7 +728,7 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
         const PoolTensor tensors[3] = {{q, qbar, nullptr, (uint32_t)BH},
                                        {k, kbar, kbar_il, (uint32_t)BKV},
                                        {nullptr, nullptr, nullptr, 0}};
-        const hipError_t e = launch_pool_tensors(sizeof(T) == 2, tensors, g, D, stream);
+        const hipError_t e = launch_pool_tensors(sizeof(T) == 2, tensors, LocalLists{}, g, D, stream);
         if (e != hipSuccess) return e;
     }
     // launch t pools part t and ranks part t - 1
@@ -718,7 +754,7 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
             return hipErrorInvalidValue;
         hipLaunchKernelGGL((pool_select_kernel<T, VEC, D, BIG>), dim3((unsigned)(n_poolers + n_sel)),
                            dim3(256), lds, stream, (const T*)q, (const T*)k, qbar, kbar, kbar_il,
-                           (const float*)qbar, (const float*)kbar, (const float*)kbar_il, sel_idx,
+                           (const float*)qbar, (const float*)kbar_il, sel_idx,
                            g, G, pq0, pnq, pk0,
                            wgs_per_slice, (uint32_t)n_pool, (uint32_t)n_poolers,
                            (uint32_t)sel_first);
@@ -746,6 +782,72 @@ hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float*
     case 128: return is_bf16 ? BSA_PS(uint16_t, 8, 128) : BSA_PS(float, 4, 128);
     }
 #undef BSA_PS
+    return hipErrorInvalidValue;
+}
+
+template <int D, bool BIG>
+static hipError_t launch_rank_coarse_t(const float* qbar, const float* kbar_il, const float* vbar,
+                                       float* obar, int32_t* sel_idx, const Geom& g, int64_t BH,
+                                       hipStream_t stream)
+{
+    const int m = g.n_blocks;
+    const int G = select_group_for(m, D, BH), Gc = coarse_group_for(m, D, BH);
+    if (G == 0 || Gc == 0) return hipErrorInvalidValue;
+    const size_t rank_lds = select_lds_bytes(G, m, D), coarse_lds = coarse_lds_bytes(Gc, m, D);
+    static bool attr_set[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!attr_set[dev]) {
+        hipError_t e = hipFuncSetAttribute((const void*)rank_coarse_kernel<D, BIG>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)(kSelectLdsBudget > kCoarseLdsBudget
+                                                     ? kSelectLdsBudget : kCoarseLdsBudget));
+        if (e != hipSuccess) return e;
+        attr_set[dev] = true;
+    }
+    const int64_t n_rank = BH * ((m + G - 1) / G), n_coarse = BH * ((m + Gc - 1) / Gc);
+    if (n_rank + n_coarse >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    rank_coarse_kernel<D, BIG><<<dim3((unsigned)(n_rank + n_coarse)), dim3(256),
+                                 rank_lds > coarse_lds ? rank_lds : coarse_lds, stream>>>(
+        qbar, kbar_il, vbar, obar, sel_idx, g, G, Gc, (uint32_t)n_rank);
+    return hipGetLastError();
+}
+
+hipError_t launch_blocks_three_branch(bool is_bf16, const void* q, const void* k, const void* v,
+                                      float* qbar, float* kbar, float* vbar, float* kbar_il,
+                                      int32_t* sel_idx, float* obar, int32_t* lists, int local_h,
+                                      int local_w, const Geom& g, int D, int64_t BH,
+                                      hipStream_t stream)
+{
+    const int m = g.n_blocks;
+    const int64_t BKV = BH / g.kv_group;
+    const LocalLists ll = {lists, local_h, local_w, BH * m * (local_h * local_w - 1), 0};
+    const PoolTensor none = {nullptr, nullptr, nullptr, 0};
+    const PoolTensor tv = {v, vbar, nullptr, (uint32_t)BKV};
+    if (select_parts(BH, BKV, g, D, is_bf16 ? 2 : 4) > 1) {
+        hipError_t e = launch_pool_select(is_bf16, q, k, qbar, kbar, kbar_il, sel_idx, g, D, BH,
+                                          stream);
+        if (e != hipSuccess) return e;
+        const PoolTensor t[3] = {tv, none, none};
+        e = launch_pool_tensors(is_bf16, t, ll, g, D, stream);
+        return e != hipSuccess ? e : launch_coarse(qbar, kbar_il, vbar, obar, g, D, BH, stream);
+    }
+    const PoolTensor t[3] = {{q, qbar, nullptr, (uint32_t)BH}, {k, kbar, kbar_il, (uint32_t)BKV}, tv};
+    const hipError_t e = launch_pool_tensors(is_bf16, t, ll, g, D, stream);
+    if (e != hipSuccess) return e;
+    const bool big = m > 64 * kSlots && m <= 64 * kBigSlots;
+#define BSA_RC(D_)                                                                                 \
+    case D_:                                                                                       \
+        return big ? launch_rank_coarse_t<D_, true>(qbar, kbar_il, vbar, obar, sel_idx, g, BH,     \
+                                                    stream)                                        \
+                   : launch_rank_coarse_t<D_, false>(qbar, kbar_il, vbar, obar, sel_idx, g, BH,    \
+                                                     stream);
+    switch (D) {
+        BSA_RC(32)
+        BSA_RC(64)
+        BSA_RC(128)
+    }
+#undef BSA_RC
     return hipErrorInvalidValue;
 }
 

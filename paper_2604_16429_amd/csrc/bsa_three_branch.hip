@@ -6,187 +6,34 @@
 //                        (block-level attention equation) applied to the
 //                        mean-pooled values (coarse-grained output equation);
 //                        one fp32 row [D] per query block.
-//   local_lists_kernel   the other mesh tiles of the large local block that
-//                        contains tile i (Local Attention paragraph); the
-//                        local branch is then the forward kernel run on "tile
-//                        i and these tiles".
 //   combine_kernel       o = g_cg * o_cg(block of the token) + g_fg * o_fg +
 //                        g_l * o_l with caller-supplied gate values
 //                        (aggregation equation of the Native Sparse Attention
 //                        subsection).  HBM-bound, one pass.
 //
-// The selection branch itself is the forward kernel in its list-only mode.
+// The selection branch is the forward kernel in its list-only mode, the local branch
+// the forward kernel run on "tile i and the other tiles of its large block" (Local
+// Attention paragraph; the pooling launch writes those lists).
+#include "bsa_coarse.h"
 #include "bsa_device.h"
 #include "bsa_launch.h"
 
 namespace bsa {
 
-namespace {
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kCoarseRows = 8;                      // most query blocks per workgroup
-constexpr size_t kCoarseLdsBudget = 144 * 1024;
-
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
-}
-
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
-}  // namespace
-
-// One workgroup of 256 threads handles G <= 8 consecutive query blocks of one
-// (batch, head).
-//   phase 1: thread t owns key block j = chunk*256 + t, holds kbar_j in
-//            registers and scores it against the G pooled queries (scalar
-//            operands); scaled scores (base-2 domain) land in LDS.
-//   phase 2: one wavefront per query block: row maximum, weights
-//            exp2(s - max) written back in place, 1 / row sum.
-//   phase 3: thread = (channel quad, key partition): walks the pooled values
-//            of its key partition (a row of vbar is read by D/4 adjacent
-//            lanes, 16 bytes each) and accumulates weight * value for all G
-//            rows in registers.
-//   phase 4: the partitions' partial rows are summed, first inside each
-//            wavefront (lanes with the same channel quad), then through LDS,
-//            in fixed order, and scaled by 1 / row sum.
-// LDS: G*m (scores) + 4*G*D (partials) + G floats.
 template <int D>
 __global__ __launch_bounds__(256) void coarse_kernel(const float* __restrict__ qbar,
-                                                     const float* __restrict__ kbar,
                                                      const float* __restrict__ kbar_il,
                                                      const float* __restrict__ vbar,
                                                      float* __restrict__ obar, Geom g, int G)
 {
-    constexpr int CG = D / 4;                        // channel quads
-    constexpr int JP = 256 / CG;                     // key partitions
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int m = g.n_blocks;
-    float* red_s = (float*)smem;                     // [4 wavefronts][G][D]
-    float* inv_s = red_s + 4 * G * D;                // [8]
-    float* sc_s = inv_s + kCoarseRows;               // [G][m]
-
-    const int groups = (m + G - 1) / G;
-    const int64_t bh_idx = blockIdx.x / groups;
-    const int i0 = (int)(blockIdx.x - bh_idx * groups) * G;
-    const int rows = min(G, m - i0);
-    const int64_t kv = kv_slice_of(g, bh_idx);
-    qbar += (bh_idx * m + i0) * D;
-    kbar += kv * m * D;
-    vbar += kv * m * D;
-
-    if (kbar_il) kbar_il += kv * m * D;              // per slice [D/4][m][4]
-
-    // ---- phase 1: scaled scores.  The pooled queries are wave-uniform (scalar
-    // loads, scalar operands of the fma); the thread's pooled key comes from the
-    // channel-interleaved copy where there is one (coalesced), else from its row.
-    const float c2 = g.scale * kLog2e;
-    for (int j = threadIdx.x; j < m; j += blockDim.x) {
-        float kr[D];
-        const float4* ksrc = kbar_il ? (const float4*)kbar_il + j
-                                     : (const float4*)(kbar + (int64_t)j * D);
-        const int64_t kstep = kbar_il ? (int64_t)m : 1;
-#pragma unroll
-        for (int d4 = 0; d4 < D / 4; ++d4) {
-            const float4 t = ksrc[d4 * kstep];
-            kr[4 * d4 + 0] = t.x; kr[4 * d4 + 1] = t.y;
-            kr[4 * d4 + 2] = t.z; kr[4 * d4 + 3] = t.w;
-        }
-        for (int r = 0; r < rows; ++r) {
-            const float* __restrict__ qrow = qbar + r * D;
-            float acc = 0.0f;
-#pragma unroll
-            for (int d = 0; d < D; ++d) acc = fmaf(qrow[d], kr[d], acc);
-            sc_s[r * m + j] = acc * c2;
-        }
-    }
-    __syncthreads();
-
-    // ---- phase 2: softmax weights per row, one wavefront each
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int r = wave; r < rows; r += 4) {
-        float* row = sc_s + r * m;
-        float mx = -INFINITY;
-        for (int j = lane; j < m; j += 64) mx = fmaxf(mx, row[j]);
-        mx = wave_max(mx);
-        float sum = 0.0f;
-        for (int j = lane; j < m; j += 64) {
-            const float w = __builtin_amdgcn_exp2f(row[j] - mx);
-            row[j] = w;
-            sum += w;
-        }
-        sum = wave_sum(sum);
-        if (lane == 0) inv_s[r] = 1.0f / sum;
-    }
-    __syncthreads();
-
-    // ---- phase 3: weights times pooled values
-    const int cg = threadIdx.x % CG, jp = threadIdx.x / CG;
-    float4 acc[kCoarseRows];
-#pragma unroll
-    for (int r = 0; r < kCoarseRows; ++r) acc[r] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int j = jp; j < m; j += JP) {
-        const float4 val = *(const float4*)(vbar + (int64_t)j * D + 4 * cg);
-#pragma unroll
-        for (int r = 0; r < kCoarseRows; ++r) {
-            if (r < rows) {
-                const float w = sc_s[r * m + j];
-                acc[r].x = fmaf(w, val.x, acc[r].x);
-                acc[r].y = fmaf(w, val.y, acc[r].y);
-                acc[r].z = fmaf(w, val.z, acc[r].z);
-                acc[r].w = fmaf(w, val.w, acc[r].w);
-            }
-        }
-    }
-    // ---- phase 4: the 64 / CG partitions of a wavefront hold the same channel
-    // quad CG lanes apart: butterfly sums, then one partial row per wavefront
-#pragma unroll
-    for (int r = 0; r < kCoarseRows; ++r)
-        for (int off = CG; off < 64; off <<= 1) {
-            acc[r].x += __shfl_xor(acc[r].x, off);
-            acc[r].y += __shfl_xor(acc[r].y, off);
-            acc[r].z += __shfl_xor(acc[r].z, off);
-            acc[r].w += __shfl_xor(acc[r].w, off);
-        }
-    if (lane < CG) {
-#pragma unroll
-        for (int r = 0; r < kCoarseRows; ++r)
-            if (r < rows) *(float4*)(red_s + ((wave * G + r) * D) + 4 * cg) = acc[r];
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < rows * D; e += blockDim.x) {
-        const int r = e / D, d = e - r * D;
-        float sum = 0.0f;
-        for (int p = 0; p < 4; ++p) sum += red_s[(p * G + r) * D + d];
-        obar[(bh_idx * m + i0 + r) * D + d] = sum * inv_s[r];
-    }
-}
-
-static size_t coarse_lds_bytes(int G, int m, int D)
-{
-    return ((size_t)4 * G * D + kCoarseRows + (size_t)G * m) * 4;
-}
-
-int coarse_group_size(int m, int D)
-{
-    for (int G = kCoarseRows; G >= 1; G >>= 1)
-        if (coarse_lds_bytes(G, m, D) <= kCoarseLdsBudget) return G;
-    return 0;
+    coarse_block<D>(qbar, kbar_il, vbar, obar, g, G, blockIdx.x);
 }
 
 template <int D>
-static hipError_t launch_coarse_t(const float* qbar, const float* kbar, const float* kbar_il,
-                                  const float* vbar, float* obar, const Geom& g, int64_t BH,
-                                  hipStream_t stream)
+static hipError_t launch_coarse_t(const float* qbar, const float* kbar_il, const float* vbar,
+                                  float* obar, const Geom& g, int64_t BH, hipStream_t stream)
 {
-    const int G = coarse_group_size(g.n_blocks, D);
+    const int G = coarse_group_for(g.n_blocks, D, BH);
     if (G == 0) return hipErrorInvalidValue;
     // the attribute is per device; setting it twice (two host threads racing) is harmless
     static bool attr_set[64] = {};
@@ -201,48 +48,19 @@ static hipError_t launch_coarse_t(const float* qbar, const float* kbar, const fl
     }
     dim3 grid((unsigned)(BH * ((g.n_blocks + G - 1) / G)));
     hipLaunchKernelGGL((coarse_kernel<D>), grid, dim3(256), coarse_lds_bytes(G, g.n_blocks, D),
-                       stream, qbar, kbar, kbar_il, vbar, obar, g, G);
+                       stream, qbar, kbar_il, vbar, obar, g, G);
     return hipGetLastError();
 }
 
-hipError_t launch_coarse(const float* qbar, const float* kbar, const float* kbar_il,
-                         const float* vbar, float* obar, const Geom& g, int D, int64_t BH,
-                         hipStream_t stream)
+hipError_t launch_coarse(const float* qbar, const float* kbar_il, const float* vbar, float* obar,
+                         const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
     switch (D) {
-    case 32: return launch_coarse_t<32>(qbar, kbar, kbar_il, vbar, obar, g, BH, stream);
-    case 64: return launch_coarse_t<64>(qbar, kbar, kbar_il, vbar, obar, g, BH, stream);
-    case 128: return launch_coarse_t<128>(qbar, kbar, kbar_il, vbar, obar, g, BH, stream);
+    case 32: return launch_coarse_t<32>(qbar, kbar_il, vbar, obar, g, BH, stream);
+    case 64: return launch_coarse_t<64>(qbar, kbar_il, vbar, obar, g, BH, stream);
+    case 128: return launch_coarse_t<128>(qbar, kbar_il, vbar, obar, g, BH, stream);
     }
     return hipErrorInvalidValue;
-}
-
-// lists[bh, i, c], c = 0 .. local_h*local_w - 2: the other tiles of the aligned
-// group of local_h x local_w tiles that contains tile i, ascending.
-__global__ __launch_bounds__(256) void local_lists_kernel(int32_t* __restrict__ lists, Geom g,
-                                                          int local_h, int local_w,
-                                                          int64_t total)
-{
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const int nl = local_h * local_w - 1;
-    const int c = (int)(e % nl);
-    const int i = (int)((e / nl) % g.n_blocks);
-    const int r = i / g.blocks_per_row, col = i - r * g.blocks_per_row;
-    const int r0 = r - r % local_h, c0 = col - col % local_w;
-    const int own = (r - r0) * local_w + (col - c0);    // position of tile i in its group
-    const int pos = c < own ? c : c + 1;
-    lists[e] = (r0 + pos / local_w) * g.blocks_per_row + c0 + pos % local_w;
-}
-
-hipError_t launch_local_lists(int32_t* lists, const Geom& g, int local_h, int local_w,
-                              int64_t BH, hipStream_t stream)
-{
-    const int64_t total = BH * g.n_blocks * (local_h * local_w - 1);
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(local_lists_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
-                       stream, lists, g, local_h, local_w, total);
-    return hipGetLastError();
 }
 
 // One thread per VEC consecutive channels of one token.
@@ -436,7 +254,7 @@ __global__ __launch_bounds__(256) void coarse_bwd_rows_kernel(
 
     // scores (base-2 domain) and da_ij = dobar_i . vbar_j; the rows of qbar and
     // dobar are wave-uniform (scalar loads, scalar operands of the fma)
-    const float c2 = g.scale * kLog2e;
+    const float c2 = g.scale * kCoarseLog2e;
     for (int j = threadIdx.x; j < m; j += blockDim.x) {
         float kr[D];
         const float4* ksrc = kbar_il ? (const float4*)kbar_il + j
