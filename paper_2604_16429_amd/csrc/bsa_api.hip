@@ -327,22 +327,26 @@ extern "C" int mosaic_bsa_fwd_three_branch(const mosaic_bsa_params* params, int3
 
 namespace {
 
-// The attention backward for geometry g (selection or lists held fixed);
-// scratch: bwd_workspace(c) bytes; order: int32 per key block of every key/value
-// slice (dK and dV are done before dQ is touched, so dq may serve).
+// Scratch of the attention backward, see bwd_workspace.  order: int32 per key block of
+// every key/value slice (dK and dV are done before dQ is touched, so dq may serve).
+struct BwdScratch {
+    float *delta, *lse2;
+    uint32_t* conn;
+    int32_t* order;
+};
+
+// The attention backward for geometry g (selection or lists held fixed).  lse ==
+// nullptr: delta and lse2 are in the scratch already (out is not read then).
 hipError_t backward(const Checked& c, const bsa::Geom& g, const void* q, const void* k,
                     const void* v, const void* out, const float* lse, const void* dout,
-                    const int32_t* lists, void* dq, void* dk, void* dv, void* scratch,
-                    int32_t* order, hipStream_t stream)
+                    const int32_t* lists, void* dq, void* dk, void* dv, const BwdScratch& s,
+                    hipStream_t stream)
 {
-    float* delta = (float*)scratch;
-    float* lse2 = (float*)((char*)scratch + bwd_rows_bytes(c));
-    uint32_t* conn = (uint32_t*)((char*)scratch + 2 * bwd_rows_bytes(c));
     return bsa::bwd_mfma_supported(c.is_bf16, g, c.D)
-               ? bsa::launch_bwd_mfma(q, k, v, out, lse, dout, lists, dq, dk, dv, delta, lse2,
-                                      conn, order, g, c.D, c.BH, stream)
-               : bsa::launch_bwd(c.is_bf16, q, k, v, out, lse, dout, lists, dq, dk, dv, delta, lse2,
-                                 conn, order, g, c.D, c.BH, stream);
+               ? bsa::launch_bwd_mfma(q, k, v, out, lse, dout, lists, dq, dk, dv, s.delta, s.lse2,
+                                      s.conn, s.order, g, c.D, c.BH, stream)
+               : bsa::launch_bwd(c.is_bf16, q, k, v, out, lse, dout, lists, dq, dk, dv, s.delta,
+                                 s.lse2, s.conn, s.order, g, c.D, c.BH, stream);
 }
 
 }  // namespace
@@ -361,8 +365,11 @@ extern "C" int mosaic_bsa_bwd(const mosaic_bsa_params* params, const void* q, co
         return MOSAIC_BSA_ERR_ALIGN;
     if (!workspace || workspace_bytes < bwd_workspace(c)) return MOSAIC_BSA_ERR_WORKSPACE;
 
-    return backward(c, c.g, q, k, v, out, lse, dout, sel_idx, dq, dk, dv, workspace,
-                    (int32_t*)dq, (hipStream_t)hip_stream) == hipSuccess
+    char* ws = (char*)workspace;
+    const BwdScratch scratch = {(float*)ws, (float*)(ws + bwd_rows_bytes(c)),
+                                (uint32_t*)(ws + 2 * bwd_rows_bytes(c)), (int32_t*)dq};
+    return backward(c, c.g, q, k, v, out, lse, dout, sel_idx, dq, dk, dv, scratch,
+                    (hipStream_t)hip_stream) == hipSuccess
                ? MOSAIC_BSA_OK
                : MOSAIC_BSA_ERR_LAUNCH;
 }
@@ -371,7 +378,7 @@ namespace {
 
 // Workspace of the three-branch backward: 256-byte aligned parts in this order.
 struct ThreeBranchBwdLayout {
-    size_t attn, order, do_fg, do_l, dobar, a_mat, ds_mat, dqbar, dkbar, dvbar, total;
+    size_t rows[4], conn, order, do_fg, do_l, dobar, a_mat, ds_mat, dqbar, dkbar, dvbar, total;
     int chunk_rows;        // query blocks per pass of the coarse branch's backward
 };
 
@@ -399,7 +406,8 @@ ThreeBranchBwdLayout three_branch_bwd_layout(const Checked& c)
         at += align_up(bytes);
         return start;
     };
-    w.attn = take(bwd_workspace(c));                 // scratch of the attention backward kernels
+    for (size_t& r : w.rows) r = take(bwd_rows_bytes(c));    // delta and lse2 of both branches
+    w.conn = take((size_t)bsa::bwd_connection_words(c.g.n_blocks, c.BH) * sizeof(uint32_t));
     w.order = take((size_t)c.BKV * m * sizeof(int32_t));
     w.do_fg = take((size_t)c.BH * N * c.D * esz);
     w.do_l = take((size_t)c.BH * N * c.D * esz);
@@ -458,17 +466,23 @@ extern "C" int mosaic_bsa_bwd_three_branch(const mosaic_bsa_params* params, int3
     const int32_t* lists = (const int32_t*)(fw + f.lists);
     float* dobar = (float*)(ws + w.dobar);
 
-    // upstream gradients of the two attention branches, gate gradients, and the
-    // coarse rows' gradient (gated block sums of dout)
-    if (bsa::launch_branch_grads(c.is_bf16, obar, fw + f.o_fg, fw + f.o_l, gates, dout,
-                                 ws + w.do_fg, ws + w.do_l, dgates, dobar, c.g, c.D, c.BH,
-                                 stream) != hipSuccess)
+    // upstream gradients of the two attention branches with their delta and lse2,
+    // gate gradients, and the coarse rows' gradient (gated block sums of dout)
+    const BwdScratch fg = {(float*)(ws + w.rows[0]), (float*)(ws + w.rows[1]),
+                           (uint32_t*)(ws + w.conn), (int32_t*)(ws + w.order)};
+    const BwdScratch loc = {(float*)(ws + w.rows[2]), (float*)(ws + w.rows[3]),
+                            (uint32_t*)(ws + w.conn), (int32_t*)(ws + w.order)};
+    const bsa::BranchGrads grads = {
+        obar, fw + f.o_fg, fw + f.o_l, (const float*)(fw + f.lse_fg), (const float*)(fw + f.lse_l),
+        gates, dout, ws + w.do_fg, ws + w.do_l, dgates, dobar, fg.delta, loc.delta, fg.lse2,
+        loc.lse2};
+    if (bsa::launch_branch_grads(c.is_bf16, grads, c.g, c.D, c.BH, stream) != hipSuccess)
         return MOSAIC_BSA_ERR_LAUNCH;
     // selection branch -> dq, dk, dv
     bsa::Geom g_fg = c.g;
     g_fg.list_only = 1;
-    if (backward(c, g_fg, q, k, v, fw + f.o_fg, (const float*)(fw + f.lse_fg), ws + w.do_fg,
-                 sel_idx, dq, dk, dv, ws + w.attn, (int32_t*)(ws + w.order), stream) != hipSuccess)
+    if (backward(c, g_fg, q, k, v, nullptr, nullptr, ws + w.do_fg, sel_idx, dq, dk, dv, fg,
+                 stream) != hipSuccess)
         return MOSAIC_BSA_ERR_LAUNCH;
     // coarse branch on the pooled tensors
     if (bsa::launch_coarse_bwd(qbar, kbar,
@@ -485,8 +499,8 @@ extern "C" int mosaic_bsa_bwd_three_branch(const mosaic_bsa_params* params, int3
     g_l.add_dq = (const float*)(ws + w.dqbar);
     g_l.add_dk = (const float*)(ws + w.dkbar);
     g_l.add_dv = (const float*)(ws + w.dvbar);
-    if (backward(c, g_l, q, k, v, fw + f.o_l, (const float*)(fw + f.lse_l), ws + w.do_l, lists,
-                 dq, dk, dv, ws + w.attn, (int32_t*)(ws + w.order), stream) != hipSuccess)
+    if (backward(c, g_l, q, k, v, nullptr, nullptr, ws + w.do_l, lists, dq, dk, dv, loc, stream) !=
+        hipSuccess)
         return MOSAIC_BSA_ERR_LAUNCH;
     return MOSAIC_BSA_OK;
 }

@@ -606,7 +606,7 @@ hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v,
 {
     hipError_t e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
     if (e != hipSuccess) return e;
-    e = launch_bwd_prep(is_bf16, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
+    if (lse) e = launch_bwd_prep(is_bf16, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
     if (e != hipSuccess) return e;
 #define BSA_CASE(DD)                                                                             \
     case DD:                                                                                     \

@@ -724,7 +724,7 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
 {
     hipError_t e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
     if (e != hipSuccess) return e;
-    e = launch_bwd_prep(true, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
+    if (lse) e = launch_bwd_prep(true, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
     if (e != hipSuccess) return e;
     const int nw = g.block_tokens / 32;
     const uint32_t sx = (uint32_t)(BH / g.kv_group);           // key/value slices

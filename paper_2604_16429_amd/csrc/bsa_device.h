@@ -140,12 +140,16 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b)
     return __uint_as_float((uint32_t)b << 16);
 }
 
-__device__ __forceinline__ uint16_t f32_to_bf16(float f)   // round to nearest even
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+// Two fp32 values -> bf16 pair, round to nearest even (v_cvt_pk_bf16_f32; it
+// issues at the rate of any other three-operand vector instruction).
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    const f32x2 v = {a, b};
+    const bf16x2 r = __builtin_convertvector(v, bf16x2);
+    return __builtin_bit_cast(uint32_t, r);
 }
 
 // Element loaders: 4 consecutive channels as fp32.
@@ -176,8 +180,8 @@ __device__ __forceinline__ void store4(float* p, float4 v) { *(float4*)p = v; }
 __device__ __forceinline__ void store4(uint16_t* p, float4 v)
 {
     uint2 r;
-    r.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
-    r.y = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
+    r.x = pack_bf16(v.x, v.y);
+    r.y = pack_bf16(v.z, v.w);
     *(uint2*)p = r;
 }
 

@@ -74,6 +74,7 @@ hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v, con
 // key/value slice are worked on.  It is read before dQ is written: dq may serve.
 hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
                            float* delta, float* lse2, int64_t rows, int D, hipStream_t stream);
+// lse == nullptr in the launches below: delta and lse2 are there already.
 hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,
                               int64_t BH, hipStream_t stream);
 
@@ -113,14 +114,21 @@ hipError_t launch_combine(bool is_bf16, const float* obar, const void* o_fg, con
                           const float* gates, void* out, const Geom& g, int D, int64_t BH,
                           hipStream_t stream);
 
-// Backward of the three-branch output: upstream gradients of the two attention
-// branches and the gate gradients; the coarse branch's gradients on the pooled
+// Backward of the three-branch output: upstream gradients, delta and lse2 of the two
+// attention branches, the gate gradients and the gated block sums of dout; the coarse branch's gradients on the pooled
 // tensors, chunk_rows query blocks at a time (a_mat, ds_mat: fp32 scratch
 // [B*heads, chunk_rows, m]).
 int coarse_bwd_group_size(int m, int D);
-hipError_t launch_branch_grads(bool is_bf16, const float* obar, const void* o_fg, const void* o_l,
-                               const float* gates, const void* dout, void* do_fg, void* do_l,
-                               float* dgates, float* dobar, const Geom& g, int D, int64_t BH,
+struct BranchGrads {
+    const float* obar;                          // coarse rows
+    const void *o_fg, *o_l;                     // branch outputs
+    const float *lse_fg, *lse_l, *gates;
+    const void* dout;
+    void *do_fg, *do_l;                         // out: upstream gradients of the branches
+    float *dgates, *dobar;                      // out
+    float *delta_fg, *delta_l, *lse2_fg, *lse2_l;    // out: see launch_bwd_prep
+};
+hipError_t launch_branch_grads(bool is_bf16, const BranchGrads& x, const Geom& g, int D, int64_t BH,
                                hipStream_t stream);
 hipError_t launch_coarse_bwd(const float* qbar, const float* kbar, const float* kbar_il,
                              const float* vbar, const float* dobar, float* a_mat, float* ds_mat, float* dqbar,

@@ -9,8 +9,6 @@ namespace bsa {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
@@ -66,15 +64,6 @@ __device__ __forceinline__ float swap32(float x)
     // r[0] holds, for lanes < 32, their own value and for lanes >= 32 the value
     // of lane - 32; r[1] the opposite halves.
     return __uint_as_float(threadIdx.x & 32 ? r[0] : r[1]);
-}
-
-// Two fp32 values -> bf16 pair, round to nearest even (v_cvt_pk_bf16_f32; it
-// issues at the rate of any other three-operand vector instruction).
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    const f32x2 v = {a, b};
-    const bf16x2 r = __builtin_convertvector(v, bf16x2);
-    return __builtin_bit_cast(uint32_t, r);
 }
 
 // P^T = exp2(S^T c2 - m_ref) for one 32-key x 32-query tile, rounded to bf16 B

@@ -17,6 +17,7 @@
 #include "bsa_coarse.h"
 #include "bsa_device.h"
 #include "bsa_launch.h"
+#include "bsa_mfma_common.h"
 
 namespace bsa {
 
@@ -120,10 +121,10 @@ hipError_t launch_combine(bool is_bf16, const float* obar, const void* o_fg, con
 // Backward of the three-branch output (selection held fixed).
 //   branch_grads_kernel  dO_fg = g_fg * dO and dO_l = g_l * dO (what the
 //                        attention backward kernels of the two branches take
-//                        as upstream gradient) and the gate gradients
-//                        dg_b = dO . o_b per token.
-//   gated_block_sum_kernel  d(coarse row of block i) = sum over the tokens l
-//                        of the block of g_cg(l) * dO_l, fp32 [B*h, m, D].
+//                        as upstream gradient), delta and the base-2 log-sum-exps of
+//                        both branches, the gate gradients dg_b = dO . o_b per
+//                        token, and d(coarse row of block i) = sum over the
+//                        tokens l of the block of g_cg(l) * dO_l, fp32 [B*h, m, D].
 //   coarse_bwd_rows_kernel  per query block: block attention a_i, da_ij =
 //                        dobar_i . vbar_j, ds_ij = a_ij (da_ij - sum_j a_ij
 //                        da_ij); writes a and ds and dqbar_i = scale * sum_j
@@ -141,86 +142,160 @@ hipError_t launch_combine(bool is_bf16, const float* obar, const void* o_fg, con
 // backward, whose stores add (pooled gradient of the token's block) / b: the
 // mean pooling hands every token of a block the same share.
 // ---------------------------------------------------------------------------
-template <typename T, int VEC>
-__global__ __launch_bounds__(256) void branch_grads_kernel(
-    const float* __restrict__ obar, const T* __restrict__ o_fg, const T* __restrict__ o_l,
-    const float* __restrict__ gates, const T* __restrict__ dout, T* __restrict__ do_fg,
-    T* __restrict__ do_l, float* __restrict__ dgates, Geom g, int D, int64_t total)
+// 16 bytes as fp32 channels
+template <typename W> __device__ __forceinline__ void widen(const W& w, float (&x)[8])
 {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = e < total;
-    if (!valid) e = total - 1;                        // keep the lane groups whole
-    const int per_row = D / VEC;                      // lanes per token: a power of two <= 32
-    const int64_t row = e / per_row;
-    const int ch = (int)(e - row * per_row) * VEC;
-    const int64_t bh = row / g.n_tokens;
-    const int64_t tok = row - bh * g.n_tokens;
-    const int gr = (int)(tok / g.grid_w), gc = (int)(tok - (int64_t)gr * g.grid_w);
-    const int beta = (gr / g.block_h) * g.blocks_per_row + gc / g.block_w;
-    const float g_fg = gates[row * 3 + 1], g_l = gates[row * 3 + 2];
-    const float* ob = obar + (bh * g.n_blocks + beta) * D + ch;
-    float d_cg = 0.0f, d_fg = 0.0f, d_l = 0.0f;
 #pragma unroll
-    for (int v = 0; v < VEC; v += 4) {
-        const float4 up = load4(dout + row * D + ch + v);
-        const float4 a = *(const float4*)(ob + v);
-        const float4 f = load4(o_fg + row * D + ch + v);
-        const float4 l = load4(o_l + row * D + ch + v);
-        d_cg += up.x * a.x + up.y * a.y + up.z * a.z + up.w * a.w;
-        d_fg += up.x * f.x + up.y * f.y + up.z * f.z + up.w * f.w;
-        d_l += up.x * l.x + up.y * l.y + up.z * l.z + up.w * l.w;
-        if (valid) {
-            store4(do_fg + row * D + ch + v,
-                   make_float4(g_fg * up.x, g_fg * up.y, g_fg * up.z, g_fg * up.w));
-            store4(do_l + row * D + ch + v,
-                   make_float4(g_l * up.x, g_l * up.y, g_l * up.z, g_l * up.w));
-        }
-    }
-    for (int off = per_row >> 1; off >= 1; off >>= 1) {
-        d_cg += __shfl_xor(d_cg, off);
-        d_fg += __shfl_xor(d_fg, off);
-        d_l += __shfl_xor(d_l, off);
-    }
-    if (valid && ch == 0) {
-        dgates[row * 3 + 0] = d_cg;
-        dgates[row * 3 + 1] = d_fg;
-        dgates[row * 3 + 2] = d_l;
+    for (int e = 0; e < 4; ++e) {
+        x[2 * e] = __uint_as_float(w[e] << 16);
+        x[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
     }
 }
-
-// One thread per (block, group of VEC channels); tokens in in-tile order.
-template <typename T, int VEC>
-__global__ __launch_bounds__(256) void gated_block_sum_kernel(const T* __restrict__ dout,
-                                                              const float* __restrict__ gates,
-                                                              float* __restrict__ dobar, Geom g,
-                                                              int D, int64_t total)
+template <typename W> __device__ __forceinline__ void widen(const W& w, float (&x)[4])
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const int groups = D / VEC;
-    const int64_t blk = e / groups;                   // bh * m + beta
-    const int ch = (int)(e - blk * groups) * VEC;
-    const int64_t bh = blk / g.n_blocks;
-    const int beta = (int)(blk - bh * g.n_blocks);
-    float acc[VEC];
 #pragma unroll
-    for (int c = 0; c < VEC; ++c) acc[c] = 0.0f;
-    for (int tau = 0; tau < g.block_tokens; ++tau) {
-        const int64_t row = bh * g.n_tokens + token_of(g, beta, tau);
-        const float w = gates[row * 3 + 0];
+    for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(w[e]);
+}
+
+// The value of lane t of this lane's quad.
+__device__ __forceinline__ float quad_lane(float x, int t)
+{
+    const int i = __float_as_int(x);
+    return __int_as_float(t == 0   ? __builtin_amdgcn_update_dpp(0, i, 0x00, 0xf, 0xf, false)
+                          : t == 1 ? __builtin_amdgcn_update_dpp(0, i, 0x55, 0xf, 0xf, false)
+                          : t == 2 ? __builtin_amdgcn_update_dpp(0, i, 0xaa, 0xf, 0xf, false)
+                                   : __builtin_amdgcn_update_dpp(0, i, 0xff, 0xf, 0xf, false));
+}
+
+// One pass over dO and the two branch outputs.  A group of D/VEC adjacent lanes walks
+// the tokens of a quarter of a tile in in-tile order, VEC channels (16 bytes) per
+// lane: the dot products are summed inside the group, the gated sum of dO stays in
+// the lane's registers and the four quarters of a tile, which are neighbours in a
+// workgroup, are added through LDS in order.  delta of a branch is its gate times
+// the gate's gradient, so that the attention backward needs no pass of its own for
+// it.  One launch where there were four (gradients, gated sums, delta of each branch):
+// stage 2 at batch 8: 471 -> 268 us for
+// 1.1 GB.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void branch_grads_kernel(
+    const float* __restrict__ obar, const T* __restrict__ o_fg, const T* __restrict__ o_l,
+    const float* __restrict__ lse_fg, const float* __restrict__ lse_l,
+    const float* __restrict__ gates, const T* __restrict__ dout, T* __restrict__ do_fg,
+    T* __restrict__ do_l, float* __restrict__ dgates, float* __restrict__ dobar,
+    float* __restrict__ delta_fg, float* __restrict__ delta_l, float* __restrict__ lse2_fg,
+    float* __restrict__ lse2_l, Geom g, int64_t tiles)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int VEC = 16 / (int)sizeof(T), LANES = D / VEC;       // 4 to 32 lanes per token
+    constexpr int PARTS = 4, TILES = 256 / (LANES * PARTS);         // tiles per workgroup
+    constexpr int BATCH = 4;                                        // tokens in flight
+    __shared__ float sum_s[PARTS][TILES][D];
+    const int mine = threadIdx.x & 3;
+    const int lane = (int)threadIdx.x % LANES, part = ((int)threadIdx.x / LANES) % PARTS;
+    const int slot = (int)threadIdx.x / (LANES * PARTS);
+    int64_t tile = (int64_t)blockIdx.x * TILES + slot;              // bh * m + beta
+    const bool valid = tile < tiles;
+    if (!valid) tile = tiles - 1;                                   // keep the lane groups whole
+    const int64_t bh = tile / g.n_blocks;
+    const int beta = (int)(tile - bh * g.n_blocks);
+    const int ch = lane * VEC;
+    const int b = g.block_tokens;
+    float ob[VEC], acc[VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; v += 4) {
-            const float4 up = load4(dout + row * D + ch + v);
-            acc[v + 0] = fmaf(w, up.x, acc[v + 0]);
-            acc[v + 1] = fmaf(w, up.y, acc[v + 1]);
-            acc[v + 2] = fmaf(w, up.z, acc[v + 2]);
-            acc[v + 3] = fmaf(w, up.w, acc[v + 3]);
+    for (int v = 0; v < VEC; v += 4) {
+        const float4 t = *(const float4*)(obar + tile * D + ch + v);
+        ob[v] = t.x; ob[v + 1] = t.y; ob[v + 2] = t.z; ob[v + 3] = t.w;
+        acc[v] = acc[v + 1] = acc[v + 2] = acc[v + 3] = 0.0f;
+    }
+    const int tau_end = b * (part + 1) / PARTS;
+    int tau = b * part / PARTS, col = tau % g.block_w;
+    int64_t row = bh * g.n_tokens + token_of(g, beta, tau);         // of the next token
+    const int row_jump = g.grid_w - g.block_w;
+    while (tau < tau_end) {
+        const int count = min(BATCH, tau_end - tau);
+        int64_t rows[BATCH];
+        u32x4 w_up[BATCH], w_f[BATCH], w_l[BATCH];
+#pragma unroll
+        for (int t = 0; t < BATCH; ++t) {
+            rows[t] = row;
+            // (past the part's last token: that token again)
+            if (t + 1 < count || (t + 1 == count && tau + BATCH < tau_end)) {
+                ++row;
+                if (++col == g.block_w) { col = 0; row += row_jump; }
+            }
+            w_up[t] = *(const u32x4*)(dout + rows[t] * D + ch);
+            w_f[t] = *(const u32x4*)(o_fg + rows[t] * D + ch);
+            w_l[t] = *(const u32x4*)(o_l + rows[t] * D + ch);
         }
+        // scalars of a token: the lane whose number is t modulo 4 reads and writes
+        // those of token t, so that a wavefront's accesses cover runs of tokens; the
+        // others get them inside their quad
+        const int64_t my_row = mine == 0 ? rows[0] : mine == 1 ? rows[1]
+                               : mine == 2 ? rows[2] : rows[3];
+        float my_gate[3];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) my_gate[x] = gates[my_row * 3 + x];
+        const float my_fg = lse_fg[my_row], my_l = lse_l[my_row];
+        float my_cg = 0.0f, my_dfg = 0.0f, my_dl = 0.0f;
+#pragma unroll
+        for (int t = 0; t < BATCH; ++t) {
+            const bool live = t < count;
+            const float g_cg = quad_lane(my_gate[0], t), g_fg = quad_lane(my_gate[1], t),
+                        g_l = quad_lane(my_gate[2], t);
+            float up[VEC], f[VEC], l[VEC];
+            widen(w_up[t], up);
+            widen(w_f[t], f);
+            widen(w_l[t], l);
+            float d_cg = 0.0f, d_fg = 0.0f, d_l = 0.0f;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                d_cg = fmaf(up[v], ob[v], d_cg);
+                d_fg = fmaf(up[v], f[v], d_fg);
+                d_l = fmaf(up[v], l[v], d_l);
+                if (live) acc[v] = fmaf(g_cg, up[v], acc[v]);
+            }
+            if (valid && live) {
+#pragma unroll
+                for (int v = 0; v < VEC; v += 4) {
+                    store4(do_fg + rows[t] * D + ch + v,
+                           make_float4(g_fg * up[v], g_fg * up[v + 1], g_fg * up[v + 2],
+                                       g_fg * up[v + 3]));
+                    store4(do_l + rows[t] * D + ch + v,
+                           make_float4(g_l * up[v], g_l * up[v + 1], g_l * up[v + 2],
+                                       g_l * up[v + 3]));
+                }
+            }
+#pragma unroll
+            for (int off = LANES >> 1; off >= 1; off >>= 1) {
+                d_cg += __shfl_xor(d_cg, off);
+                d_fg += __shfl_xor(d_fg, off);
+                d_l += __shfl_xor(d_l, off);
+            }
+            my_cg = mine == t ? d_cg : my_cg;
+            my_dfg = mine == t ? d_fg : my_dfg;
+            my_dl = mine == t ? d_l : my_dl;
+        }
+        if (valid && lane < count) {                                // lane < 4: mine == lane
+            dgates[my_row * 3] = my_cg;
+            dgates[my_row * 3 + 1] = my_dfg;
+            dgates[my_row * 3 + 2] = my_dl;
+            delta_fg[my_row] = my_gate[1] * my_dfg;
+            delta_l[my_row] = my_gate[2] * my_dl;
+            lse2_fg[my_row] = my_fg * kCoarseLog2e;
+            lse2_l[my_row] = my_l * kCoarseLog2e;
+        }
+        tau += BATCH;
     }
 #pragma unroll
-    for (int v = 0; v < VEC; v += 4)
-        *(float4*)(dobar + blk * D + ch + v) =
-            make_float4(acc[v], acc[v + 1], acc[v + 2], acc[v + 3]);
+    for (int v = 0; v < VEC; ++v) sum_s[part][slot][ch + v] = acc[v];
+    __syncthreads();
+    for (int e = threadIdx.x; e < TILES * D; e += 256) {
+        const int t = e / D, d = e - t * D;
+        const int64_t out_tile = (int64_t)blockIdx.x * TILES + t;
+        if (out_tile < tiles)
+            dobar[out_tile * D + d] =
+                ((sum_s[0][t][d] + sum_s[1][t][d]) + sum_s[2][t][d]) + sum_s[3][t][d];
+    }
 }
 
 // Same workgroup shape as coarse_kernel (G <= 8 query blocks of one slice).
@@ -374,99 +449,103 @@ int coarse_bwd_group_size(int m, int D)
     return 0;
 }
 
-// One lane per key block j (a wavefront covers 64 consecutive ones of one
-// key/value slice): it walks the query blocks i = r0 .. r1-1 in ascending
-// order, reading column j of a and ds ([B*h, R, m]: lanes read consecutive
-// addresses) and adding a_ij * dobar_i and ds_ij * qbar_i into its D-channel
-// accumulators; the rows dobar_i and qbar_i are the same for the whole
-// wavefront.  The sums start from what dkbar / dvbar hold unless r0 == 0 and
-// are scaled only when r1 == m, so a sequence of calls over ascending chunks
-// adds every term once, in a fixed order.
+// The two column sums are matrix products, dvbar = a^T dobar and dkbar = ds^T qbar,
+// with the query blocks (of all heads of a group) as the contraction: fp32 matrix
+// instructions (v_mfma_f32_32x32x2_f32), a wavefront per 32 key blocks x 32
+// channels of one of them.  Both operands come straight from memory, two query
+// blocks per instruction (lane half h: block i + h), consecutive lanes reading
+// consecutive addresses; UNROLL instructions' operands are in flight.  Query blocks
+// ascend, heads of the group ascending outside: a fixed order.
+// The sums start from what dkbar / dvbar hold unless r0 == 0 and are scaled only
+// when r1 == m, so a sequence of calls over ascending chunks adds every term once.
+// (One lane per key block with the rows as scalar operands, as before, was a chain of
+// m * heads-per-group scalar-load latencies on a few wavefronts: stage 2 at batch 8
+// 381 -> 28 us.)
 template <int D>
 __global__ __launch_bounds__(256) void coarse_bwd_cols_kernel(
     const float* __restrict__ qbar, const float* __restrict__ dobar,
     const float* __restrict__ a_in, const float* __restrict__ ds_in, float* __restrict__ dkbar,
     float* __restrict__ dvbar, Geom g, int64_t waves, int R, int r0, int r1)
 {
+    constexpr int DT = D / 32, UNROLL = 8;
     const int m = g.n_blocks;
-    const int chunks = (m + 63) / 64;
-    // (made uniform for the compiler: the rows below then come in through scalar loads)
+    const int j_tiles = (m + 31) / 32;
     const int64_t wave_id =
         (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (wave_id >= waves) return;                     // whole wavefront; no barriers below
-    const int64_t kv = wave_id / chunks;              // key/value slice
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    // wave_id = ((slice * j_tiles + j tile) * DT + channel tile) * 2 + (0: values, 1: keys)
+    const bool keys = (wave_id & 1) != 0;
+    const int64_t rest = wave_id >> 1;
+    const int dt = (int)(rest % DT);
+    const int64_t kv = rest / DT / j_tiles;
+    const int j0 = (int)(rest / DT - kv * j_tiles) * 32;
     const int64_t kv_heads = g.heads / g.kv_group;
-    const int j = (int)(wave_id - kv * chunks) * 64 + (int)(threadIdx.x & 63);
-    const int jc = j < m ? j : m - 1;                 // clamped column of an idle lane
     const int64_t bh_first = (kv / kv_heads) * g.heads + (kv % kv_heads) * g.kv_group;
+    const int jc = j0 + l32 < m ? j0 + l32 : m - 1;   // an idle column repeats the last one
+    float* out = (keys ? dkbar : dvbar) + kv * m * D + 32 * dt + l32;
 
-    float acc_k[D], acc_v[D];
-    float* dk_row = dkbar + (kv * m + jc) * D;
-    float* dv_row = dvbar + (kv * m + jc) * D;
-    if (r0 == 0) {
+    // accumulator register r: key block j0 + 8 (r/4) + 4 half + r%4, channel 32 dt + l32
+    f32x16 acc;
 #pragma unroll
-        for (int d = 0; d < D; ++d) { acc_k[d] = 0.0f; acc_v[d] = 0.0f; }
-    } else {
-#pragma unroll
-        for (int d = 0; d < D; d += 4) {
-            const float4 pk = *(const float4*)(dk_row + d), pv = *(const float4*)(dv_row + d);
-            acc_k[d] = pk.x; acc_k[d + 1] = pk.y; acc_k[d + 2] = pk.z; acc_k[d + 3] = pk.w;
-            acc_v[d] = pv.x; acc_v[d + 1] = pv.y; acc_v[d + 2] = pv.z; acc_v[d + 3] = pv.w;
-        }
+    for (int r = 0; r < 16; ++r) {
+        const int j = j0 + 8 * (r >> 2) + 4 * half + (r & 3);
+        acc[r] = r0 > 0 && j < m ? out[(int64_t)j * D] : 0.0f;
     }
-    // query heads of the group in ascending order, query blocks ascending
     for (int gq = 0; gq < g.kv_group; ++gq) {
         const int64_t bh = bh_first + gq;
-        const float* a_col = a_in + bh * R * (int64_t)m + jc;
-        const float* s_col = ds_in + bh * R * (int64_t)m + jc;
-        const float* q_rows = qbar + bh * m * D;
-        const float* d_rows = dobar + bh * m * D;
-        for (int i = r0; i < r1; ++i) {
-            const float a = a_col[(int64_t)(i - r0) * m], ds = s_col[(int64_t)(i - r0) * m];
+        const float* w_col = (keys ? ds_in : a_in) + bh * R * (int64_t)m + jc;
+        const float* rows = (keys ? qbar : dobar) + bh * m * D + 32 * dt + l32;
+        for (int i0 = r0; i0 < r1; i0 += 2 * UNROLL) {
+            float w[UNROLL], x[UNROLL];
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                acc_v[d] = fmaf(a, d_rows[i * D + d], acc_v[d]);
-                acc_k[d] = fmaf(ds, q_rows[i * D + d], acc_k[d]);
+            for (int u = 0; u < UNROLL; ++u) {
+                const int i = i0 + 2 * u + half;
+                const bool in = i < r1;
+                w[u] = in ? w_col[(int64_t)(i - r0) * m] : 0.0f;
+                x[u] = in ? rows[(int64_t)i * D] : 0.0f;
             }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[u], x[u], acc, 0, 0, 0);
         }
     }
-    if (j < m) {
-        const float fk = r1 == m ? g.scale : 1.0f;
+    const float f = keys && r1 == m ? g.scale : 1.0f;
 #pragma unroll
-        for (int d = 0; d < D; d += 4) {
-            *(float4*)(dk_row + d) = make_float4(acc_k[d] * fk, acc_k[d + 1] * fk,
-                                                 acc_k[d + 2] * fk, acc_k[d + 3] * fk);
-            *(float4*)(dv_row + d) =
-                make_float4(acc_v[d], acc_v[d + 1], acc_v[d + 2], acc_v[d + 3]);
-        }
+    for (int r = 0; r < 16; ++r) {
+        const int j = j0 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (j < m) out[(int64_t)j * D] = acc[r] * f;
     }
 }
 
-hipError_t launch_branch_grads(bool is_bf16, const float* obar, const void* o_fg, const void* o_l,
-                               const float* gates, const void* dout, void* do_fg, void* do_l,
-                               float* dgates, float* dobar, const Geom& g, int D, int64_t BH,
+template <typename T, int D>
+static hipError_t launch_branch_grads_t(const BranchGrads& x, const Geom& g, int64_t BH,
+                                        hipStream_t stream)
+{
+    constexpr int TILES = 256 / (D * (int)sizeof(T) / 16 * 4);
+    const int64_t tiles = BH * g.n_blocks;
+    branch_grads_kernel<T, D><<<dim3((unsigned)((tiles + TILES - 1) / TILES)), dim3(256), 0,
+                                stream>>>(
+        x.obar, (const T*)x.o_fg, (const T*)x.o_l, x.lse_fg, x.lse_l, x.gates, (const T*)x.dout,
+        (T*)x.do_fg, (T*)x.do_l, x.dgates, x.dobar, x.delta_fg, x.delta_l, x.lse2_fg, x.lse2_l, g,
+        tiles);
+    return hipGetLastError();
+}
+
+hipError_t launch_branch_grads(bool is_bf16, const BranchGrads& x, const Geom& g, int D, int64_t BH,
                                hipStream_t stream)
 {
-    if (is_bf16) {
-        typedef uint16_t T;
-        const int64_t total = BH * g.n_tokens * (D / 8);
-        hipLaunchKernelGGL((branch_grads_kernel<T, 8>), dim3((unsigned)((total + 255) / 256)),
-                           dim3(256), 0, stream, obar, (const T*)o_fg, (const T*)o_l, gates,
-                           (const T*)dout, (T*)do_fg, (T*)do_l, dgates, g, D, total);
-        const int64_t blocks = BH * g.n_blocks * (D / 8);
-        hipLaunchKernelGGL((gated_block_sum_kernel<T, 8>), dim3((unsigned)((blocks + 255) / 256)),
-                           dim3(256), 0, stream, (const T*)dout, gates, dobar, g, D, blocks);
-    } else {
-        typedef float T;
-        const int64_t total = BH * g.n_tokens * (D / 4);
-        hipLaunchKernelGGL((branch_grads_kernel<T, 4>), dim3((unsigned)((total + 255) / 256)),
-                           dim3(256), 0, stream, obar, (const T*)o_fg, (const T*)o_l, gates,
-                           (const T*)dout, (T*)do_fg, (T*)do_l, dgates, g, D, total);
-        const int64_t blocks = BH * g.n_blocks * (D / 4);
-        hipLaunchKernelGGL((gated_block_sum_kernel<T, 4>), dim3((unsigned)((blocks + 255) / 256)),
-                           dim3(256), 0, stream, (const T*)dout, gates, dobar, g, D, blocks);
+#define BSA_CASE(DD)                                                                  \
+    case DD:                                                                          \
+        return is_bf16 ? launch_branch_grads_t<uint16_t, DD>(x, g, BH, stream)        \
+                       : launch_branch_grads_t<float, DD>(x, g, BH, stream);
+    switch (D) {
+        BSA_CASE(32)
+        BSA_CASE(64)
+        BSA_CASE(128)
     }
-    return hipGetLastError();
+#undef BSA_CASE
+    return hipErrorInvalidValue;
 }
 
 template <int D>
@@ -491,7 +570,7 @@ static hipError_t launch_coarse_bwd_t(const float* qbar, const float* kbar, cons
     const int R = chunk_rows;
     if (R < 1) return hipErrorInvalidValue;
     const int64_t BKV = BH / g.kv_group;
-    const int64_t waves = BKV * ((m + 63) / 64);
+    const int64_t waves = BKV * ((m + 31) / 32) * (D / 32) * 2;
     for (int r0 = 0; r0 < m; r0 += R) {
         const int r1 = r0 + R < m ? r0 + R : m;
         hipLaunchKernelGGL((coarse_bwd_rows_kernel<D>),

@@ -93,3 +93,36 @@ def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
         assert err <= tol, f"{name}: max error {err} > {tol}"
     again = G.gpu_bwd(cfg, q, k, v, dout, idx)
     assert all(np.array_equal(x, y) for x, y in zip(got, again))
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("heads,kv_heads,H,W,bh,bw,D,n,lh,lw", [
+    (2, 0, 9, 11, 1, 1, 32, 4, 3, 1),      # b = 1: parts of a tile without a token; m = 99
+    (2, 1, 10, 13, 5, 1, 128, 3, 2, 13),   # b = 5, m = 26: a column tile with idle columns
+    (4, 1, 33, 22, 3, 11, 64, 5, 11, 1),   # b = 33, m = 22, wide rows, group of 4
+    (2, 2, 24, 36, 4, 9, 32, 2, 1, 2),     # b = 36, m = 24
+    (1, 0, 66, 2, 2, 2, 64, 3, 1, 1),      # m = 33: one column past a 32-column tile
+])
+def test_general_three_branch(G, oracle, dtype, heads, kv_heads, H, W, bh, bw, D, n, lh, lw):
+    """Both directions of the three-branch form where the token parts of the branch
+    gradients, the 32-column tiles of the coarse branch's backward and the general
+    attention kernels have remainders.  Bounds of the repository's three-branch
+    tests: fp32 1e-4, bf16 2e-2 of max(1, largest entry); outputs 1e-5 / 2e-2."""
+    cfg = shape_ns(1, heads, H, W, bh, bw, D, n, dtype, kv_heads=kv_heads)
+    rng = np.random.default_rng(60 + H + W + D)
+    q, dout = (rng.standard_normal((1, heads, H * W, D)).astype(np.float32) for _ in range(2))
+    k, v = (rng.standard_normal((1, kv_heads or heads, H * W, D)).astype(np.float32)
+            for _ in range(2))
+    if dtype == "bf16":
+        q, k, v, dout = (round_to_bf16(x) for x in (q, k, v, dout))
+    gates = rng.uniform(-1.0, 1.0, size=(1, heads, H * W, 3)).astype(np.float32)
+    s = oracle.shape_of(cfg, own_is_candidate=True)
+    out, sel, dq, dk, dv, dg = G.gpu_three_branch_fwd_bwd(cfg, q, k, v, gates, dout, lh, lw)
+    assert np.array_equal(sel, oracle.select_all(s, q, oracle.expand_kv(k, heads)))
+    rq, rk, rv, rg, value = oracle.bwd_three_branch(s, q, k, v, gates, dout, sel, lh, lw)
+    tol = 2e-2 if dtype == "bf16" else 1e-4
+    for name, x, r in zip(("dq", "dk", "dv", "dgates"), (dq, dk, dv, dg), (rq, rk, rv, rg)):
+        err = np.abs(x - r).max()
+        assert err <= tol * max(1.0, np.abs(r).max()), f"{name}: {err}"
+    ref = np.asarray(value)
+    assert np.abs(out - ref).max() <= (2e-2 if dtype == "bf16" else 1e-5 * np.abs(ref).max())
