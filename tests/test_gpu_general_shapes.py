@@ -126,3 +126,27 @@ def test_general_three_branch(G, oracle, dtype, heads, kv_heads, H, W, bh, bw, D
         assert err <= tol * max(1.0, np.abs(r).max()), f"{name}: {err}"
     ref = np.asarray(value)
     assert np.abs(out - ref).max() <= (2e-2 if dtype == "bf16" else 1e-5 * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("H,W,bh,bw,n,levels", [
+    (24, 36, 2, 2, 70, 0),       # m = 216, more picks than one round of 32 places
+    (48, 48, 2, 2, 100, 0),      # m = 576: two key blocks per thread, four rounds
+    (48, 48, 2, 2, 16, 2),       # few distinct scores: more than 64 reach the threshold
+    (24, 36, 2, 2, 215, 2),      # n = m - 1 with ties
+    (5, 26, 1, 2, 64, 3),        # m = 65: a lane whose only candidate is removed
+    (1, 128, 1, 64, 1, 0),       # m = 2
+])
+def test_selection_rounds(G, oracle, H, W, bh, bw, n, levels):
+    """Top-n in rounds of a threshold: exact indices whatever the scores look like.
+    levels > 0: keys and queries take that many small integer values per block, so
+    that scores are exact and mostly equal."""
+    cfg = shape_ns(2, 2, H, W, bh, bw, 32, min(n, (H // bh) * (W // bw) - 1), "fp32")
+    q, k, _ = rand_qkv(cfg, 31 + n)
+    if levels:
+        rng = np.random.default_rng(n)
+        rows, cols = H // bh, W // bw
+        for x in (q, k):
+            v = rng.integers(0, levels, size=(2, 2, rows, 1, cols, 1, 1)).astype(np.float32)
+            x[:] = np.broadcast_to(v, (2, 2, rows, bh, cols, bw, 32)).reshape(x.shape)
+    s = oracle.shape_of(cfg)
+    assert np.array_equal(G.gpu_select(cfg, q, k), oracle.select(s, q, k))
