@@ -309,19 +309,19 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     for (int r = 0; r < 16; ++r) dp0[r] = neg_delta;
 
     __syncthreads();                                 // tables
-    const unsigned char* kb = (const unsigned char*)(k + kv_base);
-    const unsigned char* vb = (const unsigned char*)(v + kv_base);
+    const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
+    const RowSource ks(k + kv_base, slice_bytes), vs(v + kv_base, slice_bytes);
     const uint32_t k_dst = lds_address(k_lds), v_dst = lds_address(v_lds);
     if (wave < NL) {
         keys.look_up();
-        keys.gather_next(kb, vb, k_dst, v_dst);
+        keys.gather_next(ks, vs, k_dst, v_dst);
     }
     for (int c = 0; c < keys.tiles; ++c) {
         // tile c has landed and everyone is done with the other buffer
         wait_gathers();
         __syncthreads();
         const int buf = c & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
-        if (wave < NL && c + 1 < keys.tiles) keys.gather_next(kb, vb, k_dst + other, v_dst + other);
+        if (wave < NL && c + 1 < keys.tiles) keys.gather_next(ks, vs, k_dst + other, v_dst + other);
 #pragma unroll
         for (int hh = 0; hh < KT / 32; ++hh) {
             const uint32_t kt = k_dst + (uint32_t)buf * Tile::TILE_BYTES;
@@ -373,7 +373,8 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     __shared__ __attribute__((aligned(1024))) unsigned char g_lds[2][Tile::TILE_BYTES];
     __shared__ __attribute__((aligned(256))) float l_lds[2][64];
     __shared__ __attribute__((aligned(256))) float d_lds[2][64];
-    __shared__ uint32_t list_s[kConnCap];             // first token (in the group's rows) per block
+    __shared__ uint32_t list_s[kConnCap + repeated_entries(KT, 1)];   // first token (in the group's
+                                                      // rows) per block, the last one repeated
     __shared__ int state_s[2];                        // blocks listed, words left
     extern __shared__ __attribute__((aligned(16))) uint32_t pos_s[];        // [b]
 
@@ -397,10 +398,13 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
         const uint32_t e = unit / kv_heads, a = unit - e * kv_heads;
         bh_first = (int64_t)e * g.heads + (int64_t)a * g.kv_group;
     }
-    const unsigned char* qb = (const unsigned char*)(q + bh_first * g.n_tokens * D);
-    const unsigned char* gb = (const unsigned char*)(dout + bh_first * g.n_tokens * D);
+    const int64_t group_rows = g.kv_group * g.n_tokens;
+    const RowSource qs(q + bh_first * g.n_tokens * D, group_rows * Tile::ROW_BYTES),
+        gs(dout + bh_first * g.n_tokens * D, group_rows * Tile::ROW_BYTES);
     const float* lb = lse2 + bh_first * g.n_tokens;
     const float* db = delta + bh_first * g.n_tokens;
+    const i32x4 l_rsrc = buffer_desc(lb, (uint32_t)(group_rows * 4)),
+                d_rsrc = buffer_desc(db, (uint32_t)(group_rows * 4));
 
     fill_position_table(g, pos_s);
     TileReader<T, D> rd;
@@ -426,7 +430,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
 
     const uint32_t q_dst = lds_address(q_lds), g_dst = lds_address(g_lds);
     const uint32_t l_dst = lds_address(l_lds), d_dst = lds_address(d_lds);
-    const int step_q = KT / b, step_r = KT - step_q * b;
+    const uint32_t step_q = (uint32_t)(KT / b), step_r = (uint32_t)(KT % b);
 
     // the map's words of the group's heads, head-major: one flat sequence
     const int all_words = g.kv_group * words;
@@ -468,6 +472,15 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
         __syncthreads();
         const int listed = __builtin_amdgcn_readfirstlane(state_s[0]);
         const bool more = __builtin_amdgcn_readfirstlane(state_s[1]) != 0;
+        if (listed == 0) {
+            if (!more) break;
+            continue;
+        }
+        // rows past the end of the last tile take rows of the last block
+        const int repeats = repeated_entries(KT, b);
+        for (int e = threadIdx.x; e < repeats; e += blockDim.x)
+            list_s[listed + e] = list_s[listed - 1];
+        __syncthreads();
         const int total = listed * b;
         const int tiles = (total + KT - 1) / KT;
 
@@ -482,10 +495,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
             chunk_off[jj] = (uint32_t)Tile::swz(row, lane % Tile::LPR) * 16u;
         }
         at_row.start(lane, b);
-        auto row_of = [&](const FlatRow& r) -> uint32_t {   // past the end: the last row
-            const bool past = r.blk >= listed;
-            return list_s[past ? listed - 1 : r.blk] + pos_s[past ? b - 1 : r.tau];
-        };
+        auto row_of = [&](const FlatRow& r) -> uint32_t { return list_s[r.blk] + pos_s[r.tau]; };
         // rows of the next tile, looked up a tile before they are used
         auto look_up = [&] {
 #pragma unroll
@@ -499,21 +509,21 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
             }
         };
         auto gather_next = [&](int buf) {
-#pragma unroll
-            for (int jj = 0; jj < MINE; ++jj) {
-                const uint64_t off = (uint64_t)tok[jj] * Tile::ROW_BYTES + chunk_off[jj];
-                const uint32_t dst = (uint32_t)buf * Tile::TILE_BYTES +
-                                     (uint32_t)(wave + NL * jj) * 1024u;
-                load_lds_16_at(qb + off, q_dst + dst);
-                load_lds_16_at(gb + off, g_dst + dst);
-            }
+gather_rows<Tile, MINE, NL>(qs, gs, tok, chunk_off, wave,
+                                        q_dst + (uint32_t)buf * Tile::TILE_BYTES,
+                                        g_dst + (uint32_t)buf * Tile::TILE_BYTES);
             if (wave == 0) {
-                load_lds_4_at(lb + tok_row, l_dst + (uint32_t)buf * 256u);
-                load_lds_4_at(db + tok_row, d_dst + (uint32_t)buf * 256u);
+                if (__builtin_expect(!qs.wide, 1)) {
+                    load_lds_4(l_rsrc, tok_row * 4u, 0u, l_dst + (uint32_t)buf * 256u);
+                    load_lds_4(d_rsrc, tok_row * 4u, 0u, d_dst + (uint32_t)buf * 256u);
+                } else {
+                    load_lds_4_at(lb + tok_row, l_dst + (uint32_t)buf * 256u);
+                    load_lds_4_at(db + tok_row, d_dst + (uint32_t)buf * 256u);
+                }
             }
             look_up();
         };
-        if (wave < NL && tiles > 0) {
+        if (wave < NL) {
             look_up();
             gather_next(0);
         }

@@ -17,10 +17,17 @@ namespace bsa {
 
 constexpr int kListTable = 1024;           // listed blocks the LDS table holds
 
-// LDS of both tables for `listed` attended blocks (at most 8 KiB: b <= 1024)
+// Entries behind the last listed block that repeat it: rows past the end of the last
+// tile (of kt rows), and of the tile after it, which is looked up but not gathered,
+// then look up like any other row.  They carry no weight.
+__host__ __device__ constexpr int repeated_entries(int kt, int b) { return (2 * kt - 2) / b + 1; }
+
+// LDS of both tables for `listed` attended blocks (at most 8.5 KiB: b <= 1024)
 inline size_t flat_table_bytes(const Geom& g, int listed)
 {
-    return sizeof(uint32_t) * (size_t)(g.block_tokens + (listed < kListTable ? listed : kListTable));
+    return sizeof(uint32_t) *
+           (size_t)(g.block_tokens + (listed < kListTable ? listed : kListTable) +
+                    repeated_entries(64, g.block_tokens));
 }
 
 // Lane l: 16 bytes from src to LDS lds + 16 l (lds uniform); see load_lds_16.
@@ -53,20 +60,38 @@ __device__ __forceinline__ uint32_t block_first_token(const Geom& g, int beta)
     return (uint32_t)(br * g.block_h * g.grid_w + bc * g.block_w);
 }
 
-// Position of one row in the flat sequence: listed block, in-tile position.
+// Position of one row in the flat sequence: listed block, in-tile position.  Both
+// tables hold tokens, rows past the end need no test and the gathers take 32-bit
+// offsets from a descriptor, so that a gathered row costs about 10 vector instructions
+// (with clamped rows and 64-bit addresses 24: per 32 x 32 tile of the forward at head
+// dim 64 146 instead of 153 instructions in all; fp32 training pass, 1.5 degree grid,
+// 8 heads, 1.79 -> 1.74 ms, bf16 with tiles of 10 x 10 1.015 -> 1.006 ms).
 struct FlatRow {
-    int blk, tau;
+    uint32_t blk, tau;
     __device__ __forceinline__ void start(int p, int b)
     {
-        blk = p / b;
-        tau = p - blk * b;
+        blk = (uint32_t)p / (uint32_t)b;
+        tau = (uint32_t)p - blk * (uint32_t)b;
     }
     // step_q, step_r: quotient and remainder of the advance by b
-    __device__ __forceinline__ void advance(int step_q, int step_r, int b)
+    __device__ __forceinline__ void advance(uint32_t step_q, uint32_t step_r, uint32_t b)
     {
-        blk += step_q;
-        tau += step_r;
-        if (tau >= b) { tau -= b; ++blk; }
+        const uint32_t t = tau + step_r;
+        blk += step_q + (t >= b ? 1u : 0u);
+        tau = min(t, t - b);                 // t < b: t - b wraps to a large number
+    }
+};
+
+// Rows gathered to LDS from `bytes` bytes at base, 16 bytes per lane.  Offsets are 32
+// bits where the rows allow it (wide: they do not, and addresses are 64 bits).
+struct RowSource {
+    i32x4 rsrc;
+    const unsigned char* base;
+    bool wide;
+    __device__ __forceinline__ RowSource(const void* p, int64_t bytes)
+        : rsrc(buffer_desc(p, (uint32_t)bytes)), base((const unsigned char*)p),
+          wide(bytes >= (int64_t)1 << 31)
+    {
     }
 };
 
@@ -388,6 +413,33 @@ __device__ __forceinline__ void store_column(T* row, const f32x16 (&acc)[D / 32]
         }
 }
 
+// This wavefront's share of a tile of two tensors: slabs wave + NL j, row tok[j] of
+// both (ks and vs are equally long).
+template <typename Tile, int MINE, int NL>
+__device__ __forceinline__ void gather_rows(const RowSource& ks, const RowSource& vs,
+                                            const uint32_t (&tok)[MINE],
+                                            const uint32_t (&chunk_off)[MINE], int wave,
+                                            uint32_t k_dst, uint32_t v_dst)
+{
+    if (__builtin_expect(!ks.wide, 1)) {
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const uint32_t off = tok[j] * (uint32_t)Tile::ROW_BYTES | chunk_off[j];
+            const uint32_t dst = (uint32_t)(wave + NL * j) * 1024u;
+            load_lds_16(ks.rsrc, off, 0u, k_dst + dst);
+            load_lds_16(vs.rsrc, off, 0u, v_dst + dst);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const uint64_t off = (uint64_t)tok[j] * Tile::ROW_BYTES + chunk_off[j];
+            const uint32_t dst = (uint32_t)(wave + NL * j) * 1024u;
+            load_lds_16_at(ks.base + off, k_dst + dst);
+            load_lds_16_at(vs.base + off, v_dst + dst);
+        }
+    }
+}
+
 // The keys that a query block attends to, as a flat sequence gathered tile by tile
 // by the first NL wavefronts of a workgroup: block i itself followed by its
 // selected blocks, or, when the lists stand alone (list_only), exactly the listed
@@ -400,7 +452,8 @@ struct AttendedKeys {
     static_assert(Tile::SLABS % NL == 0, "slabs split evenly between the loading wavefronts");
 
     int total, tiles;               // keys, tiles
-    int b, n, step_q, step_r, wave;
+    int b, n, wave;
+    uint32_t step_q, step_r;
     const int32_t* sel_row;
     const uint32_t *pos_s, *first_s;
     FlatRow at[MINE];               // this lane's row of slab wave + NL j of the tile after
@@ -414,7 +467,7 @@ struct AttendedKeys {
         wave = wave_;
         b = g.block_tokens;
         uint32_t* pos = tables_s;                     // [b]
-        uint32_t* blocks = tables_s + b;              // [min(listed blocks, kListTable)]
+        uint32_t* blocks = tables_s + b;              // [min(listed blocks, kListTable) + repeats]
         pos_s = pos;
         first_s = blocks;
         const int list_only = g.list_only;
@@ -422,24 +475,38 @@ struct AttendedKeys {
         const int first = list_only ? sel_row[-1] : i;
         n = g.n_select - list_only;                   // blocks after the first
         fill_position_table(g, pos);
+        const int repeats = repeated_entries(Tile::KT, b);
         if (n < 64) {
             if (wave == 0) {
                 const int mine = lane < n ? sel_row[lane] : 0x7fffffff;
                 int rank = 1;
-                for (int t = 0; t < n; ++t)
-                    rank += __builtin_amdgcn_readlane(mine, t) < mine ? 1 : 0;
-                if (lane < n) blocks[rank] = block_first_token(g, mine);
-                if (lane == 0) blocks[0] = block_first_token(g, first);
+                for (int t = 0; t < n; ++t) {
+                    const int other = __builtin_amdgcn_readlane(mine, t);
+                    rank += other < mine || (other == mine && t < lane) ? 1 : 0;
+                }
+                if (lane < n) {
+                    const uint32_t tok0 = block_first_token(g, mine);
+                    blocks[rank] = tok0;
+                    if (rank == n)
+                        for (int e = 1; e <= repeats; ++e) blocks[n + e] = tok0;
+                }
+                if (lane == 0) {
+                    const uint32_t tok0 = block_first_token(g, first);
+                    blocks[0] = tok0;
+                    if (n == 0)
+                        for (int e = 1; e <= repeats; ++e) blocks[e] = tok0;
+                }
             }
         } else {
-            for (int t = threadIdx.x; t <= n && t < kListTable; t += blockDim.x)
-                blocks[t] = block_first_token(g, t == 0 ? first : sel_row[t - 1]);
+            const int table = min(n + 1 + repeats, kListTable);
+            for (int t = threadIdx.x; t < table; t += blockDim.x)
+                blocks[t] = block_first_token(g, t == 0 ? first : sel_row[min(t, n) - 1]);
         }
         geom = &g;
         total = (n + 1) * b;
         tiles = (total + Tile::KT - 1) / Tile::KT;
-        step_q = Tile::KT / b;
-        step_r = Tile::KT - step_q * b;
+        step_q = (uint32_t)(Tile::KT / b);
+        step_r = (uint32_t)(Tile::KT % b);
 #pragma unroll
         for (int j = 0; j < MINE; ++j) {
             const int row = Tile::RPS * (wave + NL * j) + lane / Tile::LPR;
@@ -450,33 +517,33 @@ struct AttendedKeys {
 
     // Looks up the rows of the next tile and moves on: once after the barrier, then
     // from gather_next, i.e. a whole tile before the tokens are used.  Rows past the
-    // end repeat the last row; they carry no weight.
+    // end take rows of the last block; they carry no weight.
     __device__ __forceinline__ void look_up()
     {
+        if (n + 1 + repeated_entries(Tile::KT, b) <= kListTable) {
 #pragma unroll
-        for (int j = 0; j < MINE; ++j) {
-            const bool past = at[j].blk > n;
-            const int blk = past ? n : at[j].blk, tau = past ? b - 1 : at[j].tau;
-            const uint32_t org = n < kListTable || blk < kListTable
-                                     ? first_s[blk]
-                                     : block_first_token(*geom, sel_row[blk - 1]);
-            tok[j] = org + pos_s[tau];
-            at[j].advance(step_q, step_r, b);
+            for (int j = 0; j < MINE; ++j) {
+                tok[j] = first_s[at[j].blk] + pos_s[at[j].tau];
+                at[j].advance(step_q, step_r, b);
+            }
+        } else {                                      // long lists: the rest from the selection
+#pragma unroll
+            for (int j = 0; j < MINE; ++j) {
+                const int blk = min((int)at[j].blk, n);
+                tok[j] = (blk < kListTable ? first_s[blk]
+                                           : block_first_token(*geom, sel_row[blk - 1])) +
+                         pos_s[at[j].tau];
+                at[j].advance(step_q, step_r, b);
+            }
         }
     }
 
-    // Gathers the next tile of both tensors (kb, vb: their slices; k_dst, v_dst: LDS
+    // Gathers the next tile of both tensors (ks, vs: their slices; k_dst, v_dst: LDS
     // addresses of the tiles).
-    __device__ __forceinline__ void gather_next(const unsigned char* kb, const unsigned char* vb,
+    __device__ __forceinline__ void gather_next(const RowSource& ks, const RowSource& vs,
                                                 uint32_t k_dst, uint32_t v_dst)
     {
-#pragma unroll
-        for (int j = 0; j < MINE; ++j) {
-            const uint64_t off = (uint64_t)tok[j] * Tile::ROW_BYTES + chunk_off[j];
-            const uint32_t dst = (uint32_t)(wave + NL * j) * 1024u;
-            load_lds_16_at(kb + off, k_dst + dst);
-            load_lds_16_at(vb + off, v_dst + dst);
-        }
+        gather_rows<Tile, MINE, NL>(ks, vs, tok, chunk_off, wave, k_dst, v_dst);
         look_up();
     }
 

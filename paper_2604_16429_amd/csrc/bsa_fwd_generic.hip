@@ -83,12 +83,12 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     for (int s = 0; s < RowPieces<T, D>::N; ++s) load_row(q + base + q_tok * D, qf[s], s, half);
     __syncthreads();                                 // tables
 
-    const unsigned char* kb = (const unsigned char*)(k + kv_base);
-    const unsigned char* vb = (const unsigned char*)(v + kv_base);
+    const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
+    const RowSource ks(k + kv_base, slice_bytes), vs(v + kv_base, slice_bytes);
     const uint32_t k_dst = lds_address(k_lds), v_dst = lds_address(v_lds);
     if (wave < NL) {
         keys.look_up();
-        keys.gather_next(kb, vb, k_dst, v_dst);
+        keys.gather_next(ks, vs, k_dst, v_dst);
     }
 
     const float c2 = g.scale * 1.4426950408889634f;
@@ -102,7 +102,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
         wait_gathers();
         __syncthreads();
         const int buf = c & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
-        if (wave < NL && c + 1 < keys.tiles) keys.gather_next(kb, vb, k_dst + other, v_dst + other);
+        if (wave < NL && c + 1 < keys.tiles) keys.gather_next(ks, vs, k_dst + other, v_dst + other);
         const uint32_t at = (uint32_t)buf * Tile::TILE_BYTES;
 #pragma unroll
         for (int hh = 0; hh < KT / 32; ++hh) {

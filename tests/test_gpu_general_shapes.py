@@ -35,6 +35,8 @@ SHAPES = [
     (34, 60, 17, 30, 64, 2),     # b = 510: two workgroups of eight, two idle rows
     (20, 26, 2, 2, 64, 63),      # 64 attended blocks: the last list that is sorted
     (20, 26, 2, 2, 64, 64),      # 65: kept in the given order
+    (46, 48, 1, 2, 32, 959),     # list and its repeated last entry just fit the LDS table
+    (46, 48, 1, 2, 32, 960),     # just not
     (46, 48, 1, 2, 32, 1030),    # more listed blocks than the LDS table holds
 ]
 
@@ -150,3 +152,48 @@ def test_selection_rounds(G, oracle, H, W, bh, bw, n, levels):
             x[:] = np.broadcast_to(v, (2, 2, rows, bh, cols, bw, 32)).reshape(x.shape)
     s = oracle.shape_of(cfg)
     assert np.array_equal(G.gpu_select(cfg, q, k), oracle.select(s, q, k))
+
+
+@pytest.mark.parametrize("H,grouped", [(2048, False), (1024, True)])
+def test_general_rows_past_32_bit_offsets(G, H, grouped):
+    """A slice (or the query slices that share a key/value slice) of more than 2 GiB
+    takes 64-bit addresses.  Block i attends to itself and to its successor, so the
+    last blocks' outputs and gradients follow from three blocks: checked there against
+    float64 reverse mode (outputs 1e-5, gradients 1e-4 of the largest entry)."""
+    import paper_2604_16429_amd as bsa
+    from paper_2604_16429_amd import binding
+    bh, bw, W, D, heads = 16, 43, 2064, 128, 2 if grouped else 1
+    p = bsa.Params(1, heads, H, W, bh, bw, D, 1, binding.F32, 0.0, 1)
+    N, m, rows = H * W, (H // bh) * (W // bw), W // bw
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, dout = (torch.randn((1, heads, N, D), generator=gen, device="cuda") for _ in range(2))
+    k, v = (torch.randn((1, 1, N, D), generator=gen, device="cuda") for _ in range(2))
+    idx = ((torch.arange(m, device="cuda", dtype=torch.int32) + 1) % m).view(1, 1, m, 1)
+    idx = idx.expand(1, heads, m, 1).contiguous()
+    out, dq = torch.empty_like(q), torch.empty_like(q)
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    lse = torch.empty((1, heads, N), device="cuda")
+    ws = torch.empty(bsa.mosaic_bsa_workspace_bytes(p, binding.OP_BWD), dtype=torch.uint8,
+                     device="cuda")
+    bsa.mosaic_bsa_fwd(p, q, k, v, idx, out, lse)
+    bsa.mosaic_bsa_bwd(p, q, k, v, out, lse, dout, idx, dq, dk, dv, ws)
+
+    def block(x, i):                      # [heads, b, D] in float64
+        x = x[0].view(x.shape[1], H // bh, bh, rows, bw, D)
+        return x[:, i // rows, :, i % rows].reshape(x.shape[0], bh * bw, D).double()
+
+    j = m - 2                             # attended by blocks m - 3 and m - 2
+    kv = {i: (block(k, i).requires_grad_(), block(v, i).requires_grad_()) for i in range(m - 3, m)}
+    qs = {i: block(q, i).requires_grad_() for i in (m - 3, m - 2)}
+    total = 0.0
+    for i, x in qs.items():
+        keys, values = (torch.cat([kv[i][t], kv[i + 1][t]], dim=1) for t in (0, 1))
+        o = torch.softmax(x @ keys.transpose(1, 2) / D ** 0.5, dim=-1) @ values
+        err = (block(out, i) - o).abs().max()
+        assert err <= 1e-5 * o.abs().max(), f"out of block {i}: {err}"
+        total = total + (o * block(dout, i)).sum()
+    total.backward()
+    for name, x, r in (("dq", block(dq, j), qs[j].grad), ("dk", block(dk, j), kv[j][0].grad),
+                       ("dv", block(dv, j), kv[j][1].grad)):
+        err = (x - r).abs().max()
+        assert err <= 1e-4 * r.abs().max(), f"{name} of block {j}: {err}"
