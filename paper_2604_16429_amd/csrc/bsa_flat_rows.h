@@ -384,12 +384,6 @@ __device__ __forceinline__ bool past_end(int r, int half, int left)
     return 8 * (r >> 2) + 4 * half + (r & 3) >= left;
 }
 
-__device__ __forceinline__ bf16x8 negated(bf16x8 x)
-{
-    uint4 u = __builtin_bit_cast(uint4, x);
-    u.x ^= 0x80008000u; u.y ^= 0x80008000u; u.z ^= 0x80008000u; u.w ^= 0x80008000u;
-    return __builtin_bit_cast(bf16x8, u);
-}
 __device__ __forceinline__ f32x4 negated(f32x4 x)
 {
     return -x;

@@ -66,6 +66,13 @@ __device__ __forceinline__ float swap32(float x)
     return __uint_as_float(threadIdx.x & 32 ? r[0] : r[1]);
 }
 
+__device__ __forceinline__ bf16x8 negated(bf16x8 x)
+{
+    uint4 u = __builtin_bit_cast(uint4, x);
+    u.x ^= 0x80008000u; u.y ^= 0x80008000u; u.z ^= 0x80008000u; u.w ^= 0x80008000u;
+    return __builtin_bit_cast(bf16x8, u);
+}
+
 // P^T = exp2(S^T c2 - m_ref) for one 32-key x 32-query tile, rounded to bf16 B
 // operands; returns this lane's sum of the fp32 weights.  Only builtins touch
 // the MFMA results (never inline asm): the compiler must see these reads to
