@@ -189,6 +189,21 @@ __device__ __forceinline__ f32x16 zero_tile()
     return z;
 }
 
+// Head dim 128, where a phase of matrix instructions is long (8 to 16 of them) and
+// nothing of the other phases is interleaved with it: the wavefront that is in such a
+// phase issues first, so that the two wavefronts of a SIMD drift apart and one's vector
+// work falls behind the other's matrix instructions.  Select + forward + backward,
+// 1.5 degrees, batch 4, 16 heads: 9.11 -> 8.92 ms.  At head dim 64, with phases half as
+// long, the same switches cost 0 to 4 %, and in the general kernels they give nothing.
+template <int D>
+__device__ __forceinline__ void matrix_phase(bool begin)
+{
+    if constexpr (D == 128) {
+        if (begin) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------
@@ -432,6 +447,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
             f32x16 s = zero_tile(), dp = neg_dl;
+            matrix_phase<D>(true);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -440,6 +456,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
             for (int ks = 0; ks < KS; ++ks)
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     row_frag<D>(vt_lds, 32 * kt, ks, l32, half), dof[ks], dp, 0, 0, 0);
+            matrix_phase<D>(false);
             f32x16 ds;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -448,6 +465,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
             }
             bf16x8 dsb[2];
             pack_tile(ds, dsb);
+            matrix_phase<D>(true);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -602,10 +620,12 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
             for (int qt = 0; qt < 2; ++qt) {
                 // S = Q K^T: rows = queries 32 qt .., this lane's column = its key
                 f32x16 s = zero_tile();
+                matrix_phase<D>(true);
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
                     s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         row_frag<D>(qt_lds, 32 * qt, ks, l32, half), kfb[ks], s, 0, 0, 0);
+                matrix_phase<D>(false);
                 // accumulator element r is query row 8 (r/4) + 4 half + r%4 of the tile
                 f32x16 p;
 #pragma unroll
@@ -619,6 +639,7 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
                 if constexpr (DO_DV) {
                     bf16x8 pb[2];
                     pack_tile(p, pb);
+                    matrix_phase<D>(true);
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -641,11 +662,13 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
                     for (int ks = 0; ks < KS; ++ks)
                         ds = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                             row_frag<D>(gt_lds, 32 * qt, ks, l32, half), vfb[ks], ds, 0, 0, 0);
+                    matrix_phase<D>(false);
                     // -dS; the sign goes into the scale of dK
 #pragma unroll
                     for (int r = 0; r < 16; ++r) ds[r] *= p[r];
                     bf16x8 dsb[2];
                     pack_tile(ds, dsb);
+                    matrix_phase<D>(true);
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
