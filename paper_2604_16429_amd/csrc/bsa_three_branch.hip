@@ -157,6 +157,18 @@ template <typename W> __device__ __forceinline__ void widen(const W& w, float (&
     for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(w[e]);
 }
 
+// x times f in the stored type.
+template <typename W> __device__ __forceinline__ void narrow(const float (&x)[8], float f, W& w)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = pack_bf16(f * x[2 * e], f * x[2 * e + 1]);
+}
+template <typename W> __device__ __forceinline__ void narrow(const float (&x)[4], float f, W& w)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(f * x[e]);
+}
+
 // The value of lane t of this lane's quad.
 __device__ __forceinline__ float quad_lane(float x, int t)
 {
@@ -171,11 +183,11 @@ __device__ __forceinline__ float quad_lane(float x, int t)
 // the tokens of a quarter of a tile in in-tile order, VEC channels (16 bytes) per
 // lane: the dot products are summed inside the group, the gated sum of dO stays in
 // the lane's registers and the four quarters of a tile, which are neighbours in a
-// workgroup, are added through LDS in order.  delta of a branch is its gate times
-// the gate's gradient, so that the attention backward needs no pass of its own for
-// it.  One launch where there were four (gradients, gated sums, delta of each branch):
-// stage 2 at batch 8: 471 -> 268 us for
-// 1.1 GB.
+// workgroup, are added through LDS in order.  delta of a branch is taken from the
+// upstream gradient as it is stored, i.e. rounded: the attention backward computes dP
+// from the same values, and in dP - delta their rounding then cancels for the most
+// part (gate times gate gradient, which needs no sum of its own, has no such luck).
+// One launch where there were four (gradients, gated sums, delta of each branch).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void branch_grads_kernel(
     const float* __restrict__ obar, const T* __restrict__ o_fg, const T* __restrict__ o_l,
@@ -236,7 +248,7 @@ __global__ __launch_bounds__(256) void branch_grads_kernel(
 #pragma unroll
         for (int x = 0; x < 3; ++x) my_gate[x] = gates[my_row * 3 + x];
         const float my_fg = lse_fg[my_row], my_l = lse_l[my_row];
-        float my_cg = 0.0f, my_dfg = 0.0f, my_dl = 0.0f;
+        float my_cg = 0.0f, my_dfg = 0.0f, my_dl = 0.0f, my_efg = 0.0f, my_el = 0.0f;
 #pragma unroll
         for (int t = 0; t < BATCH; ++t) {
             const bool live = t < count;
@@ -246,31 +258,36 @@ __global__ __launch_bounds__(256) void branch_grads_kernel(
             widen(w_up[t], up);
             widen(w_f[t], f);
             widen(w_l[t], l);
-            float d_cg = 0.0f, d_fg = 0.0f, d_l = 0.0f;
+            u32x4 s_fg, s_l;
+            narrow(up, g_fg, s_fg);
+            narrow(up, g_l, s_l);
+            float up_fg[VEC], up_l[VEC];                            // as they are stored
+            widen(s_fg, up_fg);
+            widen(s_l, up_l);
+            float d_cg = 0.0f, d_fg = 0.0f, d_l = 0.0f, e_fg = 0.0f, e_l = 0.0f;
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
                 d_cg = fmaf(up[v], ob[v], d_cg);
                 d_fg = fmaf(up[v], f[v], d_fg);
                 d_l = fmaf(up[v], l[v], d_l);
+                e_fg = fmaf(up_fg[v], f[v], e_fg);
+                e_l = fmaf(up_l[v], l[v], e_l);
                 if (live) acc[v] = fmaf(g_cg, up[v], acc[v]);
             }
             if (valid && live) {
-#pragma unroll
-                for (int v = 0; v < VEC; v += 4) {
-                    store4(do_fg + rows[t] * D + ch + v,
-                           make_float4(g_fg * up[v], g_fg * up[v + 1], g_fg * up[v + 2],
-                                       g_fg * up[v + 3]));
-                    store4(do_l + rows[t] * D + ch + v,
-                           make_float4(g_l * up[v], g_l * up[v + 1], g_l * up[v + 2],
-                                       g_l * up[v + 3]));
-                }
+                *(u32x4*)(do_fg + rows[t] * D + ch) = s_fg;
+                *(u32x4*)(do_l + rows[t] * D + ch) = s_l;
             }
 #pragma unroll
             for (int off = LANES >> 1; off >= 1; off >>= 1) {
                 d_cg += __shfl_xor(d_cg, off);
                 d_fg += __shfl_xor(d_fg, off);
                 d_l += __shfl_xor(d_l, off);
+                e_fg += __shfl_xor(e_fg, off);
+                e_l += __shfl_xor(e_l, off);
             }
+            my_efg = mine == t ? e_fg : my_efg;
+            my_el = mine == t ? e_l : my_el;
             my_cg = mine == t ? d_cg : my_cg;
             my_dfg = mine == t ? d_fg : my_dfg;
             my_dl = mine == t ? d_l : my_dl;
@@ -279,8 +296,8 @@ __global__ __launch_bounds__(256) void branch_grads_kernel(
             dgates[my_row * 3] = my_cg;
             dgates[my_row * 3 + 1] = my_dfg;
             dgates[my_row * 3 + 2] = my_dl;
-            delta_fg[my_row] = my_gate[1] * my_dfg;
-            delta_l[my_row] = my_gate[2] * my_dl;
+            delta_fg[my_row] = my_efg;
+            delta_l[my_row] = my_el;
             lse2_fg[my_row] = my_fg * kCoarseLog2e;
             lse2_l[my_row] = my_l * kCoarseLog2e;
         }

@@ -197,3 +197,27 @@ def test_general_rows_past_32_bit_offsets(G, H, grouped):
                        ("dv", block(dv, j), kv[j][1].grad)):
         err = (x - r).abs().max()
         assert err <= 1e-4 * r.abs().max(), f"{name} of block {j}: {err}"
+
+
+@pytest.mark.parametrize("H,W,bh,bw,D,n,lh,lw", [
+    (32, 64, 8, 8, 64, 6, 2, 2),         # the kernels specialised for head dim 64
+    (32, 64, 8, 16, 128, 6, 2, 2),       # for head dim 128
+    (20, 60, 10, 10, 32, 6, 2, 2),       # the general ones
+])
+def test_three_branch_upstream_rounding_cancels(G, H, W, bh, bw, D, n, lh, lw):
+    """Equal values everywhere: every branch returns that value whatever its weights
+    are, so dq = 0.  The gated upstream gradients are rounded to bf16 (2^-9 of every
+    entry); dP and delta have to be taken from the same rounded values, or the
+    rounding's dot product with v, about 2^-9 / 3 |g dO| sqrt(D) per token, weighs
+    the mean key into dq.  Bound: the fp32 sums of dP and delta, D 2^-24 sum |dO v|
+    each, in the two attention branches, times the softmax scale and the largest
+    key; gates are at most 1."""
+    cfg = shape_ns(1, 2, H, W, bh, bw, D, n, "bf16")
+    rng = np.random.default_rng(17 + D)
+    q, k, dout = (rng.standard_normal((1, 2, H * W, D)).astype(np.float32) for _ in range(3))
+    q, k, dout = (round_to_bf16(x) for x in (q, k + 2.0, dout))
+    v = np.broadcast_to(rng.choice([-1.0, 1.0], size=(1, 2, 1, D)), q.shape).astype(np.float32)
+    gates = rng.uniform(0.0, 1.0, size=(1, 2, H * W, 3)).astype(np.float32)
+    dq = G.gpu_three_branch_fwd_bwd(cfg, q, k, np.ascontiguousarray(v), gates, dout, lh, lw)[2]
+    per_sum = D * 2.0 ** -24 * np.abs(dout).sum(axis=-1).max()
+    assert np.abs(dq).max() <= 2 * 2 * per_sum * np.abs(k).max() / np.sqrt(D)
