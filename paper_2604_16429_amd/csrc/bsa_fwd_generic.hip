@@ -27,13 +27,23 @@
 // dim 32, bf16, 17 blocks of 128: 9.77 -> 1.25 ms; the 32 x 64 grid in fp32: 121
 // -> 25 us (both with the selection as it is now).
 // Softmax without a row maximum per tile: weights are taken against a reference
-// that only moves when a row sum of a tile leaves the safe range.
+// that only moves when a row sum of a tile leaves the safe range.  The reference is
+// the rounded product of a score and c2, and exp2(fma(s, c2, -m_ref)) sees what the
+// rounding dropped: nothing that matters below kPlainRef, but more than the whole
+// range of exp2 once scores reach 2^31 (masks by a large finite score).  From
+// kPlainRef on a row keeps that remainder, and its weights are taken from
+// (s c2 - m_ref) - m_rest, which is exactly 0 at the largest score, in the branch
+// that moves references; rows below never leave the plain form.
 #include "bsa_device.h"
 #include "bsa_flat_rows.h"
 #include "bsa_launch.h"
 #include "bsa_mfma_common.h"
 
 namespace bsa {
+
+// References below this size are rounded by at most 2^-5: all weights of the row are
+// off by the same factor of at most 2^(1/32), which the normalisation takes out.
+constexpr float kPlainRef = 1048576.0f;
 
 // NL: wavefronts that issue the gathers (1, 2 or 4; the workgroup has at least
 // that many, up to 8).  row_chunks workgroups share a query block's rows,
@@ -95,7 +105,8 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     f32x16 oacc[D / 32];
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) oacc[dt] = zero_tile();
-    float m_ref = -INFINITY, l_run = 0.0f;
+    float m_ref = -INFINITY, m_rest = 0.0f, l_run = 0.0f;
+    uint64_t rests = 0;                              // lanes whose m_rest is not 0
 
     for (int c = 0; c < keys.tiles; ++c) {
         // tile c has landed and everyone is done with the other buffer
@@ -126,15 +137,21 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 rs1 += p[r + 1];
             }
             float rs = rs0 + rs1;
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(rs <= kSumLimit)) != 0, 0)) {
+            if (__builtin_expect((__builtin_amdgcn_ballot_w64(!(rs <= kSumLimit)) | rests) != 0,
+                                 0)) {
                 // new reference from the row maxima; rescale what is there
                 float mx = s[0];
 #pragma unroll
                 for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
                 mx = fmaxf(mx, swap32(mx));
-                const float m_new = fmaxf(m_ref, mx * c2);
-                const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+                const bool up = fmaf(mx, c2, -m_ref) > m_rest;
+                const float m_new = up ? mx * c2 : m_ref;
+                const float rest_new =
+                    !up ? m_rest : fabsf(m_new) >= kPlainRef ? fmaf(mx, c2, -m_new) : 0.0f;
+                const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) + (m_rest - rest_new));
                 m_ref = m_new;
+                m_rest = rest_new;
+                rests = __builtin_amdgcn_ballot_w64(rest_new != 0.0f);
                 l_run *= alpha;
 #pragma unroll
                 for (int dt = 0; dt < D / 32; ++dt)
@@ -143,7 +160,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 rs = 0.0f;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -m_new));
+                    p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -m_new) - rest_new);
                     rs += p[r];
                 }
             }
@@ -158,7 +175,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
         store_column<T, D>(out + base + q_tok * D, oacc, inv_l, nullptr, 0.0f, half);
         if (lse && half == 0)
             lse[bh_idx * g.n_tokens + q_tok] =
-                (m_ref + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
+                (m_ref + (m_rest + __builtin_amdgcn_logf(l_tot))) * 0.6931471805599453f;
     }
 }
 

@@ -69,6 +69,45 @@ def test_general_forward(G, oracle, dtype, H, W, bh, bw, D, n):
     assert np.abs(lse - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
 
 
+@pytest.mark.parametrize("mask", [-1e10, -1e30, -3e38])
+@pytest.mark.parametrize("dtype,H,W,bh,bw,D", [
+    ("fp32", 10, 20, 5, 5, 32), ("fp32", 16, 32, 8, 8, 64), ("fp32", 10, 20, 5, 5, 128),
+    ("bf16", 16, 32, 8, 8, 32), ("bf16", 10, 20, 5, 5, 64), ("bf16", 10, 20, 5, 5, 128),
+])
+def test_general_forward_finite_masks(G, oracle, dtype, H, W, bh, bw, D, mask):
+    """Keys masked by a large finite score through a channel of their own.  Masked: the
+    first tiles of a row, the last ones, and all of them (block 0: the weights are
+    then equal; only for masks beside which the other channels vanish in 64 bits as
+    they do in 32).  Bounds of test_general_forward."""
+    cfg = shape_ns(1, 2, H, W, bh, bw, D, 2, dtype)
+    q, k, v = inputs_of(cfg, 3 + D)
+    rows, cols = H // bh, W // bw
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    grid = k.reshape(1, 2, rows, bh, cols, bw, D)            # blocks 0, 1, 2 are masked
+    grid[:, :, 0, :, :3, :, 0] = mask
+    if dtype == "bf16":
+        k = round_to_bf16(k)
+    idx = random_selection(cfg, 5)
+    idx[:, :, 0] = [1, 2]
+    idx[:, :, 1] = [0, cols]
+    idx[:, :, cols] = [0, cols + 1]
+    out_ref, lse_ref = oracle.fwd(oracle.shape_of(cfg), q, k, v, idx)
+    out, lse = G.gpu_fwd(cfg, q, k, v, idx)
+    keep = np.ones((H, W), dtype=bool)
+    if mask > -1e20:
+        keep[:bh, :bw] = False
+    keep = keep.reshape(-1)
+    err, ref = np.abs(out - out_ref)[:, :, keep], np.abs(out_ref)[:, :, keep]
+    if dtype == "fp32":
+        assert err.max() <= 1e-5 * ref.max()
+    else:
+        assert (err <= 2.0 ** -8 * ref + 2.0 ** -14 * np.abs(v).max()).all()
+    lse_err = np.abs(lse - lse_ref) / np.maximum(1.0, np.abs(lse_ref))
+    assert lse_err[:, :, keep].max() <= 1e-5
+    assert np.isfinite(out).all() and np.isfinite(lse).all()
+
+
 @pytest.mark.parametrize("dtype,kv_heads", [("fp32", 0), ("bf16", 0), ("fp32", 1), ("bf16", 1)])
 @pytest.mark.parametrize("H,W,bh,bw,D,n", SHAPES)
 def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
