@@ -328,7 +328,8 @@ extern "C" int mosaic_bsa_fwd_three_branch(const mosaic_bsa_params* params, int3
 namespace {
 
 // Scratch of the attention backward, see bwd_workspace.  order: int32 per key block of
-// every key/value slice (dK and dV are done before dQ is touched, so dq may serve).
+// every key/value slice (dK and dV are done before dQ is touched, so dq may serve), or
+// null: key blocks in ascending order, and dQ, which reads k and v, before dK and dV.
 struct BwdScratch {
     float *delta, *lse2;
     uint32_t* conn;
@@ -366,8 +367,10 @@ extern "C" int mosaic_bsa_bwd(const mosaic_bsa_params* params, const void* q, co
     if (!workspace || workspace_bytes < bwd_workspace(c)) return MOSAIC_BSA_ERR_WORKSPACE;
 
     char* ws = (char*)workspace;
+    const bool in_place = dk == k || dk == v || dv == k || dv == v;
     const BwdScratch scratch = {(float*)ws, (float*)(ws + bwd_rows_bytes(c)),
-                                (uint32_t*)(ws + 2 * bwd_rows_bytes(c)), (int32_t*)dq};
+                                (uint32_t*)(ws + 2 * bwd_rows_bytes(c)),
+                                in_place ? nullptr : (int32_t*)dq};
     return backward(c, c.g, q, k, v, out, lse, dout, sel_idx, dq, dk, dv, scratch,
                     (hipStream_t)hip_stream) == hipSuccess
                ? MOSAIC_BSA_OK

@@ -242,6 +242,7 @@ hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* o
     if (BH * words >= (int64_t)1 << 31) return hipErrorInvalidValue;
     bwd_connect_kernel<<<dim3((unsigned)(BH * words)), dim3(256), sizeof(uint32_t) * (size_t)cols,
                          stream>>>(sel_idx, conn, g, words);
+    if (!order) return hipGetLastError();
     bwd_order_kernel<<<dim3((unsigned)(BH / g.kv_group)), dim3(1024), 0, stream>>>(conn, order, g,
                                                                                   words);
     return hipGetLastError();
@@ -390,7 +391,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     map_unit(blockIdx.x, (uint32_t)(m * row_chunks), n_units, unit, item);
     const int place = (int)item / row_chunks;
     const int row0 = ((int)item - place * row_chunks) * chunk_rows;
-    const int j = order[(int64_t)unit * m + place];
+    const int j = order ? order[(int64_t)unit * m + place] : place;
     const int64_t base = (int64_t)unit * g.n_tokens * D;
     int64_t bh_first;
     {
@@ -593,20 +594,26 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
     if (BH * g.n_blocks * rows.chunks >= (int64_t)1 << 31) return hipErrorInvalidValue;
     const dim3 block(64 * nw), grid((unsigned)(BH * g.n_blocks * rows.chunks)),
         grid_kv((unsigned)(BKV * g.n_blocks * rows.chunks));
-    // dK and dV first: `order` may lie where dQ goes
-    auto kv_kernel = nw >= 4 ? bwd_generic_dkdv<T, D, 4>
-                     : nw >= 2 ? bwd_generic_dkdv<T, D, 2> : bwd_generic_dkdv<T, D, 1>;
-    kv_kernel<<<grid_kv, block, sizeof(uint32_t) * (size_t)g.block_tokens, stream>>>(
-        (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, conn, order, (T*)dk, (T*)dv, g,
-        (uint32_t)BKV, rows.chunks, 32 * nw);
-    const hipError_t e = hipGetLastError();
+    auto run_dkdv = [&] {
+        auto kernel = nw >= 4 ? bwd_generic_dkdv<T, D, 4>
+                      : nw >= 2 ? bwd_generic_dkdv<T, D, 2> : bwd_generic_dkdv<T, D, 1>;
+        kernel<<<grid_kv, block, sizeof(uint32_t) * (size_t)g.block_tokens, stream>>>(
+            (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, conn, order,
+            (T*)dk, (T*)dv, g, (uint32_t)BKV, rows.chunks, 32 * nw);
+        return hipGetLastError();
+    };
+    auto run_dq = [&] {
+        auto kernel = nw >= 4 ? bwd_generic_dq<T, D, 4>
+                      : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
+        kernel<<<grid, block, flat_table_bytes(g, g.n_select + 1), stream>>>(
+            (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, sel_idx, (T*)dq, g,
+            (uint32_t)BKV, rows.chunks, 32 * nw);
+        return hipGetLastError();
+    };
+    // `order` may lie where dQ goes; without it dK and dV may lie where k and v are
+    const hipError_t e = order ? run_dkdv() : run_dq();
     if (e != hipSuccess) return e;
-    auto dq_kernel = nw >= 4 ? bwd_generic_dq<T, D, 4>
-                     : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
-    dq_kernel<<<grid, block, flat_table_bytes(g, g.n_select + 1), stream>>>(
-        (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, sel_idx, (T*)dq, g,
-        (uint32_t)BKV, rows.chunks, 32 * nw);
-    return hipGetLastError();
+    return order ? run_dq() : run_dkdv();
 }
 
 hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v, const void* out,
@@ -614,9 +621,10 @@ hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v,
                       void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
                       const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
-    hipError_t e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     if (lse) e = launch_bwd_prep(is_bf16, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
+    if (e != hipSuccess) return e;
+    e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
     if (e != hipSuccess) return e;
 #define BSA_CASE(DD)                                                                             \
     case DD:                                                                                     \

@@ -525,7 +525,7 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
     {
         uint32_t unit, r;
         map_unit(blockIdx.x, (uint32_t)m, n_units, unit, r);
-        j = order[(int64_t)unit * m + r];
+        j = order ? order[(int64_t)unit * m + r] : (int)r;
         kv_unit = unit;
         base = (int64_t)unit * g.n_tokens * D;
         const uint32_t kv_heads = (uint32_t)(g.heads / g.kv_group);
@@ -764,34 +764,40 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
                            void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
                            const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
-    hipError_t e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     if (lse) e = launch_bwd_prep(true, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
+    if (e != hipSuccess) return e;
+    e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
     if (e != hipSuccess) return e;
     const int nw = g.block_tokens / 32;
     const uint32_t sx = (uint32_t)(BH / g.kv_group);           // key/value slices
     const dim3 grid((unsigned)(BH * g.n_blocks)), grid_kv(sx * (unsigned)g.n_blocks), block(64 * nw);
-    // dK and dV first: `order` may lie where dQ goes
-#define BSA_DKDV(KERNEL)                                                                          \
-    KERNEL<<<grid_kv, block, 0, stream>>>(                                                        \
-        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2,  \
-        delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);                                 \
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-#define BSA_DQ(KERNEL)                                                                            \
-    KERNEL<<<grid, block, 0, stream>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
-                                       (const uint16_t*)dout, lse2, delta, sel_idx, (uint16_t*)dq, \
-                                       g, sx);                                                    \
-    return hipGetLastError();
+    auto run_dkdv = [&](auto kernel) {
+        kernel<<<grid_kv, block, 0, stream>>>(
+            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2,
+            delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);
+        return hipGetLastError();
+    };
+    auto run_dq = [&](auto kernel) {
+        kernel<<<grid, block, 0, stream>>>((const uint16_t*)q, (const uint16_t*)k,
+                                           (const uint16_t*)v, (const uint16_t*)dout, lse2, delta,
+                                           sel_idx, (uint16_t*)dq, g, sx);
+        return hipGetLastError();
+    };
+    // `order` may lie where dQ goes; without it dK and dV may lie where k and v are (head
+    // dim 128: only dK, its pass still reads v)
 #define BSA_LAUNCH(D_, NW_)                                                                       \
     if (D == D_ && nw == NW_) {                                                                   \
-        BSA_DKDV(bwd_mfma_dv_d##D_##_w##NW_)                                                      \
-        BSA_DKDV(bwd_mfma_dk_d##D_##_w##NW_)                                                      \
-        BSA_DQ(bwd_mfma_dq_d##D_##_w##NW_)                                                        \
+        if (!order && (e = run_dq(bwd_mfma_dq_d##D_##_w##NW_)) != hipSuccess) return e;           \
+        if ((e = run_dkdv(bwd_mfma_dv_d##D_##_w##NW_)) != hipSuccess) return e;                   \
+        if ((e = run_dkdv(bwd_mfma_dk_d##D_##_w##NW_)) != hipSuccess) return e;                   \
+        return order ? run_dq(bwd_mfma_dq_d##D_##_w##NW_) : hipSuccess;                           \
     }
 #define BSA_LAUNCH_FUSED(NW_)                                                                     \
     if (D == 64 && nw == NW_) {                                                                   \
-        BSA_DKDV(bwd_mfma_dkdv_d64_w##NW_)                                                        \
-        BSA_DQ(bwd_mfma_dq_d64_w##NW_)                                                            \
+        if (!order && (e = run_dq(bwd_mfma_dq_d64_w##NW_)) != hipSuccess) return e;               \
+        if ((e = run_dkdv(bwd_mfma_dkdv_d64_w##NW_)) != hipSuccess) return e;                     \
+        return order ? run_dq(bwd_mfma_dq_d64_w##NW_) : hipSuccess;                               \
     }
     BSA_LAUNCH_FUSED(2)
     BSA_LAUNCH_FUSED(4)
@@ -800,8 +806,6 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
     BSA_LAUNCH(128, 4)
     BSA_LAUNCH(128, 8)
 #undef BSA_LAUNCH
-#undef BSA_DKDV
-#undef BSA_DQ
     return hipErrorInvalidValue;
 }
 

@@ -71,17 +71,19 @@ hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v, con
 // What both backward paths need first: delta_l = dO_l . O_l and lse_l * log2(e)
 // (fp32, `rows` of each), the reverse map of the selection in `conn` and, in
 // `order` (int32, key/value slices x m), the order in which the key blocks of each
-// key/value slice are worked on.  It is read before dQ is written: dq may serve.
+// key/value slice are worked on.  It is read before dQ is written: dq may serve; null:
+// ascending.  The preparation comes first: `order` may lie in the memory of `out`.
 hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
                            float* delta, float* lse2, int64_t rows, int D, hipStream_t stream);
-// lse == nullptr in the launches below: delta and lse2 are there already.
 hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,
                               int64_t BH, hipStream_t stream);
 
 // Backward with the selection fixed, any tile shape / head dim in {32, 64, 128} /
 // dtype.  `delta` and `lse2` are fp32 scratch of B*heads*N floats each, `conn`
 // scratch of bwd_connection_words(...) 32-bit words (the reverse map of the
-// selection: one bit per (query slice, key block, query block)).
+// selection: one bit per (query slice, key block, query block)).  lse == nullptr: delta
+// and lse2 are there already.  order == nullptr: dQ is computed before dK and dV, which
+// may then be written over k and v (a workgroup reads only the rows that it writes).
 inline int64_t bwd_connection_words(int m, int64_t BH) { return BH * m * (int64_t)((m + 31) >> 5); }
 hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v, const void* out,
                       const float* lse, const void* dout, const int32_t* sel_idx, void* dq,

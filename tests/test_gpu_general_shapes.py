@@ -136,6 +136,43 @@ def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
     assert all(np.array_equal(x, y) for x, y in zip(got, again))
 
 
+@pytest.mark.parametrize("dtype,H,W,bh,bw,D,kv_heads,dv_in_place", [
+    ("fp32", 10, 20, 5, 5, 64, 1, True),      # general kernels
+    ("bf16", 32, 40, 16, 20, 32, 2, True),    # two workgroups per block
+    ("bf16", 32, 64, 8, 8, 64, 1, True),      # head dim 64: dK and dV in one pass
+    ("bf16", 32, 64, 8, 16, 128, 2, False),   # head dim 128: two passes
+])
+def test_backward_in_place(G, dtype, H, W, bh, bw, D, kv_heads, dv_in_place):
+    """Gradients over inputs: dq in the memory of out (the order of the key blocks,
+    which lies in dq, must not be there before out is read), dk and dv in those of k
+    and v.  Bitwise the result of separate tensors."""
+    import paper_2604_16429_amd as bsa
+    from paper_2604_16429_amd import binding
+    cfg = shape_ns(2, 2, H, W, bh, bw, D, 3, dtype, kv_heads)
+    p = G.params_of(cfg)
+    element = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    q, dout = (torch.randn((2, 2, H * W, D), generator=gen, device="cuda").to(element)
+               for _ in range(2))
+    k, v = (torch.randn((2, kv_heads, H * W, D), generator=gen, device="cuda").to(element)
+            for _ in range(2))
+    idx = G.select_dev(cfg, q, k)
+    out, lse = G.fwd_dev(cfg, q, k, v, idx)
+    ws = torch.empty(bsa.mosaic_bsa_workspace_bytes(p, binding.OP_BWD), dtype=torch.uint8,
+                     device="cuda")
+    ref = [torch.empty_like(t) for t in (q, k, v)]
+    bsa.mosaic_bsa_bwd(p, q, k, v, out, lse, dout, idx, *ref, ws)
+
+    o = out.clone()
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    bsa.mosaic_bsa_bwd(p, q, k, v, o, lse, dout, idx, o, dk, dv, ws)
+    assert all(torch.equal(x, r) for x, r in zip((o, dk, dv), ref))
+    o, k2, v2 = out.clone(), k.clone(), v.clone()
+    dv = v2 if dv_in_place else torch.empty_like(v)
+    bsa.mosaic_bsa_bwd(p, q, k2, v2, o, lse, dout, idx, o, k2, dv, ws)
+    assert all(torch.equal(x, r) for x, r in zip((o, k2, dv), ref))
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("heads,kv_heads,H,W,bh,bw,D,n,lh,lw", [
     (2, 0, 9, 11, 1, 1, 32, 4, 3, 1),      # b = 1: parts of a tile without a token; m = 99
