@@ -226,43 +226,21 @@ __device__ __forceinline__ uint32_t rank_key(float s)
     return max((u & 0x80000000u) ? ~u : (u | 0x80000000u), 1u);
 }
 
-// Wave-wide reductions over all 64 lanes (all lanes must be active); the
-// result is wave-uniform.  Four DPP butterfly steps inside each row of 16
-// lanes, then two row broadcasts (lane 15 of a row into the next row, lane 31
-// into rows 2 and 3; lanes of the other rows are not written) leave the result
-// in lane 63.  Written as one instruction per step: the compiler emits three
-// for a row broadcast.  A DPP operand must not be read in the two issue slots
-// after it was written, hence the s_nop between the steps.
-#define BSA_WAVE_REDUCE(OP, V)                                                              \
-    asm volatile("s_nop 1\n\t"                                                             \
-                 OP " %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t" \
-                 OP " %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t" \
-                 OP " %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"      \
-                 OP " %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"           \
-                 OP " %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\ts_nop 1\n\t"         \
-                 OP " %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\ts_nop 1"              \
-                 : "+v"(V))
-
-__device__ __forceinline__ uint32_t wave_umax(uint32_t v)
-{
-    BSA_WAVE_REDUCE("v_max_u32_dpp", v);
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-__device__ __forceinline__ uint32_t wave_umin(uint32_t v)
-{
-    BSA_WAVE_REDUCE("v_min_u32_dpp", v);
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
 // Top-n of one row of m ranking keys (in LDS) by one wavefront; cand: 64 words of LDS
 // of its own.  A round finds a threshold that at least `want` lanes' best keys reach
 // (bit by bit, 20 of the 32 bits: a lower threshold only lets more through), collects
 // the candidates at or above it, which are therefore the best `count` >= want of all,
 // as composites (key << 32 | ~j) that are distinct and order exactly as the ranking
 // does, and places each by counting the larger ones.  On smooth scores a round of
-// 16 collects about 20 candidates.  More than 64 (clustered or equal scores): half as
-// many wanted, in the end one pick by arg-max.  Rounds repeat until n are placed.
+// 16 collects about 20 candidates.  Rounds repeat until n are placed.
+// Clustered scores (equal in their upper 20 bits) show in the number of lanes that
+// reach the threshold, which then gets all 32 bits.  Equal scores: if the threshold
+// is the largest key itself, its blocks are placed as they come, in ascending order;
+// if more than 64 candidates reach it, those above it are taken.  Otherwise more than
+// 64 mean that half as many are wanted (32 at first, 16 for most rows).
+// Ranking and pooling, n = 32: equal scores 450 blocks x 8 heads 120 -> 30 us, 4,096
+// x 4 3,770 -> 177; clustered 120 -> 33 and 3,810 -> 346; smooth 33.3 -> 33.5 and
+// 340 -> 345 (with one pick per round for equal and clustered scores before).
 // About 12 vector instructions per pick against 22 with a sorted list of 8 per lane
 // (m <= 512) and 110 with 64 candidates per lane (m <= 4096), and no registers that
 // grow with m: ranking 8,192 rows of 1,024 (head dim 32) 57 -> 30 us, 43,200
@@ -270,19 +248,14 @@ __device__ __forceinline__ uint32_t wave_umin(uint32_t v)
 __device__ __forceinline__ void topn_of_row(uint32_t* keys, uint64_t* cand,
                                             int32_t* __restrict__ dst, int m, int n, int lane)
 {
-    constexpr int kMaxWant = 32;
-    int done = 0, limit = kMaxWant;
-    while (done < n) {
-        uint32_t best = 0;
-        for (int j = lane; j < m; j += 64) best = max(best, keys[j]);
-        const int want = min(n - done, limit);
-        uint32_t floor_key = 0;
-#pragma unroll
-        for (int bit = 31; bit >= 12; --bit) {
-            const uint32_t t = floor_key | (1u << bit);
-            if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(best >= t)) >= want) floor_key = t;
-        }
-        floor_key = max(floor_key, 1u);              // 0 marks removed candidates
+    int done = 0, limit = 32;
+    // position of this lane among the set lanes of mask
+    auto place_in = [](uint64_t mask) {
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    };
+    // candidates with keys >= floor_key into cand (the first 64 of them); their number
+    auto collect = [&](uint32_t floor_key) {
         int count = 0;
         for (int j0 = 0; j0 < m; j0 += 64) {
             const int j = j0 + lane;
@@ -290,30 +263,56 @@ __device__ __forceinline__ void topn_of_row(uint32_t* keys, uint64_t* cand,
             const bool in = key >= floor_key;
             const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
             if (mask) {
-                const int at = count + (int)__builtin_amdgcn_mbcnt_hi(
-                                           (uint32_t)(mask >> 32),
-                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                const int at = count + place_in(mask);
                 if (in && at < 64) cand[at] = ((uint64_t)key << 32) | (uint32_t)~j;
                 count += __builtin_popcountll(mask);
             }
         }
-        if (count > 64 && want > 1) {
-            limit = want >> 1;
-            continue;
-        }
-        if (count > 64) {
-            // many equal scores: the best key, the smallest block index that has it
-            const uint32_t top = wave_umax(best);
-            uint32_t first = 0xffffffffu;
-            for (int j = lane; j < m; j += 64)
-                if (keys[j] == top) first = min(first, (uint32_t)j);
-            const uint32_t win = wave_umin(first);
-            if (lane == 0) {
-                dst[done] = (int32_t)win;
-                keys[win] = 0u;
+        return count;
+    };
+    while (done < n) {
+        uint32_t best = 0;
+        for (int j = lane; j < m; j += 64) best = max(best, keys[j]);
+        const int want = min(n - done, limit);
+        uint32_t floor_key = 0;
+        int bit = 31;
+        auto refine = [&](int last) {
+            for (; bit >= last; --bit) {
+                const uint32_t t = floor_key | (1u << bit);
+                if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(best >= t)) >= want)
+                    floor_key = t;
             }
-            ++done;
-            continue;
+        };
+        refine(12);
+        if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(best >= floor_key)) >= want + 8)
+            refine(0);
+        auto none_above = [&] { return __builtin_amdgcn_ballot_w64(best > floor_key) == 0; };
+        int count = 65;
+        if (bit >= 0 || !none_above()) count = collect(max(floor_key, 1u));   // 0: removed
+        if (count > 64) {
+            if (want == 1) refine(0);
+            if (bit < 0) {
+                if (none_above()) {
+                    // floor_key is the largest key left
+                    for (int j0 = 0; j0 < m && done < n; j0 += 64) {
+                        const int j = j0 + lane;
+                        const bool in = j < m && keys[j] == floor_key;
+                        const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+                        if (in) {
+                            const int at = done + place_in(mask);
+                            if (at < n) dst[at] = j;
+                            keys[j] = 0u;
+                        }
+                        done += __builtin_popcountll(mask);
+                    }
+                    continue;
+                }
+                count = collect(floor_key + 1);
+            }
+            if (count > 64) {
+                limit = want >> 1;
+                continue;
+            }
         }
         const uint64_t mine = lane < count ? cand[lane] : 0ull;
         int rank = 0;
@@ -330,6 +329,7 @@ __device__ __forceinline__ void topn_of_row(uint32_t* keys, uint64_t* cand,
             keys[block] = 0u;
         }
         done += placed;
+        if (limit < 16) limit *= 2;
     }
 }
 

@@ -213,14 +213,23 @@ def test_general_three_branch(G, oracle, dtype, heads, kv_heads, H, W, bh, bw, D
     (24, 36, 2, 2, 215, 2),      # n = m - 1 with ties
     (5, 26, 1, 2, 64, 3),        # m = 65: a lane whose only candidate is removed
     (1, 128, 1, 64, 1, 0),       # m = 2
+    (48, 48, 2, 2, 100, 1),      # all scores equal
+    (48, 48, 2, 2, 100, -1),     # clustered: distinct, equal in the threshold's first bits
+    (24, 36, 2, 2, 215, -1),
+    (48, 96, 2, 2, 90, -2),      # clustered on top of a few that stand out
 ])
 def test_selection_rounds(G, oracle, H, W, bh, bw, n, levels):
     """Top-n in rounds of a threshold: exact indices whatever the scores look like.
     levels > 0: keys and queries take that many small integer values per block, so
-    that scores are exact and mostly equal."""
+    that scores are exact and mostly equal; < 0: they share a large mean, so that
+    scores are clustered (-2: some key blocks are larger by half)."""
     cfg = shape_ns(2, 2, H, W, bh, bw, 32, min(n, (H // bh) * (W // bw) - 1), "fp32")
     q, k, _ = rand_qkv(cfg, 31 + n)
-    if levels:
+    if levels < 0:
+        q, k = q + np.float32(100.0), np.float32(0.01) * k + np.float32(100.0)
+        if levels == -2:
+            k[:, :, :3 * W] *= np.float32(1.5)
+    if levels > 0:
         rng = np.random.default_rng(n)
         rows, cols = H // bh, W // bw
         for x in (q, k):
