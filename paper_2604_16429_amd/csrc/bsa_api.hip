@@ -327,9 +327,10 @@ extern "C" int mosaic_bsa_fwd_three_branch(const mosaic_bsa_params* params, int3
 
 namespace {
 
-// Scratch of the attention backward, see bwd_workspace.  order: int32 per key block of
-// every key/value slice (dK and dV are done before dQ is touched, so dq may serve), or
-// null: key blocks in ascending order, and dQ, which reads k and v, before dK and dV.
+// Scratch of the attention backward, see bwd_workspace.  order: five bytes per key block
+// of every key/value slice (dK and dV are done before dQ is touched, so dq serves: it has
+// at least 64 bytes per block), or null: key blocks in ascending order, and dQ, which
+// reads k and v, before dK and dV.
 struct BwdScratch {
     float *delta, *lse2;
     uint32_t* conn;
@@ -381,7 +382,7 @@ namespace {
 
 // Workspace of the three-branch backward: 256-byte aligned parts in this order.
 struct ThreeBranchBwdLayout {
-    size_t rows[4], conn, order, do_fg, do_l, dobar, a_mat, ds_mat, dqbar, dkbar, dvbar, total;
+    size_t rows[4], conn, do_fg, do_l, dobar, a_mat, ds_mat, dqbar, dkbar, dvbar, total;
     int chunk_rows;        // query blocks per pass of the coarse branch's backward
 };
 
@@ -411,7 +412,6 @@ ThreeBranchBwdLayout three_branch_bwd_layout(const Checked& c)
     };
     for (size_t& r : w.rows) r = take(bwd_rows_bytes(c));    // delta and lse2 of both branches
     w.conn = take((size_t)bsa::bwd_connection_words(c.g.n_blocks, c.BH) * sizeof(uint32_t));
-    w.order = take((size_t)c.BKV * m * sizeof(int32_t));
     w.do_fg = take((size_t)c.BH * N * c.D * esz);
     w.do_l = take((size_t)c.BH * N * c.D * esz);
     w.dobar = take((size_t)c.BH * m * c.D * 4);
@@ -472,9 +472,10 @@ extern "C" int mosaic_bsa_bwd_three_branch(const mosaic_bsa_params* params, int3
     // upstream gradients of the two attention branches with their delta and lse2,
     // gate gradients, and the coarse rows' gradient (gated block sums of dout)
     const BwdScratch fg = {(float*)(ws + w.rows[0]), (float*)(ws + w.rows[1]),
-                           (uint32_t*)(ws + w.conn), (int32_t*)(ws + w.order)};
+                           (uint32_t*)(ws + w.conn), (int32_t*)dq};
+    // the local lists connect every block with the same number of others: no order
     const BwdScratch loc = {(float*)(ws + w.rows[2]), (float*)(ws + w.rows[3]),
-                            (uint32_t*)(ws + w.conn), (int32_t*)(ws + w.order)};
+                            (uint32_t*)(ws + w.conn), nullptr};
     const bsa::BranchGrads grads = {
         obar, fw + f.o_fg, fw + f.o_l, (const float*)(fw + f.lse_fg), (const float*)(fw + f.lse_l),
         gates, dout, ws + w.do_fg, ws + w.do_l, dgates, dobar, fg.delta, loc.delta, fg.lse2,

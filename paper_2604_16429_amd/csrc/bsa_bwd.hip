@@ -168,55 +168,99 @@ __global__ __launch_bounds__(256) void bwd_connect_kernel(const int32_t* __restr
 // degree grid: fp32, 8 slices, 9 blocks: 1.37 -> 0.97 ms (the longest of 3,600 lists
 // is 61 blocks, 0.5 ms of work); bf16, 48 key/value slices of 4 heads: 4.13 ->
 // 3.96 ms.
+constexpr int kClasses = 5;
+
+// Class of key block j of the slice whose query slices' map words start at base
+// (`all_words` columns of m words).  What bounds it is the latency of the reads.
+__device__ __forceinline__ int connection_class(const uint32_t* __restrict__ base, int m, int j,
+                                                int all_words, int mean)
+{
+    constexpr int BATCH = 16;
+    const uint32_t* at = base + j;
+    int deg = 0, w = 0;
+    for (; w + BATCH <= all_words; w += BATCH, at += (int64_t)BATCH * m) {
+        uint32_t x[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) x[u] = at[(int64_t)u * m];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) deg += __builtin_popcount(x[u]);
+    }
+    for (; w < all_words; ++w, at += m) deg += __builtin_popcount(*at);
+    return deg >= 4 * mean ? 0 : deg >= 3 * mean ? 1 : deg >= 2 * mean ? 2
+           : 2 * deg >= 3 * mean ? 3 : 4;
+}
+
+// First query slice of key/value slice u.
+__device__ __forceinline__ int64_t first_query_slice(const Geom& g, int64_t u)
+{
+    const int64_t kv_heads = g.heads / g.kv_group;
+    return (u / kv_heads) * g.heads + (u % kv_heads) * g.kv_group;
+}
+
+// The classes of all key blocks by the whole chip, for maps that are too large to be
+// read by one workgroup per slice; see launch_bwd_connect.
+__global__ __launch_bounds__(256) void bwd_class_kernel(const uint32_t* __restrict__ conn,
+                                                        uint8_t* __restrict__ classes, Geom g,
+                                                        int words, uint32_t chunks)
+{
+    const int m = g.n_blocks;
+    const int64_t unit = blockIdx.x / chunks;
+    const int j = (int)((blockIdx.x % chunks) * 256 + threadIdx.x);
+    if (j >= m) return;
+    classes[unit * m + j] = (uint8_t)connection_class(
+        conn + first_query_slice(g, unit) * words * (int64_t)m, m, j, g.kv_group * words,
+        g.kv_group * (g.n_select + 1 - g.list_only));
+}
+
+// One workgroup per key/value slice.  classes: from bwd_class_kernel, or null, then the
+// workgroup has a thread per key block.
 __global__ __launch_bounds__(1024) void bwd_order_kernel(const uint32_t* __restrict__ conn,
+                                                         const uint8_t* __restrict__ classes,
                                                          int32_t* __restrict__ order, Geom g,
                                                          int words)
 {
-    constexpr int CLASSES = 5;
-    __shared__ int count_s[16][CLASSES], start_s[CLASSES];
-    const int m = g.n_blocks;
+    __shared__ int count_s[16][kClasses], start_s[kClasses];
+    const int m = g.n_blocks, threads = blockDim.x, waves = threads >> 6;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t kv_heads = g.heads / g.kv_group;
-    const int64_t bh_first = (blockIdx.x / kv_heads) * g.heads +
-                             (blockIdx.x % kv_heads) * g.kv_group;
-    const uint32_t* base = conn + bh_first * words * (int64_t)m;     // the group's heads follow
-    const int all_words = g.kv_group * words;
-    const int mean = g.kv_group * (g.n_select + 1 - g.list_only);
-    auto class_of = [&](int j) {
-        int deg = 0;
-        for (int w = 0; w < all_words; ++w)
-            deg += __builtin_popcount(base[(int64_t)w * m + j]);
-        return deg >= 4 * mean ? 0 : deg >= 3 * mean ? 1 : deg >= 2 * mean ? 2
-               : 2 * deg >= 3 * mean ? 3 : 4;
-    };
+    const int64_t unit = blockIdx.x;
+    order += unit * m;
+    if (classes) classes += unit * m;
+    int first_class = kClasses;                      // of block threadIdx.x
+    if ((int)threadIdx.x < m)
+        first_class = classes ? classes[threadIdx.x]
+                              : connection_class(conn + first_query_slice(g, unit) * words * (int64_t)m,
+                                                 m, threadIdx.x, g.kv_group * words,
+                                                 g.kv_group * (g.n_select + 1 - g.list_only));
     // sizes of the classes
-    int mine[CLASSES] = {};
-    for (int j = threadIdx.x; j < m; j += 1024) {
-        const int cls = class_of(j);
+    int mine[kClasses];
 #pragma unroll
-        for (int c = 0; c < CLASSES; ++c) mine[c] += cls == c ? 1 : 0;
+    for (int c = 0; c < kClasses; ++c) mine[c] = first_class == c ? 1 : 0;
+    for (int j = threadIdx.x + threads; j < m; j += threads) {
+        const int cls = classes[j];
+#pragma unroll
+        for (int c = 0; c < kClasses; ++c) mine[c] += cls == c ? 1 : 0;
     }
 #pragma unroll
-    for (int c = 0; c < CLASSES; ++c) {
+    for (int c = 0; c < kClasses; ++c) {
         for (int off = 32; off >= 1; off >>= 1) mine[c] += __shfl_xor(mine[c], off);
         if (lane == 0) count_s[wave][c] = mine[c];
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         int at = 0;
-        for (int c = 0; c < CLASSES; ++c) {
+        for (int c = 0; c < kClasses; ++c) {
             start_s[c] = at;
-            for (int w = 0; w < 16; ++w) at += count_s[w][c];
+            for (int w = 0; w < waves; ++w) at += count_s[w][c];
         }
     }
     __syncthreads();
-    // 1,024 blocks at a time, in ascending order inside each class
-    for (int j0 = 0; j0 < m; j0 += 1024) {
+    // a block per thread at a time, in ascending order inside each class
+    for (int j0 = 0; j0 < m; j0 += threads) {
         const int j = j0 + (int)threadIdx.x;
-        const int cls = j < m ? class_of(j) : CLASSES;
+        const int cls = j0 == 0 ? first_class : j < m ? classes[j] : kClasses;
         int before = 0;
 #pragma unroll
-        for (int c = 0; c < CLASSES; ++c) {
+        for (int c = 0; c < kClasses; ++c) {
             const uint64_t mask = __builtin_amdgcn_ballot_w64(cls == c);
             if (cls == c) before = __builtin_popcountll(mask & ((1ull << lane) - 1));
             if (lane == 0) count_s[wave][c] = __builtin_popcountll(mask);
@@ -225,11 +269,11 @@ __global__ __launch_bounds__(1024) void bwd_order_kernel(const uint32_t* __restr
         if (j < m) {
             int at = start_s[cls] + before;
             for (int w = 0; w < wave; ++w) at += count_s[w][cls];
-            order[(int64_t)blockIdx.x * m + at] = j;
+            order[at] = j;
         }
         __syncthreads();
-        if (threadIdx.x < CLASSES)
-            for (int w = 0; w < 16; ++w) start_s[threadIdx.x] += count_s[w][threadIdx.x];
+        if (threadIdx.x < kClasses)
+            for (int w = 0; w < waves; ++w) start_s[threadIdx.x] += count_s[w][threadIdx.x];
         __syncthreads();
     }
 }
@@ -237,14 +281,28 @@ __global__ __launch_bounds__(1024) void bwd_order_kernel(const uint32_t* __restr
 hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,
                               int64_t BH, hipStream_t stream)
 {
-    const int words = (g.n_blocks + 31) >> 5;
-    const int cols = g.n_blocks < kMapCols ? g.n_blocks : kMapCols;
+    const int m = g.n_blocks, words = (m + 31) >> 5;
+    const int cols = m < kMapCols ? m : kMapCols;
     if (BH * words >= (int64_t)1 << 31) return hipErrorInvalidValue;
     bwd_connect_kernel<<<dim3((unsigned)(BH * words)), dim3(256), sizeof(uint32_t) * (size_t)cols,
                          stream>>>(sel_idx, conn, g, words);
     if (!order) return hipGetLastError();
-    bwd_order_kernel<<<dim3((unsigned)(BH / g.kv_group)), dim3(1024), 0, stream>>>(conn, order, g,
-                                                                                  words);
+    // A slice's map of up to 1,024 blocks and 64 words each is read where the order is
+    // made, a larger one by a launch of its own: 450 blocks with 60 words 9.9 us, in two
+    // launches 6.9 + 4.9; 1,024 with 128 8.0 + 5.0 us, 4,050 with 127 9.7 + 10.8 us (one
+    // workgroup per slice, counting twice: 93 and 205 us; the training pass of one slice
+    // of 16,200 blocks 8.9 -> 4.3 ms).
+    const int64_t BKV = BH / g.kv_group;
+    uint8_t* classes = nullptr;
+    if (m > 1024 || g.kv_group * words > 64) {
+        const uint32_t chunks = (uint32_t)(m + 255) / 256;
+        classes = (uint8_t*)(order + BKV * m);
+        bwd_class_kernel<<<dim3((unsigned)(BKV * chunks)), dim3(256), 0, stream>>>(conn, classes, g,
+                                                                                 words, chunks);
+    }
+    const int threads = m >= 1024 ? 1024 : (m + 63) / 64 * 64;
+    bwd_order_kernel<<<dim3((unsigned)BKV), dim3(threads), 0, stream>>>(conn, classes, order, g,
+                                                                        words);
     return hipGetLastError();
 }
 

@@ -70,9 +70,10 @@ hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v, con
 
 // What both backward paths need first: delta_l = dO_l . O_l and lse_l * log2(e)
 // (fp32, `rows` of each), the reverse map of the selection in `conn` and, in
-// `order` (int32, key/value slices x m), the order in which the key blocks of each
-// key/value slice are worked on.  It is read before dQ is written: dq may serve; null:
-// ascending.  The preparation comes first: `order` may lie in the memory of `out`.
+// `order` (int32, key/value slices x m, followed by as many bytes of scratch), the
+// order in which the key blocks of each key/value slice are worked on.  It is read
+// before dQ is written: dq may serve; null: ascending.  The preparation comes first:
+// `order` may lie in the memory of `out`.
 hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
                            float* delta, float* lse2, int64_t rows, int D, hipStream_t stream);
 hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,

@@ -136,6 +136,32 @@ def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
     assert all(np.array_equal(x, y) for x, y in zip(got, again))
 
 
+@pytest.mark.parametrize("heads,kv_heads,H,W,bh,bw,n", [
+    (4, 1, 40, 64, 2, 2, 9),     # m = 640: 80 words per key block, classes by the whole chip
+    (2, 1, 32, 128, 2, 2, 9),    # m = 1,024: 64 words, the last map read by its workgroup
+    (1, 0, 41, 50, 1, 2, 9),     # m = 1,025: one block in the second round of the order
+])
+def test_backward_order_of_popular_blocks(G, oracle, heads, kv_heads, H, W, bh, bw, n):
+    """A few key blocks that most query blocks attend to, so that every class of the
+    working order has members.  A block that is missing from the order keeps the NaN
+    that its gradients are filled with.  Bounds of test_general_backward."""
+    cfg = shape_ns(1, heads, H, W, bh, bw, 32, n, "fp32", kv_heads)
+    m, rng = cfg.n_blocks, np.random.default_rng(n + heads)
+    idx = np.empty((1, heads, m, n), dtype=np.int32)
+    for a in range(heads):
+        weight = 1.0 / (1.0 + rng.permutation(m))
+        for i in range(m):
+            w = np.where(np.arange(m) == i, 0.0, weight)
+            idx[0, a, i] = rng.choice(m, size=n, replace=False, p=w / w.sum())
+    q, dout = (rng.standard_normal((1, heads, H * W, 32)).astype(np.float32) for _ in range(2))
+    k, v = (rng.standard_normal((1, kv_heads or heads, H * W, 32)).astype(np.float32)
+            for _ in range(2))
+    ref = (oracle.bwd_gqa if kv_heads else oracle.bwd)(oracle.shape_of(cfg), q, k, v, dout, idx)
+    for name, x, r in zip(("dq", "dk", "dv"), G.gpu_bwd(cfg, q, k, v, dout, idx), ref):
+        err = np.abs(x - r).max()
+        assert err <= 1e-4 * np.abs(r).max(), f"{name}: max error {err}"
+
+
 @pytest.mark.parametrize("dtype,H,W,bh,bw,D,kv_heads,dv_in_place", [
     ("fp32", 10, 20, 5, 5, 64, 1, True),      # general kernels
     ("bf16", 32, 40, 16, 20, 32, 2, True),    # two workgroups per block
