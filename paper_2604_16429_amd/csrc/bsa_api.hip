@@ -130,7 +130,7 @@ int select_impl(const Checked& c, const void* q, const void* k, int32_t* sel_idx
     const hipError_t e =
         c.g.n_select > 0
             ? bsa::launch_pool_select(c.is_bf16, q, k, qbar, kbar, rest, sel_idx, c.g, c.D, c.BH,
-                                      stream)
+                                      false, stream)
             : bsa::launch_pool(c.is_bf16, q, k, qbar, kbar, c.g, c.D, c.BH, stream);
     return e == hipSuccess ? MOSAIC_BSA_OK : MOSAIC_BSA_ERR_LAUNCH;
 }

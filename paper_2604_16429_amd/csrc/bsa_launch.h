@@ -23,7 +23,8 @@ hipError_t launch_check_selection(const int32_t* sel_idx, int32_t* n_bad, const 
 
 // Pooling of Q and K, block scores and top-n as one sequence of launches in
 // which the pooling of one part of the batch runs beside the ranking of the part
-// before.  The scores of a query block stay in LDS; `scratch` is device memory
+// before (pooled: qbar, kbar and scratch are there already, only the ranking is
+// launched).  The scores of a query block stay in LDS; `scratch` is device memory
 // of select_scratch_bytes(...) bytes (BKV = batch * kv_heads): a second copy of
 // the pooled keys, per slice [D/4][m][4], which the ranking's threads (one key
 // block each) read as consecutive 16-byte groups and launch_pool_select leaves
@@ -31,7 +32,7 @@ hipError_t launch_check_selection(const int32_t* sel_idx, int32_t* n_bad, const 
 size_t select_scratch_bytes(int m, int D, int64_t BH, int64_t BKV);
 hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float* qbar,
                               float* kbar, void* scratch, int32_t* sel_idx, const Geom& g, int D,
-                              int64_t BH, hipStream_t stream);
+                              int64_t BH, bool pooled, hipStream_t stream);
 
 // Launches one or two forward jobs of `wgs` workgroups each as one grid (two, where
 // one would exceed the 2^32 work items of a launch); launch(job 0, job 1, shape,

@@ -613,7 +613,7 @@ static int select_group_for(int m, int D, int64_t BH)
 template <typename T, int VEC, int D, bool BIG>
 static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar, float* kbar,
                                        float* kbar_il, int32_t* sel_idx, const Geom& g,
-                                       int64_t BH, hipStream_t stream)
+                                       int64_t BH, bool pooled, hipStream_t stream)
 {
     const int m = g.n_blocks;
     const int G = select_group_for(m, D, BH);
@@ -631,11 +631,11 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
         attr_set[dev] = true;
     }
     const int64_t BKV = BH / g.kv_group;
-    const int parts = select_parts(BH, BKV, g, D, sizeof(T));
+    const int parts = pooled ? 1 : select_parts(BH, BKV, g, D, sizeof(T));
     const int wgs_per_slice = (m * (D / VEC) + 255) / 256;
     const int groups = (m + G - 1) / G;
     // one part: pooled by a launch of its own
-    if (parts == 1) {
+    if (parts == 1 && !pooled) {
         const PoolTensor tensors[3] = {{q, qbar, nullptr, (uint32_t)BH},
                                        {k, kbar, kbar_il, (uint32_t)BKV},
                                        {nullptr, nullptr, nullptr, 0}};
@@ -677,7 +677,7 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
 
 hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float* qbar,
                               float* kbar, void* scratch, int32_t* sel_idx, const Geom& g, int D,
-                              int64_t BH, hipStream_t stream)
+                              int64_t BH, bool pooled, hipStream_t stream)
 {
     // the channel-interleaved copy of the pooled keys
     const int m = g.n_blocks;
@@ -685,8 +685,10 @@ hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float*
     if (!il) return hipErrorInvalidValue;
     const bool big = m > 512;
 #define BSA_PS(T, VEC, D_)                                                                        \
-    (big ? launch_pool_select_t<T, VEC, D_, true>(q, k, qbar, kbar, il, sel_idx, g, BH, stream)   \
-         : launch_pool_select_t<T, VEC, D_, false>(q, k, qbar, kbar, il, sel_idx, g, BH, stream))
+    (big ? launch_pool_select_t<T, VEC, D_, true>(q, k, qbar, kbar, il, sel_idx, g, BH, pooled,   \
+                                                  stream)                                         \
+         : launch_pool_select_t<T, VEC, D_, false>(q, k, qbar, kbar, il, sel_idx, g, BH, pooled,  \
+                                                   stream))
     switch (D) {
     case 32: return is_bf16 ? BSA_PS(uint16_t, 8, 32) : BSA_PS(float, 4, 32);
     case 64: return is_bf16 ? BSA_PS(uint16_t, 8, 64) : BSA_PS(float, 4, 64);
@@ -694,6 +696,21 @@ hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float*
     }
 #undef BSA_PS
     return hipErrorInvalidValue;
+}
+
+// The ranking shares a launch with the coarse branch unless the larger LDS rows of the
+// latter would leave a ranking workgroup alone on its CU that fits twice by itself.
+// Three-branch forward in one launch against two, head dim 64: 24 blocks 37 against 42
+// us, 450 x 8 heads 157 / 164, 2,048 x 4 543 / 553, 8,192 x 1 2,316 / 2,379; where the
+// rule parts them: 4,096 x 2 1,180 / 1,090, head dim 32 4,096 x 4 1,422 / 1,266, head
+// dim 128 2,048 x 2 737 / 717.  (900 blocks at head dim 64 lose 4 % together; head dims
+// 32 and 128 win 2 to 5 % there.)
+static bool rank_beside_coarse(int m, int D, int64_t BH)
+{
+    constexpr size_t lds_of_cu = 160 * 1024, candidates = 4 * 64 * sizeof(uint64_t);
+    const size_t rank = select_lds_bytes(select_group_for(m, D, BH), m, D) + candidates;
+    const size_t coarse = coarse_lds_bytes(coarse_group_for(m, D, BH), m, D) + candidates;
+    return 2 * coarse <= lds_of_cu || 2 * rank > lds_of_cu;
 }
 
 template <int D, bool BIG>
@@ -737,7 +754,7 @@ hipError_t launch_blocks_three_branch(bool is_bf16, const void* q, const void* k
     const PoolTensor tv = {v, vbar, nullptr, (uint32_t)BKV};
     if (select_parts(BH, BKV, g, D, is_bf16 ? 2 : 4) > 1) {
         hipError_t e = launch_pool_select(is_bf16, q, k, qbar, kbar, kbar_il, sel_idx, g, D, BH,
-                                          stream);
+                                          false, stream);
         if (e != hipSuccess) return e;
         const PoolTensor t[3] = {tv, none, none};
         e = launch_pool_tensors(is_bf16, t, ll, g, D, stream);
@@ -746,6 +763,11 @@ hipError_t launch_blocks_three_branch(bool is_bf16, const void* q, const void* k
     const PoolTensor t[3] = {{q, qbar, nullptr, (uint32_t)BH}, {k, kbar, kbar_il, (uint32_t)BKV}, tv};
     const hipError_t e = launch_pool_tensors(is_bf16, t, ll, g, D, stream);
     if (e != hipSuccess) return e;
+    if (!rank_beside_coarse(m, D, BH)) {
+        const hipError_t r = launch_pool_select(is_bf16, q, k, qbar, kbar, kbar_il, sel_idx, g, D, BH,
+                                                true, stream);
+        return r != hipSuccess ? r : launch_coarse(qbar, kbar_il, vbar, obar, g, D, BH, stream);
+    }
     const bool big = m > 512;
 #define BSA_RC(D_)                                                                                 \
     case D_:                                                                                       \

@@ -232,6 +232,23 @@ def test_general_three_branch(G, oracle, dtype, heads, kv_heads, H, W, bh, bw, D
     assert np.abs(out - ref).max() <= (2e-2 if dtype == "bf16" else 1e-5 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("heads,H,W,D", [
+    (1, 64, 128, 64),        # m = 2,048: ranking and coarse branch in one launch
+    (1, 128, 128, 32),       # m = 4,096: in two, for the ranking's place on the CU
+    (1, 160, 160, 32),       # m = 6,400: in one again, neither fits twice
+])
+def test_three_branch_many_blocks(G, oracle, heads, H, W, D):
+    """Both ways to launch the ranking and the coarse branch, tiles of 2 x 2."""
+    cfg = shape_ns(1, heads, H, W, 2, 2, D, 5, "fp32")
+    q, k, v = rand_qkv(cfg, H + D)
+    gates = np.random.default_rng(D).uniform(0.0, 1.0, size=(1, heads, H * W, 3)).astype(np.float32)
+    s = oracle.shape_of(cfg, own_is_candidate=True)
+    ref, sel_ref, _ = oracle.fwd_three_branch(s, q, k, v, gates, 2, 2)
+    got, sel = G.gpu_fwd_three_branch(cfg, q, k, v, gates, 2, 2)
+    assert np.array_equal(sel, sel_ref)
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("H,W,bh,bw,n,levels", [
     (24, 36, 2, 2, 70, 0),       # m = 216, more picks than one round of 32 places
     (48, 48, 2, 2, 100, 0),      # m = 576: two key blocks per thread, four rounds
