@@ -544,7 +544,8 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
         const int tiles = (total + KT - 1) / KT;
 
         // this lane's rows of a tile (slab wave + NL jj), and for the loads of lse and
-        // delta row `lane`
+        // delta row `lane` (fp32, 32 rows: the upper lanes repeat the lower ones; rows
+        // of the tile after the last one would lie past the repeated entries)
         FlatRow at[MINE], at_row;
         uint32_t chunk_off[MINE], tok[MINE], tok_row = 0;
 #pragma unroll
@@ -553,7 +554,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
             at[jj].start(row, b);
             chunk_off[jj] = (uint32_t)Tile::swz(row, lane % Tile::LPR) * 16u;
         }
-        at_row.start(lane, b);
+        at_row.start(lane % KT, b);
         auto row_of = [&](const FlatRow& r) -> uint32_t { return list_s[r.blk] + pos_s[r.tau]; };
         // rows of the next tile, looked up a tile before they are used
         auto look_up = [&] {
@@ -568,7 +569,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
             }
         };
         auto gather_next = [&](int buf) {
-gather_rows<Tile, MINE, NL>(qs, gs, tok, chunk_off, wave,
+            gather_rows<Tile, MINE, NL>(qs, gs, tok, chunk_off, wave,
                                         q_dst + (uint32_t)buf * Tile::TILE_BYTES,
                                         g_dst + (uint32_t)buf * Tile::TILE_BYTES);
             if (wave == 0) {

@@ -162,6 +162,23 @@ def test_backward_order_of_popular_blocks(G, oracle, heads, kv_heads, H, W, bh, 
         assert err <= 1e-4 * np.abs(r).max(), f"{name}: max error {err}"
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_backward_list_of_connected_blocks_full(G, oracle, dtype):
+    """Blocks of one token and 2,112 query blocks that all attend to block 0: its list
+    is filled to its end and walked to the last of the entries that repeat the last
+    block, then filled again.  Bounds of test_general_backward, relative to the sum
+    that 2,112 terms make."""
+    cfg = shape_ns(1, 1, 33, 64, 1, 1, 32, 1, dtype)
+    q, k, v = inputs_of(cfg, 1)
+    dout = inputs_of(cfg, 2)[0]
+    idx = np.zeros((1, 1, cfg.n_blocks, 1), dtype=np.int32)
+    idx[0, 0, 0] = 1
+    ref = oracle.bwd(oracle.shape_of(cfg), q, k, v, dout, idx)
+    for name, x, r in zip(("dq", "dk", "dv"), G.gpu_bwd(cfg, q, k, v, dout, idx), ref):
+        err = np.abs(x - r).max()
+        assert err <= (1e-4 if dtype == "fp32" else 1e-2) * max(1.0, np.abs(r).max()), (name, err)
+
+
 @pytest.mark.parametrize("dtype,H,W,bh,bw,D,kv_heads,dv_in_place", [
     ("fp32", 10, 20, 5, 5, 64, 1, True),      # general kernels
     ("bf16", 32, 40, 16, 20, 32, 2, True),    # two workgroups per block
