@@ -97,10 +97,14 @@ template <typename T, int D>
 static hipError_t launch_prep_t(const void* out, const void* dout, const float* lse, float* delta,
                                 float* lse2, int64_t rows, hipStream_t stream)
 {
-    const int64_t threads = rows * (D * (int)sizeof(T) / 16);
-    bwd_prep_kernel<T, D><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream>>>(
-        (const T*)out, (const T*)dout, lse, delta, lse2, rows);
-    return hipGetLastError();
+    constexpr int LPR = D * (int)sizeof(T) / 16, RPW = 256 / LPR;     // rows per workgroup
+    return launch_slices((rows + RPW - 1) / RPW, 256, [&](int64_t first, int64_t wgs) {
+        const int64_t row = first * RPW;
+        bwd_prep_kernel<T, D><<<dim3((unsigned)wgs), dim3(256), 0, stream>>>(
+            (const T*)out + row * D, (const T*)dout + row * D, lse + row, delta + row, lse2 + row,
+            rows - row < wgs * RPW ? rows - row : wgs * RPW);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
@@ -283,10 +287,14 @@ hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* o
 {
     const int m = g.n_blocks, words = (m + 31) >> 5;
     const int cols = m < kMapCols ? m : kMapCols;
-    if (BH * words >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    bwd_connect_kernel<<<dim3((unsigned)(BH * words)), dim3(256), sizeof(uint32_t) * (size_t)cols,
-                         stream>>>(sel_idx, conn, g, words);
-    if (!order) return hipGetLastError();
+    const int64_t map = (int64_t)words * m;          // words per query slice
+    hipError_t e = launch_slices(BH, 256 * (int64_t)words, [&](int64_t first, int64_t slices) {
+        bwd_connect_kernel<<<dim3((unsigned)(slices * words)), dim3(256),
+                             sizeof(uint32_t) * (size_t)cols, stream>>>(
+            sel_idx + first * m * g.n_select, conn + first * map, g, words);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess || !order) return e;
     // A slice's map of up to 1,024 blocks and 64 words each is read where the order is
     // made, a larger one by a launch of its own: 450 blocks with 60 words 9.9 us, in two
     // launches 6.9 + 4.9; 1,024 with 128 8.0 + 5.0 us, 4,050 with 127 9.7 + 10.8 us (one
@@ -297,13 +305,20 @@ hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* o
     if (m > 1024 || g.kv_group * words > 64) {
         const uint32_t chunks = (uint32_t)(m + 255) / 256;
         classes = (uint8_t*)(order + BKV * m);
-        bwd_class_kernel<<<dim3((unsigned)(BKV * chunks)), dim3(256), 0, stream>>>(conn, classes, g,
-                                                                                 words, chunks);
+        e = launch_slices(BKV, 256 * (int64_t)chunks, [&](int64_t first, int64_t slices) {
+            bwd_class_kernel<<<dim3((unsigned)(slices * chunks)), dim3(256), 0, stream>>>(
+                conn + first * g.kv_group * map, classes + first * m, g, words, chunks);
+            return hipGetLastError();
+        });
+        if (e != hipSuccess) return e;
     }
     const int threads = m >= 1024 ? 1024 : (m + 63) / 64 * 64;
-    bwd_order_kernel<<<dim3((unsigned)BKV), dim3(threads), 0, stream>>>(conn, classes, order, g,
-                                                                        words);
-    return hipGetLastError();
+    return launch_slices(BKV, threads, [&](int64_t first, int64_t slices) {
+        bwd_order_kernel<<<dim3((unsigned)slices), dim3(threads), 0, stream>>>(
+            conn + first * g.kv_group * map, classes ? classes + first * m : nullptr,
+            order + first * m, g, words);
+        return hipGetLastError();
+    });
 }
 
 // ---------------------------------------------------------------------------

@@ -190,13 +190,25 @@ static hipError_t launch_t(const void* q, const void* k, const void* v, const Fw
     int listed = 0;
     for (int j = 0; j < n_jobs; ++j)
         listed = jobs[j].n_select + 1 > listed ? jobs[j].n_select + 1 : listed;
-    return launch_jobs(jobs, n_jobs, BH * g.n_blocks * rows.chunks, 64 * nw,
-                       [&](const FwdJob& a, const FwdJob& b, const FwdShape& j, unsigned grid) {
-                           kernel<<<dim3(grid), dim3(64 * nw), flat_table_bytes(g, listed), stream>>>(
-                               (const T*)q, (const T*)k, (const T*)v, a.lists, b.lists, (T*)a.out,
-                               (T*)b.out, a.lse, b.lse, j, g,
-                               (uint32_t)(BH / g.kv_group), rows.chunks, 32 * nw);
-                       });
+    const int64_t wgs = (int64_t)g.kv_group * g.n_blocks * rows.chunks;    // per key/value slice
+    return launch_slices(BH / g.kv_group, wgs * 64 * nw, [&](int64_t first, int64_t slices) {
+        const int64_t row = first * g.kv_group * g.n_tokens, kv = first * g.n_tokens * D;
+        FwdJob piece[2];
+        for (int j = 0; j < n_jobs; ++j) {
+            piece[j] = jobs[j];
+            piece[j].lists += first * g.kv_group * g.n_blocks * jobs[j].n_select;
+            piece[j].out = (T*)jobs[j].out + row * D;
+            if (jobs[j].lse) piece[j].lse += row;
+        }
+        return launch_jobs(piece, n_jobs, slices * wgs, 64 * nw,
+                           [&](const FwdJob& a, const FwdJob& b, const FwdShape& j, unsigned grid) {
+                               kernel<<<dim3(grid), dim3(64 * nw), flat_table_bytes(g, listed),
+                                        stream>>>((const T*)q + row * D, (const T*)k + kv,
+                                                  (const T*)v + kv, a.lists, b.lists, (T*)a.out,
+                                                  (T*)b.out, a.lse, b.lse, j, g, (uint32_t)slices,
+                                                  rows.chunks, 32 * nw);
+                           });
+    });
 }
 
 hipError_t launch_fwd_generic(bool is_bf16, const void* q, const void* k, const void* v,

@@ -34,6 +34,19 @@ hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float*
                               float* kbar, void* scratch, int32_t* sel_idx, const Geom& g, int D,
                               int64_t BH, bool pooled, hipStream_t stream);
 
+// A launch holds less than 2^32 work items.  Work of `items` of them per slice is
+// launched in pieces of whole slices: launch(first slice, slices) returns the status.
+template <class F>
+inline hipError_t launch_slices(int64_t slices, int64_t items, F launch)
+{
+    const int64_t fit = (((int64_t)1 << 32) - 1) / items, most = fit < 1 ? 1 : fit;
+    for (int64_t first = 0; first < slices; first += most) {
+        const hipError_t e = launch(first, slices - first < most ? slices - first : most);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // Launches one or two forward jobs of `wgs` workgroups each as one grid (two, where
 // one would exceed the 2^32 work items of a launch); launch(job 0, job 1, shape,
 // grid) does it.

@@ -540,13 +540,17 @@ static hipError_t launch_branch_grads_t(const BranchGrads& x, const Geom& g, int
                                         hipStream_t stream)
 {
     constexpr int TILES = 256 / (D * (int)sizeof(T) / 16 * 4);
-    const int64_t tiles = BH * g.n_blocks;
-    branch_grads_kernel<T, D><<<dim3((unsigned)((tiles + TILES - 1) / TILES)), dim3(256), 0,
-                                stream>>>(
-        x.obar, (const T*)x.o_fg, (const T*)x.o_l, x.lse_fg, x.lse_l, x.gates, (const T*)x.dout,
-        (T*)x.do_fg, (T*)x.do_l, x.dgates, x.dobar, x.delta_fg, x.delta_l, x.lse2_fg, x.lse2_l, g,
-        tiles);
-    return hipGetLastError();
+    const int64_t m = g.n_blocks;
+    return launch_slices(BH, 256 * (m / TILES + 1), [&](int64_t first, int64_t slices) {
+        const int64_t tiles = slices * m, row = first * g.n_tokens, at = row * D, pooled = first * m * D;
+        branch_grads_kernel<T, D><<<dim3((unsigned)((tiles + TILES - 1) / TILES)), dim3(256), 0,
+                                    stream>>>(
+            x.obar + pooled, (const T*)x.o_fg + at, (const T*)x.o_l + at, x.lse_fg + row,
+            x.lse_l + row, x.gates + 3 * row, (const T*)x.dout + at, (T*)x.do_fg + at,
+            (T*)x.do_l + at, x.dgates + 3 * row, x.dobar + pooled, x.delta_fg + row, x.delta_l + row,
+            x.lse2_fg + row, x.lse2_l + row, g, tiles);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_branch_grads(bool is_bf16, const BranchGrads& x, const Geom& g, int D, int64_t BH,
@@ -587,7 +591,7 @@ static hipError_t launch_coarse_bwd_t(const float* qbar, const float* kbar, cons
     const int R = chunk_rows;
     if (R < 1) return hipErrorInvalidValue;
     const int64_t BKV = BH / g.kv_group;
-    const int64_t waves = BKV * ((m + 31) / 32) * (D / 32) * 2;
+    const int64_t waves = (int64_t)((m + 31) / 32) * (D / 32) * 2;    // per key/value slice
     for (int r0 = 0; r0 < m; r0 += R) {
         const int r1 = r0 + R < m ? r0 + R : m;
         hipLaunchKernelGGL((coarse_bwd_rows_kernel<D>),
@@ -596,10 +600,14 @@ static hipError_t launch_coarse_bwd_t(const float* qbar, const float* kbar, cons
                            a_mat, ds_mat, dqbar, g, G, R, r0, r1);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((coarse_bwd_cols_kernel<D>), dim3((unsigned)((waves + 3) / 4)),
-                           dim3(256), 0, stream, qbar, dobar, a_mat, ds_mat, dkbar, dvbar, g,
-                           waves, R, r0, r1);
-        e = hipGetLastError();
+        e = launch_slices(BKV, 64 * waves + 256, [&](int64_t first, int64_t slices) {
+            const int64_t q_rows = first * g.kv_group * m * D, mat = first * g.kv_group * R * m;
+            coarse_bwd_cols_kernel<D><<<dim3((unsigned)((slices * waves + 3) / 4)), dim3(256), 0,
+                                        stream>>>(
+                qbar + q_rows, dobar + q_rows, a_mat + mat, ds_mat + mat, dkbar + first * m * D,
+                dvbar + first * m * D, g, slices * waves, R, r0, r1);
+            return hipGetLastError();
+        });
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

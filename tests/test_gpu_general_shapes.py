@@ -299,6 +299,33 @@ def test_selection_rounds(G, oracle, H, W, bh, bw, n, levels):
     assert np.array_equal(G.gpu_select(cfg, q, k), oracle.select(s, q, k))
 
 
+@pytest.mark.parametrize("batch", [1 << 18, 1 << 20])
+def test_general_more_than_2_32_work_items(G, batch):
+    """2^22 and 2^24 slices of one token: with 1,024 and 256 threads per slice kernels
+    would need 2^32 work items, which one launch cannot have.
+    The output is v and the only weight 1, so dv = dout and dq = dk = 0 up to the fp32
+    sums of dP and delta (32 terms each, at most 2^-19 of sum |dO v|, times scale and
+    key, which are below 1)."""
+    import paper_2604_16429_amd as bsa
+    from paper_2604_16429_amd import binding
+    heads, D = 16, 32
+    p = bsa.Params(batch, heads, 1, 1, 1, 1, D, 0, binding.BF16)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    q, k, v, dout = (torch.rand((batch, heads, 1, D), generator=gen, device="cuda",
+                                dtype=torch.bfloat16) for _ in range(4))
+    out, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+    lse = torch.empty((batch, heads, 1), device="cuda")
+    ws = torch.empty(bsa.mosaic_bsa_workspace_bytes(p, binding.OP_BWD), dtype=torch.uint8,
+                     device="cuda")
+    none = torch.empty((batch, heads, 1, 0), dtype=torch.int32, device="cuda")
+    bsa.mosaic_bsa_fwd(p, q, k, v, none, out, lse)
+    bsa.mosaic_bsa_bwd(p, q, k, v, out, lse, dout, none, dq, dk, dv, ws)
+    assert torch.equal(out, v)
+    assert (dv.float() - dout.float()).abs().max() <= 2.0 ** -8
+    for x in (dq, dk):
+        assert x.float().abs().max() <= 32 * 2.0 ** -19
+
+
 @pytest.mark.parametrize("H,grouped", [(2048, False), (1024, True)])
 def test_general_rows_past_32_bit_offsets(G, H, grouped):
     """A slice (or the query slices that share a key/value slice) of more than 2 GiB
