@@ -87,7 +87,7 @@ size_t pooled_bytes(const Checked& c)
 
 size_t select_workspace(const Checked& c)
 {
-    return 2 * pooled_bytes(c) + align_up(bsa::select_scratch_bytes(c.g.n_blocks, c.D, c.BH, c.BKV));
+    return 2 * pooled_bytes(c) + align_up(bsa::select_scratch_bytes(c.g.n_blocks, c.D, c.BKV));
 }
 
 // delta | lse * log2(e) | connection map
@@ -168,7 +168,7 @@ extern "C" int mosaic_bsa_select(const mosaic_bsa_params* params, const void* q,
     if (c.g.n_select > 0 && !sel_idx) return MOSAIC_BSA_ERR_NULL;
     if (misaligned(q) || misaligned(k) || misaligned(workspace)) return MOSAIC_BSA_ERR_ALIGN;
     if (!workspace || workspace_bytes < select_workspace(c)) return MOSAIC_BSA_ERR_WORKSPACE;
-    if (bsa::select_group_size(c.g.n_blocks, c.D) == 0) return MOSAIC_BSA_ERR_SHAPE;
+    if (bsa::select_group_size(c.g.n_blocks) == 0) return MOSAIC_BSA_ERR_SHAPE;
     return select_impl(c, q, k, sel_idx, workspace, (hipStream_t)hip_stream);
 }
 
@@ -180,7 +180,7 @@ extern "C" int mosaic_bsa_select_static(const mosaic_bsa_params* params, const v
     if (!q || !k) return MOSAIC_BSA_ERR_NULL;
     if (c.g.n_select > 0 && !sel_idx) return MOSAIC_BSA_ERR_NULL;
     if (misaligned(q) || misaligned(k)) return MOSAIC_BSA_ERR_ALIGN;
-    if (bsa::select_group_size(c.g.n_blocks, c.D) == 0) return MOSAIC_BSA_ERR_SHAPE;
+    if (bsa::select_group_size(c.g.n_blocks) == 0) return MOSAIC_BSA_ERR_SHAPE;
     if (select_workspace(c) > (size_t)MOSAIC_BSA_STATIC_SCRATCH_BYTES)
         return MOSAIC_BSA_ERR_WORKSPACE;
     void* ws = nullptr;
@@ -244,7 +244,7 @@ ThreeBranchLayout three_branch_layout(const Checked& c, int local_tiles)
     w.kbar = take((size_t)c.BKV * m * c.D * 4);
     w.vbar = take((size_t)c.BKV * m * c.D * 4);
     w.obar = take((size_t)c.BH * m * c.D * 4);
-    w.keys = take(bsa::select_scratch_bytes(c.g.n_blocks, c.D, c.BH, c.BKV));
+    w.keys = take(bsa::select_scratch_bytes(c.g.n_blocks, c.D, c.BKV));
     w.lists = take((size_t)c.BH * m * (size_t)(local_tiles - 1) * 4);
     w.o_fg = take((size_t)c.BH * (size_t)c.g.n_tokens * c.D * esz);
     w.o_l = take((size_t)c.BH * (size_t)c.g.n_tokens * c.D * esz);
@@ -269,7 +269,7 @@ extern "C" size_t mosaic_bsa_three_branch_workspace_bytes(const mosaic_bsa_param
 {
     Checked c;
     if (check_params(params, &c, true) || check_local(params, local_h, local_w)) return 0;
-    if (bsa::select_group_size(c.g.n_blocks, c.D) == 0 ||
+    if (bsa::select_group_size(c.g.n_blocks) == 0 ||
         bsa::coarse_group_size(c.g.n_blocks, c.D) == 0)
         return 0;
     return three_branch_layout(c, local_h * local_w).total;
@@ -288,7 +288,7 @@ extern "C" int mosaic_bsa_fwd_three_branch(const mosaic_bsa_params* params, int3
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out) ||
         misaligned(workspace))
         return MOSAIC_BSA_ERR_ALIGN;
-    if (bsa::select_group_size(c.g.n_blocks, c.D) == 0 ||
+    if (bsa::select_group_size(c.g.n_blocks) == 0 ||
         bsa::coarse_group_size(c.g.n_blocks, c.D) == 0)
         return MOSAIC_BSA_ERR_SHAPE;
     const int local_tiles = local_h * local_w;

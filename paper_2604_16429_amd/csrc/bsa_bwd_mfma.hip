@@ -193,8 +193,11 @@ __device__ __forceinline__ f32x16 zero_tile()
 // nothing of the other phases is interleaved with it: the wavefront that is in such a
 // phase issues first, so that the two wavefronts of a SIMD drift apart and one's vector
 // work falls behind the other's matrix instructions.  Select + forward + backward,
-// 1.5 degrees, batch 4, 16 heads: 9.11 -> 8.92 ms.  At head dim 64, with phases half as
-// long, the same switches cost 0 to 4 %, and in the general kernels they give nothing.
+// 1.5 degrees, batch 4, 16 heads: 9.11 -> 8.92 ms.  Two phases are not marked as such,
+// because the pass is faster without: the end of a tile's last one (the priority stays
+// up through the wait for the next tile; lowered 8.54 -> 8.55 ms) and the dP products
+// of the dK pass (raised 8.54 -> 8.60 ms).  At head dim 64, with phases half as long,
+// the same switches cost 0 to 4 %, and in the general kernels they give nothing.
 template <int D>
 __device__ __forceinline__ void matrix_phase(bool begin)
 {

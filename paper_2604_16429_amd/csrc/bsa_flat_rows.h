@@ -139,7 +139,10 @@ __device__ __forceinline__ f32x16 zero_tile()
 // addresses per lane: everything else is a constant that goes into the read's
 // offset field.  (Written out because the compiler otherwise keeps an address
 // register per read, which at 64 fp32 channels no longer fits: it spilled them, and
-// a reload from scratch memory waits for every gather in flight.)
+// a reload from scratch memory waits for every gather in flight.  That cured the
+// forward and dQ; the fp32 dK/dV kernels still spill, 43 registers at 64 channels with
+// two gathering wavefronts, where five reloads per tile wait in this way, 21 with four
+// and 57 at 128 channels with one, outside the tile loop.)
 template <typename T, int D> struct TileReader;
 
 template <typename V>

@@ -10,7 +10,7 @@
 namespace bsa {
 
 // Query blocks ranked per workgroup by the selection kernel; 0 = m too large.
-int select_group_size(int m, int D);
+int select_group_size(int m);
 
 hipError_t launch_pool(bool is_bf16, const void* q, const void* k, float* qbar, float* kbar,
                        const Geom& g, int D, int64_t BH, hipStream_t stream);
@@ -29,7 +29,7 @@ hipError_t launch_check_selection(const int32_t* sel_idx, int32_t* n_bad, const 
 // the pooled keys, per slice [D/4][m][4], which the ranking's threads (one key
 // block each) read as consecutive 16-byte groups and launch_pool_select leaves
 // there.
-size_t select_scratch_bytes(int m, int D, int64_t BH, int64_t BKV);
+size_t select_scratch_bytes(int m, int D, int64_t BKV);
 hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float* qbar,
                               float* kbar, void* scratch, int32_t* sel_idx, const Geom& g, int D,
                               int64_t BH, bool pooled, hipStream_t stream);
@@ -132,9 +132,9 @@ hipError_t launch_combine(bool is_bf16, const float* obar, const void* o_fg, con
                           hipStream_t stream);
 
 // Backward of the three-branch output: upstream gradients, delta and lse2 of the two
-// attention branches, the gate gradients and the gated block sums of dout; the coarse branch's gradients on the pooled
-// tensors, chunk_rows query blocks at a time (a_mat, ds_mat: fp32 scratch
-// [B*heads, chunk_rows, m]).
+// attention branches, the gate gradients and the gated block sums of dout; the coarse
+// branch's gradients on the pooled tensors, chunk_rows query blocks at a time (a_mat,
+// ds_mat: fp32 scratch [B*heads, chunk_rows, m]; kbar_il: see launch_pool_select).
 int coarse_bwd_group_size(int m, int D);
 struct BranchGrads {
     const float* obar;                          // coarse rows

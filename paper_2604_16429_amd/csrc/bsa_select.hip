@@ -511,22 +511,21 @@ hipError_t launch_check_selection(const int32_t* sel_idx, int32_t* n_bad, const 
 // ---------------------------------------------------------------------------
 static constexpr size_t kSelectLdsBudget = 144 * 1024;
 
-static size_t select_lds_bytes(int G, int m, int D)
+static size_t select_lds_bytes(int G, int m)
 {
-    (void)D;
     return (size_t)G * (size_t)m * 4;
 }
 
-int select_group_size(int m, int D)
+int select_group_size(int m)
 {
     // the largest G in [1, 8] whose LDS footprint fits, and fits twice where
     // that is possible with G >= 4 (two workgroups per CU cover each other's
     // loads, and a pooling workgroup fits beside a ranking one); 0 if even
     // G = 1 does not fit
     for (int G = 8; G >= 4; G >>= 1)
-        if (2 * select_lds_bytes(G, m, D) <= kSelectLdsBudget) return G;
+        if (2 * select_lds_bytes(G, m) <= kSelectLdsBudget) return G;
     for (int G = 8; G >= 1; G >>= 1)
-        if (select_lds_bytes(G, m, D) <= kSelectLdsBudget) return G;
+        if (select_lds_bytes(G, m) <= kSelectLdsBudget) return G;
     return 0;
 }
 
@@ -572,9 +571,8 @@ hipError_t launch_pool(bool is_bf16, const void* q, const void* k, float* qbar, 
     return launch_pool_tensors(is_bf16, t, LocalLists{}, g, D, stream);
 }
 
-size_t select_scratch_bytes(int m, int D, int64_t BH, int64_t BKV)
+size_t select_scratch_bytes(int m, int D, int64_t BKV)
 {
-    (void)BH;
     // the ranking reads a second, channel-interleaved copy of the pooled keys
     return (size_t)BKV * (size_t)m * (size_t)D * 4;
 }
@@ -603,9 +601,9 @@ static int select_parts(int64_t BH, int64_t BKV, const Geom& g, int D, size_t el
 // Few query blocks: fewer per workgroup, down to a workgroup each, until there are
 // two workgroups per CU (ranking 480 blocks 9.8 -> 5.1 us, 3,600 blocks 15.9 -> 13.4
 // us, 64 blocks 6.3 -> 3.9 us).
-static int select_group_for(int m, int D, int64_t BH)
+static int select_group_for(int m, int64_t BH)
 {
-    int G = select_group_size(m, D);
+    int G = select_group_size(m);
     while (G > 1 && BH * ((m + G - 1) / G) < 512) G >>= 1;
     return G;
 }
@@ -616,9 +614,9 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
                                        int64_t BH, bool pooled, hipStream_t stream)
 {
     const int m = g.n_blocks;
-    const int G = select_group_for(m, D, BH);
+    const int G = select_group_for(m, BH);
     if (G == 0) return hipErrorInvalidValue;
-    const size_t lds = select_lds_bytes(G, m, D);
+    const size_t lds = select_lds_bytes(G, m);
     // the attribute is per device; setting it twice (two host threads racing) is harmless
     static bool attr_set[64] = {};
     int dev = 0;
@@ -708,7 +706,7 @@ hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float*
 static bool rank_beside_coarse(int m, int D, int64_t BH)
 {
     constexpr size_t lds_of_cu = 160 * 1024, candidates = 4 * 64 * sizeof(uint64_t);
-    const size_t rank = select_lds_bytes(select_group_for(m, D, BH), m, D) + candidates;
+    const size_t rank = select_lds_bytes(select_group_for(m, BH), m) + candidates;
     const size_t coarse = coarse_lds_bytes(coarse_group_for(m, D, BH), m, D) + candidates;
     return 2 * coarse <= lds_of_cu || 2 * rank > lds_of_cu;
 }
@@ -719,9 +717,9 @@ static hipError_t launch_rank_coarse_t(const float* qbar, const float* kbar_il, 
                                        hipStream_t stream)
 {
     const int m = g.n_blocks;
-    const int G = select_group_for(m, D, BH), Gc = coarse_group_for(m, D, BH);
+    const int G = select_group_for(m, BH), Gc = coarse_group_for(m, D, BH);
     if (G == 0 || Gc == 0) return hipErrorInvalidValue;
-    const size_t rank_lds = select_lds_bytes(G, m, D), coarse_lds = coarse_lds_bytes(Gc, m, D);
+    const size_t rank_lds = select_lds_bytes(G, m), coarse_lds = coarse_lds_bytes(Gc, m, D);
     static bool attr_set[64] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;

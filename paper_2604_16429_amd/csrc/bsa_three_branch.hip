@@ -342,19 +342,17 @@ __global__ __launch_bounds__(256) void coarse_bwd_rows_kernel(
     vbar += kv * m * D;
     const int64_t row0 = bh_idx * m + i0;
     const int64_t out_row0 = bh_idx * R + (i0 - r0);    // row of a_out / ds_out
-    if (kbar_il) kbar_il += kv * m * D;              // per slice [D/4][m][4]
+    kbar_il += kv * m * D;                           // per slice [D/4][m][4]
 
     // scores (base-2 domain) and da_ij = dobar_i . vbar_j; the rows of qbar and
     // dobar are wave-uniform (scalar loads, scalar operands of the fma)
     const float c2 = g.scale * kCoarseLog2e;
     for (int j = threadIdx.x; j < m; j += blockDim.x) {
         float kr[D];
-        const float4* ksrc = kbar_il ? (const float4*)kbar_il + j
-                                     : (const float4*)(kbar + (int64_t)j * D);
-        const int64_t kstep = kbar_il ? (int64_t)m : 1;
+        const float4* ksrc = (const float4*)kbar_il + j;
 #pragma unroll
         for (int d4 = 0; d4 < D / 4; ++d4) {
-            const float4 t = ksrc[d4 * kstep];
+            const float4 t = ksrc[(int64_t)d4 * m];
             kr[4 * d4 + 0] = t.x; kr[4 * d4 + 1] = t.y; kr[4 * d4 + 2] = t.z; kr[4 * d4 + 3] = t.w;
         }
         for (int r = 0; r < rows; ++r) {
