@@ -48,6 +48,12 @@
  *   Errors    0 on success, a negative MOSAIC_BSA_ERR_* code otherwise.  All
  *             argument checks run on the host before anything is enqueued;
  *             on error nothing has been launched.  Inputs must be finite.
+ *   Masks     by a large finite score (a channel of their own): the forward takes
+ *             scores softmax_scale * q.k of any size in fp32 and wherever the
+ *             general kernels run.  The bf16 kernels for head dims 64 and 128
+ *             (blocks of 64 * T tokens, width a power of two; 64, 128 or 256 tokens
+ *             at 128) need one score of magnitude below 2^30 among the first 32
+ *             attended keys of a row.  Every backward needs one in the row.
  */
 #ifndef MOSAIC_BSA_H
 #define MOSAIC_BSA_H
