@@ -404,7 +404,7 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
             const int left = keys.total - (KT * c + 32 * hh);
             if (left <= 0) break;
             f32x16 s = zero_tile(), dp = dp0;
-            dot_tiles(rd, kt, vt, hh * HALF, qf, dof, s, dp);
+            dot_tiles<false>(rd, kt, vt, hh * HALF, qf, dof, s, dp);
             ColumnPieces<T, D> k0;
             read_columns(rd, kt, hh * HALF, 0, k0);
             if (left < 32)
@@ -621,7 +621,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                     dp[4 * r4] = d4.x; dp[4 * r4 + 1] = d4.y;
                     dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
                 }
-                dot_tiles(rd, qt, gt, hh * HALF, kf, vf, p, dp);
+                dot_tiles<true>(rd, qt, gt, hh * HALF, kf, vf, p, dp);
                 ColumnPieces<T, D> c0;
                 read_columns(rd, gt, hh * HALF, 0, c0);
                 if (left < 32)

@@ -140,9 +140,9 @@ __device__ __forceinline__ f32x16 zero_tile()
 // offset field.  (Written out because the compiler otherwise keeps an address
 // register per read, which at 64 fp32 channels no longer fits: it spilled them, and
 // a reload from scratch memory waits for every gather in flight.  That cured the
-// forward and dQ; the fp32 dK/dV kernels still spill, 43 registers at 64 channels with
-// two gathering wavefronts, where five reloads per tile wait in this way, 21 with four
-// and 57 at 128 channels with one, outside the tile loop.)
+// forward and dQ; the fp32 dK/dV kernels still spill, 44 registers at 64 channels with
+// two gathering wavefronts, where reloads in the tile loop wait in this way, 22 with
+// four and 76 at 128 channels with one.)
 template <typename T, int D> struct TileReader;
 
 template <typename V>
@@ -251,17 +251,23 @@ __device__ __forceinline__ f32x16 dot_tile(
     }
     return acc;
 }
-// Two row products side by side (two independent accumulation chains).
-template <typename T, int D>
+// Two row products side by side (two independent accumulation chains).  APART, fp32 at
+// 64 and 128 channels: the first product in four chains, summed one by one.  A score
+// that is one chain of 128 products is rounded twice as far as four of 32, and its
+// weight carries that into dV and dK (scores of 22 whose terms have one sign: 3.5e-6
+// against 1.6e-6 of them; fp32 training passes 0.3 to 1.3 % longer).
+template <bool APART, typename T, int D>
 __device__ __forceinline__ void dot_tiles(
     const TileReader<T, D>& rd, uint32_t tile_a, uint32_t tile_b, int imm,
     const typename RowPieces<T, D>::type (&ya)[RowPieces<T, D>::N],
     const typename RowPieces<T, D>::type (&yb)[RowPieces<T, D>::N], f32x16& acc_a, f32x16& acc_b)
 {
-    constexpr int G = RowPieces<T, D>::GROUP, GROUPS = RowPieces<T, D>::N / G;
+    constexpr int G = RowPieces<T, D>::GROUP, N = RowPieces<T, D>::N, GROUPS = N / G;
+    constexpr int CHAIN = APART && sizeof(T) == 4 && D > 32 ? N / 4 : N;     // pieces
     typename RowPieces<T, D>::type a[2][G], b[2][G];
     read_rows(rd, tile_a, imm, 0, a[0]);
     read_rows(rd, tile_b, imm, 0, b[0]);
+    f32x16 chain = acc_a;
 #pragma unroll
     for (int gr = 0; gr < GROUPS; ++gr) {
         if (gr + 1 < GROUPS) {
@@ -271,8 +277,11 @@ __device__ __forceinline__ void dot_tiles(
         if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < G; ++u) {
-            acc_a = mul_piece(a[gr & 1][u], ya[gr * G + u], acc_a);
-            acc_b = mul_piece(b[gr & 1][u], yb[gr * G + u], acc_b);
+            const int piece = gr * G + u;
+            if (piece > 0 && piece % CHAIN == 0) chain = zero_tile();
+            chain = mul_piece(a[gr & 1][u], ya[piece], chain);
+            acc_b = mul_piece(b[gr & 1][u], yb[piece], acc_b);
+            if ((piece + 1) % CHAIN == 0) acc_a = piece < CHAIN ? chain : acc_a + chain;
         }
         if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
     }

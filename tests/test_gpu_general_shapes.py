@@ -162,6 +162,28 @@ def test_backward_order_of_popular_blocks(G, oracle, heads, kv_heads, H, W, bh, 
         assert err <= 1e-4 * np.abs(r).max(), f"{name}: max error {err}"
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_backward_fp32_score_rounding(G, oracle, D):
+    """Scores whose terms all have one sign, mean s (22 and 31 here): a chain of c
+    products is rounded by 2^-24 / sqrt(3) sqrt(c / 3) of its value, so that a score in
+    four chains of D / 4 is off by about 2^-24 0.6 (sqrt(D / 12) / 2 + 1) s, 1.25 to 1.5
+    times 2^-24 s, and in one chain of D by 2.7 to 3.8 times (less what it shares with
+    the lse).  The error of a score is the relative error of its weight in dK and dV:
+    2-norm within 1.8 times 2^-24 s."""
+    cfg = shape_ns(1, 2, 32, 32, 8, 4, D, 2, "fp32")
+    rng = np.random.default_rng(1)
+    q, k = (rng.uniform(0.5, 1.5, size=(1, 2, 1024, D)).astype(np.float32)
+            * np.float32(0.7 * np.sqrt(512 / D)) for _ in range(2))
+    v, dout = (rng.standard_normal((1, 2, 1024, D)).astype(np.float32) for _ in range(2))
+    idx = random_selection(cfg, 1)
+    score = (q[0, 0] @ k[0, 0].T).mean() / np.sqrt(D)
+    _, dk, dv = G.gpu_bwd(cfg, q, k, v, dout, idx)
+    _, rk, rv = oracle.bwd(oracle.shape_of(cfg), q, k, v, dout, idx)
+    for name, x, r in (("dk", dk, rk), ("dv", dv, rv)):
+        err = np.linalg.norm(x - r) / np.linalg.norm(r)
+        assert err <= 1.8 * 2.0 ** -24 * score, f"{name}: {err / score * 2 ** 24}"
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_backward_list_of_connected_blocks_full(G, oracle, dtype):
     """Blocks of one token and 2,112 query blocks that all attend to block 0: its list
