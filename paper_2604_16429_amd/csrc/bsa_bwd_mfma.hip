@@ -32,6 +32,10 @@
 //                dV^T += dO^T P, dK^T += Q^T dS with the transposing LDS read
 //                of the dO / Q tile.  For head dim 128 the two accumulators do
 //                not fit next to the operands, so dV and dK are two passes.
+// Waits for gathers are of the form that the compiler accounts for (wait_gathers):
+// otherwise it waits, in front of the first use of the stationary rows inside the loop,
+// for the loads that it issued before the loop, i.e. for the tile that was just
+// requested.
 // The difference dP - delta costs no vector instruction: the accumulator of dP
 // starts from it (dq: 16 registers that hold the lane's -delta; dk/dv: delta as it is
 // read from LDS, V negated in registers, so that -dS comes out and dK is scaled by
@@ -339,7 +343,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
             // tile c has landed (own loads, then everyone's), every LDS read of
             // the tile before has returned and everyone is done with the other
             // buffer: refill it with tile c + 1
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            wait_gathers_and_reads();
             __syncthreads();
             if (c + 1 < pairs) {
                 const uint32_t o = origin_of_pair(c + 1);
@@ -438,7 +442,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
     for (int c = 0; c < pairs; ++c) {
         // tile c has landed (own loads, then everyone's) and everyone is done
         // with the other buffer: refill it with tile c + 1
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        wait_gathers();
         __syncthreads();
         if (c + 1 < pairs) {
             const uint32_t o = origin_of_pair(c + 1);
@@ -612,7 +616,7 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
         if (items > 0) issue_item(0, 0);
         for (int it = 0; it < items; ++it) {
             // item `it` has landed and everyone is done with the other buffers
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            wait_gathers();
             __syncthreads();
             if (it + 1 < items) issue_item(it + 1, (it + 1) & 1);
             const unsigned char* qt_lds = q_lds[it & 1];
@@ -698,6 +702,309 @@ __device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
     }
 }
 
+// The query blocks connected to key block j, for the query heads of the group that
+// share it: heads in ascending order, blocks in ascending order within each, which
+// fixes the summation order.  An entry is the first token of the block with the head
+// inside the group, counted from head_base, above it (a slice has less than 2^24
+// tokens: 32-bit byte offsets).  One wavefront reads 64 words of the reverse map at a
+// time, one per lane, and takes as many of them, in order, as the list has room for;
+// what is left goes into the next list.
+constexpr int kListCap = 1024;
+struct ConnectedList {
+    uint32_t entry[kListCap];
+    int count, more, head_base;
+};
+__device__ __forceinline__ int fill_list(ConnectedList& list, const Geom& g,
+                                         const uint32_t* __restrict__ conn, int64_t bh_first, int j,
+                                         int next_word, int lane)
+{
+    const int m = g.n_blocks, words = (m + 31) >> 5, all_words = g.kv_group * words;
+    const int head_base = next_word / words;
+    int count = 0;
+    bool full = false;
+    while (next_word < all_words && !full) {
+        const int w = next_word + lane;
+        const int head = w / words, wi = w - head * words;
+        uint32_t bits = w < all_words ? conn[((bh_first + head) * words + wi) * m + j] : 0u;
+        const int mine = __builtin_popcount(bits);
+        int upto = mine;                              // inclusive prefix sum over the lanes
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(upto, off);
+            upto += lane >= off ? t : 0;
+        }
+        const uint64_t fits = __builtin_amdgcn_ballot_w64(
+            w < all_words && count + upto <= kListCap && head - head_base < 256);
+        const int taken = __builtin_popcountll(fits);         // a prefix of the lanes
+        if (lane >= taken) bits = 0u;
+        int at = count + upto - mine;
+        while (bits) {
+            const int i = 32 * wi + __builtin_ctz(bits);
+            bits &= bits - 1;
+            const int br = i / g.blocks_per_row, bc = i - br * g.blocks_per_row;
+            list.entry[at++] = (uint32_t)(br * g.block_h * g.grid_w + bc * g.block_w) |
+                               (uint32_t)(head - head_base) << 24;
+        }
+        if (taken > 0) count += __builtin_amdgcn_readlane(upto, taken - 1);
+        next_word += taken;
+        full = taken < 64;
+    }
+    if (lane == 0) {
+        list.count = count;
+        list.more = next_word < all_words ? 1 : 0;
+        list.head_base = head_base;
+    }
+    return next_word;
+}
+
+// dK and dV in one pass at head dim 64.  What bounds the unpipelined form (fragments
+// read right before the matrix instructions, weights between them) is waiting: 44 % of
+// the wavefronts' cycles, matrix pipe busy 40 %, and a launch of 16 scan rounds per
+// group of 4 heads each of which fills and drains the tile pipeline.  Here
+//   * one list holds the connected blocks of the whole group (up to kListCap), its
+//     entries are looked up a tile ahead and need no division;
+//   * fragments are read W matrix instructions before the one that uses them, in the
+//     order of their use: 32 registers that hide the LDS latency at any point;
+//   * a tile is two halves of 32 queries: S and dP of half 0, then S and dP of half 1
+//     with the weights of half 0 behind them, then dV and dK of half 0 with the weights
+//     of half 1, then dV and dK of half 1.  Behind an instruction go the exponentials of
+//     two weights, the fma of the next two and the products and packs of the two before,
+//     so that nothing waits for the instruction in front of it; the order is written out
+//     and pinned.
+// 1.5 degree grid, 16 heads on 4, batch 12: 3.83 -> 3.23 ms, its training pass 8.99 -> 8.29 (cycles -23 %: the chip is
+// power-limited here and the clock gives part of it back, 1.80 -> 1.62 GHz).
+template <int NW>
+__device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
+                                              const uint16_t* __restrict__ k,
+                                              const uint16_t* __restrict__ v,
+                                              const uint16_t* __restrict__ dout,
+                                              const float* __restrict__ lse2,
+                                              const float* __restrict__ delta,
+                                              const uint32_t* __restrict__ conn,
+                                              const int32_t* __restrict__ order,
+                                              uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
+                                              const Geom& g, uint32_t n_units)
+{
+    constexpr int D = 64, KS = 4, SUBS = NW / 2, ROW = 128, TILE = 64 * ROW;
+    using IO = TileIO<D, NW>;
+    // [buffer][Q tile, dO tile]; the buffers alternate by bit 14 of the address
+    __shared__ __attribute__((aligned(32768))) unsigned char tiles_s[2][2][TILE];
+    __shared__ __attribute__((aligned(1024))) float rows_s[2][2][64];     // [buffer][lse2, delta]
+    __shared__ ConnectedList list;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int m = g.n_blocks;
+
+    // workgroup -> (key/value slice, key block), slices dealt to the 8 XCDs
+    // whole; the query slices that share the key/value slice are consecutive
+    uint32_t unit, r_unit;
+    map_unit(blockIdx.x, (uint32_t)m, n_units, unit, r_unit);
+    const int j = order ? order[(int64_t)unit * m + r_unit] : (int)r_unit;
+    const int64_t base = (int64_t)unit * g.n_tokens * D;
+    int64_t bh_first;
+    {
+        const uint32_t kv_heads = (uint32_t)(g.heads / g.kv_group);
+        const uint32_t e = unit / kv_heads, a = unit - e * kv_heads;
+        bh_first = (int64_t)e * g.heads + (int64_t)a * g.kv_group;
+    }
+    const uint32_t slice_bytes = (uint32_t)(g.n_tokens * D * 2), row_bytes = (uint32_t)(g.n_tokens * 4);
+
+    IO io;
+    io.init(g, lane, wave);
+
+    // this wavefront's 32 key rows: K and -V as B operands
+    bf16x8 kfb[KS], vfb[KS];
+    int64_t k_tok;
+    {
+        const int bw_shift = __builtin_ctz((unsigned)g.block_w);
+        const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
+        const int64_t tok0 = (int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w;
+        const int t = 32 * wave + l32;
+        const int rr = t >> bw_shift, cc = t & (g.block_w - 1);
+        k_tok = tok0 + (int64_t)rr * g.grid_w + cc;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            kfb[ks] = *(const bf16x8*)(k + base + k_tok * D + 16 * ks + 8 * half);
+            vfb[ks] = negated(*(const bf16x8*)(v + base + k_tok * D + 16 * ks + 8 * half));
+        }
+    }
+    const float c2 = g.scale * kLog2e;
+
+    f32x16 acck[2], accv[2];
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) acck[dt] = accv[dt] = zero_tile();
+
+    // addresses of this lane's fragments (row_frag, trans_frag) in the buffer that is
+    // read next; everything else is a constant
+    uint32_t row_at[KS], tr_at[2], val_at;
+    {
+        const uint32_t t0 = lds_address(tiles_s);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            row_at[ks] = t0 + (uint32_t)(l32 * ROW + swz(l32, 2 * ks + half) * 16);
+        const int s16 = lane & 15, gq = lane >> 4, r = 4 * (gq >> 1) + (s16 >> 2);
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) {
+            const int col = 16 * (gq & 1) + 4 * (s16 & 3) + 32 * dt;
+            tr_at[dt] = t0 + (uint32_t)(r * ROW + swz(r, col >> 3) * 16 + (col & 7) * 2);
+        }
+        val_at = lds_address(rows_s) + 16u * (uint32_t)half;
+    }
+    // fragment `i` of a tile in the order in which the matrix instructions take them:
+    //   0- 7  Q rows, dO rows of queries 0..31 (S, dP)     8-15  the same of 32..63
+    //  16-23  dO, Q transposed of queries 0..31 (dV, dK)  24-31  the same of 32..63
+    auto read_frag = [&](int i) -> bf16x8 {
+        const int u = i & 3;
+        if (i < 16) {
+            const int qt = i >> 3, is_g = (i >> 2) & 1;
+            return lds_read<bf16x8>(row_at[u], is_g * TILE + qt * 32 * ROW);
+        }
+        const int qt = (i - 16) >> 3, is_g = 1 - ((i >> 2) & 1), h = u >> 1, dt = u & 1;
+        bf16x4 part[2];
+#pragma unroll
+        for (int rd = 0; rd < 2; ++rd)
+            part[rd] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                (__attribute__((address_space(3))) bf16x4*)(uintptr_t)(
+                    tr_at[dt] + (uint32_t)(is_g * TILE + (32 * qt + 16 * h + 8 * rd) * ROW)));
+        return __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+
+    int next_word = 0;                                // wavefront 0 only
+    for (;;) {
+        __syncthreads();                              // the previous list is used up
+        if (wave == 0) next_word = fill_list(list, g, conn, bh_first, j, next_word, lane);
+        __syncthreads();
+        const int items = __builtin_amdgcn_readfirstlane(list.count) * SUBS;
+        const bool more = __builtin_amdgcn_readfirstlane(list.more) != 0;
+        const int64_t bh0 = bh_first + __builtin_amdgcn_readfirstlane(list.head_base);
+
+        auto entry_of = [&](int item) -> uint32_t { return list.entry[min(item, items - 1) / SUBS]; };
+        auto issue_item = [&](int item, uint32_t entry, int buf) {
+            const uint64_t bh = (uint64_t)(bh0 + (entry >> 24));
+            const uint32_t tok = (entry & 0xffffffu) + (uint32_t)sub_tile_first(g, item % SUBS);
+            const i32x4 q_rsrc = buffer_desc((const char*)q + bh * slice_bytes, slice_bytes);
+            const i32x4 g_rsrc = buffer_desc((const char*)dout + bh * slice_bytes, slice_bytes);
+            io.gather(q_rsrc, tok * ROW, tiles_s[buf][0]);
+            io.gather(g_rsrc, tok * ROW, tiles_s[buf][1]);
+            if (wave == 0)
+                io.gather_f32(buffer_desc((const char*)lse2 + bh * row_bytes, row_bytes), tok,
+                              rows_s[buf][0]);
+            if (wave == NW - 1)
+                io.gather_f32(buffer_desc((const char*)delta + bh * row_bytes, row_bytes), tok,
+                              rows_s[buf][1]);
+        };
+        if (items > 0) {
+            uint32_t entry = __builtin_amdgcn_readfirstlane(entry_of(0));
+            issue_item(0, entry, 0);
+            entry = __builtin_amdgcn_readfirstlane(entry_of(1));
+            // tile 0 of a list lies in buffer 0
+            const uint32_t flip = row_at[0] & 16384u;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) row_at[ks] -= flip;
+            tr_at[0] -= flip; tr_at[1] -= flip;
+            val_at -= flip >> 5;
+            for (int it = 0; it < items; ++it) {
+                // item `it` has landed and everyone is done with the other buffers
+                wait_gathers();
+                __syncthreads();
+                if (it + 1 < items) issue_item(it + 1, entry, (it + 1) & 1);
+                const uint32_t entry_v = entry_of(it + 2);
+
+                constexpr int W = 8;                  // fragments read ahead
+                bf16x8 f[W];
+                f32x16 s[2], dp[2];
+                f32x4 l4[4];
+                uint32_t pw[2][8], dw[2][8];
+                float fm[2][2], ex[2][2];
+                // delta - dP: the accumulator starts from delta, one value per row, as
+                // it lies in LDS (element r is query row 8 (r/4) + 4 half + r%4)
+                auto read_delta = [&](int qt) {
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        const f32x4 d4 = lds_read<f32x4>(val_at, 256 + 128 * qt + 32 * r4);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) dp[qt][4 * r4 + r] = d4[r];
+                    }
+                };
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f[i] = read_frag(i);
+                read_delta(0);
+#pragma unroll
+                for (int i = 4; i < W; ++i) f[i] = read_frag(i);
+                s[0] = zero_tile();
+                s[1] = zero_tile();
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 32; ++i) {
+                    const int u = i & 3;
+                    const bf16x8 x = f[i % W];
+                    if (i < 16) {
+                        const int qt = i >> 3;
+                        if ((i & 4) == 0)
+                            s[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, kfb[u], s[qt], 0, 0, 0);
+                        else
+                            dp[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, vfb[u], dp[qt], 0, 0, 0);
+                    } else {
+                        const int qt = (i - 16) >> 3, h = u >> 1, dt = u & 1;
+                        const uint32_t(&w)[8] = (i & 4) == 0 ? pw[qt] : dw[qt];
+                        const bf16x8 b = __builtin_bit_cast(
+                            bf16x8, make_uint4(w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]));
+                        if ((i & 4) == 0)
+                            accv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b, accv[dt], 0, 0, 0);
+                        else
+                            acck[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b, acck[dt], 0, 0, 0);
+                    }
+                    if (i + W < 32) f[i % W] = read_frag(i + W);
+                    // lse of the queries whose weights come next, delta of the second half
+                    if (i >= 3 && i < 7) l4[i - 3] = lds_read<f32x4>(val_at, 32 * (i - 3));
+                    if (i == 7) read_delta(1);
+                    if (i >= 10 && i < 18 && (i & 1) == 0)
+                        l4[(i - 10) >> 1] = lds_read<f32x4>(val_at, 128 + 32 * ((i - 10) >> 1));
+                    // weights of half qt behind the instructions 8 + 8 qt ..: per slot the
+                    // exponentials of two elements, the fma of the next two and the products
+                    // and packs of the two before
+                    if (i >= 7 && i < 23) {
+                        const int qt = (i - 7) >> 3, e = 2 * ((i - 7) & 7);
+                        fm[(i + 1) & 1][0] = fmaf(s[qt][e], c2, -l4[e >> 2][e & 3]);
+                        fm[(i + 1) & 1][1] = fmaf(s[qt][e + 1], c2, -l4[e >> 2][(e & 3) + 1]);
+                        asm volatile("" : "+v"(fm[(i + 1) & 1][0]), "+v"(fm[(i + 1) & 1][1]));
+                    }
+                    if (i >= 8 && i < 24) {
+                        ex[i & 1][0] = __builtin_amdgcn_exp2f(fm[i & 1][0]);
+                        ex[i & 1][1] = __builtin_amdgcn_exp2f(fm[i & 1][1]);
+                        asm volatile("" : "+v"(ex[i & 1][0]), "+v"(ex[i & 1][1]));
+                    }
+                    if (i >= 9 && i < 25) {
+                        const int qt = (i - 9) >> 3, e = 2 * ((i - 9) & 7), o = (i - 1) & 1;
+                        pw[qt][e >> 1] = pack_bf16(ex[o][0], ex[o][1]);
+                        dw[qt][e >> 1] = pack_bf16(ex[o][0] * dp[qt][e], ex[o][1] * dp[qt][e + 1]);
+                        asm volatile("" : "+v"(pw[qt][e >> 1]), "+v"(dw[qt][e >> 1]));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                entry = __builtin_amdgcn_readfirstlane(entry_v);
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) row_at[ks] ^= 16384u;
+                tr_at[0] ^= 16384u; tr_at[1] ^= 16384u;
+                val_at ^= 512u;
+            }
+        }
+        if (!more) break;
+    }
+
+    const float inv_b = 1.0f / (float)g.block_tokens;
+    const int64_t pooled_row = ((int64_t)unit * m + j) * D;
+    const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
+    const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) {
+        store_tile(dk + base + k_tok * D, dt, half, acck[dt], -g.scale, extra_k, inv_b);
+        store_tile(dv + base + k_tok * D, dt, half, accv[dt], 1.0f, extra_v, inv_b);
+    }
+}
+
 }  // namespace bwdm
 
 // plain kernels per (head dim, wavefronts per workgroup); the bodies are templates
@@ -738,8 +1045,7 @@ BSA_BWD_DQ(128, 8)
         const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order, uint16_t* dk, \
         uint16_t* dv, Geom g, uint32_t n_units)                                                 \
     {                                                                                             \
-        bwdm::dkdv_body<64, NW, bwdm::PASS_DV | bwdm::PASS_DK>(q, k, v, dout, lse2, delta,        \
-                                                               conn, order, dk, dv, g, n_units);      \
+        bwdm::dkdv_d64_body<NW>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g, n_units);      \
     }
 BSA_BWD_FUSED(2)
 BSA_BWD_FUSED(4)

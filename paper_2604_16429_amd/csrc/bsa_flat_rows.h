@@ -145,12 +145,6 @@ __device__ __forceinline__ f32x16 zero_tile()
 // four and 76 at 128 channels with one.)
 template <typename T, int D> struct TileReader;
 
-template <typename V>
-__device__ __forceinline__ V lds_read(uint32_t addr, int imm)
-{
-    return *(const __attribute__((address_space(3))) V*)(uintptr_t)(addr + (uint32_t)imm);
-}
-
 template <int D> struct TileReader<uint16_t, D> {
     using Tile = FlatTile<uint16_t, D>;
     static constexpr int STEPS = D / 16, BASES = STEPS < 4 ? STEPS : 4;
@@ -370,14 +364,6 @@ __device__ __forceinline__ void weighted_rows(const TileReader<T, D>& rd, uint32
         add_columns(cur, w, gr, acc);
         if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
     }
-}
-
-// Waits for this wavefront's direct-to-LDS loads in a form that the compiler
-// accounts for: it then knows that loads it issued itself are done as well and
-// does not wait for them (and for the gathers issued since) inside the loop.
-__device__ __forceinline__ void wait_gathers()
-{
-    __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
 }
 
 __device__ __forceinline__ void load_row(const uint16_t* row, bf16x8& f, int step, int half)

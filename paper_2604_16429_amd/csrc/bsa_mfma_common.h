@@ -55,6 +55,27 @@ __device__ __forceinline__ void load_lds_4(i32x4 rsrc, uint32_t voff, uint32_t s
 }
 #pragma clang diagnostic pop
 
+// Waits for this wavefront's direct-to-LDS loads in a form that the compiler
+// accounts for: it then knows that loads it issued itself are done as well and
+// does not wait for them (and for the gathers issued since) inside the loop.
+__device__ __forceinline__ void wait_gathers()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+}
+// The same, and for its LDS reads (of a tile that is about to be overwritten).
+__device__ __forceinline__ void wait_gathers_and_reads()
+{
+    __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) lgkmcnt(0)
+}
+
+// 16 (or sizeof(V)) bytes from LDS byte address addr + imm: the constant goes into the
+// read's offset field.
+template <typename V>
+__device__ __forceinline__ V lds_read(uint32_t addr, int imm)
+{
+    return *(const __attribute__((address_space(3))) V*)(uintptr_t)(addr + (uint32_t)imm);
+}
+
 // Exchange with the lane 32 away (lanes l < 32 get the value of l + 32 and
 // vice versa).
 __device__ __forceinline__ float swap32(float x)

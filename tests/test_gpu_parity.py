@@ -478,6 +478,44 @@ def test_backward_with_more_query_blocks_than_one_scan_round(G, oracle, H, W, bh
     check_grads(cfg, got, ref)
 
 
+def masked_attention_grads(cfg, q, k, v, dout, idx):
+    """Gradients by the library's reverse mode over dense fp32 attention whose mask
+    lets a query block see itself and its selected blocks (GPU, one batch entry)."""
+    m, kv = cfg.n_blocks, cfg.kv_heads
+    group = cfg.heads // kv
+    tok = torch.arange(cfg.grid_h * cfg.grid_w, device="cuda")
+    r, c = tok // cfg.grid_w, tok % cfg.grid_w
+    blk = (r // cfg.block_h) * (cfg.grid_w // cfg.block_w) + c // cfg.block_w
+    leaf = [torch.from_numpy(x[0]).cuda().requires_grad_() for x in (q, k, v)]
+    do = torch.from_numpy(dout[0]).cuda()
+    for a in range(cfg.heads):
+        see = torch.eye(m, dtype=torch.bool, device="cuda")
+        see.scatter_(1, torch.from_numpy(idx[0, a]).long().cuda(), True)
+        s = leaf[0][a] @ leaf[1][a // group].T / cfg.head_dim ** 0.5
+        s = s.masked_fill(~see[blk][:, blk], float("-inf"))
+        (torch.softmax(s, -1) @ leaf[2][a // group]).backward(do[a])
+    return tuple(x.grad.cpu().numpy()[None] for x in leaf)
+
+
+@pytest.mark.parametrize("heads,H,W,bh,bw,D,n", [
+    (264, 16, 32, 8, 8, 64, 2),     # more than 256 heads to a key/value head
+    (32, 64, 64, 8, 8, 64, 63),     # 2,048 connected blocks per key block: two full lists
+    (72, 32, 64, 8, 16, 64, 15),    # 1,152: the list ends inside a head
+    (130, 32, 64, 16, 16, 64, 7),   # 1,040, 256-token blocks
+])
+def test_backward_long_connected_lists(G, heads, H, W, bh, bw, D, n):
+    """Key blocks with more connected query blocks than one list holds (1,024 blocks,
+    256 heads)."""
+    cfg = shape_ns(1, heads, H, W, bh, bw, D, n, "bf16", kv_heads=1)
+    q = round_to_bf16(rand_qkv(cfg, 960 + heads)[0])
+    kv = shape_ns(1, 1, H, W, bh, bw, D, n, "bf16")
+    k, v = (round_to_bf16(x) for x in rand_qkv(kv, 961 + heads)[1:])
+    dout = round_to_bf16(rand_qkv(cfg, 962 + heads)[0])
+    idx = random_selection(cfg, 48)
+    check_grads(cfg, G.gpu_bwd(cfg, q, k, v, dout, idx),
+                masked_attention_grads(cfg, q, k, v, dout, idx))
+
+
 def slices_against_oracle_bwd(G, oracle, p, slices, idx_d=None):
     """Forward + backward of the whole problem on the GPU (the launch
     configuration the benchmark times); the gradients of the given (batch, head)
