@@ -29,7 +29,8 @@
 // the other side's rows broadcast from LDS): 1.5 degree grid, batch 2, 8 heads,
 // head dim 64, bf16, tiles of 10 x 10, 9 blocks: dQ 2.76 -> 0.33 ms, dK and dV
 // 4.38 -> 0.57 ms; fp32, batch 1, tiles of 8 x 8: dQ 0.81 -> 0.51 ms, dK and dV 1.55
-// -> 1.37 ms (0.97 since the key blocks are ordered).  delta: 233 -> 21 us and 113 -> 20 us (one thread walked a row).
+// -> 1.37 ms (0.97 since the key blocks are ordered).  fp32 with 16-row wavefronts
+// instead of 32: dQ 0.48 -> 0.45 ms, dK and dV 0.88 -> 0.67.  delta: 233 -> 21 us and 113 -> 20 us (one thread walked a row).
 #include "bsa_device.h"
 #include "bsa_flat_rows.h"
 #include "bsa_launch.h"
@@ -324,17 +325,23 @@ hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* o
 // ---------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------
-// Launch bounds: workgroups of up to 4 wavefronts at head dim 128 (the stationary
-// rows and accumulators need more registers than two wavefronts per SIMD have), up
-// to 8 below.
-template <int D> struct BwdLimits {
-    static constexpr int MAX_WAVES = D == 128 ? 4 : 8;
-    static constexpr int PER_SIMD = D == 128 ? 1 : 2;
+// Launch bounds (wavefronts per SIMD as the registers allow, 32-row bf16 against 16-row
+// fp32 wavefronts) and the most wavefronts of a workgroup: 4 where three of them share a
+// SIMD (workgroups of 8 would leave it two), so that larger fp32 blocks are split.  fp32,
+// blocks of 128, head dim 64, 8 slices: training pass 2.90 ms with workgroups of 8, 2.65
+// with 4; head dim 128, 5.58 ms with one wavefront per SIMD in dK/dV, 5.29 with two (27
+// registers spill outside of the tile loop), but 2.63 against 3.52 where two wavefronts
+// gather, which then reload inside the loop.
+template <typename T, int D> struct BwdLimits {
+    static constexpr bool WIDE = sizeof(T) == 2 && D == 128;
+    static constexpr int MAX_WAVES = WIDE || sizeof(T) == 4 ? 4 : 8;
+    static constexpr int DQ = WIDE ? 1 : sizeof(T) == 4 && D < 128 ? 3 : 2;
+    static constexpr int DKDV = WIDE ? 1 : sizeof(T) == 4 && D < 128 ? 3 : 2;
 };
 
 template <typename T, int D, int NL>
-__global__ __launch_bounds__(NL == 4 ? 64 * BwdLimits<D>::MAX_WAVES : NL == 2 ? 192 : 64,
-                             NL == 1 ? 1 : BwdLimits<D>::PER_SIMD)
+__global__ __launch_bounds__(NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
+                             NL == 1 ? 1 : (BwdLimits<T, D>::DQ))
 void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                     const T* __restrict__ dout, const float* __restrict__ lse2,
                     const float* __restrict__ delta, const int32_t* __restrict__ sel_idx,
@@ -348,7 +355,8 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, half = lane >> 5;
+    using W = WaveTile<T>;
+    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int b = g.block_tokens;
 
     int item;
@@ -364,23 +372,21 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     AttendedKeys<T, D, NL> keys;
     keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave);
 
-    const int tau_q = row0 + 32 * wave + l32;
+    const int tau_q = row0 + W::ROWS * wave + col;
     const bool valid = tau_q < min(b, row0 + chunk_rows);
     const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
     typename RowPieces<T, D>::type qf[RowPieces<T, D>::N], dof[RowPieces<T, D>::N];
 #pragma unroll
     for (int s = 0; s < RowPieces<T, D>::N; ++s) {
-        load_row(q + base + q_tok * D, qf[s], s, half);
-        load_row(dout + base + q_tok * D, dof[s], s, half);
+        load_row(q + base + q_tok * D, qf[s], s, part);
+        load_row(dout + base + q_tok * D, dof[s], s, part);
     }
     const float neg_l2 = -lse2[bh_idx * g.n_tokens + q_tok];
     const float neg_delta = -delta[bh_idx * g.n_tokens + q_tok];
     const float c2 = g.scale * kLog2e;
-    f32x16 acc[D / 32], dp0;
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) acc[dt] = zero_tile();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dp0[r] = neg_delta;
+    Column<T, D> acc;
+    clear_column<T, D>(acc);
+    const typename W::vec dp0 = constant_tile<T>(neg_delta);
 
     __syncthreads();                                 // tables
     const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
@@ -403,16 +409,16 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
             constexpr int HALF = 32 * Tile::ROW_BYTES;
             const int left = keys.total - (KT * c + 32 * hh);
             if (left <= 0) break;
-            f32x16 s = zero_tile(), dp = dp0;
-            dot_tiles<false>(rd, kt, vt, hh * HALF, qf, dof, s, dp);
+            typename W::vec s = constant_tile<T>(0.0f), dp = dp0;
+            dot_tiles<false, T, D>(rd, kt, vt, hh * HALF, qf, dof, s, dp);
             ColumnPieces<T, D> k0;
             read_columns(rd, kt, hh * HALF, 0, k0);
             if (left < 32)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (past_end(r, half, left)) s[r] = -INFINITY;
+                for (int r = 0; r < W::NR; ++r)
+                    if (past_end<T>(r, part, left)) s[r] = -INFINITY;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) dp[r] *= __builtin_amdgcn_exp2f(fmaf(s[r], c2, neg_l2));
+            for (int r = 0; r < W::NR; ++r) dp[r] *= __builtin_amdgcn_exp2f(fmaf(s[r], c2, neg_l2));
             weighted_rows(rd, kt, hh * HALF, k0, dp, acc);
         }
     }
@@ -420,7 +426,7 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     if (valid) {
         const float inv_b = 1.0f / (float)b;
         const float* extra = g.add_dq ? g.add_dq + (bh_idx * g.n_blocks + i) * D : nullptr;
-        store_column<T, D>(dq + base + q_tok * D, acc, g.scale, extra, inv_b, half);
+        store_column<D>(dq + base + q_tok * D, acc, g.scale, extra, inv_b, part);
     }
 }
 
@@ -433,8 +439,8 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
 constexpr int kConnCap = 2048;
 
 template <typename T, int D, int NL>
-__global__ __launch_bounds__(NL == 4 ? 64 * BwdLimits<D>::MAX_WAVES : NL == 2 ? 192 : 64,
-                             NL == 1 ? 1 : BwdLimits<D>::PER_SIMD)
+__global__ __launch_bounds__(NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
+                             NL == 4 ? (BwdLimits<T, D>::DKDV) : NL == 2 && D < 128 ? 2 : 1)
 void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                       const T* __restrict__ dout, const float* __restrict__ lse2,
                       const float* __restrict__ delta, const uint32_t* __restrict__ conn,
@@ -454,7 +460,8 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, half = lane >> 5;
+    using W = WaveTile<T>;
+    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int m = g.n_blocks, b = g.block_tokens;
     const int words = (m + 31) >> 5;                  // of a key block's row of the reverse map
 
@@ -487,20 +494,20 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     // this wavefront's 32 key rows.  V enters negated: the accumulator that starts
     // from delta then ends as delta - dP without an instruction per element, and
     // dK is stored with the sign turned.
-    const int tau_k = row0 + 32 * wave + l32;
+    const int tau_k = row0 + W::ROWS * wave + col;
     const bool valid = tau_k < min(b, row0 + chunk_rows);
     const int64_t k_tok = token_of(g, j, valid ? tau_k : 0);
     typename RowPieces<T, D>::type kf[RowPieces<T, D>::N], vf[RowPieces<T, D>::N];
 #pragma unroll
     for (int s = 0; s < RowPieces<T, D>::N; ++s) {
-        load_row(k + base + k_tok * D, kf[s], s, half);
-        load_row(v + base + k_tok * D, vf[s], s, half);
+        load_row(k + base + k_tok * D, kf[s], s, part);
+        load_row(v + base + k_tok * D, vf[s], s, part);
         vf[s] = negated(vf[s]);
     }
     const float c2 = g.scale * kLog2e;
-    f32x16 acck[D / 32], accv[D / 32];
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) acck[dt] = accv[dt] = zero_tile();
+    Column<T, D> acck, accv;
+    clear_column<T, D>(acck);
+    clear_column<T, D>(accv);
 
     const uint32_t q_dst = lds_address(q_lds), g_dst = lds_address(g_lds);
     const uint32_t l_dst = lds_address(l_lds), d_dst = lds_address(d_lds);
@@ -614,23 +621,23 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                 constexpr int HALF = 32 * Tile::ROW_BYTES;
                 const int left = total - (KT * c + 32 * hh);
                 if (left <= 0) break;
-                f32x16 p = zero_tile(), dp;
+                typename W::vec p = constant_tile<T>(0.0f), dp;
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const float4 d4 = *(const float4*)(d_lds[buf] + 32 * hh + 8 * r4 + 4 * half);
+                for (int r4 = 0; r4 < W::NR / 4; ++r4) {
+                    const float4 d4 = *(const float4*)(d_lds[buf] + 32 * hh + W::STEP * r4 + 4 * part);
                     dp[4 * r4] = d4.x; dp[4 * r4 + 1] = d4.y;
                     dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
                 }
-                dot_tiles<true>(rd, qt, gt, hh * HALF, kf, vf, p, dp);
+                dot_tiles<true, T, D>(rd, qt, gt, hh * HALF, kf, vf, p, dp);
                 ColumnPieces<T, D> c0;
                 read_columns(rd, gt, hh * HALF, 0, c0);
                 if (left < 32)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (past_end(r, half, left)) p[r] = -INFINITY;
+                    for (int r = 0; r < W::NR; ++r)
+                        if (past_end<T>(r, part, left)) p[r] = -INFINITY;
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const float4 l4 = *(const float4*)(l_lds[buf] + 32 * hh + 8 * r4 + 4 * half);
+                for (int r4 = 0; r4 < W::NR / 4; ++r4) {
+                    const float4 l4 = *(const float4*)(l_lds[buf] + 32 * hh + W::STEP * r4 + 4 * part);
                     p[4 * r4] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4], c2, -l4.x));
                     p[4 * r4 + 1] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 1], c2, -l4.y));
                     p[4 * r4 + 2] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 2], c2, -l4.z));
@@ -639,7 +646,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                 weighted_rows(rd, gt, hh * HALF, c0, p, accv);
                 read_columns(rd, qt, hh * HALF, 0, c0);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) dp[r] *= p[r];
+                for (int r = 0; r < W::NR; ++r) dp[r] *= p[r];
                 weighted_rows(rd, qt, hh * HALF, c0, dp, acck);
             }
         }
@@ -649,10 +656,10 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     if (valid) {
         const float inv_b = 1.0f / (float)b;
         const int64_t pooled_row = ((int64_t)unit * m + j) * D;
-        store_column<T, D>(dk + base + k_tok * D, acck, -g.scale,
-                           g.add_dk ? g.add_dk + pooled_row : nullptr, inv_b, half);
-        store_column<T, D>(dv + base + k_tok * D, accv, 1.0f,
-                           g.add_dv ? g.add_dv + pooled_row : nullptr, inv_b, half);
+        store_column<D>(dk + base + k_tok * D, acck, -g.scale,
+                           g.add_dk ? g.add_dk + pooled_row : nullptr, inv_b, part);
+        store_column<D>(dv + base + k_tok * D, accv, 1.0f,
+                           g.add_dv ? g.add_dv + pooled_row : nullptr, inv_b, part);
     }
 }
 
@@ -662,7 +669,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
                                const float* delta, const float* lse2, const uint32_t* conn,
                                const int32_t* order, const Geom& g, int64_t BH, hipStream_t stream)
 {
-    const RowSplit rows(g.block_tokens, BwdLimits<D>::MAX_WAVES);
+    const RowSplit rows(g.block_tokens, BwdLimits<T, D>::MAX_WAVES, WaveTile<T>::ROWS);
     const int nw = rows.waves;
     const int64_t BKV = BH / g.kv_group;
     if (BH * g.n_blocks * rows.chunks >= (int64_t)1 << 31) return hipErrorInvalidValue;
@@ -673,7 +680,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
                       : nw >= 2 ? bwd_generic_dkdv<T, D, 2> : bwd_generic_dkdv<T, D, 1>;
         kernel<<<grid_kv, block, sizeof(uint32_t) * (size_t)g.block_tokens, stream>>>(
             (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, conn, order,
-            (T*)dk, (T*)dv, g, (uint32_t)BKV, rows.chunks, 32 * nw);
+            (T*)dk, (T*)dv, g, (uint32_t)BKV, rows.chunks, WaveTile<T>::ROWS * nw);
         return hipGetLastError();
     };
     auto run_dq = [&] {
@@ -681,7 +688,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
                       : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
         kernel<<<grid, block, flat_table_bytes(g, g.n_select + 1), stream>>>(
             (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, sel_idx, (T*)dq, g,
-            (uint32_t)BKV, rows.chunks, 32 * nw);
+            (uint32_t)BKV, rows.chunks, WaveTile<T>::ROWS * nw);
         return hipGetLastError();
     };
     // `order` may lie where dQ goes; without it dK and dV may lie where k and v are

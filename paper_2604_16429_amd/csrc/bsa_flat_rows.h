@@ -128,21 +128,62 @@ __device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint3
     lo = pack_bf16(a - __uint_as_float(ua & 0xffff0000u), b - __uint_as_float(ub & 0xffff0000u));
 }
 
-__device__ __forceinline__ f32x16 zero_tile()
+// What a wavefront holds of a 32-row tile against its own ROWS stationary rows (one per
+// lane column, `col`): NR values per lane, value r of tile row
+// STEP (r/4) + 4 part + r%4, part = lane / ROWS.
+//   bf16: 32 stationary rows, v_mfma_f32_32x32x16_bf16.
+//   fp32: 16, v_mfma_f32_16x16x4_f32: the same rate as 32x32x2 (64 operations per cycle
+//         and SIMD) with half the registers, so that twice as many wavefronts share a
+//         block: a chain of products that depend on each other is half as long, and four
+//         (dK/dV three) wavefronts per SIMD instead of two cover it.
+template <typename T> struct WaveTile;
+template <> struct WaveTile<uint16_t> {
+    static constexpr int ROWS = 32, NR = 16, STEP = 8;
+    typedef f32x16 vec;
+};
+template <> struct WaveTile<float> {
+    static constexpr int ROWS = 16, NR = 8, STEP = 16;
+    typedef __attribute__((ext_vector_type(8))) float vec;
+};
+template <typename T>
+__device__ __forceinline__ typename WaveTile<T>::vec constant_tile(float x)
 {
-    const f32x16 z = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
-                      0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    return z;
+    typename WaveTile<T>::vec v;
+#pragma unroll
+    for (int r = 0; r < WaveTile<T>::NR; ++r) v[r] = x;
+    return v;
 }
-
+// Largest value and sum over the lanes that share a column.
+template <typename T> __device__ __forceinline__ float column_max(float x)
+{
+    x = fmaxf(x, swap32(x));
+    return WaveTile<T>::ROWS == 16 ? fmaxf(x, __shfl_xor(x, 16)) : x;
+}
+template <typename T> __device__ __forceinline__ float column_sum(float x)
+{
+    x += swap32(x);
+    return WaveTile<T>::ROWS == 16 ? x + __shfl_xor(x, 16) : x;
+}
+// A column of D channels: the accumulators of weighted_rows.
+template <typename T, int D> struct Column;
+template <int D> struct Column<uint16_t, D> { f32x16 a[D / 32]; };
+template <int D> struct Column<float, D> { f32x4 a[D / 16]; };
+template <typename T, int D>
+__device__ __forceinline__ void scale_column(Column<T, D>& c, float f)
+{
+#pragma unroll
+    for (auto& a : c.a) a *= f;
+}
+template <typename T, int D> __device__ __forceinline__ void clear_column(Column<T, D>& c)
+{
+#pragma unroll
+    for (auto& a : c.a) a = 0.0f;
+}
 // Where a lane reads a 32-row tile in LDS.  The swizzle leaves few distinct
 // addresses per lane: everything else is a constant that goes into the read's
-// offset field.  (Written out because the compiler otherwise keeps an address
-// register per read, which at 64 fp32 channels no longer fits: it spilled them, and
-// a reload from scratch memory waits for every gather in flight.  That cured the
-// forward and dQ; the fp32 dK/dV kernels still spill, 44 registers at 64 channels with
-// two gathering wavefronts, where reloads in the tile loop wait in this way, 22 with
-// four and 76 at 128 channels with one.)
+// offset field.  (Written out because the compiler otherwise keeps an address register
+// per read, which does not fit beside the rest: it spills them, and a reload from
+// scratch memory waits for every gather in flight.)
 template <typename T, int D> struct TileReader;
 
 template <int D> struct TileReader<uint16_t, D> {
@@ -169,19 +210,20 @@ template <int D> struct TileReader<uint16_t, D> {
 };
 template <int D> struct TileReader<float, D> {
     using Tile = FlatTile<float, D>;
-    static constexpr int BASES = 4;
-    uint32_t row[BASES];        // chunk 2 s + half of row l32, s < 4
-    uint32_t col[4];            // channel l32 of row 4 half + r, r < 4
+    static constexpr int BASES = 2;
+    uint32_t row[BASES];        // chunk 4 s + part of row col, s < 2
+    uint32_t col[4];            // row 4 part + r, r < 4, channels VEC col ..
+    static constexpr int VEC = D == 32 ? 2 : 4;
     __device__ __forceinline__ void init(int lane)
     {
-        const int l32 = lane & 31, half = lane >> 5;
+        const int c16 = lane & 15, part = lane >> 4;
 #pragma unroll
         for (int s = 0; s < BASES; ++s)
-            row[s] = (uint32_t)(l32 * Tile::ROW_BYTES + Tile::swz(l32, 2 * s + half) * 16);
+            row[s] = (uint32_t)(c16 * Tile::ROW_BYTES + Tile::swz(c16, 4 * s + part) * 16);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int rr = 4 * half + r;
-            col[r] = (uint32_t)(rr * Tile::ROW_BYTES + Tile::swz(rr, l32 >> 2) * 16 + (l32 & 3) * 4);
+            const int rr = 4 * part + r, at = 4 * VEC * c16;
+            col[r] = (uint32_t)(rr * Tile::ROW_BYTES + Tile::swz(rr, at >> 4) * 16 + (at & 15));
         }
     }
 };
@@ -191,49 +233,74 @@ template <int D> struct TileReader<float, D> {
 // reuse one group's registers and expose the read latency between groups.
 //
 // Row products, acc + X Y^T: this lane's column is its stationary row (y: its
-// pieces), accumulator register r is tile row 8 (r/4) + 4 half + r%4.  A piece is 16
-// channels in bf16, 8 in fp32 (channels 8 s + 4 half + 0..3 of each lane).
+// pieces).  A piece is 16 channels: in bf16 channels 16 s + 8 part + 0..7 of each lane,
+// one instruction; in fp32 16 s + 4 part + 0..3, four instructions for each of the two
+// 16-row halves of the tile.
 template <typename T, int D> struct RowPieces;
 template <int D> struct RowPieces<uint16_t, D> {
-    typedef bf16x8 type;
+    typedef bf16x8 type, frag;
     static constexpr int N = D / 16, GROUP = N < 4 ? N : 4;
+};
+struct RowFrag16 {
+    f32x4 t[2];
 };
 template <int D> struct RowPieces<float, D> {
     typedef f32x4 type;
-    static constexpr int N = D / 8, GROUP = 4;
+    typedef RowFrag16 frag;
+    static constexpr int N = D / 16, GROUP = 1;
 };
 
-template <typename T, int D>
-__device__ __forceinline__ void read_rows(const TileReader<T, D>& rd, uint32_t tile, int imm, int group,
-                                          typename RowPieces<T, D>::type (&x)[RowPieces<T, D>::GROUP])
+template <int D>
+__device__ __forceinline__ void read_rows(const TileReader<uint16_t, D>& rd, uint32_t tile, int imm,
+                                          int group, bf16x8 (&x)[RowPieces<uint16_t, D>::GROUP])
 {
-    typedef typename RowPieces<T, D>::type V;
 #pragma unroll
-    for (int u = 0; u < RowPieces<T, D>::GROUP; ++u) {
-        const int s = group * RowPieces<T, D>::GROUP + u;
-        x[u] = lds_read<V>(rd.row[s % rd.BASES] + tile, imm + (s / rd.BASES) * 128);
+    for (int u = 0; u < RowPieces<uint16_t, D>::GROUP; ++u) {
+        const int s = group * RowPieces<uint16_t, D>::GROUP + u;
+        x[u] = lds_read<bf16x8>(rd.row[s % rd.BASES] + tile, imm + (s / rd.BASES) * 128);
     }
+}
+template <int D>
+__device__ __forceinline__ void read_rows(const TileReader<float, D>& rd, uint32_t tile, int imm,
+                                          int group, RowFrag16 (&x)[RowPieces<float, D>::GROUP])
+{
+#pragma unroll
+    for (int u = 0; u < RowPieces<float, D>::GROUP; ++u) {
+        const int s = group * RowPieces<float, D>::GROUP + u;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            x[u].t[t] = lds_read<f32x4>(rd.row[s % rd.BASES] + tile,
+                                        imm + (s / rd.BASES) * 128 + 16 * t * FlatTile<float, D>::ROW_BYTES);
+    }
+}
+typedef WaveTile<float>::vec f32x8;
+__device__ __forceinline__ f32x4 half_tile(const f32x8& v, int t)
+{
+    return t ? __builtin_shufflevector(v, v, 4, 5, 6, 7) : __builtin_shufflevector(v, v, 0, 1, 2, 3);
 }
 __device__ __forceinline__ f32x16 mul_piece(bf16x8 x, bf16x8 y, f32x16 acc)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
 }
-__device__ __forceinline__ f32x16 mul_piece(f32x4 x, f32x4 y, f32x16 acc)
+__device__ __forceinline__ f32x8 mul_piece(const RowFrag16& x, f32x4 y, f32x8 acc)
 {
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc, 0, 0, 0);
+    f32x4 a = half_tile(acc, 0), b = half_tile(acc, 1);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        a = __builtin_amdgcn_mfma_f32_16x16x4f32(x.t[0][c], y[c], a, 0, 0, 0);
+        b = __builtin_amdgcn_mfma_f32_16x16x4f32(x.t[1][c], y[c], b, 0, 0, 0);
+    }
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 // acc + X Y^T.  tile: LDS address of the tile (uniform), imm: constant to add.
 template <typename T, int D>
-__device__ __forceinline__ f32x16 dot_tile(
+__device__ __forceinline__ typename WaveTile<T>::vec dot_tile(
     const TileReader<T, D>& rd, uint32_t tile, int imm,
-    const typename RowPieces<T, D>::type (&y)[RowPieces<T, D>::N], f32x16 acc)
+    const typename RowPieces<T, D>::type (&y)[RowPieces<T, D>::N], typename WaveTile<T>::vec acc)
 {
     constexpr int G = RowPieces<T, D>::GROUP, GROUPS = RowPieces<T, D>::N / G;
-    typename RowPieces<T, D>::type x[2][G];
+    typename RowPieces<T, D>::frag x[2][G];
     read_rows(rd, tile, imm, 0, x[0]);
 #pragma unroll
     for (int gr = 0; gr < GROUPS; ++gr) {
@@ -254,14 +321,15 @@ template <bool APART, typename T, int D>
 __device__ __forceinline__ void dot_tiles(
     const TileReader<T, D>& rd, uint32_t tile_a, uint32_t tile_b, int imm,
     const typename RowPieces<T, D>::type (&ya)[RowPieces<T, D>::N],
-    const typename RowPieces<T, D>::type (&yb)[RowPieces<T, D>::N], f32x16& acc_a, f32x16& acc_b)
+    const typename RowPieces<T, D>::type (&yb)[RowPieces<T, D>::N], typename WaveTile<T>::vec& acc_a,
+    typename WaveTile<T>::vec& acc_b)
 {
     constexpr int G = RowPieces<T, D>::GROUP, N = RowPieces<T, D>::N, GROUPS = N / G;
     constexpr int CHAIN = APART && sizeof(T) == 4 && D > 32 ? N / 4 : N;     // pieces
-    typename RowPieces<T, D>::type a[2][G], b[2][G];
+    typename RowPieces<T, D>::frag a[2][G], b[2][G];
     read_rows(rd, tile_a, imm, 0, a[0]);
     read_rows(rd, tile_b, imm, 0, b[0]);
-    f32x16 chain = acc_a;
+    typename WaveTile<T>::vec chain = acc_a;
 #pragma unroll
     for (int gr = 0; gr < GROUPS; ++gr) {
         if (gr + 1 < GROUPS) {
@@ -272,7 +340,7 @@ __device__ __forceinline__ void dot_tiles(
 #pragma unroll
         for (int u = 0; u < G; ++u) {
             const int piece = gr * G + u;
-            if (piece > 0 && piece % CHAIN == 0) chain = zero_tile();
+            if (piece > 0 && piece % CHAIN == 0) chain = constant_tile<T>(0.0f);
             chain = mul_piece(a[gr & 1][u], ya[piece], chain);
             acc_b = mul_piece(b[gr & 1][u], yb[piece], acc_b);
             if ((piece + 1) % CHAIN == 0) acc_a = piece < CHAIN ? chain : acc_a + chain;
@@ -283,16 +351,21 @@ __device__ __forceinline__ void dot_tiles(
 
 // Weighted row sums, acc^T += X^T W^T: channels x this lane's column; w: the
 // column's weights of the 32 rows in the accumulator layout of dot_tile, which is
-// the B operand as it stands.  Groups: 16 rows in bf16, 8 in fp32.  The caller
-// reads group 0 (read_columns) before it computes the weights.
+// the B operand as it stands.  Groups of 16 rows in bf16, of eight instructions in fp32;
+// the caller reads group 0 (read_columns) before it computes the weights.
+// fp32: the operand of output tile c is channel VEC col + c % VEC (+ 64 for c >= 4), so
+// that one 16-byte read (8 at head dim 32) feeds four (two) instructions, and a lane ends
+// up with consecutive channels of its column.
 template <typename T, int D> struct ColumnPieces;
 template <int D> struct ColumnPieces<uint16_t, D> {
     static constexpr int GROUPS = 2;
     bf16x8 x[D / 32];                       // A operand: channels 32 dt .. x 16 rows
 };
 template <int D> struct ColumnPieces<float, D> {
-    static constexpr int GROUPS = 4;
-    float x[4][D / 32];                     // row 4 half + r, channel 32 dt + l32
+    static constexpr int VEC = TileReader<float, D>::VEC;
+    typedef __attribute__((ext_vector_type(VEC))) float vec;
+    static constexpr int STEPS = 128 / D, GROUPS = 8 / STEPS;
+    vec x[STEPS][D / (16 * VEC)];           // row 16 (step / 4) + 4 part + step % 4
 };
 template <int D>
 __device__ __forceinline__ void read_columns(const TileReader<uint16_t, D>& rd, uint32_t tile, int imm,
@@ -316,15 +389,18 @@ __device__ __forceinline__ void read_columns(const TileReader<float, D>& rd, uin
                                              int group, ColumnPieces<float, D>& c)
 {
     constexpr int ROW = FlatTile<float, D>::ROW_BYTES;
+    typedef typename ColumnPieces<float, D>::vec V;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int u = 0; u < c.STEPS; ++u) {
+        const int step = c.STEPS * group + u;
 #pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-            c.x[r][dt] = lds_read<float>(rd.col[r] + tile, imm + 8 * group * ROW + 128 * dt);
+        for (int e = 0; e < D / (16 * c.VEC); ++e)
+            c.x[u][e] = lds_read<V>(rd.col[step & 3] + tile, imm + 16 * (step >> 2) * ROW + 256 * e);
+    }
 }
 template <int D>
 __device__ __forceinline__ void add_columns(const ColumnPieces<uint16_t, D>& c, const f32x16& w,
-                                            int group, f32x16 (&acc)[D / 32])
+                                            int group, Column<uint16_t, D>& acc)
 {
     uint32_t hi[4], lo[4];
 #pragma unroll
@@ -334,25 +410,25 @@ __device__ __forceinline__ void add_columns(const ColumnPieces<uint16_t, D>& c, 
     const bf16x8 w_lo = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) {
-        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.x[dt], w_hi, acc[dt], 0, 0, 0);
-        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.x[dt], w_lo, acc[dt], 0, 0, 0);
+        acc.a[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.x[dt], w_hi, acc.a[dt], 0, 0, 0);
+        acc.a[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.x[dt], w_lo, acc.a[dt], 0, 0, 0);
     }
 }
 template <int D>
-__device__ __forceinline__ void add_columns(const ColumnPieces<float, D>& c, const f32x16& w, int group,
-                                            f32x16 (&acc)[D / 32])
+__device__ __forceinline__ void add_columns(const ColumnPieces<float, D>& c, const f32x8& w, int group,
+                                            Column<float, D>& acc)
 {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int u = 0; u < c.STEPS; ++u)
 #pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-            acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(c.x[r][dt], w[4 * group + r], acc[dt], 0, 0,
-                                                           0);
+        for (int t = 0; t < D / 16; ++t)
+            acc.a[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                c.x[u][t / c.VEC][t % c.VEC], w[c.STEPS * group + u], acc.a[t], 0, 0, 0);
 }
 template <typename T, int D>
 __device__ __forceinline__ void weighted_rows(const TileReader<T, D>& rd, uint32_t tile, int imm,
-                                              ColumnPieces<T, D>& first, const f32x16& w,
-                                              f32x16 (&acc)[D / 32])
+                                              ColumnPieces<T, D>& first,
+                                              const typename WaveTile<T>::vec& w, Column<T, D>& acc)
 {
     constexpr int GROUPS = ColumnPieces<T, D>::GROUPS;
     ColumnPieces<T, D> second;
@@ -366,20 +442,20 @@ __device__ __forceinline__ void weighted_rows(const TileReader<T, D>& rd, uint32
     }
 }
 
-__device__ __forceinline__ void load_row(const uint16_t* row, bf16x8& f, int step, int half)
+__device__ __forceinline__ void load_row(const uint16_t* row, bf16x8& f, int step, int part)
 {
-    f = *(const bf16x8*)(row + 16 * step + 8 * half);
+    f = *(const bf16x8*)(row + 16 * step + 8 * part);
 }
-__device__ __forceinline__ void load_row(const float* row, f32x4& f, int step, int half)
+__device__ __forceinline__ void load_row(const float* row, f32x4& f, int step, int part)
 {
-    f = *(const f32x4*)(row + 8 * step + 4 * half);
+    f = *(const f32x4*)(row + 16 * step + 4 * part);
 }
 
-// Padding of the last tile: register r of a 32-row tile with `left` rows is a row
-// past the end.
-__device__ __forceinline__ bool past_end(int r, int half, int left)
+// Padding of the last tile: value r of a 32-row tile with `left` rows is a row past the
+// end.
+template <typename T> __device__ __forceinline__ bool past_end(int r, int part, int left)
 {
-    return 8 * (r >> 2) + 4 * half + (r & 3) >= left;
+    return WaveTile<T>::STEP * (r >> 2) + 4 * part + (r & 3) >= left;
 }
 
 __device__ __forceinline__ f32x4 negated(f32x4 x)
@@ -387,22 +463,40 @@ __device__ __forceinline__ f32x4 negated(f32x4 x)
     return -x;
 }
 
-// Stores this lane's column of D channels (accumulators of weighted_rows), scaled
-// by f, to its token row; with `extra` see store4_or_add.
-template <typename T, int D>
-__device__ __forceinline__ void store_column(T* row, const f32x16 (&acc)[D / 32], float f,
-                                             const float* extra, float inv_b, int half)
+// Stores this lane's column of D channels, scaled by f, to its token row; with `extra`
+// see store4_or_add.
+template <int D>
+__device__ __forceinline__ void store_column(uint16_t* row, const Column<uint16_t, D>& acc, float f,
+                                             const float* extra, float inv_b, int part)
 {
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-            const int d = 32 * dt + 8 * r4 + 4 * half;
+            const int d = 32 * dt + 8 * r4 + 4 * part;
+            const f32x16& a = acc.a[dt];
             store4_or_add(row + d,
-                          make_float4(acc[dt][4 * r4] * f, acc[dt][4 * r4 + 1] * f,
-                                      acc[dt][4 * r4 + 2] * f, acc[dt][4 * r4 + 3] * f),
+                          make_float4(a[4 * r4] * f, a[4 * r4 + 1] * f, a[4 * r4 + 2] * f,
+                                      a[4 * r4 + 3] * f),
                           extra ? extra + d : nullptr, inv_b);
         }
+}
+// (value r of output tile c is channel VEC (4 part + r) + c % VEC, + 64 for c >= 4)
+template <int D>
+__device__ __forceinline__ void store_column(float* row, const Column<float, D>& acc, float f,
+                                             const float* extra, float inv_b, int part)
+{
+    constexpr int VEC = TileReader<float, D>::VEC;
+    auto value = [&](int d) {                         // channel VEC 4 part + d of its 64
+        return acc.a[d / (4 * VEC) * VEC + d % VEC][d % (4 * VEC) / VEC] * f;
+    };
+#pragma unroll
+    for (int d = 0; d < D / 4; d += 4) {
+        const int at = 64 * (d / 16) + 4 * VEC * part + d % 16;
+        store4_or_add(row + at,
+                      make_float4(value(d), value(d + 1), value(d + 2), value(d + 3)),
+                      extra ? extra + at : nullptr, inv_b);
+    }
 }
 
 // This wavefront's share of a tile of two tensors: slabs wave + NL j, row tok[j] of
@@ -543,13 +637,13 @@ private:
     const Geom* geom;
 };
 
-// Rows of a block over workgroups of at most `max_waves` wavefronts of 32 rows
+// Rows of a block over workgroups of at most `max_waves` wavefronts of `rows` rows
 // each: as few workgroups as hold them, as even as possible.
 struct RowSplit {
     int chunks, waves;
-    RowSplit(int block_tokens, int max_waves)
+    RowSplit(int block_tokens, int max_waves, int rows)
     {
-        const int row_tiles = (block_tokens + 31) / 32;
+        const int row_tiles = (block_tokens + rows - 1) / rows;
         chunks = (row_tiles + max_waves - 1) / max_waves;
         waves = (row_tiles + chunks - 1) / chunks;
     }

@@ -4,21 +4,24 @@
 //
 // Every token of query block i attends, in one softmax, to the tokens of block
 // i and of its n selected blocks (fine-grained attention equation plus the
-// local block).  A wavefront owns 32 query rows; a workgroup of up to 8
-// wavefronts owns up to 256 rows of one query block, whose wavefronts attend to
+// local block).  A wavefront owns 32 query rows (fp32: 16); a workgroup of up to 8
+// wavefronts owns up to 256 (128) rows of one query block, whose wavefronts attend to
 // the same keys.  The attended keys are walked as one flat sequence
 // (bsa_flat_rows.h) in tiles of 64 (bf16) or 32 (fp32) keys that the workgroup
 // shares through LDS: gathered with direct-to-LDS loads, double buffered, one
 // barrier per tile.
 //
 // Transposed products as in the specialised kernels: S^T = K Q^T and
-// O^T = V^T P^T with 32x32 accumulators, so that a lane holds one query column,
-// the softmax reductions are in-register, and the S^T accumulator registers are
-// the B operand of the second product.
-//   fp32: v_mfma_f32_32x32x2_f32, i.e. fp32 products and sums throughout.  Lane
-//         half h supplies channels 8 j + 4 h + 0..3 of its row, so a 16-byte
-//         read feeds four instructions; accumulator register r is, as it is, the
-//         B operand of the keys 8 (r/4) + r%4 (+ 4 for the upper half).
+// O^T = V^T P^T, so that a lane holds one query column, the softmax reductions are
+// in-register, and the S^T accumulator registers are the B operand of the second
+// product.
+//   fp32: v_mfma_f32_16x16x4_f32, i.e. fp32 products and sums throughout.  Lane
+//         part p (of 4) supplies channels 16 j + 4 p + 0..3 of its row, so a 16-byte
+//         read feeds four instructions; accumulator register r of 16 keys is, as it is,
+//         the B operand of the keys 4 p + r.  With 16 rows to a wavefront instead of 32
+//         the four that share a block of 64 cover each other's dependent products: 1.5
+//         degrees, 8 heads, 385 -> 317 us (matrix pipe busy 62 -> 79 %), the 32 x 64
+//         grid 18.2 -> 12.7 us.
 //   bf16: v_mfma_f32_32x32x16_bf16.  The weights enter the second product as two
 //         bf16 terms (16 significant bits): these shapes have always had their
 //         weights multiplied in fp32, and keep that precision.
@@ -69,7 +72,8 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, half = lane >> 5;
+    using W = WaveTile<T>;
+    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int b = g.block_tokens;
 
     int item;
@@ -85,12 +89,12 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave);
 
     // this wavefront's 32 query rows
-    const int tau_q = row0 + 32 * wave + l32;
+    const int tau_q = row0 + W::ROWS * wave + col;
     const bool valid = tau_q < min(b, row0 + chunk_rows);
     const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
     typename RowPieces<T, D>::type qf[RowPieces<T, D>::N];
 #pragma unroll
-    for (int s = 0; s < RowPieces<T, D>::N; ++s) load_row(q + base + q_tok * D, qf[s], s, half);
+    for (int s = 0; s < RowPieces<T, D>::N; ++s) load_row(q + base + q_tok * D, qf[s], s, part);
     __syncthreads();                                 // tables
 
     const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
@@ -102,9 +106,8 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     }
 
     const float c2 = g.scale * 1.4426950408889634f;
-    f32x16 oacc[D / 32];
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) oacc[dt] = zero_tile();
+    Column<T, D> oacc;
+    clear_column<T, D>(oacc);
     float m_ref = -INFINITY, m_rest = 0.0f, l_run = 0.0f;
     uint64_t rests = 0;                              // lanes whose m_rest is not 0
 
@@ -117,20 +120,20 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
         const uint32_t at = (uint32_t)buf * Tile::TILE_BYTES;
 #pragma unroll
         for (int hh = 0; hh < KT / 32; ++hh) {
-            f32x16 s = dot_tile(rd, k_dst + at, 32 * hh * Tile::ROW_BYTES, qf, zero_tile());
+            typename W::vec s = dot_tile(rd, k_dst + at, 32 * hh * Tile::ROW_BYTES, qf, constant_tile<T>(0.0f));
             const int left = keys.total - (KT * c + 32 * hh);     // keys from this half tile on
             if (left < 32) {
                 if (left <= 0) break;
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (past_end(r, half, left)) s[r] = -INFINITY;
+                for (int r = 0; r < W::NR; ++r)
+                    if (past_end<T>(r, part, left)) s[r] = -INFINITY;
             }
             ColumnPieces<T, D> v0;
             read_columns(rd, v_dst + at, 32 * hh * Tile::ROW_BYTES, 0, v0);
-            f32x16 p;
+            typename W::vec p;
             float rs0 = 0.0f, rs1 = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
+            for (int r = 0; r < W::NR; r += 2) {
                 p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -m_ref));
                 p[r + 1] = __builtin_amdgcn_exp2f(fmaf(s[r + 1], c2, -m_ref));
                 rs0 += p[r];
@@ -142,8 +145,8 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 // new reference from the row maxima; rescale what is there
                 float mx = s[0];
 #pragma unroll
-                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-                mx = fmaxf(mx, swap32(mx));
+                for (int r = 1; r < W::NR; ++r) mx = fmaxf(mx, s[r]);
+                mx = column_max<T>(mx);
                 const bool up = fmaf(mx, c2, -m_ref) > m_rest;
                 const float m_new = up ? mx * c2 : m_ref;
                 const float rest_new =
@@ -153,13 +156,10 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 m_rest = rest_new;
                 rests = __builtin_amdgcn_ballot_w64(rest_new != 0.0f);
                 l_run *= alpha;
-#pragma unroll
-                for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+                scale_column<T, D>(oacc, alpha);
                 rs = 0.0f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
+                for (int r = 0; r < W::NR; ++r) {
                     p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -m_new) - rest_new);
                     rs += p[r];
                 }
@@ -169,11 +169,11 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
         }
     }
 
-    const float l_tot = l_run + swap32(l_run);
+    const float l_tot = column_sum<T>(l_run);
     if (valid) {
         const float inv_l = 1.0f / l_tot;
-        store_column<T, D>(out + base + q_tok * D, oacc, inv_l, nullptr, 0.0f, half);
-        if (lse && half == 0)
+        store_column<D>(out + base + q_tok * D, oacc, inv_l, nullptr, 0.0f, part);
+        if (lse && part == 0)
             lse[bh_idx * g.n_tokens + q_tok] =
                 (m_ref + (m_rest + __builtin_amdgcn_logf(l_tot))) * 0.6931471805599453f;
     }
@@ -183,7 +183,7 @@ template <typename T, int D>
 static hipError_t launch_t(const void* q, const void* k, const void* v, const FwdJob* jobs,
                            int n_jobs, const Geom& g, int64_t BH, hipStream_t stream)
 {
-    const RowSplit rows(g.block_tokens, 8);
+    const RowSplit rows(g.block_tokens, 8, WaveTile<T>::ROWS);
     const int nw = rows.waves;
     auto kernel = nw >= 4 ? fwd_generic_kernel<T, D, 4>
                   : nw >= 2 ? fwd_generic_kernel<T, D, 2> : fwd_generic_kernel<T, D, 1>;
@@ -206,7 +206,7 @@ static hipError_t launch_t(const void* q, const void* k, const void* v, const Fw
                                         stream>>>((const T*)q + row * D, (const T*)k + kv,
                                                   (const T*)v + kv, a.lists, b.lists, (T*)a.out,
                                                   (T*)b.out, a.lse, b.lse, j, g, (uint32_t)slices,
-                                                  rows.chunks, 32 * nw);
+                                                  rows.chunks, WaveTile<T>::ROWS * nw);
                            });
     });
 }

@@ -35,6 +35,9 @@ SHAPES = [
     (34, 60, 17, 30, 64, 2),     # b = 510: two workgroups of eight, two idle rows
     (20, 26, 2, 2, 64, 63),      # 64 attended blocks: the last list that is sorted
     (20, 26, 2, 2, 64, 64),      # 65: kept in the given order
+    (16, 30, 16, 1, 64, 5),      # b = 16: one fp32 wavefront of 16 rows
+    (34, 12, 17, 1, 128, 4),     # b = 17: one row in the second of them
+    (24, 36, 8, 6, 64, 7),       # b = 48: three, two of which gather
     (46, 48, 1, 2, 32, 959),     # list and its repeated last entry just fit the LDS table
     (46, 48, 1, 2, 32, 960),     # just not
     (46, 48, 1, 2, 32, 1030),    # more listed blocks than the LDS table holds
