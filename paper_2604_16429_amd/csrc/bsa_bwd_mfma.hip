@@ -30,8 +30,8 @@
 //                sub-tiles.  Per 32-query tile: S = Q K^T and dP = dO V^T (rows
 //                are queries now: lse and delta come from LDS per row), and
 //                dV^T += dO^T P, dK^T += Q^T dS with the transposing LDS read
-//                of the dO / Q tile.  For head dim 128 the two accumulators do
-//                not fit next to the operands, so dV and dK are two passes.
+//                of the dO / Q tile.  One pass for both head dims: at 128, where
+//                the accumulators take half of the registers, V stays in LDS.
 // Waits for gathers are of the form that the compiler accounts for (wait_gathers):
 // otherwise it waits, in front of the first use of the stationary rows inside the loop,
 // for the loads that it issued before the loop, i.e. for the tile that was just
@@ -193,15 +193,12 @@ __device__ __forceinline__ f32x16 zero_tile()
     return z;
 }
 
-// Head dim 128, where a phase of matrix instructions is long (8 to 16 of them) and
+// dQ at head dim 128, where a phase of matrix instructions is long (8 to 16 of them) and
 // nothing of the other phases is interleaved with it: the wavefront that is in such a
 // phase issues first, so that the two wavefronts of a SIMD drift apart and one's vector
 // work falls behind the other's matrix instructions.  Select + forward + backward,
-// 1.5 degrees, batch 4, 16 heads: 9.11 -> 8.92 ms.  Two phases are not marked as such,
-// because the pass is faster without: the end of a tile's last one (the priority stays
-// up through the wait for the next tile; lowered 8.54 -> 8.55 ms) and the dP products
-// of the dK pass (raised 8.54 -> 8.60 ms).  At head dim 64, with phases half as long,
-// the same switches cost 0 to 4 %, and in the general kernels they give nothing.
+// 1.5 degrees, batch 4, 16 heads: 9.11 -> 8.92 ms (with dK/dV kernels of the same form).
+// The priority stays up through the wait for the next tile (lowered 8.54 -> 8.55 ms).
 template <int D>
 __device__ __forceinline__ void matrix_phase(bool begin)
 {
@@ -493,215 +490,6 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
 // ---------------------------------------------------------------------------
 // dK / dV
 // ---------------------------------------------------------------------------
-constexpr int PASS_DV = 1, PASS_DK = 2;
-
-template <int D, int NW, int PASS>
-__device__ __forceinline__ void dkdv_body(const uint16_t* __restrict__ q,
-                                          const uint16_t* __restrict__ k,
-                                          const uint16_t* __restrict__ v,
-                                          const uint16_t* __restrict__ dout,
-                                          const float* __restrict__ lse2,
-                                          const float* __restrict__ delta,
-                                          const uint32_t* __restrict__ conn,
-                                          const int32_t* __restrict__ order,
-                                          uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
-                                          const Geom& g, uint32_t n_units)
-{
-    constexpr int KS = D / 16, DT = D / 32;
-    constexpr bool DO_DV = (PASS & PASS_DV) != 0, DO_DK = (PASS & PASS_DK) != 0;
-    constexpr int SCAN = 64 * NW;                  // query blocks examined per scan round
-    using IO = TileIO<D, NW>;
-    __shared__ __attribute__((aligned(1024))) unsigned char q_lds[2][IO::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char g_lds[2][IO::TILE_BYTES];
-    __shared__ __attribute__((aligned(256))) float l_lds[2][64];
-    __shared__ __attribute__((aligned(256))) float d_lds[2][64];
-    __shared__ int list_s[SCAN];
-    __shared__ int wave_cnt[NW];
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, half = lane >> 5;
-    const int m = g.n_blocks;
-    const int subs = g.block_tokens / 64;
-    const int words = (m + 31) >> 5;               // of a key block's row of the connection map
-
-    // workgroup -> (key/value slice, key block), slices dealt to the 8 XCDs
-    // whole; the query slices that share the key/value slice are consecutive
-    int j;
-    int64_t base, bh_first, kv_unit;
-    {
-        uint32_t unit, r;
-        map_unit(blockIdx.x, (uint32_t)m, n_units, unit, r);
-        j = order ? order[(int64_t)unit * m + r] : (int)r;
-        kv_unit = unit;
-        base = (int64_t)unit * g.n_tokens * D;
-        const uint32_t kv_heads = (uint32_t)(g.heads / g.kv_group);
-        const uint32_t e = unit / kv_heads, a = unit - e * kv_heads;
-        bh_first = (int64_t)e * g.heads + (int64_t)a * g.kv_group;
-    }
-    const uint32_t slice_bytes = (uint32_t)(g.n_tokens * D * 2);
-
-    IO io;
-    io.init(g, lane, wave);
-    auto origin_of = [&](int beta) -> uint32_t {     // byte offset of a block's first token
-        const int br = beta / g.blocks_per_row, bc = beta - br * g.blocks_per_row;
-        return (uint32_t)((br * g.block_h * g.grid_w + bc * g.block_w) * (D * 2));
-    };
-
-    // this wavefront's 32 key rows: K (and -V) as B operands
-    bf16x8 kfb[KS], vfb[DO_DK ? KS : 1];
-    int64_t k_tok;
-    {
-        const int bw_shift = __builtin_ctz((unsigned)g.block_w);
-        const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
-        const int64_t tok0 = (int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w;
-        const int t = 32 * wave + l32;
-        const int rr = t >> bw_shift, cc = t & (g.block_w - 1);
-        k_tok = tok0 + (int64_t)rr * g.grid_w + cc;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            kfb[ks] = *(const bf16x8*)(k + base + k_tok * D + 16 * ks + 8 * half);
-            if constexpr (DO_DK)
-                vfb[ks] = negated(*(const bf16x8*)(v + base + k_tok * D + 16 * ks + 8 * half));
-        }
-    }
-    const float c2 = g.scale * kLog2e;
-
-    f32x16 acck[DO_DK ? DT : 1], accv[DO_DV ? DT : 1];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-        if constexpr (DO_DK) acck[dt] = zero_tile();
-        if constexpr (DO_DV) accv[dt] = zero_tile();
-    }
-
-    // query heads of the group in ascending order, query blocks in ascending
-    // order within each: the summation order is fixed
-    for (int gq = 0; gq < g.kv_group; ++gq) {
-    const int64_t bh_idx = bh_first + gq;
-    const uint32_t* conn_col = conn + bh_idx * (int64_t)words * m + j;
-    const i32x4 q_rsrc = buffer_desc(q + bh_idx * g.n_tokens * D, slice_bytes);
-    const i32x4 g_rsrc = buffer_desc(dout + bh_idx * g.n_tokens * D, slice_bytes);
-    const i32x4 l_rsrc = buffer_desc(lse2 + bh_idx * g.n_tokens, (uint32_t)(g.n_tokens * 4));
-    const i32x4 d_rsrc = buffer_desc(delta + bh_idx * g.n_tokens, (uint32_t)(g.n_tokens * 4));
-
-    // items of a round: (connected query block e, sub-tile ct), e-major
-    auto issue_item = [&](int item, int buf) {
-        const int e = item / subs, ct = item - e * subs;
-        const uint32_t o = origin_of(list_s[e]) + (uint32_t)(sub_tile_first(g, ct) * (D * 2));
-        io.gather(q_rsrc, o, q_lds[buf]);
-        io.gather(g_rsrc, o, g_lds[buf]);
-        if (wave == 0) io.gather_f32(l_rsrc, o / (uint32_t)(D * 2), l_lds[buf]);
-        if (wave == NW - 1) io.gather_f32(d_rsrc, o / (uint32_t)(D * 2), d_lds[buf]);
-    };
-
-    for (int i0 = 0; i0 < m; i0 += SCAN) {
-        // ---- which of the query blocks i0 .. i0+SCAN-1 attend to block j?  One
-        // bit each in the connection map; ascending order, so the summation
-        // order below is fixed
-        const int i_mine = i0 + (int)threadIdx.x;
-        const bool hit = i_mine < m && ((conn_col[(int64_t)(i_mine >> 5) * m] >> (i_mine & 31)) & 1u) != 0;
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
-        __syncthreads();                      // previous round's list and tiles fully consumed
-        if (lane == 0) wave_cnt[wave] = __builtin_popcountll(mask);
-        __syncthreads();
-        int offset = 0, total = 0;
-        for (int w = 0; w < NW; ++w) {
-            if (w < wave) offset += wave_cnt[w];
-            total += wave_cnt[w];
-        }
-        if (hit) list_s[offset + __builtin_popcountll(mask & ((1ull << lane) - 1))] = i_mine;
-        __syncthreads();
-
-        const int items = total * subs;
-        if (items > 0) issue_item(0, 0);
-        for (int it = 0; it < items; ++it) {
-            // item `it` has landed and everyone is done with the other buffers
-            wait_gathers();
-            __syncthreads();
-            if (it + 1 < items) issue_item(it + 1, (it + 1) & 1);
-            const unsigned char* qt_lds = q_lds[it & 1];
-            const unsigned char* gt_lds = g_lds[it & 1];
-            const float* lt = l_lds[it & 1];
-            const float* dtl = d_lds[it & 1];
-#pragma unroll
-            for (int qt = 0; qt < 2; ++qt) {
-                // S = Q K^T: rows = queries 32 qt .., this lane's column = its key
-                f32x16 s = zero_tile();
-                matrix_phase<D>(true);
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        row_frag<D>(qt_lds, 32 * qt, ks, l32, half), kfb[ks], s, 0, 0, 0);
-                matrix_phase<D>(false);
-                // accumulator element r is query row 8 (r/4) + 4 half + r%4 of the tile
-                f32x16 p;
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const float4 l4 = *(const float4*)(lt + 32 * qt + 8 * r4 + 4 * half);
-                    p[4 * r4 + 0] = __builtin_amdgcn_exp2f(fmaf(s[4 * r4 + 0], c2, -l4.x));
-                    p[4 * r4 + 1] = __builtin_amdgcn_exp2f(fmaf(s[4 * r4 + 1], c2, -l4.y));
-                    p[4 * r4 + 2] = __builtin_amdgcn_exp2f(fmaf(s[4 * r4 + 2], c2, -l4.z));
-                    p[4 * r4 + 3] = __builtin_amdgcn_exp2f(fmaf(s[4 * r4 + 3], c2, -l4.w));
-                }
-                if constexpr (DO_DV) {
-                    bf16x8 pb[2];
-                    pack_tile(p, pb);
-                    matrix_phase<D>(true);
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int dt = 0; dt < DT; ++dt)
-                            accv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                trans_frag<D>(gt_lds, 32 * qt + 16 * h, dt, lane), pb[h], accv[dt],
-                                0, 0, 0);
-                }
-                if constexpr (DO_DK) {
-                    // delta - dP: the accumulator starts from delta, one value per
-                    // row, as it lies in LDS
-                    f32x16 ds;
-#pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        const f32x4 d4 = *(const f32x4*)(dtl + 32 * qt + 8 * r4 + 4 * half);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) ds[4 * r4 + r] = d4[r];
-                    }
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-                        ds = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            row_frag<D>(gt_lds, 32 * qt, ks, l32, half), vfb[ks], ds, 0, 0, 0);
-                    matrix_phase<D>(false);
-                    // -dS; the sign goes into the scale of dK
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) ds[r] *= p[r];
-                    bf16x8 dsb[2];
-                    pack_tile(ds, dsb);
-                    matrix_phase<D>(true);
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int dt = 0; dt < DT; ++dt)
-                            acck[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                trans_frag<D>(qt_lds, 32 * qt + 16 * h, dt, lane), dsb[h],
-                                acck[dt], 0, 0, 0);
-                }
-            }
-        }
-    }
-    }
-
-    const float inv_b = 1.0f / (float)g.block_tokens;
-    const int64_t pooled_row = (kv_unit * m + j) * D;
-    const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
-    const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-        if constexpr (DO_DK)
-            store_tile(dk + base + k_tok * D, dt, half, acck[dt], -g.scale, extra_k, inv_b);
-        if constexpr (DO_DV)
-            store_tile(dv + base + k_tok * D, dt, half, accv[dt], 1.0f, extra_v, inv_b);
-    }
-}
-
 // The query blocks connected to key block j, for the query heads of the group that
 // share it: heads in ascending order, blocks in ascending order within each, which
 // fixes the summation order.  An entry is the first token of the block with the head
@@ -1005,6 +793,260 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
     }
 }
 
+// dK and dV in one pass at head dim 128.  Both accumulators take 128 of the 256 registers
+// that two wavefronts per SIMD leave, K 32; V lies in LDS (negated, each wavefront its own
+// 32 rows) and its fragments are read with those of dO.  Tiles of 32 queries, so that two
+// workgroups (blocks of 256: one) fit a CU beside it.  Fragments are read W of them ahead
+// in the order of their use; the exponentials go behind the dP instructions, the products
+// behind those of dV.  Against a pass each for dV and dK, which compute S twice, gather
+// every tile twice and wait 40 % of the time for fragments: 1.5 degrees, batch 4, 16 heads
+// 1.85 + 2.38 -> 3.23 ms, training pass 8.65 -> 7.56; the same bits.
+template <int NW>
+__device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
+                                               const uint16_t* __restrict__ k,
+                                               const uint16_t* __restrict__ v,
+                                               const uint16_t* __restrict__ dout,
+                                               const float* __restrict__ lse2,
+                                               const float* __restrict__ delta,
+                                               const uint32_t* __restrict__ conn,
+                                               const int32_t* __restrict__ order,
+                                               uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
+                                               const Geom& g, uint32_t n_units)
+{
+    constexpr int D = 128, KS = 8, SUBS = NW, ROW = 256, TILE = 32 * ROW, MINE = 8 / NW;
+    // [buffer][Q tile, dO tile]; the buffers alternate by bit 14 of the address
+    __shared__ __attribute__((aligned(32768))) unsigned char tiles_s[2][2][TILE];
+    __shared__ __attribute__((aligned(1024))) float rows_s[2][2][64];     // [buffer][lse2, delta]
+    __shared__ __attribute__((aligned(1024))) unsigned char v_s[NW][TILE];
+    __shared__ ConnectedList list;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int m = g.n_blocks;
+
+    // workgroup -> (key/value slice, key block), see dkdv_d64_body
+    uint32_t unit, r_unit;
+    map_unit(blockIdx.x, (uint32_t)m, n_units, unit, r_unit);
+    const int j = order ? order[(int64_t)unit * m + r_unit] : (int)r_unit;
+    const int64_t base = (int64_t)unit * g.n_tokens * D;
+    int64_t bh_first;
+    {
+        const uint32_t kv_heads = (uint32_t)(g.heads / g.kv_group);
+        const uint32_t e = unit / kv_heads, a = unit - e * kv_heads;
+        bh_first = (int64_t)e * g.heads + (int64_t)a * g.kv_group;
+    }
+    const uint32_t slice_bytes = (uint32_t)(g.n_tokens * D * 2), row_bytes = (uint32_t)(g.n_tokens * 4);
+
+    // gathers: slab wave + NW jj holds tile rows 4 slab .. + 3
+    uint32_t voff[MINE];
+#pragma unroll
+    for (int jj = 0; jj < MINE; ++jj) {
+        const int t = 4 * (wave + NW * jj) + (lane >> 4);
+        voff[jj] = (uint32_t)(sub_tile_pos(g, t) * ROW + swz(t, lane & 15) * 16);
+    }
+    const uint32_t tok_off = (uint32_t)(sub_tile_pos(g, l32) * 4);
+
+    // this wavefront's 32 key rows: K as B operand, -V to LDS
+    bf16x8 kfb[KS];
+    int64_t k_tok;
+    {
+        const int bw_shift = __builtin_ctz((unsigned)g.block_w);
+        const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
+        const int64_t tok0 = (int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w;
+        const int t = 32 * wave + l32;
+        const int rr = t >> bw_shift, cc = t & (g.block_w - 1);
+        k_tok = tok0 + (int64_t)rr * g.grid_w + cc;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            kfb[ks] = *(const bf16x8*)(k + base + k_tok * D + 16 * ks + 8 * half);
+            *(bf16x8*)(v_s[wave] + l32 * ROW + swz(l32, 2 * ks + half) * 16) =
+                negated(*(const bf16x8*)(v + base + k_tok * D + 16 * ks + 8 * half));
+        }
+    }
+    const float c2 = g.scale * kLog2e;
+
+    f32x16 acck[4], accv[4];
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) acck[dt] = accv[dt] = zero_tile();
+
+    // addresses of this lane's fragments (row_frag, trans_frag) in the buffer that is
+    // read next, and of its V rows; everything else is a constant
+    uint32_t row_at[4], v_at[4], tr_at[2], val_at;
+    {
+        const uint32_t t0 = lds_address(tiles_s), v0 = lds_address(v_s[0]) + (uint32_t)wave * TILE;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const uint32_t at = (uint32_t)(l32 * ROW + swz(l32, 2 * ks + half) * 16);
+            row_at[ks] = t0 + at;
+            v_at[ks] = v0 + at;
+        }
+        const int s16 = lane & 15, gq = lane >> 4, r = 4 * (gq >> 1) + (s16 >> 2);
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) {
+            const int col = 16 * (gq & 1) + 4 * (s16 & 3) + 32 * dt;
+            tr_at[dt] = t0 + (uint32_t)(r * ROW + swz(r, col >> 3) * 16 + (col & 7) * 2);
+        }
+        val_at = lds_address(rows_s) + 16u * (uint32_t)half;
+    }
+    // fragment `i` of a tile in the order in which the matrix instructions take them:
+    // 0-7 Q rows (S), 8-23 dO rows and V in turn (dP), 24-31 dO transposed (dV),
+    // 32-39 Q transposed (dK)
+    auto read_frag = [&](int i) -> bf16x8 {
+        if (i < 24) {
+            const int ks = i < 8 ? i : (i - 8) >> 1, imm = (ks >> 2) * 128;
+            if (i >= 8 && (i & 1)) return lds_read<bf16x8>(v_at[ks & 3], imm);
+            return lds_read<bf16x8>(row_at[ks & 3], imm + (i >= 8 ? TILE : 0));
+        }
+        const int is_g = i < 32, h = (i >> 2) & 1, dt = i & 3;
+        bf16x4 part[2];
+#pragma unroll
+        for (int rd = 0; rd < 2; ++rd)
+            part[rd] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                (__attribute__((address_space(3))) bf16x4*)(uintptr_t)(
+                    tr_at[dt & 1] +
+                    (uint32_t)(is_g * TILE + (16 * h + 8 * rd) * ROW + (dt >> 1) * 128)));
+        return __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+
+    int next_word = 0;                                // wavefront 0 only
+    for (;;) {
+        __syncthreads();                              // the previous list is used up
+        if (wave == 0) next_word = fill_list(list, g, conn, bh_first, j, next_word, lane);
+        __syncthreads();
+        const int items = __builtin_amdgcn_readfirstlane(list.count) * SUBS;
+        const bool more = __builtin_amdgcn_readfirstlane(list.more) != 0;
+        const int64_t bh0 = bh_first + __builtin_amdgcn_readfirstlane(list.head_base);
+
+        auto entry_of = [&](int item) -> uint32_t { return list.entry[min(item, items - 1) / SUBS]; };
+        auto issue_item = [&](int item, uint32_t entry, int buf) {
+            const uint64_t bh = (uint64_t)(bh0 + (entry >> 24));
+            const int ct = item % SUBS;
+            const uint32_t tok = (entry & 0xffffffu) + (uint32_t)sub_tile_first(g, ct >> 1) +
+                                 (uint32_t)((ct & 1) * sub_tile_pos(g, 32));
+            const i32x4 q_rsrc = buffer_desc((const char*)q + bh * slice_bytes, slice_bytes);
+            const i32x4 g_rsrc = buffer_desc((const char*)dout + bh * slice_bytes, slice_bytes);
+            const uint32_t q_dst = lds_address(tiles_s[buf][0]), g_dst = lds_address(tiles_s[buf][1]);
+#pragma unroll
+            for (int jj = 0; jj < MINE; ++jj) {
+                load_lds_16(q_rsrc, voff[jj], tok * ROW, q_dst + (uint32_t)(wave + NW * jj) * 1024u);
+                load_lds_16(g_rsrc, voff[jj], tok * ROW, g_dst + (uint32_t)(wave + NW * jj) * 1024u);
+            }
+            if (wave == 0)
+                load_lds_4(buffer_desc((const char*)lse2 + bh * row_bytes, row_bytes), tok_off,
+                           tok * 4u, lds_address(rows_s[buf][0]));
+            if (wave == NW - 1)
+                load_lds_4(buffer_desc((const char*)delta + bh * row_bytes, row_bytes), tok_off,
+                           tok * 4u, lds_address(rows_s[buf][1]));
+        };
+        if (items > 0) {
+            uint32_t entry = __builtin_amdgcn_readfirstlane(entry_of(0));
+            issue_item(0, entry, 0);
+            entry = __builtin_amdgcn_readfirstlane(entry_of(1));
+            // tile 0 of a list lies in buffer 0
+            const uint32_t flip = row_at[0] & 16384u;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) row_at[ks] -= flip;
+            tr_at[0] -= flip; tr_at[1] -= flip;
+            val_at -= flip >> 5;
+            for (int it = 0; it < items; ++it) {
+                // item `it` has landed and everyone is done with the other buffers
+                wait_gathers();
+                __syncthreads();
+                if (it + 1 < items) issue_item(it + 1, entry, (it + 1) & 1);
+                const uint32_t entry_v = entry_of(it + 2);
+
+                constexpr int W = 6;                  // fragments read ahead
+                bf16x8 f[W];
+                f32x16 s = zero_tile(), dp;
+                f32x4 l4[2];
+                uint32_t pw[8], dw[8];
+                float fm[2][2];
+#pragma unroll
+                for (int i = 0; i < W; ++i) f[i] = read_frag(i);
+                __builtin_amdgcn_sched_barrier(0);
+                // the fragment that a slot's instruction has taken makes room for the one W
+                // further on
+                auto ask = [&](int i) {
+                    if (i + W < 40) f[i % W] = read_frag(i + W);
+                };
+                auto operand = [](const uint32_t(&w)[8], int h) {
+                    return __builtin_bit_cast(
+                        bf16x8, make_uint4(w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]));
+                };
+#pragma unroll
+                for (int t = 0; t < 32; ++t) {
+                    const int i = t & 7, h = i >> 2, dt = i & 3;
+                    if (t < 8) {
+                        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % W], kfb[i], s, 0, 0, 0);
+                        ask(i);
+                    } else if (t < 16) {
+                        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            f[(8 + 2 * i) % W], f[(9 + 2 * i) % W], dp, 0, 0, 0);
+                        ask(8 + 2 * i);
+                        ask(9 + 2 * i);
+                    } else if (t < 24) {
+                        accv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            f[(24 + i) % W], operand(pw, h), accv[dt], 0, 0, 0);
+                        ask(24 + i);
+                    } else {
+                        acck[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            f[(32 + i) % W], operand(dw, h), acck[dt], 0, 0, 0);
+                        ask(32 + i);
+                    }
+                    // delta - dP: the accumulator starts from delta, one value per row, as
+                    // it lies in LDS (element r is query row 8 (r/4) + 4 half + r%4)
+                    if (t >= 2 && t < 6) {
+                        const f32x4 d4 = lds_read<f32x4>(val_at, 256 + 32 * (t - 2));
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) dp[4 * (t - 2) + r] = d4[r];
+                    }
+                    if (t == 6 || t == 7) l4[t - 6] = lds_read<f32x4>(val_at, 32 * (t - 6));
+                    // two weights: the fma in slot 9 + e/2, the exponentials (and P) a slot
+                    // later, the products (-dS; the sign goes into the scale of dK) behind
+                    // dV and the first of dK
+                    if (t >= 10 && t < 18) {
+                        const int e = 2 * (t - 10);
+                        s[e] = __builtin_amdgcn_exp2f(fm[t & 1][0]);
+                        s[e + 1] = __builtin_amdgcn_exp2f(fm[t & 1][1]);
+                        pw[e >> 1] = pack_bf16(s[e], s[e + 1]);
+                        asm volatile("" : "+v"(pw[e >> 1]));
+                    }
+                    if (t >= 9 && t < 17) {
+                        const int e = 2 * (t - 9);
+                        fm[(t + 1) & 1][0] = fmaf(s[e], c2, -l4[(e >> 2) & 1][e & 3]);
+                        fm[(t + 1) & 1][1] = fmaf(s[e + 1], c2, -l4[(e >> 2) & 1][(e & 3) + 1]);
+                        asm volatile("" : "+v"(fm[(t + 1) & 1][0]), "+v"(fm[(t + 1) & 1][1]));
+                    }
+                    if (t == 10 || t == 12) l4[(t - 10) >> 1] = lds_read<f32x4>(val_at, 64 + 16 * (t - 10));
+                    if (t >= 18 && t < 26) {
+                        const int e = 2 * (t - 18);
+                        dw[e >> 1] = pack_bf16(s[e] * dp[e], s[e + 1] * dp[e + 1]);
+                        asm volatile("" : "+v"(dw[e >> 1]));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                entry = __builtin_amdgcn_readfirstlane(entry_v);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) row_at[ks] ^= 16384u;
+                tr_at[0] ^= 16384u; tr_at[1] ^= 16384u;
+                val_at ^= 512u;
+            }
+        }
+        if (!more) break;
+    }
+
+    const float inv_b = 1.0f / (float)g.block_tokens;
+    const int64_t pooled_row = ((int64_t)unit * m + j) * D;
+    const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
+    const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) {
+        store_tile(dk + base + k_tok * D, dt, half, acck[dt], -g.scale, extra_k, inv_b);
+        store_tile(dv + base + k_tok * D, dt, half, accv[dt], 1.0f, extra_v, inv_b);
+    }
+}
+
 }  // namespace bwdm
 
 // plain kernels per (head dim, wavefronts per workgroup); the bodies are templates
@@ -1016,45 +1058,26 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
     {                                                                                             \
         bwdm::dq_body<D, NW>(q, k, v, dout, lse2, delta, sel_idx, dq, g, n_units);             \
     }
-#define BSA_BWD_TWO_PASSES(D, NW)                                                                 \
-    __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dv_d##D##_w##NW(                       \
-        const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dout,            \
-        const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order, uint16_t* dk, \
-        uint16_t* dv, Geom g, uint32_t n_units)                                                 \
-    {                                                                                             \
-        bwdm::dkdv_body<D, NW, bwdm::PASS_DV>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g,        \
-                                              n_units);                                        \
-    }                                                                                             \
-    __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dk_d##D##_w##NW(                       \
-        const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dout,            \
-        const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order, uint16_t* dk, \
-        uint16_t* dv, Geom g, uint32_t n_units)                                                 \
-    {                                                                                             \
-        bwdm::dkdv_body<D, NW, bwdm::PASS_DK>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g,        \
-                                              n_units);                                        \
-    }
 BSA_BWD_DQ(64, 2)
 BSA_BWD_DQ(64, 4)
 BSA_BWD_DQ(64, 8)
 BSA_BWD_DQ(128, 4)
 BSA_BWD_DQ(128, 8)
-// head dim 64: both accumulators fit, dK and dV in one pass
-#define BSA_BWD_FUSED(NW)                                                                         \
-    __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dkdv_d64_w##NW(                        \
+#define BSA_BWD_DKDV(D, NW)                                                                       \
+    __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dkdv_d##D##_w##NW(                     \
         const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dout,            \
-        const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order, uint16_t* dk, \
-        uint16_t* dv, Geom g, uint32_t n_units)                                                 \
+        const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order,        \
+        uint16_t* dk, uint16_t* dv, Geom g, uint32_t n_units)                                     \
     {                                                                                             \
-        bwdm::dkdv_d64_body<NW>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g, n_units);      \
+        bwdm::dkdv_d##D##_body<NW>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g, n_units);  \
     }
-BSA_BWD_FUSED(2)
-BSA_BWD_FUSED(4)
-BSA_BWD_FUSED(8)
-#undef BSA_BWD_FUSED
-BSA_BWD_TWO_PASSES(128, 4)
-BSA_BWD_TWO_PASSES(128, 8)
+BSA_BWD_DKDV(64, 2)
+BSA_BWD_DKDV(64, 4)
+BSA_BWD_DKDV(64, 8)
+BSA_BWD_DKDV(128, 4)
+BSA_BWD_DKDV(128, 8)
 #undef BSA_BWD_DQ
-#undef BSA_BWD_TWO_PASSES
+#undef BSA_BWD_DKDV
 
 bool bwd_mfma_supported(bool is_bf16, const Geom& g, int D)
 {
@@ -1093,25 +1116,16 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
                                            sel_idx, (uint16_t*)dq, g, sx);
         return hipGetLastError();
     };
-    // `order` may lie where dQ goes; without it dK and dV may lie where k and v are (head
-    // dim 128: only dK, its pass still reads v)
+    // `order` may lie where dQ goes; without it dK and dV may lie where k and v are
 #define BSA_LAUNCH(D_, NW_)                                                                       \
     if (D == D_ && nw == NW_) {                                                                   \
         if (!order && (e = run_dq(bwd_mfma_dq_d##D_##_w##NW_)) != hipSuccess) return e;           \
-        if ((e = run_dkdv(bwd_mfma_dv_d##D_##_w##NW_)) != hipSuccess) return e;                   \
-        if ((e = run_dkdv(bwd_mfma_dk_d##D_##_w##NW_)) != hipSuccess) return e;                   \
+        if ((e = run_dkdv(bwd_mfma_dkdv_d##D_##_w##NW_)) != hipSuccess) return e;                 \
         return order ? run_dq(bwd_mfma_dq_d##D_##_w##NW_) : hipSuccess;                           \
     }
-#define BSA_LAUNCH_FUSED(NW_)                                                                     \
-    if (D == 64 && nw == NW_) {                                                                   \
-        if (!order && (e = run_dq(bwd_mfma_dq_d64_w##NW_)) != hipSuccess) return e;               \
-        if ((e = run_dkdv(bwd_mfma_dkdv_d64_w##NW_)) != hipSuccess) return e;                     \
-        return order ? run_dq(bwd_mfma_dq_d64_w##NW_) : hipSuccess;                               \
-    }
-    BSA_LAUNCH_FUSED(2)
-    BSA_LAUNCH_FUSED(4)
-    BSA_LAUNCH_FUSED(8)
-#undef BSA_LAUNCH_FUSED
+    BSA_LAUNCH(64, 2)
+    BSA_LAUNCH(64, 4)
+    BSA_LAUNCH(64, 8)
     BSA_LAUNCH(128, 4)
     BSA_LAUNCH(128, 8)
 #undef BSA_LAUNCH
