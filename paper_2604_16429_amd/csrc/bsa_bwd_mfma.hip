@@ -43,6 +43,8 @@
 // part, so the 32 instructions per 32 x 32 tile count: select + forward + backward at
 // 1.5 degrees, head dim 128, batch 4: 8.97 -> 8.79 ms; grouped heads at head dim 64,
 // batch 12: 8.99 -> 8.84 ms.
+#include <type_traits>
+
 #include "bsa_device.h"
 #include "bsa_launch.h"
 #include "bsa_mfma_common.h"
@@ -193,21 +195,6 @@ __device__ __forceinline__ f32x16 zero_tile()
     return z;
 }
 
-// dQ at head dim 128, where a phase of matrix instructions is long (8 to 16 of them) and
-// nothing of the other phases is interleaved with it: the wavefront that is in such a
-// phase issues first, so that the two wavefronts of a SIMD drift apart and one's vector
-// work falls behind the other's matrix instructions.  Select + forward + backward,
-// 1.5 degrees, batch 4, 16 heads: 9.11 -> 8.92 ms (with dK/dV kernels of the same form).
-// The priority stays up through the wait for the next tile (lowered 8.54 -> 8.55 ms).
-template <int D>
-__device__ __forceinline__ void matrix_phase(bool begin)
-{
-    if constexpr (D == 128) {
-        if (begin) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------
@@ -224,8 +211,8 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
 {
     constexpr int KS = D / 16, DT = D / 32;
     using IO = TileIO<D, NW>;
-    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][IO::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_lds[2][IO::TILE_BYTES];
+    // [buffer][K tile, V tile]
+    __shared__ __attribute__((aligned(4 * IO::TILE_BYTES))) unsigned char tiles_s[2][2][IO::TILE_BYTES];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -267,8 +254,8 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
         return origin_of(beta) + (uint32_t)(sub_tile_first(g, ct) * (D * 2));
     };
 
-    io.gather(k_rsrc, origin_of_pair(0), k_lds[0]);
-    io.gather(v_rsrc, origin_of_pair(0), v_lds[0]);
+    io.gather(k_rsrc, origin_of_pair(0), tiles_s[0][0]);
+    io.gather(v_rsrc, origin_of_pair(0), tiles_s[0][1]);
 
     // this wavefront's 32 query rows: Q and dO as B operands, lse and delta of
     // the lane's query column
@@ -344,11 +331,11 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
             __syncthreads();
             if (c + 1 < pairs) {
                 const uint32_t o = origin_of_pair(c + 1);
-                io.gather(k_rsrc, o, k_lds[(c + 1) & 1]);
-                io.gather(v_rsrc, o, v_lds[(c + 1) & 1]);
+                io.gather(k_rsrc, o, tiles_s[(c + 1) & 1][0]);
+                io.gather(v_rsrc, o, tiles_s[(c + 1) & 1][1]);
             }
-            const unsigned char* kt_lds = k_lds[c & 1];
-            const unsigned char* vt_lds = v_lds[c & 1];
+            const unsigned char* kt_lds = tiles_s[c & 1][0];
+            const unsigned char* vt_lds = tiles_s[c & 1][1];
             bf16x8 kf[KS], vf[KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -435,48 +422,116 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
                 acc[k & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[k >> 1][k & 1], dsb[k >> 1],
                                                                      acc[k & 1], 0, 0, 0);
         }
-    } else
-    for (int c = 0; c < pairs; ++c) {
-        // tile c has landed (own loads, then everyone's) and everyone is done
-        // with the other buffer: refill it with tile c + 1
-        wait_gathers();
-        __syncthreads();
-        if (c + 1 < pairs) {
-            const uint32_t o = origin_of_pair(c + 1);
-            io.gather(k_rsrc, o, k_lds[(c + 1) & 1]);
-            io.gather(v_rsrc, o, v_lds[(c + 1) & 1]);
-        }
-        const unsigned char* kt_lds = k_lds[c & 1];
-        const unsigned char* vt_lds = v_lds[c & 1];
+    } else {
+        // Head dim 128.  Per tile of 64 keys, S0 and dP0 of its first half, then S1, dP1,
+        // dQ^T += K^T dS^T of half 0 and of half 1, eight matrix instructions each; behind
+        // dP0 and dP1 go the exponentials of their half, behind S1 and the first dQ the
+        // products.  Fragments are read W instructions ahead.  Against fragments read right
+        // before their use and all vector work between the phases (35 % of the wavefronts'
+        // cycles were waits): 1.5 degrees, batch 4, 16 heads 2.19 -> 2.03 ms.
+        constexpr int ROW = 256, TILE = IO::TILE_BYTES, W = 8;
+        uint32_t row_at[4], tr_at[2];
+        {
+            const uint32_t t0 = lds_address(tiles_s);
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            f32x16 s = zero_tile(), dp = neg_dl;
-            matrix_phase<D>(true);
+            for (int ks = 0; ks < 4; ++ks)
+                row_at[ks] = t0 + (uint32_t)(l32 * ROW + swz(l32, 2 * ks + half) * 16);
+            const int s16 = lane & 15, gq = lane >> 4, r = 4 * (gq >> 1) + (s16 >> 2);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    row_frag<D>(kt_lds, 32 * kt, ks, l32, half), qf[ks], s, 0, 0, 0);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    row_frag<D>(vt_lds, 32 * kt, ks, l32, half), dof[ks], dp, 0, 0, 0);
-            matrix_phase<D>(false);
-            f32x16 ds;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(s[r], c2, neg_l2));
-                ds[r] = p * dp[r];
+            for (int dt = 0; dt < 2; ++dt) {
+                const int col = 16 * (gq & 1) + 4 * (s16 & 3) + 32 * dt;
+                tr_at[dt] = t0 + (uint32_t)(r * ROW + swz(r, col >> 3) * 16 + (col & 7) * 2);
             }
-            bf16x8 dsb[2];
-            pack_tile(ds, dsb);
-            matrix_phase<D>(true);
+        }
+        // fragment `i` of a tile: K rows, V rows of half 0 (8 each), the same of half 1,
+        // K transposed of half 0, of half 1
+        auto read_frag = [&](int i) -> bf16x8 {
+            const int u = i & 7;
+            if (i < 32)
+                return lds_read<bf16x8>(row_at[u & 3], ((i >> 3) & 1) * TILE + (i >> 4) * 32 * ROW +
+                                                           (u >> 2) * 128);
+            const int dt = u & 3, row0 = (i >= 40 ? 32 : 0) + 16 * (u >> 2);
+            bf16x4 part[2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int rd = 0; rd < 2; ++rd)
+                part[rd] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                    (__attribute__((address_space(3))) bf16x4*)(uintptr_t)(
+                        tr_at[dt & 1] + (uint32_t)((row0 + 8 * rd) * ROW + (dt >> 1) * 128)));
+            return __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        uint32_t o_next = pairs > 1 ? origin_of_pair(1) : 0u;
+        for (int c = 0; c < pairs; ++c) {
+            // tile c has landed (own loads, then everyone's) and everyone is done
+            // with the other buffer: refill it with tile c + 1
+            wait_gathers();
+            __syncthreads();
+            if (c + 1 < pairs) {
+                io.gather(k_rsrc, o_next, tiles_s[(c + 1) & 1][0]);
+                io.gather(v_rsrc, o_next, tiles_s[(c + 1) & 1][1]);
+            }
+            bf16x8 f[W];
+            f32x16 s[2], dp[2];
+            uint32_t w[2][8];
+            float fm[2][2];
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
-                    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        trans_frag<D>(kt_lds, 32 * kt + 16 * h, dt, lane), dsb[h], acc[dt], 0, 0,
-                        0);
+            for (int i = 0; i < W; ++i) f[i] = read_frag(i);
+            s[0] = zero_tile();
+            s[1] = zero_tile();
+            __builtin_amdgcn_sched_barrier(0);
+            auto group = [&](auto g_tag) {
+            constexpr int G = decltype(g_tag)::value, hh = (G >> 1) & 1;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int t = 8 * G + u;
+                if (G < 4 && (G & 1) == 0)
+                    s[hh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[t % W], qf[u], s[hh], 0, 0, 0);
+                else if (G < 4)
+                    dp[hh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        f[t % W], dof[u], u == 0 ? neg_dl : dp[hh], 0, 0, 0);
+                else {
+                    const uint32_t(&x)[8] = w[G & 1];
+                    const int h = u >> 2;
+                    acc[u & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        f[t % W],
+                        __builtin_bit_cast(bf16x8, make_uint4(x[4 * h], x[4 * h + 1], x[4 * h + 2],
+                                                              x[4 * h + 3])),
+                        acc[u & 3], 0, 0, 0);
+                }
+                if (t + W < 48) f[t % W] = read_frag(t + W);
+                // two weights per slot: fma in slot 9 + 16 hh + e/2, the exponentials a slot
+                // later, products and packs eight slots after that
+                {
+                    const int x = t >= 25 ? 1 : 0, e = 2 * (t - 9 - 16 * x);
+                    if (e >= 2 && e < 18) {
+                        s[x][e - 2] = __builtin_amdgcn_exp2f(fm[t & 1][0]);
+                        s[x][e - 1] = __builtin_amdgcn_exp2f(fm[t & 1][1]);
+                    }
+                    if (e >= 0 && e < 16) {
+                        fm[(t + 1) & 1][0] = fmaf(s[x][e], c2, neg_l2);
+                        fm[(t + 1) & 1][1] = fmaf(s[x][e + 1], c2, neg_l2);
+                        asm volatile("" : "+v"(fm[(t + 1) & 1][0]), "+v"(fm[(t + 1) & 1][1]));
+                    }
+                }
+                {
+                    const int x = t >= 34 ? 1 : 0, e = 2 * (t - 18 - 16 * x);
+                    if (e >= 0 && e < 16) {
+                        w[x][e >> 1] = pack_bf16(s[x][e] * dp[x][e], s[x][e + 1] * dp[x][e + 1]);
+                        asm volatile("" : "+v"(w[x][e >> 1]));
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            };
+            group(std::integral_constant<int, 0>{});
+            group(std::integral_constant<int, 1>{});
+            group(std::integral_constant<int, 2>{});
+            group(std::integral_constant<int, 3>{});
+            group(std::integral_constant<int, 4>{});
+            group(std::integral_constant<int, 5>{});
+            o_next = c + 2 < pairs ? origin_of_pair(c + 2) : 0u;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) row_at[ks] ^= 2u * TILE;
+            tr_at[0] ^= 2u * TILE; tr_at[1] ^= 2u * TILE;
         }
     }
 
