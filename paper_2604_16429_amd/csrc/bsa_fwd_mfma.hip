@@ -593,26 +593,41 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
             oacc[dt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][2 + h], p[1][h],
                                                                   oacc[dt][1], 0, 0, 0);
 
-    // ---- normalise, store O rows (4 consecutive channels per store)
+    // ---- normalise; O rows go through LDS (the tiles are used up), so that a store
+    // instruction writes 1 KiB runs instead of 8 bytes of 64 places (see store_rows): 64
+    // rows of 128 bytes per wavefront, swizzled like the tiles
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // gathers of pairs past the end
+    wg_barrier();
+    unsigned char* const o_lds =
+        NW == 1 ? nullptr : NW == 2 ? (wave == 0 ? x_a[0] : x_b[0])
+                                    : wave == 0 ? x_a[0] : wave == 1 ? y_a[0] : wave == 2 ? x_b[0] : y_b[0];
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
         const float l_tot = l_run[nt] + swap32(l_run[nt]);
         const float inv_l = 1.0f / l_tot;
-        uint16_t* orow = out + q_tok[nt] * D;
+        unsigned char* const half_lds = NW == 1 ? (nt == 0 ? x_a[0] : y_a[0]) : o_lds + nt * 4096;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                const int d = 32 * dt + 8 * r4 + 4 * half;
                 uint2 w;
                 w.x = pack_bf16(oacc[dt][nt][4 * r4] * inv_l, oacc[dt][nt][4 * r4 + 1] * inv_l);
                 w.y = pack_bf16(oacc[dt][nt][4 * r4 + 2] * inv_l,
                                 oacc[dt][nt][4 * r4 + 3] * inv_l);
-                *(uint2*)(orow + d) = w;
+                *(uint2*)(half_lds + l32 * 128 + swz(l32, 4 * dt + r4) * 16 + 8 * half) = w;
             }
         if (lse && half == 0)
             lse[bh_idx * g.n_tokens + q_tok[nt]] =
                 (m_ref[nt] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
+    }
+    out += (origin_of(i) >> 1) + (uint32_t)(sub_tile_first(g, qsub) * D);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const unsigned char* const half_lds =
+            NW == 1 ? (j < 4 ? x_a[0] : y_a[0]) : o_lds + (j >> 2) * 4096;
+        const int t = 8 * j + (lane >> 3);
+        *(uint4*)(out + sub_tile_pos(g, t) * D + swz(t, lane & 7) * 8) =
+            *(const uint4*)(half_lds + (j & 3) * 1024 + lane * 16);
     }
 }
 

@@ -458,21 +458,17 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
             oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][h], p[1][h], oacc[dt], 0, 0,
                                                                0);
 
-    // ---- normalise, store O rows (4 consecutive channels per store)
+    // ---- normalise, store O rows (through the LDS of the tiles, which are used up)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // gathers of pairs past the end
+    __builtin_amdgcn_s_barrier();
     {
         const float l_tot = l_run + swap32(l_run);
         const float inv_l = 1.0f / l_tot;
-        uint16_t* orow = out + q_tok * D;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int d = 32 * dt + 8 * r4 + 4 * half;
-                uint2 w;
-                w.x = pack_bf16(oacc[dt][4 * r4] * inv_l, oacc[dt][4 * r4 + 1] * inv_l);
-                w.y = pack_bf16(oacc[dt][4 * r4 + 2] * inv_l, oacc[dt][4 * r4 + 3] * inv_l);
-                *(uint2*)(orow + d) = w;
-            }
+        static_assert(HALF_BYTES == 8192 && NW <= 8, "4 KiB per wavefront in four half tiles");
+        unsigned char* const lds = (wave >> 1) == 0 ? k_lds0 : (wave >> 1) == 1 ? k_lds1
+                                   : (wave >> 1) == 2 ? v_lds0 : v_lds1;
+        store_rows<D>(out + (origin_of(i) >> 1), g, 32 * wave, oacc, inv_l, lds + (wave & 1) * 4096,
+                      lane);
         if (lse && half == 0)
             lse[bh_idx * g.n_tokens + q_tok] =
                 (m_ref + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
