@@ -160,34 +160,6 @@ __device__ __forceinline__ void pack_tile(const f32x16& x, bf16x8 (&b)[2])
                                pack_bf16(x[8 * h + 6], x[8 * h + 7])));
 }
 
-// Store one accumulator tile (rows = channels 32 dt .., this lane's column =
-// one token row) scaled by f: 4 consecutive channels per 8-byte store.  With
-// `extra` (fp32 row of D channels) the tile is added to what the row holds,
-// together with extra * inv_b (without: store_rows).
-__device__ __forceinline__ void store_tile(uint16_t* row_ptr, int dt, int half, const f32x16& a,
-                                           float f, const float* extra = nullptr,
-                                           float inv_b = 0.0f)
-{
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-        const int d = 32 * dt + 8 * r4 + 4 * half;
-        float x0 = a[4 * r4] * f, x1 = a[4 * r4 + 1] * f, x2 = a[4 * r4 + 2] * f,
-              x3 = a[4 * r4 + 3] * f;
-        if (extra) {
-            const uint2 old = *(const uint2*)(row_ptr + d);
-            const float4 e = *(const float4*)(extra + d);
-            x0 += __uint_as_float(old.x << 16) + e.x * inv_b;
-            x1 += __uint_as_float(old.x & 0xffff0000u) + e.y * inv_b;
-            x2 += __uint_as_float(old.y << 16) + e.z * inv_b;
-            x3 += __uint_as_float(old.y & 0xffff0000u) + e.w * inv_b;
-        }
-        uint2 w;
-        w.x = pack_bf16(x0, x1);
-        w.y = pack_bf16(x2, x3);
-        *(uint2*)(row_ptr + d) = w;
-    }
-}
-
 __device__ __forceinline__ f32x16 zero_tile()
 {
     const f32x16 z = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
@@ -535,17 +507,13 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
         }
     }
 
-    uint16_t* row_ptr = dq + base + q_tok * D;
     const float inv_b = 1.0f / (float)g.block_tokens;
     const float* extra = g.add_dq ? g.add_dq + (bh_idx * g.n_blocks + i) * D : nullptr;
-    if (extra) {
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) store_tile(row_ptr, dt, half, acc[dt], g.scale, extra, inv_b);
-        return;
-    }
     __syncthreads();                                  // the tiles are used up
-    store_rows<D>(dq + base + (origin_of(i) >> 1), g, 32 * wave, acc, g.scale,
-                  &tiles_s[0][0][0] + wave * 4096, lane);
+    unsigned char* const lds = &tiles_s[0][0][0] + wave * 4096;
+    uint16_t* const block = dq + base + (origin_of(i) >> 1);
+    if (extra) add_rows<D>(block, g, 32 * wave, acc, g.scale, extra, inv_b, lds, lane);
+    else store_rows<D>(block, g, 32 * wave, acc, g.scale, lds, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -847,21 +815,15 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
     const int64_t pooled_row = ((int64_t)unit * m + j) * D;
     const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
     const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
-    if (extra_k || extra_v) {
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt) {
-            store_tile(dk + base + k_tok * D, dt, half, acck[dt], -g.scale, extra_k, inv_b);
-            store_tile(dv + base + k_tok * D, dt, half, accv[dt], 1.0f, extra_v, inv_b);
-        }
-        return;
-    }
     __syncthreads();                                  // the tiles are used up
     unsigned char* const lds = &tiles_s[0][0][0] + wave * 4096;
     const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
     const int64_t block =
         base + ((int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w) * D;
-    store_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, lds, lane);
-    store_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, lds, lane);
+    if (extra_k) add_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, extra_k, inv_b, lds, lane);
+    else store_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, lds, lane);
+    if (extra_v) add_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, extra_v, inv_b, lds, lane);
+    else store_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, lds, lane);
 }
 
 // dK and dV in one pass at head dim 128.  Both accumulators take 128 of the 256 registers
@@ -1111,21 +1073,15 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
     const int64_t pooled_row = ((int64_t)unit * m + j) * D;
     const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
     const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
-    if (extra_k || extra_v) {
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-            store_tile(dk + base + k_tok * D, dt, half, acck[dt], -g.scale, extra_k, inv_b);
-            store_tile(dv + base + k_tok * D, dt, half, accv[dt], 1.0f, extra_v, inv_b);
-        }
-        return;
-    }
     __syncthreads();                                  // the tiles are used up
     unsigned char* const lds = &tiles_s[0][0][0] + wave * 4096;
     const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
     const int64_t block =
         base + ((int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w) * D;
-    store_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, lds, lane);
-    store_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, lds, lane);
+    if (extra_k) add_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, extra_k, inv_b, lds, lane);
+    else store_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, lds, lane);
+    if (extra_v) add_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, extra_v, inv_b, lds, lane);
+    else store_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, lds, lane);
 }
 
 }  // namespace bwdm

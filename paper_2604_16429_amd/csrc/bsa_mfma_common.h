@@ -160,4 +160,54 @@ __device__ __forceinline__ void store_rows(uint16_t* block, const Geom& g, int p
     }
 }
 
+
+// The same, added to what the rows hold together with extra * inv_b (extra: fp32, D
+// channels).  32 channels at a time, which fp32 takes the same 4 KiB for.
+template <int D>
+__device__ __forceinline__ void add_rows(uint16_t* block, const Geom& g, int pos0,
+                                         const f32x16 (&acc)[D / 32], float f, const float* extra,
+                                         float inv_b, unsigned char* lds, int lane)
+{
+    const int l32 = lane & 31, half = lane >> 5, part = lane & 3;
+    const int shift = __builtin_ctz((unsigned)g.block_w);
+    auto chunk_of = [](int row, int chunk) {
+        return chunk ^ (((row & 3) << 1) | ((row >> 2) & 1));
+    };
+    uint16_t* row[2];
+    uint4 old[2][D / 32];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int pos = pos0 + 16 * j + (lane >> 2);
+        row[j] = block + ((int64_t)(pos >> shift) * g.grid_w + (pos & (g.block_w - 1))) * D + 8 * part;
+#pragma unroll
+        for (int c = 0; c < D / 32; ++c) old[j][c] = *(const uint4*)(row[j] + 32 * c);
+    }
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c) {
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+            *(float4*)(lds + l32 * 128 + chunk_of(l32, 2 * r4 + half) * 16) =
+                make_float4(acc[c][4 * r4] * f, acc[c][4 * r4 + 1] * f, acc[c][4 * r4 + 2] * f,
+                            acc[c][4 * r4 + 3] * f);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int t = 16 * j + (lane >> 2);
+            const uint32_t o[4] = {old[j][c].x, old[j][c].y, old[j][c].z, old[j][c].w};
+            uint32_t w[4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float4 v = *(const float4*)(lds + t * 128 + chunk_of(t, 2 * part + u) * 16);
+                const float4 e = *(const float4*)(extra + 32 * c + 8 * part + 4 * u);
+                const float x0 = v.x + (__uint_as_float(o[2 * u] << 16) + e.x * inv_b);
+                const float x1 = v.y + (__uint_as_float(o[2 * u] & 0xffff0000u) + e.y * inv_b);
+                const float x2 = v.z + (__uint_as_float(o[2 * u + 1] << 16) + e.z * inv_b);
+                const float x3 = v.w + (__uint_as_float(o[2 * u + 1] & 0xffff0000u) + e.w * inv_b);
+                w[2 * u] = pack_bf16(x0, x1);
+                w[2 * u + 1] = pack_bf16(x2, x3);
+            }
+            *(uint4*)(row[j] + 32 * c) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+}
+
 }  // namespace bsa
