@@ -18,16 +18,19 @@ namespace bsa {
 constexpr int kListTable = 1024;           // listed blocks the LDS table holds
 
 // Entries behind the last listed block that repeat it: rows past the end of the last
-// tile (of kt rows), and of the tile after it, which is looked up but not gathered,
-// then look up like any other row.  They carry no weight.
-__host__ __device__ constexpr int repeated_entries(int kt, int b) { return (2 * kt - 2) / b + 1; }
+// tile (of kt rows), and of the tile after it (split: the last of as many tiles), which is
+// looked up but not gathered, then look up like any other row.  They carry no weight.
+__host__ __device__ constexpr int repeated_entries(int kt, int b, int split = 1)
+{
+    return ((split + 1) * kt - 2) / b + 1;
+}
 
-// LDS of both tables for `listed` attended blocks (at most 8.5 KiB: b <= 1024)
-inline size_t flat_table_bytes(const Geom& g, int listed)
+// LDS of both tables for `listed` attended blocks (at most 9 KiB: b <= 1024)
+inline size_t flat_table_bytes(const Geom& g, int listed, int split = 1)
 {
     return sizeof(uint32_t) *
            (size_t)(g.block_tokens + (listed < kListTable ? listed : kListTable) +
-                    repeated_entries(64, g.block_tokens));
+                    repeated_entries(64, g.block_tokens, split));
 }
 
 // Lane l: 16 bytes from src to LDS lds + 16 l (lds uniform); see load_lds_16.
@@ -530,8 +533,9 @@ __device__ __forceinline__ void gather_rows(const RowSource& ks, const RowSource
 // by the first NL wavefronts of a workgroup: block i itself followed by its
 // selected blocks, or, when the lists stand alone (list_only), exactly the listed
 // blocks.  Up to 63 listed blocks are visited in ascending order (query blocks
-// that run together then sweep the slice's K/V in the same direction).
-template <typename T, int D, int NL>
+// that run together then sweep the slice's K/V in the same direction).  SPLIT: as many
+// groups of wavefronts take the tiles in turn, `wave` counts inside a group.
+template <typename T, int D, int NL, int SPLIT = 1>
 struct AttendedKeys {
     using Tile = FlatTile<T, D>;
     static constexpr int MINE = Tile::SLABS / NL;
@@ -548,7 +552,8 @@ struct AttendedKeys {
 
     // Fills the LDS tables (flat_table_bytes); a barrier has to follow.
     __device__ __forceinline__ void init(const Geom& g, const int32_t* sel_idx, int64_t bh_idx,
-                                         int i, uint32_t* tables_s, int lane, int wave_)
+                                         int i, uint32_t* tables_s, int lane, int wave_,
+                                         int group = 0)
     {
         wave = wave_;
         b = g.block_tokens;
@@ -561,7 +566,7 @@ struct AttendedKeys {
         const int first = list_only ? sel_row[-1] : i;
         n = g.n_select - list_only;                   // blocks after the first
         fill_position_table(g, pos);
-        const int repeats = repeated_entries(Tile::KT, b);
+        const int repeats = repeated_entries(Tile::KT, b, SPLIT);
         if (n < 64) {
             if (wave == 0) {
                 const int mine = lane < n ? sel_row[lane] : 0x7fffffff;
@@ -591,12 +596,12 @@ struct AttendedKeys {
         geom = &g;
         total = (n + 1) * b;
         tiles = (total + Tile::KT - 1) / Tile::KT;
-        step_q = (uint32_t)(Tile::KT / b);
-        step_r = (uint32_t)(Tile::KT % b);
+        step_q = (uint32_t)(SPLIT * Tile::KT / b);
+        step_r = (uint32_t)(SPLIT * Tile::KT % b);
 #pragma unroll
         for (int j = 0; j < MINE; ++j) {
             const int row = Tile::RPS * (wave + NL * j) + lane / Tile::LPR;
-            at[j].start(row, b);
+            at[j].start(Tile::KT * group + row, b);
             chunk_off[j] = (uint32_t)Tile::swz(row, lane % Tile::LPR) * 16u;
         }
     }
@@ -606,7 +611,7 @@ struct AttendedKeys {
     // end take rows of the last block; they carry no weight.
     __device__ __forceinline__ void look_up()
     {
-        if (n + 1 + repeated_entries(Tile::KT, b) <= kListTable) {
+        if (n + 1 + repeated_entries(Tile::KT, b, SPLIT) <= kListTable) {
 #pragma unroll
             for (int j = 0; j < MINE; ++j) {
                 tok[j] = first_s[at[j].blk] + pos_s[at[j].tau];

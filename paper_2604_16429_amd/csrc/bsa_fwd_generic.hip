@@ -51,8 +51,12 @@ constexpr float kPlainRef = 1048576.0f;
 // NL: wavefronts that issue the gathers (1, 2 or 4; the workgroup has at least
 // that many, up to 8).  row_chunks workgroups share a query block's rows,
 // chunk_rows each.
-template <typename T, int D, int NL>
-__global__ __launch_bounds__(NL == 4 ? 512 : NL == 2 ? 192 : 64, NL == 1 || (NL == 2 && D == 128) ? 1 : D == 32 ? 4 : 2)
+// SPLIT > 1: as many groups of wavefronts (4 at most in each) own the same rows and take
+// the key tiles in turn, with tiles and a softmax of their own; the first group merges them
+// at the end.  For launches that leave the chip idle; see key_split.
+template <typename T, int D, int NL, int SPLIT>
+__global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * (NL == 2 ? 3 : NL) : NL == 4 ? 512 : NL == 2 ? 192 : 64,
+                             SPLIT > 1 || NL == 1 || (NL == 2 && D == 128) ? 1 : D == 32 ? 4 : 2)
 void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                         BSA_FWD_JOB_PARAMS(T), Geom g, uint32_t n_units, int row_chunks, int chunk_rows)
 {
@@ -66,12 +70,14 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     g.list_only = jobs.list_only[second_job ? 1 : 0];
     using Tile = FlatTile<T, D>;
     constexpr int KT = Tile::KT;
-    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][Tile::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_lds[2][Tile::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[SPLIT][2][Tile::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_lds[SPLIT][2][Tile::TILE_BYTES];
     extern __shared__ __attribute__((aligned(16))) uint32_t tables_s[];
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = SPLIT == 1 ? 0 : (int)(blockDim.x >> 6) / SPLIT;       // of a group
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = SPLIT == 1 ? 0 : wg_wave / waves, wave = wg_wave - group * waves;
     using W = WaveTile<T>;
     const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int b = g.block_tokens;
@@ -85,8 +91,8 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
     TileReader<T, D> rd;
     rd.init(lane);
-    AttendedKeys<T, D, NL> keys;
-    keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave);
+    AttendedKeys<T, D, NL, SPLIT> keys;
+    keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave, group);
 
     // this wavefront's 32 query rows
     const int tau_q = row0 + W::ROWS * wave + col;
@@ -99,10 +105,10 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 
     const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
     const RowSource ks(k + kv_base, slice_bytes), vs(v + kv_base, slice_bytes);
-    const uint32_t k_dst = lds_address(k_lds), v_dst = lds_address(v_lds);
+    const uint32_t k_dst = lds_address(k_lds[group]), v_dst = lds_address(v_lds[group]);
     if (wave < NL) {
         keys.look_up();
-        keys.gather_next(ks, vs, k_dst, v_dst);
+        if (SPLIT == 1 || group < keys.tiles) keys.gather_next(ks, vs, k_dst, v_dst);
     }
 
     const float c2 = g.scale * 1.4426950408889634f;
@@ -111,12 +117,14 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     float m_ref = -INFINITY, m_rest = 0.0f, l_run = 0.0f;
     uint64_t rests = 0;                              // lanes whose m_rest is not 0
 
-    for (int c = 0; c < keys.tiles; ++c) {
+    for (int c0 = 0; c0 < keys.tiles; c0 += SPLIT) {
         // tile c has landed and everyone is done with the other buffer
         wait_gathers();
         __syncthreads();
-        const int buf = c & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
-        if (wave < NL && c + 1 < keys.tiles) keys.gather_next(ks, vs, k_dst + other, v_dst + other);
+        const int c = c0 + group;
+        if (SPLIT > 1 && c >= keys.tiles) continue;       // (the last round)
+        const int buf = c0 / SPLIT & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
+        if (wave < NL && c + SPLIT < keys.tiles) keys.gather_next(ks, vs, k_dst + other, v_dst + other);
         const uint32_t at = (uint32_t)buf * Tile::TILE_BYTES;
 #pragma unroll
         for (int hh = 0; hh < KT / 32; ++hh) {
@@ -151,7 +159,10 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 const float m_new = up ? mx * c2 : m_ref;
                 const float rest_new =
                     !up ? m_rest : fabsf(m_new) >= kPlainRef ? fmaf(mx, c2, -m_new) : 0.0f;
-                const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) + (m_rest - rest_new));
+                // (a group's first keys may all have scores of minus infinity)
+                const bool none = SPLIT > 1 && m_new == -INFINITY;
+                const float alpha =
+                    none ? 1.0f : __builtin_amdgcn_exp2f((m_ref - m_new) + (m_rest - rest_new));
                 m_ref = m_new;
                 m_rest = rest_new;
                 rests = __builtin_amdgcn_ballot_w64(rest_new != 0.0f);
@@ -160,12 +171,53 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 rs = 0.0f;
 #pragma unroll
                 for (int r = 0; r < W::NR; ++r) {
-                    p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -m_new) - rest_new);
+                    p[r] = none ? 0.0f : __builtin_amdgcn_exp2f(fmaf(s[r], c2, -m_new) - rest_new);
                     rs += p[r];
                 }
             }
             l_run += rs;
             weighted_rows(rd, v_dst + at, 32 * hh * Tile::ROW_BYTES, v0, p, oacc);
+        }
+    }
+
+    if constexpr (SPLIT > 1) {
+        // groups 1 .. hand over what they have, lane by lane; the first group adds it up
+        constexpr int VALUES = (int)sizeof(Column<T, D>) / 4 + 3;
+        static_assert((SPLIT - 1) * (NL == 2 ? 3 : NL) * VALUES * 256 <= SPLIT * 2 * Tile::TILE_BYTES * 2,
+                      "fits the tiles");
+        constexpr int HALF = SPLIT * 2 * Tile::TILE_BYTES / 256;       // values per array and lane
+        auto place = [&](int of_group, int value) -> float* {
+            const int at = ((of_group - 1) * waves + wave) * VALUES + value;
+            return (at < HALF ? (float*)k_lds + at * 64 : (float*)v_lds + (at - HALF) * 64) + lane;
+        };
+        __syncthreads();
+        if (group > 0) {
+            *place(group, 0) = m_ref;
+            *place(group, 1) = m_rest;
+            *place(group, 2) = l_run;
+            int at = 3;
+#pragma unroll
+            for (auto& a : oacc.a)
+#pragma unroll
+                for (int r = 0; r < (int)sizeof(a) / 4; ++r) *place(group, at++) = a[r];
+        }
+        __syncthreads();
+        if (group > 0) return;
+        for (int from = 1; from < SPLIT; ++from) {
+            const float m = *place(from, 0), rest = *place(from, 1), l = *place(from, 2);
+            const bool up = m > m_ref || (m == m_ref && rest > m_rest);
+            const float m_new = up ? m : m_ref, rest_new = up ? rest : m_rest;
+            const bool none = m_new == -INFINITY;
+            const float old = none ? 1.0f : __builtin_amdgcn_exp2f((m_ref - m_new) + (m_rest - rest_new));
+            const float add = none ? 1.0f : __builtin_amdgcn_exp2f((m - m_new) + (rest - rest_new));
+            m_ref = m_new;
+            m_rest = rest_new;
+            l_run = l_run * old + l * add;
+            int at = 3;
+#pragma unroll
+            for (auto& a : oacc.a)
+#pragma unroll
+                for (int r = 0; r < (int)sizeof(a) / 4; ++r) a[r] = a[r] * old + *place(from, at++) * add;
         }
     }
 
@@ -179,19 +231,55 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     }
 }
 
+// Row wavefronts of a workgroup at most, and groups that share its keys, for a launch of
+// `wavefronts` row wavefronts.  What bounds a small launch is the chain of one wavefront
+// through all its keys while most CUs are idle: up to 256 row wavefronts get a workgroup
+// each and four groups (a wavefront per SIMD of its CU), up to 512 share one in pairs with
+// two groups, which is also the most that the LDS holds at head dim 128.  One workgroup per
+// CU is all that fits at 64 channels and more, so beyond 256 workgroups this loses.
+// Forward alone, us, unsplit | 1 x 4 | 2 x 2: 256 wavefronts, fp32, 320 keys, head dim 32
+// 12.0 | 9.4 | 9.5, 64 17.7 | 11.5 | 12.3, 128 29.1 | - | 19.4; 1,088 keys 30.6 | 14.5 | 19.2,
+// 48.5 | 22.1 | 29.1, 85.0 | - | 51.3; 288 wavefronts, head dim 64, 225 keys 15.5 | 18.0 |
+// 10.9; 1,024 wavefronts, head dim 64 19.4 | 39.1 | 18.8, 128 31.4 | - | 38.0; bf16, 128
+// wavefronts, head dim 32, 1,088 keys 20.6 | 11.4 | 13.4.
+struct KeySplit {
+    int max_waves, groups;
+};
+static KeySplit key_split(int64_t wavefronts, int D)
+{
+    if (wavefronts <= 256 && D < 128) return {1, 4};
+    if (wavefronts <= 512) return {2, 2};
+    return {8, 1};
+}
+
+template <typename T, int D, int SPLIT>
+static auto kernel_of(int waves)
+{
+    if constexpr (SPLIT == 4) {                       // (head dim 128: not chosen)
+        return fwd_generic_kernel<T, D, 1, D == 128 ? 2 : 4>;
+    } else if constexpr (SPLIT == 2) {
+        return waves >= 2 ? fwd_generic_kernel<T, D, 2, 2> : fwd_generic_kernel<T, D, 1, 2>;
+    } else {
+        return waves >= 4 ? fwd_generic_kernel<T, D, 4, 1>
+               : waves >= 2 ? fwd_generic_kernel<T, D, 2, 1> : fwd_generic_kernel<T, D, 1, 1>;
+    }
+}
+
 template <typename T, int D>
 static hipError_t launch_t(const void* q, const void* k, const void* v, const FwdJob* jobs,
                            int n_jobs, const Geom& g, int64_t BH, hipStream_t stream)
 {
-    const RowSplit rows(g.block_tokens, 8, WaveTile<T>::ROWS);
-    const int nw = rows.waves;
-    auto kernel = nw >= 4 ? fwd_generic_kernel<T, D, 4>
-                  : nw >= 2 ? fwd_generic_kernel<T, D, 2> : fwd_generic_kernel<T, D, 1>;
+    const RowSplit whole(g.block_tokens, 8, WaveTile<T>::ROWS);
+    const KeySplit ks = key_split(BH * g.n_blocks * whole.chunks * whole.waves * n_jobs, D);
+    const RowSplit rows(g.block_tokens, ks.max_waves, WaveTile<T>::ROWS);
+    const int nw = rows.waves, split = ks.groups;
     int listed = 0;
     for (int j = 0; j < n_jobs; ++j)
         listed = jobs[j].n_select + 1 > listed ? jobs[j].n_select + 1 : listed;
     const int64_t wgs = (int64_t)g.kv_group * g.n_blocks * rows.chunks;    // per key/value slice
-    return launch_slices(BH / g.kv_group, wgs * 64 * nw, [&](int64_t first, int64_t slices) {
+    auto kernel = split == 4 ? kernel_of<T, D, 4>(nw)
+                  : split == 2 ? kernel_of<T, D, 2>(nw) : kernel_of<T, D, 1>(nw);
+    return launch_slices(BH / g.kv_group, wgs * 64 * nw * split, [&](int64_t first, int64_t slices) {
         const int64_t row = first * g.kv_group * g.n_tokens, kv = first * g.n_tokens * D;
         FwdJob piece[2];
         for (int j = 0; j < n_jobs; ++j) {
@@ -200,9 +288,9 @@ static hipError_t launch_t(const void* q, const void* k, const void* v, const Fw
             piece[j].out = (T*)jobs[j].out + row * D;
             if (jobs[j].lse) piece[j].lse += row;
         }
-        return launch_jobs(piece, n_jobs, slices * wgs, 64 * nw,
+        return launch_jobs(piece, n_jobs, slices * wgs, 64 * nw * split,
                            [&](const FwdJob& a, const FwdJob& b, const FwdShape& j, unsigned grid) {
-                               kernel<<<dim3(grid), dim3(64 * nw), flat_table_bytes(g, listed),
+                               kernel<<<dim3(grid), dim3(64 * nw * split), flat_table_bytes(g, listed, split),
                                         stream>>>((const T*)q + row * D, (const T*)k + kv,
                                                   (const T*)v + kv, a.lists, b.lists, (T*)a.out,
                                                   (T*)b.out, a.lse, b.lse, j, g, (uint32_t)slices,

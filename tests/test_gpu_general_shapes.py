@@ -72,6 +72,36 @@ def test_general_forward(G, oracle, dtype, H, W, bh, bw, D, n):
     assert np.abs(lse - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("wavefronts", [400, 600])
+@pytest.mark.parametrize("H,W,bh,bw,D,n", [
+    (9, 12, 3, 3, 64, 6),        # 63 keys: fewer tiles than groups
+    (10, 13, 5, 1, 128, 12),     # 65 keys
+    (22, 33, 11, 3, 32, 3),      # b = 33
+    (14, 57, 7, 19, 64, 4),      # b = 133
+    (46, 48, 1, 2, 32, 1030),    # long lists
+])
+def test_general_forward_key_split(G, oracle, dtype, wavefronts, H, W, bh, bw, D, n):
+    """Launches of up to 256, up to 512 and more row wavefronts (16 rows in fp32, 32 in
+    bf16) take the keys in four groups, two or one: the same entry as often as it takes.
+    All copies agree exactly, and with the oracle as in test_general_forward."""
+    cfg = shape_ns(1, 2, H, W, bh, bw, D, min(n, (H // bh) * (W // bw) - 1), dtype)
+    q, k, v = inputs_of(cfg, 70 + H + W + D)
+    idx = random_selection(cfg, 9)
+    out_ref, lse_ref = oracle.fwd(oracle.shape_of(cfg), q, k, v, idx)
+    per_entry = 2 * cfg.n_blocks * -(-cfg.block_tokens // (16 if dtype == "fp32" else 32))
+    cfg.batch = -(-wavefronts // per_entry)
+    copies = lambda x: np.repeat(x, cfg.batch, axis=0)
+    out, lse = G.gpu_fwd(cfg, copies(q), copies(k), copies(v), copies(idx))
+    assert (out == out[:1]).all() and (lse == lse[:1]).all()
+    err, top = np.abs(out[:1] - out_ref), np.abs(out_ref).max()
+    if dtype == "fp32":
+        assert err.max() <= 1e-5 * top
+    else:
+        assert (err <= 2.0 ** -8 * np.abs(out_ref) + 2.0 ** -14 * np.abs(v).max()).all()
+    assert np.abs(lse[:1] - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
+
+
 @pytest.mark.parametrize("mask", [-1e10, -1e30, -3e38])
 @pytest.mark.parametrize("dtype,H,W,bh,bw,D", [
     ("fp32", 10, 20, 5, 5, 32), ("fp32", 16, 32, 8, 8, 64), ("fp32", 10, 20, 5, 5, 128),
