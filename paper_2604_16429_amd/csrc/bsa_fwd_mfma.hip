@@ -352,6 +352,10 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
         gather_slab<NW, NW == 1 ? 6 : 0>(RSRC, ORIGIN, voff, LDS, wave_kib);           \
         gather_slab<NW, NW == 1 ? 7 : 0>(RSRC, ORIGIN, voff, LDS, wave_kib);           \
     }
+    // the lists are asked for first: the order below then waits for them alone, not for
+    // the gathers and Q that are requested before it (0.25 degrees 0.9 %, one member 1.1 %
+    // shorter; a wavefront's life before its first pair is 8,000 to 13,000 cycles)
+    const int mine = (sorted && lane >= 1 && lane <= n) ? sel_row[lane - 1] : 0x7fffffff;
     // K(0) and V(0) go to LDS (set a), in the order K half 0, K half 1, V half 0,
     // V half 1: the waits below count on it
     {
@@ -382,7 +386,6 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
 
     if (sorted) {
         // lane l in 1..n holds a selected block; rank = 1 + number of smaller ones
-        const int mine = (lane >= 1 && lane <= n) ? sel_row[lane - 1] : 0x7fffffff;
         int rank = 1;
         for (int t = 1; t <= n; ++t)
             rank += __builtin_amdgcn_readlane(mine, t) < mine ? 1 : 0;

@@ -170,6 +170,9 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
         }
     };
 
+    // the list is asked for first: the order below then waits for it alone, not for the
+    // gathers and Q that are requested before it
+    const int mine = (sorted && lane >= 1 && lane <= n) ? sel_row[lane - 1] : 0x7fffffff;
     // pair 0: K (both halves) and the lower half of V go to LDS
     {
         const uint32_t origin_0 = origin_of(first);
@@ -195,7 +198,6 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
 
     if (sorted) {
         // lane l in 1..n holds a selected block; rank = 1 + number of smaller ones
-        const int mine = (lane >= 1 && lane <= n) ? sel_row[lane - 1] : 0x7fffffff;
         int rank = 1;
         for (int t = 1; t <= n; ++t)
             rank += __builtin_amdgcn_readlane(mine, t) < mine ? 1 : 0;

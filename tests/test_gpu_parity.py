@@ -502,6 +502,9 @@ def masked_attention_grads(cfg, q, k, v, dout, idx):
     (32, 64, 64, 8, 8, 64, 63),     # 2,048 connected blocks per key block: two full lists
     (72, 32, 64, 8, 16, 64, 15),    # 1,152: the list ends inside a head
     (130, 32, 64, 16, 16, 64, 7),   # 1,040, 256-token blocks
+    (72, 32, 64, 8, 16, 128, 15),   # head dim 128
+    (130, 32, 64, 16, 16, 128, 7),
+    (264, 8, 64, 2, 64, 128, 1),    # tiles one load wide
 ])
 def test_backward_long_connected_lists(G, heads, H, W, bh, bw, D, n):
     """Key blocks with more connected query blocks than one list holds (1,024 blocks,
