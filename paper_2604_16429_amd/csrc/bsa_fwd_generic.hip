@@ -56,7 +56,8 @@ constexpr float kPlainRef = 1048576.0f;
 // at the end.  For launches that leave the chip idle; see key_split.
 template <typename T, int D, int NL, int SPLIT>
 __global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * (NL == 2 ? 3 : NL) : NL == 4 ? 512 : NL == 2 ? 192 : 64,
-                             SPLIT > 1 || NL == 1 || (NL == 2 && D == 128) ? 1 : D == 32 ? 4 : 2)
+                             SPLIT > 1 || NL == 1 || (NL == 2 && D == 128) ? 1
+                             : D == 32 || (sizeof(T) == 4 && D == 128) ? 4 : 2)
 void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                         BSA_FWD_JOB_PARAMS(T), Geom g, uint32_t n_units, int row_chunks, int chunk_rows)
 {
@@ -245,11 +246,11 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 struct KeySplit {
     int max_waves, groups;
 };
-static KeySplit key_split(int64_t wavefronts, int D)
+static KeySplit key_split(int64_t wavefronts, int D, int most)
 {
     if (wavefronts <= 256 && D < 128) return {1, 4};
     if (wavefronts <= 512) return {2, 2};
-    return {8, 1};
+    return {most, 1};
 }
 
 template <typename T, int D, int SPLIT>
@@ -269,8 +270,13 @@ template <typename T, int D>
 static hipError_t launch_t(const void* q, const void* k, const void* v, const FwdJob* jobs,
                            int n_jobs, const Geom& g, int64_t BH, hipStream_t stream)
 {
-    const RowSplit whole(g.block_tokens, 8, WaveTile<T>::ROWS);
-    const KeySplit ks = key_split(BH * g.n_blocks * whole.chunks * whole.waves * n_jobs, D);
+    // fp32, head dim 32: with 8 wavefronts, of 16 rows, the last of an odd number of them
+    // leaves SIMDs uneven (10 x 10 tiles 589 us, with 4 568, with 32-row wavefronts 560;
+    // 16 x 16 1,168 against 1,170).  At head dim 128 four wavefronts per SIMD need 128
+    // registers (5 spill outside of the tile loop): blocks of 256 4.37 -> 4.10 ms.
+    const int most = sizeof(T) == 4 && D == 32 ? 4 : 8;
+    const RowSplit whole(g.block_tokens, most, WaveTile<T>::ROWS);
+    const KeySplit ks = key_split(BH * g.n_blocks * whole.chunks * whole.waves * n_jobs, D, most);
     const RowSplit rows(g.block_tokens, ks.max_waves, WaveTile<T>::ROWS);
     const int nw = rows.waves, split = ks.groups;
     int listed = 0;
