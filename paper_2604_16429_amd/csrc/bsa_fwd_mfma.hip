@@ -599,8 +599,10 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
     // ---- normalise; O rows go through LDS (the tiles are used up), so that a store
     // instruction writes 1 KiB runs instead of 8 bytes of 64 places (see store_rows): 64
     // rows of 128 bytes per wavefront, swizzled like the tiles
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // gathers of pairs past the end
+    // (the waits: gathers of pairs past the end, reads of the last tiles)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     wg_barrier();
+    lane_exchange();
     unsigned char* const o_lds =
         NW == 1 ? nullptr : NW == 2 ? (wave == 0 ? x_a[0] : x_b[0])
                                     : wave == 0 ? x_a[0] : wave == 1 ? y_a[0] : wave == 2 ? x_b[0] : y_b[0];
@@ -623,6 +625,7 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
             lse[bh_idx * g.n_tokens + q_tok[nt]] =
                 (m_ref[nt] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
     }
+    lane_exchange();
     out += (origin_of(i) >> 1) + (uint32_t)(sub_tile_first(g, qsub) * D);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {

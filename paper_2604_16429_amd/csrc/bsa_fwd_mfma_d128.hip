@@ -461,8 +461,10 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
                                                                0);
 
     // ---- normalise, store O rows (through the LDS of the tiles, which are used up)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // gathers of pairs past the end
+    // (the waits: gathers of pairs past the end, reads of the last tiles)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
+    lane_exchange();
     {
         const float l_tot = l_run + swap32(l_run);
         const float inv_l = 1.0f / l_tot;

@@ -119,6 +119,14 @@ __device__ __forceinline__ float tile_weights(const f32x16& s, float c2, float n
 
 constexpr float kSumLimit = 4096.0f;
 
+// Orders a wavefront's LDS writes before reads by other lanes of it, and the other way
+// round: the hardware keeps the order by itself, the compiler, which sees one lane's
+// addresses and types, has to be told.  No instruction.
+__device__ __forceinline__ void lane_exchange()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // Stores a wavefront's 32 rows of D channels, bf16 (accumulators of transposed products:
 // lane l32 of both halves holds row l32, register 4 r + e of tile dt channel 32 dt + 8 r +
 // 4 half + e), scaled by f, to the in-tile positions pos0 .. pos0 + 31 of the block whose
@@ -150,6 +158,7 @@ __device__ __forceinline__ void store_rows(uint16_t* block, const Geom& g, int p
                 w.y = pack_bf16(a[4 * r4 + 2] * f, a[4 * r4 + 3] * f);
                 *(uint2*)(lds + l32 * 128 + chunk_of(l32, 4 * dt + r4) * 16 + 8 * half) = w;
             }
+        lane_exchange();
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int t = 8 * j + (lane >> 3), pos = pos0 + t;
@@ -157,9 +166,9 @@ __device__ __forceinline__ void store_rows(uint16_t* block, const Geom& g, int p
             *(uint4*)(block + tok * D + 64 * c + chunk_of(t, lane & 7) * 8) =
                 *(const uint4*)(lds + 1024 * j + 16 * lane);
         }
+        lane_exchange();
     }
 }
-
 
 // The same, added to what the rows hold together with extra * inv_b (extra: fp32, D
 // channels).  32 channels at a time, which fp32 takes the same 4 KiB for.
@@ -189,6 +198,7 @@ __device__ __forceinline__ void add_rows(uint16_t* block, const Geom& g, int pos
             *(float4*)(lds + l32 * 128 + chunk_of(l32, 2 * r4 + half) * 16) =
                 make_float4(acc[c][4 * r4] * f, acc[c][4 * r4 + 1] * f, acc[c][4 * r4 + 2] * f,
                             acc[c][4 * r4 + 3] * f);
+        lane_exchange();
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int t = 16 * j + (lane >> 2);
@@ -207,6 +217,7 @@ __device__ __forceinline__ void add_rows(uint16_t* block, const Geom& g, int pos
             }
             *(uint4*)(row[j] + 32 * c) = make_uint4(w[0], w[1], w[2], w[3]);
         }
+        lane_exchange();
     }
 }
 
