@@ -50,7 +50,9 @@
  *             on error nothing has been launched.  Inputs must be finite.
  *   Masks     by a large finite score (a channel of their own): the forward takes
  *             scores softmax_scale * q.k of any size in fp32 and wherever the
- *             general kernels run.  The bf16 kernels for head dims 64 and 128
+ *             general kernels run (past -2.3e38, where the product with log2(e)
+ *             leaves the range of fp32, a key weighs 0, and a row that has no other
+ *             key is undefined).  The bf16 kernels for head dims 64 and 128
  *             (blocks of 64 * T tokens, width a power of two; 64, 128 or 256 tokens
  *             at 128) need one score of magnitude below 2^30 among the first 32
  *             attended keys of a row.  Every backward needs one in the row.

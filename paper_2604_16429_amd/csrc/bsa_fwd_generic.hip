@@ -158,10 +158,13 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 mx = column_max<T>(mx);
                 const bool up = fmaf(mx, c2, -m_ref) > m_rest;
                 const float m_new = up ? mx * c2 : m_ref;
+                // no reference yet: all scores so far are below the range of fp32 once
+                // multiplied with c2.  Their weights are exp2 of that product, i.e. 0;
+                // NaN stays NaN
+                const bool none = m_new == -INFINITY;
+                const float neg_m = none ? 0.0f : -m_new;
                 const float rest_new =
-                    !up ? m_rest : fabsf(m_new) >= kPlainRef ? fmaf(mx, c2, -m_new) : 0.0f;
-                // (a group's first keys may all have scores of minus infinity)
-                const bool none = SPLIT > 1 && m_new == -INFINITY;
+                    !up ? m_rest : !none && fabsf(m_new) >= kPlainRef ? fmaf(mx, c2, neg_m) : 0.0f;
                 const float alpha =
                     none ? 1.0f : __builtin_amdgcn_exp2f((m_ref - m_new) + (m_rest - rest_new));
                 m_ref = m_new;
@@ -172,7 +175,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 rs = 0.0f;
 #pragma unroll
                 for (int r = 0; r < W::NR; ++r) {
-                    p[r] = none ? 0.0f : __builtin_amdgcn_exp2f(fmaf(s[r], c2, -m_new) - rest_new);
+                    p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, neg_m) - rest_new);
                     rs += p[r];
                 }
             }

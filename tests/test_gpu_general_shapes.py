@@ -141,6 +141,58 @@ def test_general_forward_finite_masks(G, oracle, dtype, H, W, bh, bw, D, mask):
     assert np.isfinite(out).all() and np.isfinite(lse).all()
 
 
+def times(cfg, groups, *tensors):
+    """One entry as often as it takes for a launch of up to 256 row wavefronts (four groups
+    share the keys of a wavefront's rows), of up to 512 (two) or more (one)."""
+    rows = 16 if cfg.dtype == "fp32" else 32
+    per_entry = cfg.heads * cfg.n_blocks * -(-cfg.block_tokens // rows)
+    cfg.batch = {4: 256 // per_entry, 2: 512 // per_entry, 1: 512 // per_entry + 1}[groups]
+    low, high = {4: (0, 256), 2: (256, 512), 1: (512, 1 << 30)}[groups]
+    assert low < cfg.batch * per_entry <= high
+    return [np.repeat(x, cfg.batch, axis=0) for x in tensors]
+
+
+@pytest.mark.parametrize("groups", [4, 2, 1])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_general_forward_nan_keys(G, dtype, groups):
+    """A row that attends to a block of NaN keys (values finite) becomes NaN, whatever the
+    place of the block in the row's list and the size of the launch; the others do not."""
+    cfg = shape_ns(1, 1, 32, 32, 8, 8, 32, 8, dtype)
+    q, k, v = inputs_of(cfg, 11)
+    k[0, 0].reshape(4, 8, 4, 8, 32)[1, :, 2] = np.nan        # block 6
+    idx = random_selection(cfg, 12)
+    out, lse = G.gpu_fwd(cfg, *times(cfg, groups, q, k, v, idx))
+    sees = (idx[0, 0] == 6).any(axis=1) | (np.arange(16) == 6)
+    sees = np.broadcast_to(sees.reshape(4, 1, 4, 1), (4, 8, 4, 8)).reshape(-1)
+    assert (np.isnan(lse) == sees).all() and (np.isnan(out) == sees[:, None]).all()
+
+
+@pytest.mark.parametrize("groups", [4, 2, 1])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_general_forward_masks_past_the_range(G, oracle, dtype, groups):
+    """Keys masked by a score of -3e38, which times log2(e) leaves the range of fp32, as the
+    first keys of a row, the first that a group takes and others: weight 0.  Bounds of
+    test_general_forward."""
+    cfg = shape_ns(1, 1, 32, 32, 8, 8, 32, 8, dtype)
+    q, k, v = (0.4 * x for x in inputs_of(cfg, 13))
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    keys = k[0, 0].reshape(4, 8, 4, 8, 32)
+    keys[0, :, :, :, 0] = -3e38                              # blocks 0 to 3
+    keys[2, :4, 1, :, 0] = -3e38                             # half of block 9
+    if dtype == "bf16":
+        q, k, v = (round_to_bf16(x) for x in (q, k, v))
+    idx = random_selection(cfg, 14)
+    out_ref, lse_ref = oracle.fwd(oracle.shape_of(cfg), q, k, v, idx, 1.0)
+    out, lse = G.gpu_fwd(cfg, *times(cfg, groups, q, k, v, idx), softmax_scale=1.0)
+    err = np.abs(out - out_ref)
+    if dtype == "fp32":
+        assert err.max() <= 1e-5 * np.abs(out_ref).max()
+    else:
+        assert (err <= 2.0 ** -8 * np.abs(out_ref) + 2.0 ** -14 * np.abs(v).max()).all()
+    assert np.abs(lse - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
+
+
 @pytest.mark.parametrize("dtype,kv_heads", [("fp32", 0), ("bf16", 0), ("fp32", 1), ("bf16", 1)])
 @pytest.mark.parametrize("H,W,bh,bw,D,n", SHAPES)
 def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
