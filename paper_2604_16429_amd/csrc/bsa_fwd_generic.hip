@@ -236,23 +236,26 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 }
 
 // Row wavefronts of a workgroup at most, and groups that share its keys, for a launch of
-// `wavefronts` row wavefronts.  What bounds a small launch is the chain of one wavefront
-// through all its keys while most CUs are idle: up to 256 row wavefronts get a workgroup
-// each and four groups (a wavefront per SIMD of its CU), up to 512 share one in pairs with
-// two groups, which is also the most that the LDS holds at head dim 128.  One workgroup per
-// CU is all that fits at 64 channels and more, so beyond 256 workgroups this loses.
+// `wavefronts` row wavefronts in `pairs` workgroups of one or two of them.  What bounds a
+// small launch is the chain of one wavefront through all its keys while most CUs are idle:
+// up to 256 row wavefronts get a workgroup each and four groups (a wavefront per SIMD of its
+// CU), up to 512 share one in pairs with two groups.  At head dim 128 the tiles of two
+// groups take 128 KiB of LDS, one workgroup per CU, so that more than 256 workgroups (blocks
+// of one row wavefront, or three) run in two rounds; the 64 KiB of unsplit ones fit twice.
 // Forward alone, us, unsplit | 1 x 4 | 2 x 2: 256 wavefronts, fp32, 320 keys, head dim 32
 // 12.0 | 9.4 | 9.5, 64 17.7 | 11.5 | 12.3, 128 29.1 | - | 19.4; 1,088 keys 30.6 | 14.5 | 19.2,
 // 48.5 | 22.1 | 29.1, 85.0 | - | 51.3; 288 wavefronts, head dim 64, 225 keys 15.5 | 18.0 |
 // 10.9; 1,024 wavefronts, head dim 64 19.4 | 39.1 | 18.8, 128 31.4 | - | 38.0; bf16, 128
-// wavefronts, head dim 32, 1,088 keys 20.6 | 11.4 | 13.4.
+// wavefronts, head dim 32, 1,088 keys 20.6 | 11.4 | 13.4.  Blocks of 16 at head dim 128, 256
+// keys, unsplit | 2 x 2: 240 wavefronts fp32 27.9 | 18.9, bf16 14.3 | 12.6; 368 29.5 | 35.1,
+// 15.5 | 23.2.
 struct KeySplit {
     int max_waves, groups;
 };
-static KeySplit key_split(int64_t wavefronts, int D, int most)
+static KeySplit key_split(int64_t wavefronts, int64_t pairs, int D, int most)
 {
     if (wavefronts <= 256 && D < 128) return {1, 4};
-    if (wavefronts <= 512) return {2, 2};
+    if (wavefronts <= 512 && (D < 128 || pairs <= 256)) return {2, 2};
     return {most, 1};
 }
 
@@ -279,7 +282,10 @@ static hipError_t launch_t(const void* q, const void* k, const void* v, const Fw
     // registers (5 spill outside of the tile loop): blocks of 256 4.37 -> 4.10 ms.
     const int most = sizeof(T) == 4 && D == 32 ? 4 : 8;
     const RowSplit whole(g.block_tokens, most, WaveTile<T>::ROWS);
-    const KeySplit ks = key_split(BH * g.n_blocks * whole.chunks * whole.waves * n_jobs, D, most);
+    const int64_t blocks = BH * g.n_blocks * n_jobs;
+    const KeySplit ks =
+        key_split(blocks * whole.chunks * whole.waves,
+                  blocks * RowSplit(g.block_tokens, 2, WaveTile<T>::ROWS).chunks, D, most);
     const RowSplit rows(g.block_tokens, ks.max_waves, WaveTile<T>::ROWS);
     const int nw = rows.waves, split = ks.groups;
     int listed = 0;

@@ -193,6 +193,21 @@ def test_general_forward_masks_past_the_range(G, oracle, dtype, groups):
     assert np.abs(lse - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
 
 
+@pytest.mark.parametrize("dtype,groups,H,W,bh,bw,D,n", [
+    ("fp32", 2, 16, 32, 4, 4, 128, 20),      # one row wavefront per block: no pairs, and
+    ("bf16", 2, 16, 32, 4, 4, 128, 20),      # more workgroups than CUs
+    ("fp32", 2, 12, 48, 6, 6, 128, 9),       # three
+])
+def test_general_forward_unsplit_small_launches(G, dtype, groups, H, W, bh, bw, D, n):
+    """Launches that do not split the keys although they are small: the bits of a large
+    one."""
+    cfg = shape_ns(1, 1, H, W, bh, bw, D, n, dtype)
+    inputs = *inputs_of(cfg, 21), random_selection(cfg, 22)
+    large = G.gpu_fwd(cfg, *times(cfg, 1, *inputs))
+    small = G.gpu_fwd(cfg, *times(cfg, groups, *inputs))
+    assert all(np.array_equal(x[0], y[0]) for x, y in zip(small, large))
+
+
 @pytest.mark.parametrize("dtype,kv_heads", [("fp32", 0), ("bf16", 0), ("fp32", 1), ("bf16", 1)])
 @pytest.mark.parametrize("H,W,bh,bw,D,n", SHAPES)
 def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
