@@ -236,26 +236,37 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 }
 
 // Row wavefronts of a workgroup at most, and groups that share its keys, for a launch of
-// `wavefronts` row wavefronts in `pairs` workgroups of one or two of them.  What bounds a
-// small launch is the chain of one wavefront through all its keys while most CUs are idle:
-// up to 256 row wavefronts get a workgroup each and four groups (a wavefront per SIMD of its
-// CU), up to 512 share one in pairs with two groups.  At head dim 128 the tiles of two
-// groups take 128 KiB of LDS, one workgroup per CU, so that more than 256 workgroups (blocks
-// of one row wavefront, or three) run in two rounds; the 64 KiB of unsplit ones fit twice.
-// Forward alone, us, unsplit | 1 x 4 | 2 x 2: 256 wavefronts, fp32, 320 keys, head dim 32
-// 12.0 | 9.4 | 9.5, 64 17.7 | 11.5 | 12.3, 128 29.1 | - | 19.4; 1,088 keys 30.6 | 14.5 | 19.2,
-// 48.5 | 22.1 | 29.1, 85.0 | - | 51.3; 288 wavefronts, head dim 64, 225 keys 15.5 | 18.0 |
-// 10.9; 1,024 wavefronts, head dim 64 19.4 | 39.1 | 18.8, 128 31.4 | - | 38.0; bf16, 128
-// wavefronts, head dim 32, 1,088 keys 20.6 | 11.4 | 13.4.  Blocks of 16 at head dim 128, 256
-// keys, unsplit | 2 x 2: 240 wavefronts fp32 27.9 | 18.9, bf16 14.3 | 12.6; 368 29.5 | 35.1,
-// 15.5 | 23.2.
+// `wavefronts` row wavefronts, which take `pairs` workgroups when two share one where a block
+// has two, and `tiles` key tiles each.  What bounds a small launch is the chain of one
+// wavefront through its tiles while most CUs are idle; what a split costs is two barriers
+// and the merge, 0.5 to 2 us.
+// 1 x 4: a workgroup per row wavefront, four groups (a wavefront per SIMD of its CU).
+// 2 x 2: pairs, two groups.  us, unsplit | 1 x 4 | 2 x 2, tiles of 32 (fp32) or 64 keys:
+//   * up to 256 wavefronts, fp32, blocks of 16, head dim 32: 1 tile 4.8 | 5.9 | 5.3, 2 tiles
+//     5.7 | 6.1 | 5.5, 3 6.6 | 6.2 | 6.3, 8 11.2 | 7.6 | 8.5; 64: 1 5.9 | 7.4 | 6.6, 2 7.4 |
+//     7.8 | 6.8, 3 9.0 | 7.8 | 8.4, 8 16.9 | 10.1 | 11.7.  bf16, blocks of 36, head dim 64: 1
+//     5.4 | 8.2 | 6.4, 3 8.2 | 8.8 | 8.1, 4 9.5 | 9.0 | 8.3, 6 11.9 | 10.5 | 9.6, 8 14.6 |
+//     10.9 | 11.0.
+//   * up to 512 in at most 256 pairs: as the pairs above (bf16 head dim 64, 480 wavefronts,
+//     4 tiles 9.5 | - | 8.4; 128, 6 tiles 17.3 | - | 14.2).
+//   * more workgroups than CUs (blocks of one row wavefront, or three).  Head dim 128: the
+//     tiles of two groups take 128 KiB of LDS, so that these run in two rounds, where
+//     unsplit ones fit a CU twice: never (368 wavefronts, fp32, 8 tiles 29.5 | - | 35.1, bf16,
+//     4 15.5 | - | 23.2).  64: single wavefronts as above (fp32, 368, 2 tiles 7.9 | - | 7.3, 8
+//     17.3 | - | 12.7; bf16, 4 10.6 | - | 9.6), three not (fp32, 480, 4 tiles 9.8 | - | 10.3).
+//     32: from 8 tiles (fp32, 368, 4 tiles 7.8 | - | 8.1, 8 11.5 | - | 11.2).
+// 1,024 wavefronts: head dim 64, 10 tiles 19.4 | 39.1 | 18.8, 128 31.4 | - | 38.0.
 struct KeySplit {
     int max_waves, groups;
 };
-static KeySplit key_split(int64_t wavefronts, int64_t pairs, int D, int most)
+template <typename T, int D>
+static KeySplit key_split(int64_t wavefronts, int64_t pairs, bool single, int64_t tiles, int most)
 {
-    if (wavefronts <= 256 && D < 128) return {1, 4};
-    if (wavefronts <= 512 && (D < 128 || pairs <= 256)) return {2, 2};
+    // tiles from which two groups and four pay
+    const int two = sizeof(T) == 4 ? 2 : 4, four = sizeof(T) == 4 ? 3 : 7;
+    if (wavefronts <= 256 && D < 128 && tiles >= four) return {1, 4};
+    const bool pays = pairs <= 256 || (D == 64 && single) ? tiles >= two : D == 32 && tiles >= 8;
+    if (wavefronts <= 512 && pays) return {2, 2};
     return {most, 1};
 }
 
@@ -282,15 +293,21 @@ static hipError_t launch_t(const void* q, const void* k, const void* v, const Fw
     // registers (5 spill outside of the tile loop): blocks of 256 4.37 -> 4.10 ms.
     const int most = sizeof(T) == 4 && D == 32 ? 4 : 8;
     const RowSplit whole(g.block_tokens, most, WaveTile<T>::ROWS);
+    int listed = 0;
+    int64_t keys = 0;                                 // of the job with most
+    for (int j = 0; j < n_jobs; ++j) {
+        listed = jobs[j].n_select + 1 > listed ? jobs[j].n_select + 1 : listed;
+        const int64_t attended =
+            (int64_t)(jobs[j].n_select + 1 - jobs[j].list_only) * g.block_tokens;
+        keys = attended > keys ? attended : keys;
+    }
+    constexpr int KT = FlatTile<T, D>::KT;
     const int64_t blocks = BH * g.n_blocks * n_jobs;
-    const KeySplit ks =
-        key_split(blocks * whole.chunks * whole.waves,
-                  blocks * RowSplit(g.block_tokens, 2, WaveTile<T>::ROWS).chunks, D, most);
+    const RowSplit pairs(g.block_tokens, 2, WaveTile<T>::ROWS);
+    const KeySplit ks = key_split<T, D>(blocks * whole.chunks * whole.waves, blocks * pairs.chunks,
+                                        pairs.waves == 1, (keys + KT - 1) / KT, most);
     const RowSplit rows(g.block_tokens, ks.max_waves, WaveTile<T>::ROWS);
     const int nw = rows.waves, split = ks.groups;
-    int listed = 0;
-    for (int j = 0; j < n_jobs; ++j)
-        listed = jobs[j].n_select + 1 > listed ? jobs[j].n_select + 1 : listed;
     const int64_t wgs = (int64_t)g.kv_group * g.n_blocks * rows.chunks;    // per key/value slice
     auto kernel = split == 4 ? kernel_of<T, D, 4>(nw)
                   : split == 2 ? kernel_of<T, D, 2>(nw) : kernel_of<T, D, 1>(nw);

@@ -197,6 +197,12 @@ def test_general_forward_masks_past_the_range(G, oracle, dtype, groups):
     ("fp32", 2, 16, 32, 4, 4, 128, 20),      # one row wavefront per block: no pairs, and
     ("bf16", 2, 16, 32, 4, 4, 128, 20),      # more workgroups than CUs
     ("fp32", 2, 12, 48, 6, 6, 128, 9),       # three
+    ("fp32", 2, 12, 48, 6, 6, 64, 9),
+    ("fp32", 2, 16, 32, 4, 4, 32, 13),       # 7 tiles at head dim 32
+    ("bf16", 4, 16, 32, 8, 8, 32, 2),        # 3 tiles
+    ("bf16", 2, 16, 32, 8, 8, 32, 2),
+    ("bf16", 4, 12, 24, 6, 6, 64, 4),
+    ("bf16", 2, 12, 24, 6, 6, 128, 4),
 ])
 def test_general_forward_unsplit_small_launches(G, dtype, groups, H, W, bh, bw, D, n):
     """Launches that do not split the keys although they are small: the bits of a large
