@@ -670,26 +670,41 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
                                const int32_t* order, const Geom& g, int64_t BH, hipStream_t stream)
 {
     const RowSplit rows(g.block_tokens, BwdLimits<T, D>::MAX_WAVES, WaveTile<T>::ROWS);
-    const int nw = rows.waves;
-    const int64_t BKV = BH / g.kv_group;
-    if (BH * g.n_blocks * rows.chunks >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    const dim3 block(64 * nw), grid((unsigned)(BH * g.n_blocks * rows.chunks)),
-        grid_kv((unsigned)(BKV * g.n_blocks * rows.chunks));
+    const int nw = rows.waves, m = g.n_blocks, words = (m + 31) >> 5;
+    const int64_t BKV = BH / g.kv_group, N = g.n_tokens;
+    const int64_t wgs = (int64_t)m * rows.chunks;                 // per slice
+    const dim3 block(64 * nw);
     auto run_dkdv = [&] {
         auto kernel = nw >= 4 ? bwd_generic_dkdv<T, D, 4>
                       : nw >= 2 ? bwd_generic_dkdv<T, D, 2> : bwd_generic_dkdv<T, D, 1>;
-        kernel<<<grid_kv, block, sizeof(uint32_t) * (size_t)g.block_tokens, stream>>>(
-            (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, conn, order,
-            (T*)dk, (T*)dv, g, (uint32_t)BKV, rows.chunks, WaveTile<T>::ROWS * nw);
-        return hipGetLastError();
+        return launch_slices(BKV, wgs * 64 * nw, [&](int64_t first, int64_t slices) {
+            const int64_t bh = first * g.kv_group, row = bh * N, kv = first * N * D;
+            Geom piece = g;
+            if (g.add_dk) piece.add_dk += first * m * D;
+            if (g.add_dv) piece.add_dv += first * m * D;
+            kernel<<<dim3((unsigned)(slices * wgs)), block, sizeof(uint32_t) * (size_t)g.block_tokens,
+                     stream>>>((const T*)q + row * D, (const T*)k + kv, (const T*)v + kv,
+                               (const T*)dout + row * D, lse2 + row, delta + row,
+                               conn + bh * words * m, order ? order + first * m : nullptr,
+                               (T*)dk + kv, (T*)dv + kv, piece, (uint32_t)slices, rows.chunks,
+                               WaveTile<T>::ROWS * nw);
+            return hipGetLastError();
+        });
     };
     auto run_dq = [&] {
         auto kernel = nw >= 4 ? bwd_generic_dq<T, D, 4>
                       : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
-        kernel<<<grid, block, flat_table_bytes(g, g.n_select + 1), stream>>>(
-            (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse2, delta, sel_idx, (T*)dq, g,
-            (uint32_t)BKV, rows.chunks, WaveTile<T>::ROWS * nw);
-        return hipGetLastError();
+        return launch_slices(BKV, g.kv_group * wgs * 64 * nw, [&](int64_t first, int64_t slices) {
+            const int64_t bh = first * g.kv_group, row = bh * N, kv = first * N * D;
+            Geom piece = g;
+            if (g.add_dq) piece.add_dq += bh * m * D;
+            kernel<<<dim3((unsigned)(slices * g.kv_group * wgs)), block,
+                     flat_table_bytes(g, g.n_select + 1), stream>>>(
+                (const T*)q + row * D, (const T*)k + kv, (const T*)v + kv, (const T*)dout + row * D,
+                lse2 + row, delta + row, sel_idx + bh * m * g.n_select, (T*)dq + row * D, piece,
+                (uint32_t)slices, rows.chunks, WaveTile<T>::ROWS * nw);
+            return hipGetLastError();
+        });
     };
     // `order` may lie where dQ goes; without it dK and dV may lie where k and v are
     const hipError_t e = order ? run_dkdv() : run_dq();

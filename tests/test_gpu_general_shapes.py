@@ -454,6 +454,44 @@ def test_general_more_than_2_32_work_items(G, batch):
         assert x.float().abs().max() <= 32 * 2.0 ** -19
 
 
+def test_general_backward_more_than_2_32_work_items(G):
+    """2^25 blocks of 17 tokens, two to a slice that both attend to all of it, 128 work items
+    each in dQ: more than one launch can have.  One buffer of 68 GiB serves as q, out and
+    dout, lse is 3.  Against the formulas in 64 bits for the first batch entries and the
+    last, which take another launch; bound of test_general_backward."""
+    import paper_2604_16429_amd as bsa
+    from paper_2604_16429_amd import binding
+    batch, heads, N, D = 1 << 18, 64, 34, 32
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 180 << 30:
+        pytest.skip("needs 180 GiB of device memory")
+    p = bsa.Params(batch, heads, N, 1, 17, 1, D, 1, binding.F32, 0.0, 1)
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    some = torch.randn((1021, N, D), generator=gen, device="cuda")      # q, repeated
+    q = torch.empty((batch, heads, N, D), device="cuda")
+    rows = q.view(-1, N, D)
+    for at in range(0, rows.shape[0], 1021 << 10):
+        part = rows[at:at + (1021 << 10)]
+        part.copy_(some.repeat(-(-part.shape[0] // 1021), 1, 1)[:part.shape[0]])
+    k, v = (torch.randn((batch, 1, N, D), generator=gen, device="cuda") for _ in range(2))
+    lse = torch.full((batch, heads, N), 3.0, device="cuda")
+    idx = torch.tensor([1, 0], dtype=torch.int32, device="cuda").repeat(batch * heads)
+    dq = torch.full_like(q, float("nan"))
+    dk, dv = (torch.full_like(k, float("nan")) for _ in range(2))
+    ws = torch.empty(bsa.mosaic_bsa_workspace_bytes(p, binding.OP_BWD), dtype=torch.uint8,
+                     device="cuda")
+    bsa.mosaic_bsa_bwd(p, q, k, v, q, lse, q, idx, dq, dk, dv, ws)
+    assert not any(torch.isnan(x.sum()) for x in (dq, dk, dv))
+    for e in (0, 1, batch - 2, batch - 1):
+        qe, ke, ve = (x[e].double() for x in (q, k, v))
+        w = torch.exp(qe @ ke[0].T / D ** 0.5 - 3.0)
+        ds = w * (qe @ ve[0].T - (qe * qe).sum(-1, keepdim=True)) / D ** 0.5
+        for name, x, r in (("dq", dq, ds @ ke[0]), ("dk", dk, (ds.transpose(1, 2) @ qe).sum(0)),
+                           ("dv", dv, (w.transpose(1, 2) @ qe).sum(0))):
+            err = (x[e].double() - r).abs().max()
+            assert err <= 1e-4 * r.abs().max(), f"{name} of entry {e}: {err}"
+
+
 @pytest.mark.parametrize("dtype,H,W,D,grouped", [
     ("fp32", 2048, 2064, 128, False), ("fp32", 1024, 2064, 128, True),
     ("bf16", 4096, 4128, 64, False), ("bf16", 4096, 4128, 32, True),
