@@ -168,6 +168,10 @@ int mosaic_bsa_select_static(const mosaic_bsa_params *params, const void *q, con
  *                  alias an input.
  *   lse       out  device, fp32 [B, heads, N]; may be NULL.
  *   workspace      unused by this op (may be NULL with workspace_bytes 0).
+ * The same call gives the same bits from run to run.  They may differ between calls
+ * that hold different numbers of slices: small calls in fp32, and in bf16 where the
+ * general kernels run, sum a row's keys in two or four groups (results within the
+ * rounding of fp32 sums of each other).
  */
 int mosaic_bsa_fwd(const mosaic_bsa_params *params, const void *q, const void *k,
                    const void *v, const int32_t *sel_idx, void *out, float *lse,

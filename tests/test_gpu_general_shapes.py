@@ -51,10 +51,25 @@ def inputs_of(cfg, seed):
     return q, k, v
 
 
+def times(cfg, groups, *tensors):
+    """One entry as often as it takes for a launch of up to 256 row wavefronts, of up to 512
+    or more, which is where four, two groups or one take the keys of long enough lists."""
+    rows, most = (16, 4 if cfg.head_dim == 32 else 8) if cfg.dtype == "fp32" else (32, 8)
+    tiles = -(-cfg.block_tokens // rows)
+    chunks = -(-tiles // most)
+    per_entry = cfg.heads * cfg.n_blocks * chunks * -(-tiles // chunks)
+    cfg.batch = {4: 256 // per_entry, 2: 512 // per_entry, 1: 512 // per_entry + 1}[groups]
+    low, high = {4: (0, 256), 2: (256, 512), 1: (512, 1 << 30)}[groups]
+    assert low < cfg.batch * per_entry <= high
+    return [np.repeat(x, cfg.batch, axis=0) for x in tensors]
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("large", [False, True])
 @pytest.mark.parametrize("H,W,bh,bw,D,n", SHAPES)
-def test_general_forward(G, oracle, dtype, H, W, bh, bw, D, n):
-    """fp32: 1e-5 of the largest output, lse likewise.  bf16: the output is one
+def test_general_forward(G, oracle, large, dtype, H, W, bh, bw, D, n):
+    """large: the entry as often as it takes for the workgroups of a launch that does not
+    split the keys.  fp32: 1e-5 of the largest output, lse likewise.  bf16: the output is one
     rounding (half an ulp: at most 2^-8 of the value) of a sum whose weights are
     kept as two bf16 terms (truncated to 2^-7, the rest rounded to 2^-8 of itself:
     2^-15 of the largest value; twice that covers the fp32 sums as well)."""
@@ -63,7 +78,7 @@ def test_general_forward(G, oracle, dtype, H, W, bh, bw, D, n):
     s = oracle.shape_of(cfg)
     idx = random_selection(cfg, 7)
     out_ref, lse_ref = oracle.fwd(s, q, k, v, idx)
-    out, lse = G.gpu_fwd(cfg, q, k, v, idx)
+    out, lse = G.gpu_fwd(cfg, *(times(cfg, 1, q, k, v, idx) if large else (q, k, v, idx)))
     err = np.abs(out - out_ref)
     if dtype == "fp32":
         assert err.max() <= 1e-5 * np.abs(out_ref).max()
@@ -72,46 +87,84 @@ def test_general_forward(G, oracle, dtype, H, W, bh, bw, D, n):
     assert np.abs(lse - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
 
 
-@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("wavefronts", [400, 600])
-@pytest.mark.parametrize("H,W,bh,bw,D,n", [
-    (9, 12, 3, 3, 64, 6),        # 63 keys: fewer tiles than groups
-    (10, 13, 5, 1, 128, 12),     # 65 keys
-    (22, 33, 11, 3, 32, 3),      # b = 33
-    (14, 57, 7, 19, 64, 4),      # b = 133
-    (46, 48, 1, 2, 32, 1030),    # long lists
+@pytest.mark.parametrize("groups", [4, 2, 1])
+@pytest.mark.parametrize("dtype,H,W,bh,bw,D,n", [
+    ("fp32", 9, 12, 3, 3, 64, 6),          # 63 keys: two tiles, in two groups
+    ("fp32", 10, 20, 5, 5, 32, 7),         # 200: seven, the last round of four not full
+    ("bf16", 16, 28, 8, 7, 32, 7),         # 448: seven
+    ("bf16", 12, 30, 2, 15, 64, 7),        # 240: four, in two groups of one wavefront
+    ("fp32", 22, 33, 11, 3, 32, 13),       # b = 33
+    ("bf16", 22, 33, 11, 3, 64, 13),
+    ("fp32", 14, 57, 7, 19, 64, 4),        # b = 133
+    ("bf16", 16, 60, 8, 15, 64, 4),        # b = 120
+    ("fp32", 16, 28, 8, 7, 128, 7),        # two groups at the most
+    ("bf16", 16, 28, 8, 7, 128, 7),
+    ("fp32", 12, 44, 2, 4, 32, 64),        # 65 listed blocks: in the given order
+    ("bf16", 12, 44, 2, 4, 32, 64),
 ])
-def test_general_forward_key_split(G, oracle, dtype, wavefronts, H, W, bh, bw, D, n):
-    """Launches of up to 256, up to 512 and more row wavefronts (16 rows in fp32, 32 in
-    bf16) take the keys in four groups, two or one: the same entry as often as it takes.
-    All copies agree exactly, and with the oracle as in test_general_forward."""
-    cfg = shape_ns(1, 2, H, W, bh, bw, D, min(n, (H // bh) * (W // bw) - 1), dtype)
+def test_general_forward_key_split(G, oracle, dtype, groups, H, W, bh, bw, D, n):
+    """Launches that take the keys in four groups, two or one.  All copies of the entry
+    agree exactly, and with the oracle as in test_general_forward; the bits tell that the
+    small launches did split (see test_general_forward_unsplit_small_launches) and stay
+    within those bounds of the large launch's (bf16: two roundings of the output)."""
+    cfg = shape_ns(1, 1, H, W, bh, bw, D, min(n, (H // bh) * (W // bw) - 1), dtype)
     q, k, v = inputs_of(cfg, 70 + H + W + D)
     idx = random_selection(cfg, 9)
     out_ref, lse_ref = oracle.fwd(oracle.shape_of(cfg), q, k, v, idx)
-    per_entry = 2 * cfg.n_blocks * -(-cfg.block_tokens // (16 if dtype == "fp32" else 32))
-    cfg.batch = -(-wavefronts // per_entry)
-    copies = lambda x: np.repeat(x, cfg.batch, axis=0)
-    out, lse = G.gpu_fwd(cfg, copies(q), copies(k), copies(v), copies(idx))
-    assert (out == out[:1]).all() and (lse == lse[:1]).all()
+    out, lse = G.gpu_fwd(cfg, *times(cfg, groups, q, k, v, idx))
+    assert cfg.batch > 1 and (out == out[:1]).all() and (lse == lse[:1]).all()
     err, top = np.abs(out[:1] - out_ref), np.abs(out_ref).max()
     if dtype == "fp32":
         assert err.max() <= 1e-5 * top
     else:
         assert (err <= 2.0 ** -8 * np.abs(out_ref) + 2.0 ** -14 * np.abs(v).max()).all()
     assert np.abs(lse[:1] - lse_ref).max() <= 1e-5 * max(1.0, np.abs(lse_ref).max())
+    whole = G.gpu_fwd(cfg, *times(cfg, 1, q, k, v, idx))
+    assert np.array_equal(whole[1][0], lse[0]) == (groups == 1)
+    apart = np.abs(whole[0][0] - out[0])
+    if dtype == "fp32":
+        assert apart.max() <= 1e-5 * top
+    else:
+        assert (apart <= 2.0 ** -7 * np.abs(out_ref) + 2.0 ** -13 * np.abs(v).max()).all()
 
 
+@pytest.mark.parametrize("groups", [4, 2, 1])
+@pytest.mark.parametrize("dtype,D", [("fp32", 32), ("fp32", 64), ("fp32", 128),
+                                     ("bf16", 32), ("bf16", 64), ("bf16", 128)])
+def test_general_forward_rising_maxima(G, oracle, dtype, D, groups):
+    """Scores of up to about 80 whose maxima grow with the block index, so that the
+    reference of the softmax moves at most tiles.  A score is off by up to
+    2^-24 (sqrt(D / 12) + 1) of its value, 2.1e-5, and a weight by that of two: 1e-4 of the
+    largest output (bf16: on top of the bound of test_general_forward) and of lse."""
+    cfg = shape_ns(1, 1, 24, 36, 6, 6, D, 15, dtype)
+    q, k, v = inputs_of(cfg, 33 + D)
+    grow = (1.0 + 6.0 * np.arange(24) / 23).astype(np.float32).reshape(4, 1, 6, 1, 1)
+    k = (k.reshape(4, 6, 6, 6, D) * grow).reshape(k.shape)
+    q = 3.0 * q
+    if dtype == "bf16":
+        q, k = round_to_bf16(q), round_to_bf16(k)
+    idx = random_selection(cfg, 34)
+    out_ref, lse_ref = oracle.fwd(oracle.shape_of(cfg), q, k, v, idx)
+    assert np.abs(lse_ref).max() > 40.0
+    out, lse = G.gpu_fwd(cfg, *times(cfg, groups, q, k, v, idx))
+    err, bound = np.abs(out - out_ref), 1e-4 * np.abs(out_ref).max()
+    if dtype == "bf16":
+        bound = bound + 2.0 ** -8 * np.abs(out_ref) + 2.0 ** -14 * np.abs(v).max()
+    assert (err <= bound).all()
+    assert np.abs(lse - lse_ref).max() <= 1e-4 * max(1.0, np.abs(lse_ref).max())
+
+
+@pytest.mark.parametrize("large", [False, True])
 @pytest.mark.parametrize("mask", [-1e10, -1e30, -3e38])
 @pytest.mark.parametrize("dtype,H,W,bh,bw,D", [
     ("fp32", 10, 20, 5, 5, 32), ("fp32", 16, 32, 8, 8, 64), ("fp32", 10, 20, 5, 5, 128),
     ("bf16", 16, 32, 8, 8, 32), ("bf16", 10, 20, 5, 5, 64), ("bf16", 10, 20, 5, 5, 128),
 ])
-def test_general_forward_finite_masks(G, oracle, dtype, H, W, bh, bw, D, mask):
+def test_general_forward_finite_masks(G, oracle, dtype, H, W, bh, bw, D, mask, large):
     """Keys masked by a large finite score through a channel of their own.  Masked: the
     first tiles of a row, the last ones, and all of them (block 0: the weights are
     then equal; only for masks beside which the other channels vanish in 64 bits as
-    they do in 32).  Bounds of test_general_forward."""
+    they do in 32).  `large` and bounds as in test_general_forward."""
     cfg = shape_ns(1, 2, H, W, bh, bw, D, 2, dtype)
     q, k, v = inputs_of(cfg, 3 + D)
     rows, cols = H // bh, W // bw
@@ -126,7 +179,7 @@ def test_general_forward_finite_masks(G, oracle, dtype, H, W, bh, bw, D, mask):
     idx[:, :, 1] = [0, cols]
     idx[:, :, cols] = [0, cols + 1]
     out_ref, lse_ref = oracle.fwd(oracle.shape_of(cfg), q, k, v, idx)
-    out, lse = G.gpu_fwd(cfg, q, k, v, idx)
+    out, lse = G.gpu_fwd(cfg, *(times(cfg, 1, q, k, v, idx) if large else (q, k, v, idx)))
     keep = np.ones((H, W), dtype=bool)
     if mask > -1e20:
         keep[:bh, :bw] = False
@@ -139,17 +192,6 @@ def test_general_forward_finite_masks(G, oracle, dtype, H, W, bh, bw, D, mask):
     lse_err = np.abs(lse - lse_ref) / np.maximum(1.0, np.abs(lse_ref))
     assert lse_err[:, :, keep].max() <= 1e-5
     assert np.isfinite(out).all() and np.isfinite(lse).all()
-
-
-def times(cfg, groups, *tensors):
-    """One entry as often as it takes for a launch of up to 256 row wavefronts (four groups
-    share the keys of a wavefront's rows), of up to 512 (two) or more (one)."""
-    rows = 16 if cfg.dtype == "fp32" else 32
-    per_entry = cfg.heads * cfg.n_blocks * -(-cfg.block_tokens // rows)
-    cfg.batch = {4: 256 // per_entry, 2: 512 // per_entry, 1: 512 // per_entry + 1}[groups]
-    low, high = {4: (0, 256), 2: (256, 512), 1: (512, 1 << 30)}[groups]
-    assert low < cfg.batch * per_entry <= high
-    return [np.repeat(x, cfg.batch, axis=0) for x in tensors]
 
 
 @pytest.mark.parametrize("groups", [4, 2, 1])
