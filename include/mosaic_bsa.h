@@ -196,8 +196,7 @@ int mosaic_bsa_fwd(const mosaic_bsa_params *params, const void *q, const void *k
  *                            block, key block)).  dq serves as scratch before it
  *                            is written.
  * Memory that gradients may share with an input, whole tensors only: dq with out
- * (which then is lost), dk with k and dv with v.  With bf16 at head dim 128 dv may
- * share none.  Everything else must not overlap.
+ * (which then is lost), dk with k and dv with v.  Everything else must not overlap.
  * dk/dv of a key block are reduced over the query blocks that attend to it in
  * a fixed order (no floating-point atomics): results are run-to-run identical.
  */
