@@ -15,11 +15,11 @@
 // the matrix cores (fp32 and bf16, head dim 32, 64 or 128, any tile of up to 1024
 // tokens), with the tiles, products and precision of the general forward: the
 // rows of the other side are walked as one flat sequence (bsa_flat_rows.h).
-//   bwd_generic_dq    a wavefront owns 32 query rows, walks the attended keys:
+//   bwd_generic_dq    a wavefront owns 32 query rows (fp32: 16), walks the attended keys:
 //                     S^T = K Q^T and dP^T = V dO^T (a lane holds one query: lse
 //                     and delta are scalars of the lane, -delta is the accumulator
 //                     that dP^T starts from), dQ^T += K^T dS^T.
-//   bwd_generic_dkdv  a wavefront owns 32 rows of a key block, walks the rows of
+//   bwd_generic_dkdv  a wavefront owns 32 (16) rows of a key block, walks the rows of
 //                     the query blocks connected to it: S = Q K^T, dP = dO V^T,
 //                     dV^T += dO^T P, dK^T += Q^T dS.  The blocks are listed in
 //                     ascending order per query head, heads of a group ascending:
@@ -335,13 +335,12 @@ hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* o
 template <typename T, int D> struct BwdLimits {
     static constexpr bool WIDE = sizeof(T) == 2 && D == 128;
     static constexpr int MAX_WAVES = WIDE || sizeof(T) == 4 ? 4 : 8;
-    static constexpr int DQ = WIDE ? 1 : sizeof(T) == 4 && D < 128 ? 3 : 2;
-    static constexpr int DKDV = WIDE ? 1 : sizeof(T) == 4 && D < 128 ? 3 : 2;
+    static constexpr int PER_SIMD = WIDE ? 1 : sizeof(T) == 4 && D < 128 ? 3 : 2;
 };
 
 template <typename T, int D, int NL>
 __global__ __launch_bounds__(NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
-                             NL == 1 ? 1 : (BwdLimits<T, D>::DQ))
+                             NL == 1 ? 1 : (BwdLimits<T, D>::PER_SIMD))
 void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                     const T* __restrict__ dout, const float* __restrict__ lse2,
                     const float* __restrict__ delta, const int32_t* __restrict__ sel_idx,
@@ -440,7 +439,7 @@ constexpr int kConnCap = 2048;
 
 template <typename T, int D, int NL>
 __global__ __launch_bounds__(NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
-                             NL == 4 ? (BwdLimits<T, D>::DKDV) : NL == 2 && D < 128 ? 2 : 1)
+                             NL == 4 ? (BwdLimits<T, D>::PER_SIMD) : NL == 2 && D < 128 ? 2 : 1)
 void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                       const T* __restrict__ dout, const float* __restrict__ lse2,
                       const float* __restrict__ delta, const uint32_t* __restrict__ conn,
@@ -491,7 +490,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     TileReader<T, D> rd;
     rd.init(lane);
 
-    // this wavefront's 32 key rows.  V enters negated: the accumulator that starts
+    // this wavefront's key rows.  V enters negated: the accumulator that starts
     // from delta then ends as delta - dP without an instruction per element, and
     // dK is stored with the sign turned.
     const int tau_k = row0 + W::ROWS * wave + col;

@@ -148,18 +148,6 @@ __device__ __forceinline__ bf16x8 trans_frag(const unsigned char* tile, int row0
     return __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// 16 fp32 accumulator values -> two bf16 B operands (round to nearest even)
-__device__ __forceinline__ void pack_tile(const f32x16& x, bf16x8 (&b)[2])
-{
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-        b[h] = __builtin_bit_cast(
-            bf16x8, make_uint4(pack_bf16(x[8 * h + 0], x[8 * h + 1]),
-                               pack_bf16(x[8 * h + 2], x[8 * h + 3]),
-                               pack_bf16(x[8 * h + 4], x[8 * h + 5]),
-                               pack_bf16(x[8 * h + 6], x[8 * h + 7])));
-}
-
 __device__ __forceinline__ f32x16 zero_tile()
 {
     const f32x16 z = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
@@ -274,7 +262,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
         //       S^T, dP^T of half 1 (8 slots)      | dS^T of half 0
         //   G3  dQ^T += K^T dS^T of half 0 (4 slots)
         // Carried between tiles: S^T, dP^T of half 1 and its transposed K
-        // fragments.  The sums run in the same order as in the plain loop below.
+        // fragments.
         f32x16 s1, dp1;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { s1[r] = -1.0e30f; dp1[r] = 0.0f; }   // weights 0

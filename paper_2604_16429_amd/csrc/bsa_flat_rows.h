@@ -138,7 +138,7 @@ __device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint3
 //   fp32: 16, v_mfma_f32_16x16x4_f32: the same rate as 32x32x2 (64 operations per cycle
 //         and SIMD) with half the registers, so that twice as many wavefronts share a
 //         block: a chain of products that depend on each other is half as long, and four
-//         (dK/dV three) wavefronts per SIMD instead of two cover it.
+//         (backward three) wavefronts per SIMD instead of two cover it.
 template <typename T> struct WaveTile;
 template <> struct WaveTile<uint16_t> {
     static constexpr int ROWS = 32, NR = 16, STEP = 8;

@@ -51,11 +51,11 @@ constexpr float kPlainRef = 1048576.0f;
 // NL: wavefronts that issue the gathers (1, 2 or 4; the workgroup has at least
 // that many, up to 8).  row_chunks workgroups share a query block's rows,
 // chunk_rows each.
-// SPLIT > 1: as many groups of wavefronts (4 at most in each) own the same rows and take
+// SPLIT > 1: as many groups of one or two (NL) wavefronts own the same rows and take
 // the key tiles in turn, with tiles and a softmax of their own; the first group merges them
 // at the end.  For launches that leave the chip idle; see key_split.
 template <typename T, int D, int NL, int SPLIT>
-__global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * (NL == 2 ? 3 : NL) : NL == 4 ? 512 : NL == 2 ? 192 : 64,
+__global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL : NL == 4 ? 512 : NL == 2 ? 192 : 64,
                              SPLIT > 1 || NL == 1 || (NL == 2 && D == 128) ? 1
                              : D == 32 || (sizeof(T) == 4 && D == 128) ? 4 : 2)
 void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
@@ -95,7 +95,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     AttendedKeys<T, D, NL, SPLIT> keys;
     keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave, group);
 
-    // this wavefront's 32 query rows
+    // this wavefront's query rows
     const int tau_q = row0 + W::ROWS * wave + col;
     const bool valid = tau_q < min(b, row0 + chunk_rows);
     const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
@@ -187,7 +187,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     if constexpr (SPLIT > 1) {
         // groups 1 .. hand over what they have, lane by lane; the first group adds it up
         constexpr int VALUES = (int)sizeof(Column<T, D>) / 4 + 3;
-        static_assert((SPLIT - 1) * (NL == 2 ? 3 : NL) * VALUES * 256 <= SPLIT * 2 * Tile::TILE_BYTES * 2,
+        static_assert((SPLIT - 1) * NL * VALUES * 256 <= SPLIT * 2 * Tile::TILE_BYTES * 2,
                       "fits the tiles");
         constexpr int HALF = SPLIT * 2 * Tile::TILE_BYTES / 256;       // values per array and lane
         auto place = [&](int of_group, int value) -> float* {

@@ -454,20 +454,18 @@ def test_backward_matrix_core_shapes(G, oracle, H, W, bh, bw, D, n):
 
 
 @pytest.mark.parametrize("H,W,bh,bw,D,n,sel_seed", [
-    (96, 128, 8, 8, 64, 5, 43),      # 64-token blocks: rounds of 128 query blocks, m = 192
-    (136, 256, 8, 16, 128, 3, 44),   # 128-token blocks, head dim 128: rounds of 256, m = 272
+    (96, 128, 8, 8, 64, 5, 43),      # 64-token blocks, m = 192
+    (136, 256, 8, 16, 128, 3, 44),   # 128-token blocks, head dim 128, m = 272
     (34, 1024, 1, 128, 64, 4, 45),   # block-contiguous 128-token blocks, head dim 64, m = 272
-    (384, 384, 16, 16, 64, 1, 46),   # 256-token blocks: rounds of 512, m = 576
+    (384, 384, 16, 16, 64, 1, 46),   # 256-token blocks, m = 576
     (72, 80, 8, 8, 64, 70, 47),      # n > 64: the attended blocks do not fit one wavefront
-    (40, 128, 8, 8, 64, 0, 0),       # n = 0 with several rounds: only the own block is connected
+    (40, 128, 8, 8, 64, 0, 0),       # n = 0: only the own block is connected
 ])
-def test_backward_with_more_query_blocks_than_one_scan_round(G, oracle, H, W, bh, bw, D, n,
-                                                             sel_seed):
-    """The dK/dV kernels collect the query blocks connected to a key block in
-    rounds of 64 x (wavefronts per workgroup) candidates; these shapes need two
-    or more rounds per key block (the benchmark configurations need four to
-    eight), and one of them has more attended blocks than a wavefront has
-    lanes.  Arbitrary valid selections in random order."""
+def test_backward_with_many_query_blocks(G, oracle, H, W, bh, bw, D, n, sel_seed):
+    """The dK/dV kernels list the query blocks connected to a key block from the words of
+    the reverse map, 32 query blocks each: several words per key block (the last one not
+    full), and more attended blocks than a wavefront has lanes.  Arbitrary valid selections
+    in random order; lists that do not fit at once: test_backward_long_connected_lists."""
     cfg = shape_ns(1, 2, H, W, bh, bw, D, n, "bf16")
     q, k, v = (round_to_bf16(x) for x in rand_qkv(cfg, 950 + bh + D + n))
     dout = round_to_bf16(rand_qkv(cfg, 951 + bh + D + n)[0])
