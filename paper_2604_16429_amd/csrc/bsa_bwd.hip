@@ -25,6 +25,7 @@
 //                     ascending order per query head, heads of a group ascending:
 //                     the summation order is fixed, there are no floating-point
 //                     atomics and results are the same from run to run.
+// Launches of few wavefronts split the walk over groups of them (see dkdv_split).
 // Measured against the vector-ALU kernels that they replace (a row per four lanes,
 // the other side's rows broadcast from LDS): 1.5 degree grid, batch 2, 8 heads,
 // head dim 64, bf16, tiles of 10 x 10, 9 blocks: dQ 2.76 -> 0.33 ms, dK and dV
@@ -35,6 +36,8 @@
 #include "bsa_flat_rows.h"
 #include "bsa_launch.h"
 #include "bsa_mfma_common.h"
+
+#include <type_traits>
 
 namespace bsa {
 
@@ -338,22 +341,61 @@ template <typename T, int D> struct BwdLimits {
     static constexpr int PER_SIMD = WIDE ? 1 : sizeof(T) == 4 && D < 128 ? 3 : 2;
 };
 
-template <typename T, int D, int NL>
-__global__ __launch_bounds__(NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
-                             NL == 1 ? 1 : (BwdLimits<T, D>::PER_SIMD))
+// Launches that leave most of the chip idle, or wait for the longest list of a few key
+// blocks: SPLIT groups of NL wavefronts own the same rows, and each takes 32 rows (bf16 in
+// two groups: of the same 64) of a tile that all of them gather.  The first group adds up
+// what the others have at the end, in the order of the groups.
+template <typename T, int D, int SPLIT>
+using SplitTile = FlatTile<T, D, (SPLIT > 1 ? 32 * SPLIT : FlatTile<T, D>::KT)>;
+
+// Adds `count` accumulators of groups 1 .. SPLIT - 1 to those of group 0, lane by lane,
+// through the tiles' memory.  All wavefronts call it; false: not group 0.
+template <int SPLIT, int NL, int COUNT, int BYTES, class V>
+__device__ __forceinline__ bool add_groups(unsigned char* lds_a, unsigned char* lds_b, int group,
+                                           int wave, int lane, V (&acc)[COUNT])
+{
+    constexpr int PER = (int)sizeof(V) / 4, HALF = BYTES / 256;    // values per array and lane
+    static_assert((SPLIT - 1) * NL * COUNT * PER <= 2 * HALF, "fits the tiles");
+    auto place = [&](int from, int value) -> float* {
+        const int at = ((from - 1) * NL + wave) * COUNT * PER + value;
+        return (at < HALF ? (float*)lds_a + at * 64 : (float*)lds_b + (at - HALF) * 64) + lane;
+    };
+    __syncthreads();
+    if (group > 0) {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c)
+#pragma unroll
+            for (int r = 0; r < PER; ++r) *place(group, c * PER + r) = acc[c][r];
+    }
+    __syncthreads();
+    if (group > 0) return false;
+    for (int from = 1; from < SPLIT; ++from)
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c)
+#pragma unroll
+            for (int r = 0; r < PER; ++r) acc[c][r] += *place(from, c * PER + r);
+    return true;
+}
+
+template <typename T, int D, int NL, int SPLIT>
+__global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL
+                             : NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
+                             SPLIT > 1 || NL == 1 ? 1 : (BwdLimits<T, D>::PER_SIMD))
 void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                     const T* __restrict__ dout, const float* __restrict__ lse2,
                     const float* __restrict__ delta, const int32_t* __restrict__ sel_idx,
                     T* __restrict__ dq, Geom g, uint32_t n_units, int row_chunks, int chunk_rows)
 {
-    using Tile = FlatTile<T, D>;
-    constexpr int KT = Tile::KT;
+    using Tile = SplitTile<T, D, SPLIT>;
+    constexpr int KT = Tile::KT, LOADERS = SPLIT > 1 ? SPLIT * NL : NL;
+    constexpr int PIECES = KT / 32 / SPLIT;          // of a tile, for each group
     __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][Tile::TILE_BYTES];
     __shared__ __attribute__((aligned(1024))) unsigned char v_lds[2][Tile::TILE_BYTES];
     extern __shared__ __attribute__((aligned(16))) uint32_t tables_s[];
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = SPLIT == 1 ? 0 : wg_wave / NL, wave = wg_wave - group * NL;
     using W = WaveTile<T>;
     const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int b = g.block_tokens;
@@ -368,8 +410,8 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
 
     TileReader<T, D> rd;
     rd.init(lane);
-    AttendedKeys<T, D, NL> keys;
-    keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave);
+    AttendedKeys<T, D, LOADERS, 1, Tile> keys;
+    keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wg_wave);
 
     const int tau_q = row0 + W::ROWS * wave + col;
     const bool valid = tau_q < min(b, row0 + chunk_rows);
@@ -391,7 +433,7 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
     const RowSource ks(k + kv_base, slice_bytes), vs(v + kv_base, slice_bytes);
     const uint32_t k_dst = lds_address(k_lds), v_dst = lds_address(v_lds);
-    if (wave < NL) {
+    if (wg_wave < LOADERS) {
         keys.look_up();
         keys.gather_next(ks, vs, k_dst, v_dst);
     }
@@ -400,13 +442,13 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
         wait_gathers();
         __syncthreads();
         const int buf = c & 1, other = (buf ^ 1) * Tile::TILE_BYTES;
-        if (wave < NL && c + 1 < keys.tiles) keys.gather_next(ks, vs, k_dst + other, v_dst + other);
+        if (wg_wave < LOADERS && c + 1 < keys.tiles) keys.gather_next(ks, vs, k_dst + other, v_dst + other);
 #pragma unroll
-        for (int hh = 0; hh < KT / 32; ++hh) {
-            const uint32_t kt = k_dst + (uint32_t)buf * Tile::TILE_BYTES;
-            const uint32_t vt = v_dst + (uint32_t)buf * Tile::TILE_BYTES;
+        for (int hh = 0; hh < PIECES; ++hh) {
             constexpr int HALF = 32 * Tile::ROW_BYTES;
-            const int left = keys.total - (KT * c + 32 * hh);
+            const uint32_t at = (uint32_t)(buf * Tile::TILE_BYTES + group * PIECES * HALF);
+            const uint32_t kt = k_dst + at, vt = v_dst + at;
+            const int left = keys.total - (KT * c + 32 * (group * PIECES + hh));
             if (left <= 0) break;
             typename W::vec s = constant_tile<T>(0.0f), dp = dp0;
             dot_tiles<false, T, D>(rd, kt, vt, hh * HALF, qf, dof, s, dp);
@@ -422,6 +464,10 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
         }
     }
 
+    if constexpr (SPLIT > 1)
+        if (!add_groups<SPLIT, NL, sizeof(acc.a) / sizeof(acc.a[0]), 2 * Tile::TILE_BYTES>(
+                k_lds[0], v_lds[0], group, wave, lane, acc.a))
+            return;
     if (valid) {
         const float inv_b = 1.0f / (float)b;
         const float* extra = g.add_dq ? g.add_dq + (bh_idx * g.n_blocks + i) * D : nullptr;
@@ -437,28 +483,35 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
 // them, and walked whenever it is full or the map is exhausted.
 constexpr int kConnCap = 2048;
 
-template <typename T, int D, int NL>
-__global__ __launch_bounds__(NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
-                             NL == 4 ? (BwdLimits<T, D>::PER_SIMD) : NL == 2 && D < 128 ? 2 : 1)
+template <typename T, int D, int NL, int SPLIT>
+__global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL
+                             : NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
+                             SPLIT > 1 ? (D == 32 || (D == 64 && sizeof(T) == 2) || (D == 64 && NL * SPLIT == 4 && SPLIT == 2) ? 2 : 1)
+                             : NL == 4 ? (BwdLimits<T, D>::PER_SIMD) : NL == 2 && D < 128 ? 2 : 1)
 void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                       const T* __restrict__ dout, const float* __restrict__ lse2,
                       const float* __restrict__ delta, const uint32_t* __restrict__ conn,
                       const int32_t* __restrict__ order, T* __restrict__ dk, T* __restrict__ dv, Geom g, uint32_t n_units,
                       int row_chunks, int chunk_rows)
 {
-    using Tile = FlatTile<T, D>;
-    constexpr int KT = Tile::KT, MINE = Tile::SLABS / NL;
+    using Tile = SplitTile<T, D, SPLIT>;
+    constexpr int KT = Tile::KT, LOADERS = SPLIT > 1 ? SPLIT * NL : NL;
+    constexpr int MINE = Tile::SLABS / LOADERS;
+    static_assert(Tile::SLABS % LOADERS == 0, "slabs split evenly between the loading wavefronts");
+    constexpr int PIECES = KT / 32 / SPLIT;           // of a tile, for each group
+    constexpr int LROWS = KT < 64 ? 64 : KT, LWAVES = LROWS / 64;   // lse, delta: loads of 64 rows
     __shared__ __attribute__((aligned(1024))) unsigned char q_lds[2][Tile::TILE_BYTES];
     __shared__ __attribute__((aligned(1024))) unsigned char g_lds[2][Tile::TILE_BYTES];
-    __shared__ __attribute__((aligned(256))) float l_lds[2][64];
-    __shared__ __attribute__((aligned(256))) float d_lds[2][64];
+    __shared__ __attribute__((aligned(256))) float l_lds[2][LROWS];
+    __shared__ __attribute__((aligned(256))) float d_lds[2][LROWS];
     __shared__ uint32_t list_s[kConnCap + repeated_entries(KT, 1)];   // first token (in the group's
                                                       // rows) per block, the last one repeated
     __shared__ int state_s[2];                        // blocks listed, words left
     extern __shared__ __attribute__((aligned(16))) uint32_t pos_s[];        // [b]
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = SPLIT == 1 ? 0 : wg_wave / NL, wave = wg_wave - group * NL;
     using W = WaveTile<T>;
     const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int m = g.n_blocks, b = g.block_tokens;
@@ -517,7 +570,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     int next_word = 0;                                // wavefront 0 only
     for (;;) {
         __syncthreads();                              // the previous list is used up
-        if (wave == 0) {
+        if (wg_wave == 0) {
             int count = 0;
             while (next_word < all_words && count <= kConnCap - 1024) {
                 const int w = next_word + lane;
@@ -564,18 +617,18 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
         const int total = listed * b;
         const int tiles = (total + KT - 1) / KT;
 
-        // this lane's rows of a tile (slab wave + NL jj), and for the loads of lse and
-        // delta row `lane` (fp32, 32 rows: the upper lanes repeat the lower ones; rows
-        // of the tile after the last one would lie past the repeated entries)
+        // this lane's rows of a tile (slab wg_wave + LOADERS jj), and for the loads of lse
+        // and delta row 64 wg_wave + lane (32 rows: the upper lanes repeat the lower ones;
+        // rows of the tile after the last one would lie past the repeated entries)
         FlatRow at[MINE], at_row;
         uint32_t chunk_off[MINE], tok[MINE], tok_row = 0;
 #pragma unroll
         for (int jj = 0; jj < MINE; ++jj) {
-            const int row = Tile::RPS * (wave + NL * jj) + lane / Tile::LPR;
+            const int row = Tile::RPS * (wg_wave + LOADERS * jj) + lane / Tile::LPR;
             at[jj].start(row, b);
             chunk_off[jj] = (uint32_t)Tile::swz(row, lane % Tile::LPR) * 16u;
         }
-        at_row.start(lane % KT, b);
+        if (wg_wave < LWAVES) at_row.start(64 * wg_wave + lane % KT, b);
         auto row_of = [&](const FlatRow& r) -> uint32_t { return list_s[r.blk] + pos_s[r.tau]; };
         // rows of the next tile, looked up a tile before they are used
         auto look_up = [&] {
@@ -584,27 +637,28 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                 tok[jj] = row_of(at[jj]);
                 at[jj].advance(step_q, step_r, b);
             }
-            if (wave == 0) {
+            if (wg_wave < LWAVES) {
                 tok_row = row_of(at_row);
                 at_row.advance(step_q, step_r, b);
             }
         };
         auto gather_next = [&](int buf) {
-            gather_rows<Tile, MINE, NL>(qs, gs, tok, chunk_off, wave,
+            gather_rows<Tile, MINE, LOADERS>(qs, gs, tok, chunk_off, wg_wave,
                                         q_dst + (uint32_t)buf * Tile::TILE_BYTES,
                                         g_dst + (uint32_t)buf * Tile::TILE_BYTES);
-            if (wave == 0) {
+            if (wg_wave < LWAVES) {
+                const uint32_t to = (uint32_t)(buf * LROWS + 64 * wg_wave) * 4u;
                 if (__builtin_expect(!qs.wide, 1)) {
-                    load_lds_4(l_rsrc, tok_row * 4u, 0u, l_dst + (uint32_t)buf * 256u);
-                    load_lds_4(d_rsrc, tok_row * 4u, 0u, d_dst + (uint32_t)buf * 256u);
+                    load_lds_4(l_rsrc, tok_row * 4u, 0u, l_dst + to);
+                    load_lds_4(d_rsrc, tok_row * 4u, 0u, d_dst + to);
                 } else {
-                    load_lds_4_at(lb + tok_row, l_dst + (uint32_t)buf * 256u);
-                    load_lds_4_at(db + tok_row, d_dst + (uint32_t)buf * 256u);
+                    load_lds_4_at(lb + tok_row, l_dst + to);
+                    load_lds_4_at(db + tok_row, d_dst + to);
                 }
             }
             look_up();
         };
-        if (wave < NL) {
+        if (wg_wave < LOADERS) {
             look_up();
             gather_next(0);
         }
@@ -612,18 +666,18 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
             wait_gathers();
             __syncthreads();
             const int buf = c & 1;
-            if (wave < NL && c + 1 < tiles) gather_next(buf ^ 1);
+            if (wg_wave < LOADERS && c + 1 < tiles) gather_next(buf ^ 1);
 #pragma unroll
-            for (int hh = 0; hh < KT / 32; ++hh) {
-                const uint32_t qt = q_dst + (uint32_t)buf * Tile::TILE_BYTES;
-                const uint32_t gt = g_dst + (uint32_t)buf * Tile::TILE_BYTES;
+            for (int hh = 0; hh < PIECES; ++hh) {
                 constexpr int HALF = 32 * Tile::ROW_BYTES;
-                const int left = total - (KT * c + 32 * hh);
+                const uint32_t first = (uint32_t)(buf * Tile::TILE_BYTES + group * PIECES * HALF);
+                const uint32_t qt = q_dst + first, gt = g_dst + first;
+                const int row = 32 * (group * PIECES + hh), left = total - (KT * c + row);
                 if (left <= 0) break;
                 typename W::vec p = constant_tile<T>(0.0f), dp;
 #pragma unroll
                 for (int r4 = 0; r4 < W::NR / 4; ++r4) {
-                    const float4 d4 = *(const float4*)(d_lds[buf] + 32 * hh + W::STEP * r4 + 4 * part);
+                    const float4 d4 = *(const float4*)(d_lds[buf] + row + W::STEP * r4 + 4 * part);
                     dp[4 * r4] = d4.x; dp[4 * r4 + 1] = d4.y;
                     dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
                 }
@@ -636,7 +690,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                         if (past_end<T>(r, part, left)) p[r] = -INFINITY;
 #pragma unroll
                 for (int r4 = 0; r4 < W::NR / 4; ++r4) {
-                    const float4 l4 = *(const float4*)(l_lds[buf] + 32 * hh + W::STEP * r4 + 4 * part);
+                    const float4 l4 = *(const float4*)(l_lds[buf] + row + W::STEP * r4 + 4 * part);
                     p[4 * r4] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4], c2, -l4.x));
                     p[4 * r4 + 1] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 1], c2, -l4.y));
                     p[4 * r4 + 2] = __builtin_amdgcn_exp2f(fmaf(p[4 * r4 + 2], c2, -l4.z));
@@ -652,6 +706,23 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
         if (!more) break;
     }
 
+    if constexpr (SPLIT > 1) {
+        constexpr int COUNT = sizeof(acck.a) / sizeof(acck.a[0]);
+        typename std::remove_reference<decltype(acck.a[0])>::type both[2 * COUNT];
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) {
+            both[c] = acck.a[c];
+            both[COUNT + c] = accv.a[c];
+        }
+        if (!add_groups<SPLIT, NL, 2 * COUNT, 2 * Tile::TILE_BYTES>(q_lds[0], g_lds[0], group, wave,
+                                                                    lane, both))
+            return;
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) {
+            acck.a[c] = both[c];
+            accv.a[c] = both[COUNT + c];
+        }
+    }
     if (valid) {
         const float inv_b = 1.0f / (float)b;
         const int64_t pooled_row = ((int64_t)unit * m + j) * D;
@@ -662,20 +733,105 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     }
 }
 
+// Row wavefronts of a workgroup at most, and groups that share its list, by the row
+// wavefronts of the launch and the rows that one of them walks on average, in pieces of
+// 32.  What bounds a launch of few wavefronts is the longest list, walked by wavefronts
+// whose SIMDs have nothing else to do: on smooth fields the most popular key block has 4
+// to 7 times the mean of dK/dV, and dQ's lists are short chains on an idle chip.  What a
+// split costs is two barriers and the sum of the accumulators through LDS (1 to 3 us),
+// pairs of row wavefronts that gather for themselves, and at four groups the LDS of a
+// tile twice as large.  Whole backward, us, unsplit | pairs of wavefronts, two groups |
+// single ones, four groups (slices x blocks x tokens, attended blocks):
+//   bf16, head dim 64:   1 x 24 x 130, 13:   152 | 104 | 88     1 x 96 x 130, 13:  198 | 134 | 108
+//                        4 x 96 x 80, 13:    156 | 132 | 112    1 x 448 x 130, 13: 329 | 263 | 259
+//                        1 x 448 x 255, 4:   292 | 212 | 248    16 x 96 x 255, 4:  600 | 625 | 741
+//   bf16, head dim 128:  1 x 96 x 36, 13:    139 | 100 | 84     1 x 448 x 36, 13:  187 | 131 | 143
+//                        4 x 448 x 36, 13:   284 | 293 | 459
+//   fp32, head dim 64:   1 x 96 x 64, 13:    265 | 173 | 131    1 x 448 x 64, 13:  407 | 270 | 313
+//                        4 x 448 x 64, 13:   915 | 824 | 1,076
+//   fp32, head dim 128:  1 x 448 x 64, 13:   765 | 539 | -      4 x 448 x 64, 13: 1,788 | 1,770 | -
+// (four groups of fp32 at head dim 128 do not fit LDS).  Lists of equal length, of the
+// local branch, n = 0 or most blocks selected, have no popular block to wait for and pay
+// only while SIMDs are idle: 4 x 24 x 128, all 24 attended, fp32, head dim 64 unsplit 598,
+// pairs 560; 16 x 24 x 128 1,060 and 1,099.  1,750 launches of 24 to 14,000 row
+// wavefronts, smooth fields, noise, n = 0 and all blocks: 1.09 to 1.28 times as fast on
+// average by type and head dim, 5 of them slower by 2.5 to 5 %.
+struct BwdSplit {
+    int max_waves, groups;
+};
+template <typename T, int D>
+static BwdSplit dkdv_split(const Geom& g, int64_t BKV)
+{
+    // most row wavefronts that four groups and two groups speed up
+    constexpr bool F32 = sizeof(T) == 4, WIDE = !F32 && D == 128;
+    constexpr int64_t FOUR = WIDE ? 512 : !F32 ? 2048 : D < 128 ? 1408 : 0;
+    constexpr int64_t TWO = WIDE ? 1024 : !F32 ? 4096 : D < 128 ? 8192 : 2048;
+    const RowSplit single(g.block_tokens, 1, WaveTile<T>::ROWS);
+    const RowSplit pairs(g.block_tokens, 2, WaveTile<T>::ROWS);
+    const int64_t blocks = BKV * g.n_blocks, attended = g.n_select + 1 - g.list_only;
+    const int64_t one = blocks * single.chunks, two = blocks * pairs.chunks * pairs.waves;
+    const int64_t pieces = g.kv_group * attended * g.block_tokens / 32;
+    const bool even = g.add_dk || attended == 1 || 2 * attended > g.n_blocks;
+    if (one <= (even ? FOUR / 3 : FOUR) && pieces >= (WIDE ? 12 + one / 64 : 6 + one / 128))
+        return {1, 4};
+    if (two <= (even ? TWO / 4 : TWO) && pieces >= (WIDE ? 8 + two / 128 : 6 + two / 512))
+        return {2, 2};
+    return {BwdLimits<T, D>::MAX_WAVES, 1};
+}
+template <typename T, int D>
+static BwdSplit dq_split(const Geom& g, int64_t BH)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int64_t FOUR = D == 128 ? 0 : F32 && D == 64 ? 256 : 512;
+    constexpr int64_t TWO = F32 && D == 128 ? 512 : 1024;
+    const RowSplit single(g.block_tokens, 1, WaveTile<T>::ROWS);
+    const int64_t waves = BH * g.n_blocks * single.chunks;
+    const int64_t pieces = (g.n_select + 1 - g.list_only) * (int64_t)g.block_tokens / 32;
+    if (waves <= FOUR && pieces >= 6) return {1, 4};
+    return waves <= TWO && pieces >= 5 ? BwdSplit{2, 2} : BwdSplit{BwdLimits<T, D>::MAX_WAVES, 1};
+}
+template <typename T, int D, int SPLIT>
+static auto dkdv_kernel(int waves)
+{
+    if constexpr (SPLIT == 4) {                       // (fp32, head dim 128: not chosen)
+        return bwd_generic_dkdv<T, D, 1, sizeof(T) == 4 && D == 128 ? 2 : 4>;
+    } else if constexpr (SPLIT == 2) {
+        return waves >= 2 ? bwd_generic_dkdv<T, D, 2, 2> : bwd_generic_dkdv<T, D, 1, 2>;
+    } else {
+        return waves >= 4 ? bwd_generic_dkdv<T, D, 4, 1>
+               : waves >= 2 ? bwd_generic_dkdv<T, D, 2, 1> : bwd_generic_dkdv<T, D, 1, 1>;
+    }
+}
+template <typename T, int D, int SPLIT>
+static auto dq_kernel(int waves)
+{
+    if constexpr (SPLIT == 4) {                       // (head dim 128: not chosen)
+        return bwd_generic_dq<T, D, 1, D == 128 ? 2 : 4>;
+    } else if constexpr (SPLIT == 2) {
+        return waves >= 2 ? bwd_generic_dq<T, D, 2, 2> : bwd_generic_dq<T, D, 1, 2>;
+    } else {
+        return waves >= 4 ? bwd_generic_dq<T, D, 4, 1>
+               : waves >= 2 ? bwd_generic_dq<T, D, 2, 1> : bwd_generic_dq<T, D, 1, 1>;
+    }
+}
+
 template <typename T, int D>
 static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void* dout,
                                const int32_t* sel_idx, void* dq, void* dk, void* dv,
                                const float* delta, const float* lse2, const uint32_t* conn,
                                const int32_t* order, const Geom& g, int64_t BH, hipStream_t stream)
 {
-    const RowSplit rows(g.block_tokens, BwdLimits<T, D>::MAX_WAVES, WaveTile<T>::ROWS);
-    const int nw = rows.waves, m = g.n_blocks, words = (m + 31) >> 5;
+    const int m = g.n_blocks, words = (m + 31) >> 5;
     const int64_t BKV = BH / g.kv_group, N = g.n_tokens;
-    const int64_t wgs = (int64_t)m * rows.chunks;                 // per slice
-    const dim3 block(64 * nw);
     auto run_dkdv = [&] {
-        auto kernel = nw >= 4 ? bwd_generic_dkdv<T, D, 4>
-                      : nw >= 2 ? bwd_generic_dkdv<T, D, 2> : bwd_generic_dkdv<T, D, 1>;
+        const BwdSplit split = dkdv_split<T, D>(g, BKV);
+        const RowSplit rows(g.block_tokens, split.max_waves, WaveTile<T>::ROWS);
+        const int64_t wgs = (int64_t)m * rows.chunks;             // per slice
+        const int nw = rows.waves * split.groups;
+        auto kernel = split.groups == 4 ? dkdv_kernel<T, D, 4>(rows.waves)
+                      : split.groups == 2 ? dkdv_kernel<T, D, 2>(rows.waves)
+                                          : dkdv_kernel<T, D, 1>(rows.waves);
+        const dim3 block(64 * nw);
         return launch_slices(BKV, wgs * 64 * nw, [&](int64_t first, int64_t slices) {
             const int64_t bh = first * g.kv_group, row = bh * N, kv = first * N * D;
             Geom piece = g;
@@ -686,22 +842,28 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
                                (const T*)dout + row * D, lse2 + row, delta + row,
                                conn + bh * words * m, order ? order + first * m : nullptr,
                                (T*)dk + kv, (T*)dv + kv, piece, (uint32_t)slices, rows.chunks,
-                               WaveTile<T>::ROWS * nw);
+                               WaveTile<T>::ROWS * rows.waves);
             return hipGetLastError();
         });
     };
     auto run_dq = [&] {
-        auto kernel = nw >= 4 ? bwd_generic_dq<T, D, 4>
-                      : nw >= 2 ? bwd_generic_dq<T, D, 2> : bwd_generic_dq<T, D, 1>;
+        const BwdSplit split = dq_split<T, D>(g, BH);
+        const RowSplit rows(g.block_tokens, split.max_waves, WaveTile<T>::ROWS);
+        const int64_t wgs = (int64_t)m * rows.chunks;
+        const int nw = rows.waves * split.groups;
+        auto kernel = split.groups == 4 ? dq_kernel<T, D, 4>(rows.waves)
+                      : split.groups == 2 ? dq_kernel<T, D, 2>(rows.waves)
+                                          : dq_kernel<T, D, 1>(rows.waves);
+        const dim3 block(64 * nw);
         return launch_slices(BKV, g.kv_group * wgs * 64 * nw, [&](int64_t first, int64_t slices) {
             const int64_t bh = first * g.kv_group, row = bh * N, kv = first * N * D;
             Geom piece = g;
             if (g.add_dq) piece.add_dq += bh * m * D;
             kernel<<<dim3((unsigned)(slices * g.kv_group * wgs)), block,
-                     flat_table_bytes(g, g.n_select + 1), stream>>>(
+                     flat_table_bytes(g, g.n_select + 1, 1, split.groups > 2 ? 128 : 64), stream>>>(
                 (const T*)q + row * D, (const T*)k + kv, (const T*)v + kv, (const T*)dout + row * D,
                 lse2 + row, delta + row, sel_idx + bh * m * g.n_select, (T*)dq + row * D, piece,
-                (uint32_t)slices, rows.chunks, WaveTile<T>::ROWS * nw);
+                (uint32_t)slices, rows.chunks, WaveTile<T>::ROWS * rows.waves);
             return hipGetLastError();
         });
     };

@@ -26,11 +26,11 @@ __host__ __device__ constexpr int repeated_entries(int kt, int b, int split = 1)
 }
 
 // LDS of both tables for `listed` attended blocks (at most 9 KiB: b <= 1024)
-inline size_t flat_table_bytes(const Geom& g, int listed, int split = 1)
+inline size_t flat_table_bytes(const Geom& g, int listed, int split = 1, int kt = 64)
 {
     return sizeof(uint32_t) *
            (size_t)(g.block_tokens + (listed < kListTable ? listed : kListTable) +
-                    repeated_entries(64, g.block_tokens, split));
+                    repeated_entries(kt, g.block_tokens, split));
 }
 
 // Lane l: 16 bytes from src to LDS lds + 16 l (lds uniform); see load_lds_16.
@@ -103,10 +103,10 @@ struct RowSource {
 // (the same chunk of 8 consecutive rows) and the transposing bf16 read (a chunk
 // pair of 4 aligned rows) are free of bank conflicts.  The swizzle is applied on
 // the global side of the direct-to-LDS load.
-template <typename T, int D>
+template <typename T, int D, int ROWS = sizeof(T) == 2 ? 64 : 32>
 struct FlatTile {
     static constexpr int ROW_BYTES = D * (int)sizeof(T);
-    static constexpr int KT = sizeof(T) == 2 ? 64 : 32;         // rows
+    static constexpr int KT = ROWS;
     static constexpr int TILE_BYTES = KT * ROW_BYTES;
     static constexpr int SLABS = TILE_BYTES / 1024;             // loads of 64 x 16 bytes
     static constexpr int RPS = 1024 / ROW_BYTES;                // rows per slab
@@ -535,9 +535,9 @@ __device__ __forceinline__ void gather_rows(const RowSource& ks, const RowSource
 // blocks.  Up to 63 listed blocks are visited in ascending order (query blocks
 // that run together then sweep the slice's K/V in the same direction).  SPLIT: as many
 // groups of wavefronts take the tiles in turn, `wave` counts inside a group.
-template <typename T, int D, int NL, int SPLIT = 1>
+template <typename T, int D, int NL, int SPLIT = 1, class Tile_ = FlatTile<T, D>>
 struct AttendedKeys {
-    using Tile = FlatTile<T, D>;
+    using Tile = Tile_;
     static constexpr int MINE = Tile::SLABS / NL;
     static_assert(Tile::SLABS % NL == 0, "slabs split evenly between the loading wavefronts");
 

@@ -284,6 +284,47 @@ def test_general_backward(G, oracle, dtype, kv_heads, H, W, bh, bw, D, n):
     assert all(np.array_equal(x, y) for x, y in zip(got, again))
 
 
+# row wavefronts of dK/dV up to which four groups and two share a list (the backward's rule)
+SPLIT_LIMITS = {("bf16", 32): (2048, 4096), ("bf16", 64): (2048, 4096), ("bf16", 128): (512, 1024),
+                ("fp32", 32): (1408, 8192), ("fp32", 64): (1408, 8192), ("fp32", 128): (0, 2048)}
+
+
+@pytest.mark.parametrize("dtype,D", list(SPLIT_LIMITS))
+@pytest.mark.parametrize("heads,kv_heads,H,W,bh,bw,n", [
+    (1, 1, 32, 30, 8, 6, 9),     # b = 48: row wavefronts in pairs, bf16 one, fp32 two per block
+    (2, 1, 44, 15, 11, 3, 9),    # b = 33; 330 rows and more to a list, the last piece not full
+    (1, 1, 32, 32, 4, 4, 27),    # b = 16: one row wavefront, in two groups or four
+])
+def test_general_backward_split(G, oracle, dtype, D, heads, kv_heads, H, W, bh, bw, n):
+    """One entry as often as it takes for launches whose lists are walked by four groups of
+    wavefronts, by two and by one.  The bounds of test_general_backward against the oracle,
+    all copies bitwise equal; the bits of dK tell that the smaller launches did split."""
+    cfg = shape_ns(1, heads, H, W, bh, bw, D, n, dtype, kv_heads)
+    rng = np.random.default_rng(D + n)
+    shape = (1, heads, H * W, D)
+    q, dout = (rng.standard_normal(shape).astype(np.float32) for _ in range(2))
+    k, v = (rng.standard_normal((1, kv_heads, H * W, D)).astype(np.float32) for _ in range(2))
+    if dtype == "bf16":
+        q, k, v, dout = (round_to_bf16(x) for x in (q, k, v, dout))
+    idx = random_selection(cfg, 3)
+    ref = (oracle.bwd_gqa if heads > kv_heads else oracle.bwd)(
+        oracle.shape_of(cfg), q, k, v, dout, idx)
+    rows = 16 if dtype == "fp32" else 32
+    per_entry = kv_heads * cfg.n_blocks * -(-cfg.block_tokens // rows)
+    four, two = SPLIT_LIMITS[dtype, D]
+    bits = []
+    for batch in (1, four // per_entry + 1, two // per_entry + 1):
+        cfg.batch = batch
+        got = G.gpu_bwd(cfg, *(np.repeat(x, batch, axis=0) for x in (q, k, v, dout, idx)))
+        for name, x, r in zip(("dq", "dk", "dv"), got, ref):
+            assert (x == x[:1]).all(), (name, batch)
+            tol = 1e-4 * np.abs(r).max() if dtype == "fp32" else 1e-2 * max(1.0, np.abs(r).max())
+            err = np.abs(x[:1] - r).max()
+            assert err <= tol, f"{name}, batch {batch}: max error {err} > {tol}"
+        bits.append(got[1][0])
+    assert not np.array_equal(bits[0], bits[2]) and not np.array_equal(bits[1], bits[2])
+
+
 @pytest.mark.parametrize("heads,kv_heads,H,W,bh,bw,n", [
     (4, 1, 40, 64, 2, 2, 9),     # m = 640: 80 words per key block, classes by the whole chip
     (2, 1, 32, 128, 2, 2, 9),    # m = 1,024: 64 words, the last map read by its workgroup
