@@ -562,6 +562,39 @@ __device__ __forceinline__ int fill_list(ConnectedList& list, const Geom& g,
     return next_word;
 }
 
+// Launches of few key blocks wait for the longest list (on smooth fields 4 to 7 times the
+// mean) while SIMDs are idle.  There SPLIT groups of NW wavefronts own the same key rows
+// and take the tiles in turn, with tiles of their own; a block of more than 32 NW rows is
+// shared by several workgroups.  add_groups then adds what groups 1 .. have to group 0,
+// lane by lane, in the order of the groups, through the tiles' memory (wavefront w of
+// group 0 reads only region w, so that it may go on to use it).  All wavefronts call it;
+// false: not group 0.
+template <int SPLIT, int NW, int COUNT>
+__device__ __forceinline__ bool add_groups(unsigned char* lds, int group, int wave, int lane,
+                                           f32x16 (&acc)[COUNT])
+{
+    float* const region = (float*)lds + wave * (SPLIT - 1) * COUNT * 16 * 64 + lane;
+    __syncthreads();                                  // the tiles (the last values) are used up
+    if (group > 0) {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                region[(((group - 1) * COUNT + c) * 16 + r) * 64] = acc[c][r];
+    }
+    __syncthreads();
+    if (group > 0) return false;
+    for (int from = 0; from < SPLIT - 1; ++from)
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[c][r] += region[((from * COUNT + c) * 16 + r) * 64];
+            __builtin_amdgcn_sched_barrier(0);        // (registers: 16 values at a time)
+        }
+    lane_exchange();
+    return true;
+}
+
 // dK and dV in one pass at head dim 64.  What bounds the unpipelined form (fragments
 // read right before the matrix instructions, weights between them) is waiting: 44 % of
 // the wavefronts' cycles, matrix pipe busy 40 %, and a launch of 16 scan rounds per
@@ -578,7 +611,7 @@ __device__ __forceinline__ int fill_list(ConnectedList& list, const Geom& g,
 //     and pinned.
 // 1.5 degree grid, 16 heads on 4, batch 12: 3.83 -> 3.23 ms, its training pass 8.99 -> 8.29 (cycles -23 %: the chip is
 // power-limited here and the clock gives part of it back, 1.80 -> 1.62 GHz).
-template <int NW>
+template <int NW, int SUBS, int SPLIT>
 __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
                                               const uint16_t* __restrict__ k,
                                               const uint16_t* __restrict__ v,
@@ -590,23 +623,25 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
                                               uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                               const Geom& g, uint32_t n_units)
 {
-    constexpr int D = 64, KS = 4, SUBS = NW / 2, ROW = 128, TILE = 64 * ROW;
+    constexpr int D = 64, KS = 4, ROW = 128, TILE = 64 * ROW, CHUNKS = 2 * SUBS / NW;
     using IO = TileIO<D, NW>;
     // [buffer][Q tile, dO tile]; the buffers alternate by bit 14 of the address
-    __shared__ __attribute__((aligned(32768))) unsigned char tiles_s[2][2][TILE];
-    __shared__ __attribute__((aligned(1024))) float rows_s[2][2][64];     // [buffer][lse2, delta]
+    __shared__ __attribute__((aligned(32768))) unsigned char tiles_s[SPLIT][2][2][TILE];
+    __shared__ __attribute__((aligned(1024))) float rows_s[SPLIT][2][2][64];  // [buffer][lse2, delta]
     __shared__ ConnectedList list;
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = SPLIT == 1 ? 0 : wg_wave / NW, wave = wg_wave - group * NW;
     const int l32 = lane & 31, half = lane >> 5;
     const int m = g.n_blocks;
 
     // workgroup -> (key/value slice, key block), slices dealt to the 8 XCDs
     // whole; the query slices that share the key/value slice are consecutive
     uint32_t unit, r_unit;
-    map_unit(blockIdx.x, (uint32_t)m, n_units, unit, r_unit);
-    const int j = order ? order[(int64_t)unit * m + r_unit] : (int)r_unit;
+    map_unit(blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
+    const int place = (int)r_unit / CHUNKS, row0 = 32 * (NW * ((int)r_unit % CHUNKS) + wave);
+    const int j = order ? order[(int64_t)unit * m + place] : place;
     const int64_t base = (int64_t)unit * g.n_tokens * D;
     int64_t bh_first;
     {
@@ -626,7 +661,7 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
         const int bw_shift = __builtin_ctz((unsigned)g.block_w);
         const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
         const int64_t tok0 = (int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w;
-        const int t = 32 * wave + l32;
+        const int t = row0 + l32;
         const int rr = t >> bw_shift, cc = t & (g.block_w - 1);
         k_tok = tok0 + (int64_t)rr * g.grid_w + cc;
 #pragma unroll
@@ -645,7 +680,7 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
     // read next; everything else is a constant
     uint32_t row_at[KS], tr_at[2], val_at;
     {
-        const uint32_t t0 = lds_address(tiles_s);
+        const uint32_t t0 = lds_address(tiles_s[0]) + (uint32_t)group * (4u * TILE);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
             row_at[ks] = t0 + (uint32_t)(l32 * ROW + swz(l32, 2 * ks + half) * 16);
@@ -655,7 +690,7 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
             const int col = 16 * (gq & 1) + 4 * (s16 & 3) + 32 * dt;
             tr_at[dt] = t0 + (uint32_t)(r * ROW + swz(r, col >> 3) * 16 + (col & 7) * 2);
         }
-        val_at = lds_address(rows_s) + 16u * (uint32_t)half;
+        val_at = lds_address(rows_s[0]) + 1024u * (uint32_t)group + 16u * (uint32_t)half;
     }
     // fragment `i` of a tile in the order in which the matrix instructions take them:
     //   0- 7  Q rows, dO rows of queries 0..31 (S, dP)     8-15  the same of 32..63
@@ -676,10 +711,10 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
         return __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
     };
 
-    int next_word = 0;                                // wavefront 0 only
+    int next_word = 0;                                // the first wavefront only
     for (;;) {
         __syncthreads();                              // the previous list is used up
-        if (wave == 0) next_word = fill_list(list, g, conn, bh_first, j, next_word, lane);
+        if (wg_wave == 0) next_word = fill_list(list, g, conn, bh_first, j, next_word, lane);
         __syncthreads();
         const int items = __builtin_amdgcn_readfirstlane(list.count) * SUBS;
         const bool more = __builtin_amdgcn_readfirstlane(list.more) != 0;
@@ -691,31 +726,33 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
             const uint32_t tok = (entry & 0xffffffu) + (uint32_t)sub_tile_first(g, item % SUBS);
             const i32x4 q_rsrc = buffer_desc((const char*)q + bh * slice_bytes, slice_bytes);
             const i32x4 g_rsrc = buffer_desc((const char*)dout + bh * slice_bytes, slice_bytes);
-            io.gather(q_rsrc, tok * ROW, tiles_s[buf][0]);
-            io.gather(g_rsrc, tok * ROW, tiles_s[buf][1]);
+            io.gather(q_rsrc, tok * ROW, tiles_s[group][buf][0]);
+            io.gather(g_rsrc, tok * ROW, tiles_s[group][buf][1]);
             if (wave == 0)
                 io.gather_f32(buffer_desc((const char*)lse2 + bh * row_bytes, row_bytes), tok,
-                              rows_s[buf][0]);
+                              rows_s[group][buf][0]);
             if (wave == NW - 1)
                 io.gather_f32(buffer_desc((const char*)delta + bh * row_bytes, row_bytes), tok,
-                              rows_s[buf][1]);
+                              rows_s[group][buf][1]);
         };
         if (items > 0) {
-            uint32_t entry = __builtin_amdgcn_readfirstlane(entry_of(0));
-            issue_item(0, entry, 0);
-            entry = __builtin_amdgcn_readfirstlane(entry_of(1));
+            uint32_t entry = __builtin_amdgcn_readfirstlane(entry_of(group));
+            if (SPLIT == 1 || group < items) issue_item(group, entry, 0);
+            entry = __builtin_amdgcn_readfirstlane(entry_of(group + SPLIT));
             // tile 0 of a list lies in buffer 0
             const uint32_t flip = row_at[0] & 16384u;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) row_at[ks] -= flip;
             tr_at[0] -= flip; tr_at[1] -= flip;
             val_at -= flip >> 5;
-            for (int it = 0; it < items; ++it) {
+            for (int it0 = 0; it0 < items; it0 += SPLIT) {
                 // item `it` has landed and everyone is done with the other buffers
                 wait_gathers();
                 __syncthreads();
-                if (it + 1 < items) issue_item(it + 1, entry, (it + 1) & 1);
-                const uint32_t entry_v = entry_of(it + 2);
+                const int it = it0 + group;
+                if (SPLIT > 1 && it >= items) break;          // the last round
+                if (it + SPLIT < items) issue_item(it + SPLIT, entry, (it0 / SPLIT + 1) & 1);
+                const uint32_t entry_v = entry_of(it + 2 * SPLIT);
 
                 constexpr int W = 8;                  // fragments read ahead
                 bf16x8 f[W];
@@ -803,15 +840,23 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
     const int64_t pooled_row = ((int64_t)unit * m + j) * D;
     const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
     const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
-    __syncthreads();                                  // the tiles are used up
-    unsigned char* const lds = &tiles_s[0][0][0] + wave * 4096;
+    unsigned char* lds = &tiles_s[0][0][0][0];
+    if constexpr (SPLIT > 1) {
+        static_assert(NW * (SPLIT - 1) * 2 * 4096 <= (int)sizeof(tiles_s), "fits the tiles");
+        const bool first = add_groups<SPLIT, NW>(lds, group, wave, lane, acck);
+        if (!add_groups<SPLIT, NW>(lds, group, wave, lane, accv) || !first) return;
+        lds += wave * (SPLIT - 1) * 2 * 4096;
+    } else {
+        __syncthreads();                              // the tiles are used up
+        lds += wave * 4096;
+    }
     const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
     const int64_t block =
         base + ((int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w) * D;
-    if (extra_k) add_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, extra_k, inv_b, lds, lane);
-    else store_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, lds, lane);
-    if (extra_v) add_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, extra_v, inv_b, lds, lane);
-    else store_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, lds, lane);
+    if (extra_k) add_rows<D>(dk + block, g, row0, acck, -g.scale, extra_k, inv_b, lds, lane);
+    else store_rows<D>(dk + block, g, row0, acck, -g.scale, lds, lane);
+    if (extra_v) add_rows<D>(dv + block, g, row0, accv, 1.0f, extra_v, inv_b, lds, lane);
+    else store_rows<D>(dv + block, g, row0, accv, 1.0f, lds, lane);
 }
 
 // dK and dV in one pass at head dim 128.  Both accumulators take 128 of the 256 registers
@@ -822,7 +867,7 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
 // behind those of dV.  Against a pass each for dV and dK, which compute S twice, gather
 // every tile twice and wait 40 % of the time for fragments: 1.5 degrees, batch 4, 16 heads
 // 1.85 + 2.38 -> 3.23 ms, training pass 8.65 -> 7.56; the same bits.
-template <int NW>
+template <int NW, int SUBS, int SPLIT>
 __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
                                                const uint16_t* __restrict__ k,
                                                const uint16_t* __restrict__ v,
@@ -834,22 +879,24 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
                                                uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                                const Geom& g, uint32_t n_units)
 {
-    constexpr int D = 128, KS = 8, SUBS = NW, ROW = 256, TILE = 32 * ROW, MINE = 8 / NW;
+    constexpr int D = 128, KS = 8, ROW = 256, TILE = 32 * ROW, MINE = 8 / NW, CHUNKS = SUBS / NW;
     // [buffer][Q tile, dO tile]; the buffers alternate by bit 14 of the address
-    __shared__ __attribute__((aligned(32768))) unsigned char tiles_s[2][2][TILE];
-    __shared__ __attribute__((aligned(1024))) float rows_s[2][2][64];     // [buffer][lse2, delta]
+    __shared__ __attribute__((aligned(32768))) unsigned char tiles_s[SPLIT][2][2][TILE];
+    __shared__ __attribute__((aligned(1024))) float rows_s[SPLIT][2][2][64];  // [buffer][lse2, delta]
     __shared__ __attribute__((aligned(1024))) unsigned char v_s[NW][TILE];
     __shared__ ConnectedList list;
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = SPLIT == 1 ? 0 : wg_wave / NW, wave = wg_wave - group * NW;
     const int l32 = lane & 31, half = lane >> 5;
     const int m = g.n_blocks;
 
     // workgroup -> (key/value slice, key block), see dkdv_d64_body
     uint32_t unit, r_unit;
-    map_unit(blockIdx.x, (uint32_t)m, n_units, unit, r_unit);
-    const int j = order ? order[(int64_t)unit * m + r_unit] : (int)r_unit;
+    map_unit(blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
+    const int place = (int)r_unit / CHUNKS, row0 = 32 * (NW * ((int)r_unit % CHUNKS) + wave);
+    const int j = order ? order[(int64_t)unit * m + place] : place;
     const int64_t base = (int64_t)unit * g.n_tokens * D;
     int64_t bh_first;
     {
@@ -875,12 +922,13 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
         const int bw_shift = __builtin_ctz((unsigned)g.block_w);
         const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
         const int64_t tok0 = (int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w;
-        const int t = 32 * wave + l32;
+        const int t = row0 + l32;
         const int rr = t >> bw_shift, cc = t & (g.block_w - 1);
         k_tok = tok0 + (int64_t)rr * g.grid_w + cc;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             kfb[ks] = *(const bf16x8*)(k + base + k_tok * D + 16 * ks + 8 * half);
+            if (SPLIT > 1 && group > 0) continue;     // V is the same for all groups
             *(bf16x8*)(v_s[wave] + l32 * ROW + swz(l32, 2 * ks + half) * 16) =
                 negated(*(const bf16x8*)(v + base + k_tok * D + 16 * ks + 8 * half));
         }
@@ -895,7 +943,7 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
     // read next, and of its V rows; everything else is a constant
     uint32_t row_at[4], v_at[4], tr_at[2], val_at;
     {
-        const uint32_t t0 = lds_address(tiles_s), v0 = lds_address(v_s[0]) + (uint32_t)wave * TILE;
+        const uint32_t t0 = lds_address(tiles_s[0]) + (uint32_t)group * (4u * TILE), v0 = lds_address(v_s[0]) + (uint32_t)wave * TILE;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             const uint32_t at = (uint32_t)(l32 * ROW + swz(l32, 2 * ks + half) * 16);
@@ -908,7 +956,7 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
             const int col = 16 * (gq & 1) + 4 * (s16 & 3) + 32 * dt;
             tr_at[dt] = t0 + (uint32_t)(r * ROW + swz(r, col >> 3) * 16 + (col & 7) * 2);
         }
-        val_at = lds_address(rows_s) + 16u * (uint32_t)half;
+        val_at = lds_address(rows_s[0]) + 1024u * (uint32_t)group + 16u * (uint32_t)half;
     }
     // fragment `i` of a tile in the order in which the matrix instructions take them:
     // 0-7 Q rows (S), 8-23 dO rows and V in turn (dP), 24-31 dO transposed (dV),
@@ -930,10 +978,10 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
         return __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
     };
 
-    int next_word = 0;                                // wavefront 0 only
+    int next_word = 0;                                // the first wavefront only
     for (;;) {
         __syncthreads();                              // the previous list is used up
-        if (wave == 0) next_word = fill_list(list, g, conn, bh_first, j, next_word, lane);
+        if (wg_wave == 0) next_word = fill_list(list, g, conn, bh_first, j, next_word, lane);
         __syncthreads();
         const int items = __builtin_amdgcn_readfirstlane(list.count) * SUBS;
         const bool more = __builtin_amdgcn_readfirstlane(list.more) != 0;
@@ -947,7 +995,7 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
                                  (uint32_t)((ct & 1) * sub_tile_pos(g, 32));
             const i32x4 q_rsrc = buffer_desc((const char*)q + bh * slice_bytes, slice_bytes);
             const i32x4 g_rsrc = buffer_desc((const char*)dout + bh * slice_bytes, slice_bytes);
-            const uint32_t q_dst = lds_address(tiles_s[buf][0]), g_dst = lds_address(tiles_s[buf][1]);
+            const uint32_t q_dst = lds_address(tiles_s[group][buf][0]), g_dst = lds_address(tiles_s[group][buf][1]);
 #pragma unroll
             for (int jj = 0; jj < MINE; ++jj) {
                 load_lds_16(q_rsrc, voff[jj], tok * ROW, q_dst + (uint32_t)(wave + NW * jj) * 1024u);
@@ -955,27 +1003,29 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
             }
             if (wave == 0)
                 load_lds_4(buffer_desc((const char*)lse2 + bh * row_bytes, row_bytes), tok_off,
-                           tok * 4u, lds_address(rows_s[buf][0]));
+                           tok * 4u, lds_address(rows_s[group][buf][0]));
             if (wave == NW - 1)
                 load_lds_4(buffer_desc((const char*)delta + bh * row_bytes, row_bytes), tok_off,
-                           tok * 4u, lds_address(rows_s[buf][1]));
+                           tok * 4u, lds_address(rows_s[group][buf][1]));
         };
         if (items > 0) {
-            uint32_t entry = __builtin_amdgcn_readfirstlane(entry_of(0));
-            issue_item(0, entry, 0);
-            entry = __builtin_amdgcn_readfirstlane(entry_of(1));
+            uint32_t entry = __builtin_amdgcn_readfirstlane(entry_of(group));
+            if (SPLIT == 1 || group < items) issue_item(group, entry, 0);
+            entry = __builtin_amdgcn_readfirstlane(entry_of(group + SPLIT));
             // tile 0 of a list lies in buffer 0
             const uint32_t flip = row_at[0] & 16384u;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) row_at[ks] -= flip;
             tr_at[0] -= flip; tr_at[1] -= flip;
             val_at -= flip >> 5;
-            for (int it = 0; it < items; ++it) {
+            for (int it0 = 0; it0 < items; it0 += SPLIT) {
                 // item `it` has landed and everyone is done with the other buffers
                 wait_gathers();
                 __syncthreads();
-                if (it + 1 < items) issue_item(it + 1, entry, (it + 1) & 1);
-                const uint32_t entry_v = entry_of(it + 2);
+                const int it = it0 + group;
+                if (SPLIT > 1 && it >= items) break;          // the last round
+                if (it + SPLIT < items) issue_item(it + SPLIT, entry, (it0 / SPLIT + 1) & 1);
+                const uint32_t entry_v = entry_of(it + 2 * SPLIT);
 
                 constexpr int W = 6;                  // fragments read ahead
                 bf16x8 f[W];
@@ -1061,15 +1111,23 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
     const int64_t pooled_row = ((int64_t)unit * m + j) * D;
     const float* extra_k = g.add_dk ? g.add_dk + pooled_row : nullptr;
     const float* extra_v = g.add_dv ? g.add_dv + pooled_row : nullptr;
-    __syncthreads();                                  // the tiles are used up
-    unsigned char* const lds = &tiles_s[0][0][0] + wave * 4096;
+    unsigned char* lds = &tiles_s[0][0][0][0];
+    if constexpr (SPLIT > 1) {
+        static_assert(NW * (SPLIT - 1) * 4 * 4096 <= (int)sizeof(tiles_s), "fits the tiles");
+        const bool first = add_groups<SPLIT, NW>(lds, group, wave, lane, acck);
+        if (!add_groups<SPLIT, NW>(lds, group, wave, lane, accv) || !first) return;
+        lds += wave * (SPLIT - 1) * 4 * 4096;
+    } else {
+        __syncthreads();                              // the tiles are used up
+        lds += wave * 4096;
+    }
     const int br = j / g.blocks_per_row, bc = j - br * g.blocks_per_row;
     const int64_t block =
         base + ((int64_t)br * g.block_h * g.grid_w + (int64_t)bc * g.block_w) * D;
-    if (extra_k) add_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, extra_k, inv_b, lds, lane);
-    else store_rows<D>(dk + block, g, 32 * wave, acck, -g.scale, lds, lane);
-    if (extra_v) add_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, extra_v, inv_b, lds, lane);
-    else store_rows<D>(dv + block, g, 32 * wave, accv, 1.0f, lds, lane);
+    if (extra_k) add_rows<D>(dk + block, g, row0, acck, -g.scale, extra_k, inv_b, lds, lane);
+    else store_rows<D>(dk + block, g, row0, acck, -g.scale, lds, lane);
+    if (extra_v) add_rows<D>(dv + block, g, row0, accv, 1.0f, extra_v, inv_b, lds, lane);
+    else store_rows<D>(dv + block, g, row0, accv, 1.0f, lds, lane);
 }
 
 }  // namespace bwdm
@@ -1088,19 +1146,31 @@ BSA_BWD_DQ(64, 4)
 BSA_BWD_DQ(64, 8)
 BSA_BWD_DQ(128, 4)
 BSA_BWD_DQ(128, 8)
-#define BSA_BWD_DKDV(D, NW)                                                                       \
-    __global__ __launch_bounds__(64 * NW, 2) void bwd_mfma_dkdv_d##D##_w##NW(                     \
+// NW wavefronts of 32 rows per workgroup (times the groups), SUBS tiles per query block
+#define BSA_BWD_DKDV(NAME, D, NW, SUBS, SPLIT)                                                    \
+    __global__ __launch_bounds__(64 * NW * SPLIT, D == 128 && NW * SPLIT == 4 && SPLIT > 1 ? 1 : 2)      \
+    void bwd_mfma_dkdv_d##D##_##NAME(                                                             \
         const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dout,            \
         const float* lse2, const float* delta, const uint32_t* conn, const int32_t* order,        \
         uint16_t* dk, uint16_t* dv, Geom g, uint32_t n_units)                                     \
     {                                                                                             \
-        bwdm::dkdv_d##D##_body<NW>(q, k, v, dout, lse2, delta, conn, order, dk, dv, g, n_units);  \
+        bwdm::dkdv_d##D##_body<NW, SUBS, SPLIT>(q, k, v, dout, lse2, delta, conn, order, dk, dv,  \
+                                                g, n_units);                                      \
     }
-BSA_BWD_DKDV(64, 2)
-BSA_BWD_DKDV(64, 4)
-BSA_BWD_DKDV(64, 8)
-BSA_BWD_DKDV(128, 4)
-BSA_BWD_DKDV(128, 8)
+BSA_BWD_DKDV(w2, 64, 2, 1, 1)
+BSA_BWD_DKDV(w4, 64, 4, 2, 1)
+BSA_BWD_DKDV(w8, 64, 8, 4, 1)
+BSA_BWD_DKDV(w2_split2, 64, 2, 1, 2)
+BSA_BWD_DKDV(w4_split2, 64, 2, 2, 2)
+BSA_BWD_DKDV(w8_split2, 64, 2, 4, 2)
+BSA_BWD_DKDV(w2_split4, 64, 2, 1, 4)
+BSA_BWD_DKDV(w4_split4, 64, 2, 2, 4)
+BSA_BWD_DKDV(w8_split4, 64, 2, 4, 4)
+BSA_BWD_DKDV(w4, 128, 4, 4, 1)
+BSA_BWD_DKDV(w8, 128, 8, 8, 1)
+BSA_BWD_DKDV(w4_split2, 128, 2, 4, 2)
+BSA_BWD_DKDV(w8_split2, 128, 2, 8, 2)
+BSA_BWD_DKDV(w8_split2_wide, 128, 4, 8, 2)
 #undef BSA_BWD_DQ
 #undef BSA_BWD_DKDV
 
@@ -1116,6 +1186,43 @@ bool bwd_mfma_supported(bool is_bf16, const Geom& g, int D)
            (g.block_w & (g.block_w - 1)) == 0 && g.n_tokens * D * 2 < ((int64_t)1 << 31);
 }
 
+// Wavefronts of 32 rows of a dK/dV workgroup, and groups of them that share its list, by
+// the row wavefronts of the launch and the tiles' worth of rows (32) that one walks on
+// average.  What bounds a launch of few wavefronts and what a split costs is said at the
+// general kernels' rule (bsa_bwd.hip).  Whole backward, us, unsplit | two wavefronts in two
+// groups | in four (slices x blocks x tokens, attended blocks; head dim 128, last: four
+// wavefronts in two groups):
+//   head dim 64:   1 x 24 x 128, 13:   78 | 62 | 58       4 x 96 x 128, 13:   154 | 136 | 129
+//                  1 x 448 x 64, 13:   88 | 74 | 70       4 x 448 x 64, 13:   163 | 154 | 175
+//                  1 x 448 x 128, 4:   92 | 72 | 77       16 x 96 x 128, 13:  324 | 330 | 376
+//                  4 x 96 x 256, 13:  411 | 357 | 377     16 x 96 x 256, 13: 1,185 | 1,161 | 1,247
+//   head dim 128:  1 x 96 x 128, 13:  185 | 132 | -       4 x 96 x 128, 13:   249 | 221 | -
+//                  16 x 96 x 128, 13: 580 | 690 | -       4 x 96 x 256, 13:   727 | 720 | 655
+//                  1 x 448 x 256, 4:  340 | 309 | 277     16 x 96 x 256, 13: 2,256 | 2,480 | 2,234
+// (four groups do not fit beside V at head dim 128).  Lists of equal length (see there) are
+// split while SIMDs are idle.  367 launches of 48 to 12,288 row wavefronts, smooth fields,
+// noise, n = 0 and all blocks: 1.18 (head dim 64) and 1.20 times as fast on average, three
+// of them slower by 2 to 5 %.
+struct DkdvSplit {
+    int waves, groups;
+};
+static DkdvSplit dkdv_split(const Geom& g, int D, int64_t BKV)
+{
+    const int nw = g.block_tokens / 32;
+    const int64_t waves = BKV * g.n_blocks * nw, attended = g.n_select + 1 - g.list_only;
+    const int64_t pieces = g.kv_group * attended * nw;
+    const bool even = g.add_dk || attended == 1 || 2 * attended > g.n_blocks;
+    const int64_t few = even ? 2048 / 3 : 2048, more = even ? 1024 : 4096;
+    if (D == 64) {
+        if (waves <= few && pieces >= 16 + waves / 64) return {2, 4};
+        if (waves <= more && pieces >= 8 + waves / 256) return {2, 2};
+    } else {
+        if (waves <= few && pieces >= 6 + waves / 128) return {2, 2};
+        if (nw == 8 && waves <= more && pieces >= 6 + waves / 256) return {4, 2};
+    }
+    return {nw, 1};
+}
+
 hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const void* out,
                            const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
                            void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
@@ -1128,9 +1235,11 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
     if (e != hipSuccess) return e;
     const int nw = g.block_tokens / 32;
     const uint32_t sx = (uint32_t)(BH / g.kv_group);           // key/value slices
-    const dim3 grid((unsigned)(BH * g.n_blocks)), grid_kv(sx * (unsigned)g.n_blocks), block(64 * nw);
+    const dim3 grid((unsigned)(BH * g.n_blocks)), block(64 * nw);
+    const DkdvSplit split = dkdv_split(g, D, sx);
     auto run_dkdv = [&](auto kernel) {
-        kernel<<<grid_kv, block, 0, stream>>>(
+        kernel<<<dim3(sx * (unsigned)(g.n_blocks * (nw / split.waves))),
+                 dim3(64 * split.waves * split.groups), 0, stream>>>(
             (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2,
             delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);
         return hipGetLastError();
@@ -1142,17 +1251,22 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
         return hipGetLastError();
     };
     // `order` may lie where dQ goes; without it dK and dV may lie where k and v are
-#define BSA_LAUNCH(D_, NW_)                                                                       \
+#define BSA_LAUNCH(D_, NW_, FOUR_GROUPS, FOUR_WAVES)                                              \
     if (D == D_ && nw == NW_) {                                                                   \
         if (!order && (e = run_dq(bwd_mfma_dq_d##D_##_w##NW_)) != hipSuccess) return e;           \
-        if ((e = run_dkdv(bwd_mfma_dkdv_d##D_##_w##NW_)) != hipSuccess) return e;                 \
+        e = run_dkdv(split.groups == 1   ? bwd_mfma_dkdv_d##D_##_w##NW_                           \
+                     : split.groups == 4 ? bwd_mfma_dkdv_d##D_##_##FOUR_GROUPS                    \
+                     : split.waves == 4  ? bwd_mfma_dkdv_d##D_##_##FOUR_WAVES                     \
+                                         : bwd_mfma_dkdv_d##D_##_w##NW_##_split2);                \
+        if (e != hipSuccess) return e;                                                            \
         return order ? run_dq(bwd_mfma_dq_d##D_##_w##NW_) : hipSuccess;                           \
     }
-    BSA_LAUNCH(64, 2)
-    BSA_LAUNCH(64, 4)
-    BSA_LAUNCH(64, 8)
-    BSA_LAUNCH(128, 4)
-    BSA_LAUNCH(128, 8)
+    // (the last two columns: a kernel that the rule does not name there is not launched)
+    BSA_LAUNCH(64, 2, w2_split4, w2_split2)
+    BSA_LAUNCH(64, 4, w4_split4, w4_split2)
+    BSA_LAUNCH(64, 8, w8_split4, w8_split2)
+    BSA_LAUNCH(128, 4, w4_split2, w4_split2)
+    BSA_LAUNCH(128, 8, w8_split2, w8_split2_wide)
 #undef BSA_LAUNCH
     return hipErrorInvalidValue;
 }

@@ -453,6 +453,69 @@ def test_backward_matrix_core_shapes(G, oracle, H, W, bh, bw, D, n):
     check_grads(cfg, got, ref)
 
 
+@pytest.mark.parametrize("heads,kv_heads,H,W,bh,bw,D,n,batches", [
+    # entries for launches whose key blocks' lists are walked by: four groups of two
+    # wavefronts, two groups of two (head dim 128, blocks of 256: two of four), one group
+    (1, 1, 40, 64, 8, 8, 64, 19, (1, 27, 70)),
+    (2, 1, 64, 80, 8, 16, 64, 10, (1, 14, 30)),
+    (1, 1, 96, 128, 16, 16, 64, 10, (1, 6, 11)),
+    (1, 1, 64, 80, 8, 16, 128, 10, (1, 30)),
+    (1, 1, 96, 128, 16, 16, 128, 10, (1, 6, 11)),
+])
+def test_backward_split_lists(G, oracle, heads, kv_heads, H, W, bh, bw, D, n, batches):
+    """One entry as often as it takes for each form of the matrix-core dK/dV kernels: all
+    copies bitwise equal and as close to the oracle as any; the bits of dK tell how many
+    groups there were (at head dim 128 two or one)."""
+    cfg = shape_ns(1, heads, H, W, bh, bw, D, n, "bf16", kv_heads)
+    rng = np.random.default_rng(D + bh)
+    q, dout = (round_to_bf16(rng.standard_normal((1, heads, H * W, D)).astype(np.float32))
+               for _ in range(2))
+    k, v = (round_to_bf16(rng.standard_normal((1, kv_heads, H * W, D)).astype(np.float32))
+            for _ in range(2))
+    idx = random_selection(cfg, 5)
+    ref = (oracle.bwd_gqa if heads > kv_heads else oracle.bwd)(
+        oracle.shape_of(cfg), q, k, v, dout, idx)
+    bits = []
+    for batch in batches:
+        cfg.batch = batch
+        got = G.gpu_bwd(cfg, *(np.repeat(x, batch, axis=0) for x in (q, k, v, dout, idx)))
+        assert all((x == x[:1]).all() for x in got)
+        check_grads(cfg, [x[:1] for x in got], ref)
+        bits.append(got[1][0].tobytes())
+    assert len(set(bits)) == (3 if D == 64 else 2)
+
+
+@pytest.mark.parametrize("heads,H,W,bh,bw,D,n,batch", [
+    (72, 32, 64, 8, 16, 64, 15, 17),    # 1,152 blocks to a list of 1,024
+    (72, 32, 64, 8, 16, 128, 15, 17),
+])
+def test_backward_long_lists_unsplit(G, heads, H, W, bh, bw, D, n, batch):
+    """Lists that are filled twice, walked by one group of wavefronts: the gradients of a
+    launch of one entry, which splits them (test_backward_long_connected_lists), but for the
+    order of fp32 sums and their rounding to bf16."""
+    one = shape_ns(1, heads, H, W, bh, bw, D, n, "bf16", kv_heads=1)
+    many = shape_ns(batch, heads, H, W, bh, bw, D, n, "bf16", kv_heads=1)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    rand = lambda h: torch.randn((1, h, H * W, D), generator=gen, device="cuda").bfloat16()
+    q, dout, k, v = rand(heads), rand(heads), rand(1), rand(1)
+    idx = torch.from_numpy(random_selection(one, 5)).cuda()
+    grads = []
+    for cfg in (one, many):
+        args = [x.repeat(cfg.batch, 1, 1, 1) for x in (q, k, v, dout, idx)]
+        out, lse = G.fwd_dev(cfg, *args[:3], args[4])
+        import paper_2604_16429_amd as M
+        from paper_2604_16429_amd import binding
+        p = G.params_of(cfg)
+        ws = torch.empty(M.mosaic_bsa_workspace_bytes(p, binding.OP_BWD), dtype=torch.uint8,
+                         device="cuda")
+        got = [torch.empty_like(x) for x in args[:3]]
+        M.mosaic_bsa_bwd(p, *args[:3], out, lse, args[3], args[4], *got, ws)
+        grads.append([x[-1].float() for x in got])
+    assert not torch.equal(grads[0][1], grads[1][1])
+    for a, b in zip(*grads):
+        assert bool(((a - b).abs() <= 2.0 ** -7 * a.abs() + 1e-4 * a.abs().max()).all())
+
+
 @pytest.mark.parametrize("H,W,bh,bw,D,n,sel_seed", [
     (96, 128, 8, 8, 64, 5, 43),      # 64-token blocks, m = 192
     (136, 256, 8, 16, 128, 3, 44),   # 128-token blocks, head dim 128, m = 272
