@@ -14,11 +14,13 @@
 // order followed by one multiply by 1/b; a score is the fp32 chain
 // acc = fma(qbar[d], kbar[d], acc) for d ascending from +0; candidates are
 // ranked by (score descending, block index ascending) and the query block
-// itself is never a candidate.  MFMA is deliberately not used here: its
-// internal accumulation order cannot be reproduced by such a loop.
+// itself is never a candidate.  Of the matrix instructions only those of one product
+// per element (fp32, K = 1) keep that chain: bsa_rank.h, for many blocks; the others
+// sum in an order that cannot be reproduced by such a loop.
 #include "bsa_coarse.h"
 #include "bsa_device.h"
 #include "bsa_launch.h"
+#include "bsa_rank.h"
 
 namespace bsa {
 
@@ -217,15 +219,6 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolTensor t0, PoolTensor t1,
 // ---------------------------------------------------------------------------
 // scores + top-n
 // ---------------------------------------------------------------------------
-// Order-preserving map fp32 -> u32 (larger float <=> larger integer).  Every
-// non-NaN input maps to a value >= 0x007fffff; the clamp keeps even a NaN bit
-// pattern away from 0, which marks "removed".
-__device__ __forceinline__ uint32_t rank_key(float s)
-{
-    const uint32_t u = __float_as_uint(s + 0.0f);    // -0 -> +0
-    return max((u & 0x80000000u) ? ~u : (u | 0x80000000u), 1u);
-}
-
 // Top-n of one row of m ranking keys (in LDS) by one wavefront; cand: 64 words of LDS
 // of its own.  A round finds a threshold that at least `want` lanes' best keys reach
 // (bit by bit, 20 of the 32 bits: a lower threshold only lets more through), collects
@@ -249,11 +242,6 @@ __device__ __forceinline__ void topn_of_row(uint32_t* keys, uint64_t* cand,
                                             int32_t* __restrict__ dst, int m, int n, int lane)
 {
     int done = 0, limit = 32;
-    // position of this lane among the set lanes of mask
-    auto place_in = [](uint64_t mask) {
-        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-    };
     // candidates with keys >= floor_key into cand (the first 64 of them); their number
     auto collect = [&](uint32_t floor_key) {
         int count = 0;
@@ -431,8 +419,8 @@ __device__ __forceinline__ void select_block(const float* __restrict__ qbar,
 // The pooled means are passed twice: written through qbar_w / kbar_w / kbar_il_w
 // (the part being pooled), read through qbar_r / kbar_il_r (the part
 // being ranked).
-template <typename T, int VEC, int D, bool BIG>
-__global__ __launch_bounds__(256) void pool_select_kernel(
+template <typename T, int VEC, int D, int MODE>
+__global__ __launch_bounds__(256, MODE == 2 ? 2 : 1) void pool_select_kernel(
     const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ qbar_w,
     float* __restrict__ kbar_w, float* __restrict__ kbar_il_w, const float* __restrict__ qbar_r,
     const float* __restrict__ kbar_il_r,
@@ -441,8 +429,13 @@ __global__ __launch_bounds__(256) void pool_select_kernel(
     uint32_t n_pool_blocks, uint32_t n_poolers, uint32_t select_first)
 {
     if (blockIdx.x >= n_poolers) {
-        select_block<D, BIG>(qbar_r, kbar_il_r, sel_idx, g, G,
-                        select_first + (blockIdx.x - n_poolers));
+        const uint32_t vblock = select_first + (blockIdx.x - n_poolers);
+        if constexpr (MODE == 2) {
+            extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+            rank_block<D>(qbar_r, kbar_il_r, sel_idx, g, G, vblock, *(RankShared<D>*)smem);
+        } else {
+            select_block<D, MODE == 1>(qbar_r, kbar_il_r, sel_idx, g, G, vblock);
+        }
         return;
     }
     for (uint32_t v = blockIdx.x; v < n_pool_blocks; v += n_poolers)
@@ -453,14 +446,14 @@ __global__ __launch_bounds__(256) void pool_select_kernel(
 // The ranking beside the coarse branch, for a batch that is pooled by a launch of its
 // own: both read only pooled means, and apart each would leave most of the chip idle
 // (of a small batch).  Workgroups below n_rank rank.
-template <int D, bool BIG>
+template <int D, int MODE>
 __global__ __launch_bounds__(256) void rank_coarse_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar_il,
     const float* __restrict__ vbar, float* __restrict__ obar, int32_t* __restrict__ sel_idx, Geom g,
     int G, int G_coarse, uint32_t n_rank)
 {
     if (blockIdx.x < n_rank)
-        select_block<D, BIG>(qbar, kbar_il, sel_idx, g, G, blockIdx.x);
+        select_block<D, MODE == 1>(qbar, kbar_il, sel_idx, g, G, blockIdx.x);
     else
         coarse_block<D>(qbar, kbar_il, vbar, obar, g, G_coarse, blockIdx.x - n_rank);
 }
@@ -608,30 +601,67 @@ static int select_group_for(int m, int64_t BH)
     return G;
 }
 
-template <typename T, int VEC, int D, bool BIG>
+// Which code ranks: 2 rank_block, 1 select_block for many blocks, 0 select_block.
+// rank_block, 32 query blocks to a workgroup, takes long for a workgroup (25 us and 5 to 10
+// per 256 blocks) and pays where the pooled keys are large and the workgroups fill the
+// chip.  select_block over rank_block, ranking alone, smooth fields, noise, equal scores,
+// rising scores: head dim 32, 16 slices of 2,048 blocks 1.6, 1.4, 1.1, 1.2, of 1,012 0.8,
+// 0.9, 0.6, 0.7; 64, 16 of 2,048 1.6, 1.5, 1.2, 1.2, of 1,012 1.1, 1.2, 0.8, 1.0, 4 of 2,048
+// 1.2, 1.2, 0.9, 0.8; 128, 16 of 1,012 1.4, 1.5, 1.2, 1.3, 4 of 2,048 1.5, 1.4, 1.3, 1.2, 16
+// of 512 1.0, 1.1, 0.9, 0.8 (n = 16; n = 64 on rising scores 0.6 to 0.9).
+static int64_t rank_workgroups(int m, int64_t BH) { return BH * ((m + kRankRows - 1) / kRankRows); }
+static int rank_mode(const Geom& g, int D, int64_t BH)
+{
+    const int m = g.n_blocks, n = g.n_select;
+    if (n >= 1 && n <= kRankPicks && (int64_t)m * D >= 98304 && rank_workgroups(m, BH) * D >= 30000)
+        return 2;
+    return m > 512 ? 1 : 0;
+}
+
+// About 0.62 of the steps of rank_block, coprime to their number.
+static int rank_stride(int m)
+{
+    const int steps = (m + 255) / 256;
+    auto gcd = [](int a, int b) {
+        while (b) { const int t = a % b; a = b; b = t; }
+        return a;
+    };
+    int stride = steps * 5 / 8;
+    if (stride < 1) stride = 1;
+    while (gcd(stride, steps) != 1) ++stride;
+    return stride;
+}
+
+template <typename T, int VEC, int D, int MODE>
 static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar, float* kbar,
                                        float* kbar_il, int32_t* sel_idx, const Geom& g,
                                        int64_t BH, bool pooled, hipStream_t stream)
 {
     const int m = g.n_blocks;
-    const int G = select_group_for(m, BH);
+    // G: query blocks per workgroup, or the stride of the groups of keys (rank_block)
+    const int G = MODE == 2 ? rank_stride(m) : select_group_for(m, BH);
     if (G == 0) return hipErrorInvalidValue;
-    const size_t lds = select_lds_bytes(G, m);
+    const size_t lds = MODE == 2 ? sizeof(RankShared<D>) : select_lds_bytes(G, m);
     // the attribute is per device; setting it twice (two host threads racing) is harmless
     static bool attr_set[64] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!attr_set[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void*)pool_select_kernel<T, VEC, D, BIG>,
+        hipError_t e = hipFuncSetAttribute((const void*)pool_select_kernel<T, VEC, D, MODE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)kSelectLdsBudget);
         if (e != hipSuccess) return e;
         attr_set[dev] = true;
     }
     const int64_t BKV = BH / g.kv_group;
-    const int parts = pooled ? 1 : select_parts(BH, BKV, g, D, sizeof(T));
+    int parts = pooled ? 1 : select_parts(BH, BKV, g, D, sizeof(T));
+    // rank_block: parts that fill the chip with workgroups of several steps (24 slices of 2,276
+    // blocks, head dim 128, 1 / 2 / 3 / 4 parts 769 / 774 / 887 / 964 us; 16 of 3,422, head dim
+    // 64, 659 / 647 / 649 / 606)
+    if (MODE == 2)
+        while (parts > 1 && rank_workgroups(m, BH) < (int64_t)parts * 6 * D) --parts;
     const int wgs_per_slice = (m * (D / VEC) + 255) / 256;
-    const int groups = (m + G - 1) / G;
+    const int groups = MODE == 2 ? (m + kRankRows - 1) / kRankRows : (m + G - 1) / G;
     // one part: pooled by a launch of its own
     if (parts == 1 && !pooled) {
         const PoolTensor tensors[3] = {{q, qbar, nullptr, (uint32_t)BH},
@@ -661,7 +691,7 @@ static hipError_t launch_pool_select_t(const void* q, const void* k, float* qbar
         if (n_pool >= ((int64_t)1 << 31) || n_poolers + n_sel >= ((int64_t)1 << 31) ||
             sel_first + n_sel >= ((int64_t)1 << 32))
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL((pool_select_kernel<T, VEC, D, BIG>), dim3((unsigned)(n_poolers + n_sel)),
+        hipLaunchKernelGGL((pool_select_kernel<T, VEC, D, MODE>), dim3((unsigned)(n_poolers + n_sel)),
                            dim3(256), lds, stream, (const T*)q, (const T*)k, qbar, kbar, kbar_il,
                            (const float*)qbar, (const float*)kbar_il, sel_idx,
                            g, G, pq0, pnq, pk0,
@@ -678,15 +708,16 @@ hipError_t launch_pool_select(bool is_bf16, const void* q, const void* k, float*
                               int64_t BH, bool pooled, hipStream_t stream)
 {
     // the channel-interleaved copy of the pooled keys
-    const int m = g.n_blocks;
     float* il = (float*)scratch;
     if (!il) return hipErrorInvalidValue;
-    const bool big = m > 512;
+    const int mode = rank_mode(g, D, BH);
 #define BSA_PS(T, VEC, D_)                                                                        \
-    (big ? launch_pool_select_t<T, VEC, D_, true>(q, k, qbar, kbar, il, sel_idx, g, BH, pooled,   \
-                                                  stream)                                         \
-         : launch_pool_select_t<T, VEC, D_, false>(q, k, qbar, kbar, il, sel_idx, g, BH, pooled,  \
-                                                   stream))
+    (mode == 2   ? launch_pool_select_t<T, VEC, D_, 2>(q, k, qbar, kbar, il, sel_idx, g, BH,      \
+                                                       pooled, stream)                            \
+     : mode == 1 ? launch_pool_select_t<T, VEC, D_, 1>(q, k, qbar, kbar, il, sel_idx, g, BH,      \
+                                                       pooled, stream)                            \
+                 : launch_pool_select_t<T, VEC, D_, 0>(q, k, qbar, kbar, il, sel_idx, g, BH,      \
+                                                       pooled, stream))
     switch (D) {
     case 32: return is_bf16 ? BSA_PS(uint16_t, 8, 32) : BSA_PS(float, 4, 32);
     case 64: return is_bf16 ? BSA_PS(uint16_t, 8, 64) : BSA_PS(float, 4, 64);
@@ -711,7 +742,7 @@ static bool rank_beside_coarse(int m, int D, int64_t BH)
     return 2 * coarse <= lds_of_cu || 2 * rank > lds_of_cu;
 }
 
-template <int D, bool BIG>
+template <int D, int MODE>
 static hipError_t launch_rank_coarse_t(const float* qbar, const float* kbar_il, const float* vbar,
                                        float* obar, int32_t* sel_idx, const Geom& g, int64_t BH,
                                        hipStream_t stream)
@@ -724,7 +755,7 @@ static hipError_t launch_rank_coarse_t(const float* qbar, const float* kbar_il, 
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!attr_set[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void*)rank_coarse_kernel<D, BIG>,
+        hipError_t e = hipFuncSetAttribute((const void*)rank_coarse_kernel<D, MODE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)(kSelectLdsBudget > kCoarseLdsBudget
                                                      ? kSelectLdsBudget : kCoarseLdsBudget));
@@ -733,7 +764,7 @@ static hipError_t launch_rank_coarse_t(const float* qbar, const float* kbar_il, 
     }
     const int64_t n_rank = BH * ((m + G - 1) / G), n_coarse = BH * ((m + Gc - 1) / Gc);
     if (n_rank + n_coarse >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    rank_coarse_kernel<D, BIG><<<dim3((unsigned)(n_rank + n_coarse)), dim3(256),
+    rank_coarse_kernel<D, MODE><<<dim3((unsigned)(n_rank + n_coarse)), dim3(256),
                                  rank_lds > coarse_lds ? rank_lds : coarse_lds, stream>>>(
         qbar, kbar_il, vbar, obar, sel_idx, g, G, Gc, (uint32_t)n_rank);
     return hipGetLastError();
@@ -761,7 +792,7 @@ hipError_t launch_blocks_three_branch(bool is_bf16, const void* q, const void* k
     const PoolTensor t[3] = {{q, qbar, nullptr, (uint32_t)BH}, {k, kbar, kbar_il, (uint32_t)BKV}, tv};
     const hipError_t e = launch_pool_tensors(is_bf16, t, ll, g, D, stream);
     if (e != hipSuccess) return e;
-    if (!rank_beside_coarse(m, D, BH)) {
+    if (rank_mode(g, D, BH) == 2 || !rank_beside_coarse(m, D, BH)) {
         const hipError_t r = launch_pool_select(is_bf16, q, k, qbar, kbar, kbar_il, sel_idx, g, D, BH,
                                                 true, stream);
         return r != hipSuccess ? r : launch_coarse(qbar, kbar_il, vbar, obar, g, D, BH, stream);

@@ -510,6 +510,68 @@ def test_selection_rounds(G, oracle, H, W, bh, bw, n, levels):
     assert np.array_equal(G.gpu_select(cfg, q, k), oracle.select(s, q, k))
 
 
+def many_blocks(cfg, kind, seed):
+    """q, k of tiles of 2 x 2 whose scores are random, mostly equal, rising with the block
+    index, falling, or subnormal."""
+    rng = np.random.default_rng(seed)
+    shape = (cfg.batch, cfg.heads, cfg.n_tokens, cfg.head_dim)
+    q, k = (rng.standard_normal(shape).astype(np.float32) for _ in range(2))
+    if kind == "levels":
+        rows, cols = cfg.grid_h // 2, cfg.grid_w // 2
+        for x in (q, k):
+            v = rng.integers(0, 2, size=shape[:2] + (rows, 1, cols, 1, 1)).astype(np.float32)
+            x[:] = np.broadcast_to(v, shape[:2] + (rows, 2, cols, 2, shape[3])).reshape(shape)
+    elif kind in ("rising", "falling"):
+        q = 1.0 + 0.01 * q
+        ramp = np.arange(cfg.n_tokens, dtype=np.float32) / cfg.n_tokens
+        k = 0.001 * k + (ramp if kind == "rising" else -ramp)[None, None, :, None]
+    elif kind == "subnormal":
+        q, k = q * np.float32(1e-20), k * np.float32(3e-21)
+    return q.astype(np.float32), k.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["random", "levels", "rising", "falling", "subnormal"])
+@pytest.mark.parametrize("heads,H,W,D,n", [
+    (10, 26, 122, 128, 32),     # 793 blocks: 25 in the last group of 64 and of 32 rows
+    (10, 32, 96, 128, 1),       # 768: three whole steps
+    (10, 64, 96, 64, 8),        # 1,536: the smallest at head dim 64
+    (10, 58, 106, 64, 17),      # 1,537: one block in the last group
+    (10, 14, 878, 32, 16),      # 3,073
+])
+def test_selection_many_blocks(G, oracle, kind, heads, H, W, D, n):
+    """Rankings of many blocks on the matrix cores: exact indices."""
+    cfg = shape_ns(1, heads, H, W, 2, 2, D, n, "fp32")
+    assert cfg.n_blocks * D >= 98304 and heads * -(-cfg.n_blocks // 32) * D >= 30000
+    q, k = many_blocks(cfg, kind, H + n)
+    assert np.array_equal(G.gpu_select(cfg, q, k), oracle.select(oracle.shape_of(cfg), q, k))
+
+
+def test_selection_many_blocks_grouped_heads_and_own_block(G, oracle):
+    """The same with three query heads to a key head, and with the own block a candidate."""
+    cfg = shape_ns(1, 9, 26, 122, 2, 2, 128, 5, "fp32", kv_heads=3)
+    q, k = many_blocks(cfg, "random", 1)
+    k = k[:, :3].copy()
+    assert np.array_equal(G.gpu_select(cfg, q, k), oracle.select_gqa(oracle.shape_of(cfg), q, k))
+    cfg = shape_ns(1, 10, 26, 122, 2, 2, 128, 5, "fp32")
+    q, k = many_blocks(cfg, "random", 2)
+    gates = np.ones((1, 10, cfg.n_tokens, 3), dtype=np.float32)
+    ref = oracle.select_all(oracle.shape_of(cfg, own_is_candidate=True), q, k)
+    assert np.array_equal(G.gpu_fwd_three_branch(cfg, q, k, k, gates, 1, 1)[1], ref)
+
+
+def test_selection_many_blocks_of_nan(G):
+    """Scores that are no numbers still give distinct blocks other than the own one."""
+    cfg = shape_ns(1, 10, 26, 122, 2, 2, 128, 7, "fp32")
+    q, k = many_blocks(cfg, "random", 3)
+    q[0, 3] = np.nan
+    k[0, 4, :2000] = np.nan
+    k[0, 5, 100] = np.nan
+    idx = np.sort(G.gpu_select(cfg, q, k), axis=-1)
+    own = np.arange(cfg.n_blocks)[:, None]
+    assert idx.min() >= 0 and idx.max() < cfg.n_blocks and (idx[0] != own).all()
+    assert (np.diff(idx, axis=-1) > 0).all()
+
+
 @pytest.mark.parametrize("batch", [1 << 18, 1 << 20])
 def test_general_more_than_2_32_work_items(G, batch):
     """2^22 and 2^24 slices of one token: with 1,024 and 256 threads per slice kernels
