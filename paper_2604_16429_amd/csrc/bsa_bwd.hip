@@ -377,17 +377,18 @@ __device__ __forceinline__ bool add_groups(unsigned char* lds_a, unsigned char* 
     return true;
 }
 
-template <typename T, int D, int NL, int SPLIT>
+template <typename T, int D, int NL, int SPLIT, bool MIXED = false>
 __global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL
-                             : NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
-                             SPLIT > 1 || NL == 1 ? 1 : (BwdLimits<T, D>::PER_SIMD))
+                             : NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL >= 2 ? 192 : 64,
+                             SPLIT > 1 || NL == 1 ? 1
+                             : D == 128 && NL > 2 ? 2 : (BwdLimits<T, D>::PER_SIMD))
 void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                     const T* __restrict__ dout, const float* __restrict__ lse2,
                     const float* __restrict__ delta, const int32_t* __restrict__ sel_idx,
                     T* __restrict__ dq, Geom g, uint32_t n_units, int row_chunks, int chunk_rows)
 {
     using Tile = SplitTile<T, D, SPLIT>;
-    constexpr int KT = Tile::KT, LOADERS = SPLIT > 1 ? SPLIT * NL : NL;
+    constexpr int KT = Tile::KT, LOADERS = SPLIT > 1 ? SPLIT * NL : NL == 3 ? 2 : NL;
     constexpr int PIECES = KT / 32 / SPLIT;          // of a tile, for each group
     __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][Tile::TILE_BYTES];
     __shared__ __attribute__((aligned(1024))) unsigned char v_lds[2][Tile::TILE_BYTES];
@@ -396,8 +397,6 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     const int lane = threadIdx.x & 63;
     const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = SPLIT == 1 ? 0 : wg_wave / NL, wave = wg_wave - group * NL;
-    using W = WaveTile<T>;
-    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int b = g.block_tokens;
 
     int item;
@@ -408,26 +407,32 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
 
-    TileReader<T, D> rd;
-    rd.init(lane);
     AttendedKeys<T, D, LOADERS, 1, Tile> keys;
     keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wg_wave);
 
-    const int tau_q = row0 + W::ROWS * wave + col;
-    const bool valid = tau_q < min(b, row0 + chunk_rows);
+    const int first_row = row0 + WaveTile<T>::ROWS * wave, end_row = min(b, row0 + chunk_rows);
+
+    with_rows<T, MIXED>(end_row - first_row, [&](auto piece_key) {
+    using K = typename decltype(piece_key)::type;
+    using W = WaveTile<K>;
+    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
+    TileReader<K, D> rd;
+    rd.init(lane);
+    const int tau_q = first_row + col;
+    const bool valid = tau_q < end_row;
     const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
-    typename RowPieces<T, D>::type qf[RowPieces<T, D>::N], dof[RowPieces<T, D>::N];
+    typename RowPieces<K, D>::type qf[RowPieces<K, D>::N], dof[RowPieces<K, D>::N];
 #pragma unroll
-    for (int s = 0; s < RowPieces<T, D>::N; ++s) {
-        load_row(q + base + q_tok * D, qf[s], s, part);
-        load_row(dout + base + q_tok * D, dof[s], s, part);
+    for (int s = 0; s < RowPieces<K, D>::N; ++s) {
+        load_row<K>(q + base + q_tok * D, qf[s], s, part);
+        load_row<K>(dout + base + q_tok * D, dof[s], s, part);
     }
     const float neg_l2 = -lse2[bh_idx * g.n_tokens + q_tok];
     const float neg_delta = -delta[bh_idx * g.n_tokens + q_tok];
     const float c2 = g.scale * kLog2e;
-    Column<T, D> acc;
-    clear_column<T, D>(acc);
-    const typename W::vec dp0 = constant_tile<T>(neg_delta);
+    Column<K, D> acc;
+    clear_column<K, D>(acc);
+    const typename W::vec dp0 = constant_tile<K>(neg_delta);
 
     __syncthreads();                                 // tables
     const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
@@ -450,14 +455,14 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
             const uint32_t kt = k_dst + at, vt = v_dst + at;
             const int left = keys.total - (KT * c + 32 * (group * PIECES + hh));
             if (left <= 0) break;
-            typename W::vec s = constant_tile<T>(0.0f), dp = dp0;
-            dot_tiles<false, T, D>(rd, kt, vt, hh * HALF, qf, dof, s, dp);
-            ColumnPieces<T, D> k0;
+            typename W::vec s = constant_tile<K>(0.0f), dp = dp0;
+            dot_tiles<false, K, D>(rd, kt, vt, hh * HALF, qf, dof, s, dp);
+            ColumnPieces<K, D> k0;
             read_columns(rd, kt, hh * HALF, 0, k0);
             if (left < 32)
 #pragma unroll
                 for (int r = 0; r < W::NR; ++r)
-                    if (past_end<T>(r, part, left)) s[r] = -INFINITY;
+                    if (past_end<K>(r, part, left)) s[r] = -INFINITY;
 #pragma unroll
             for (int r = 0; r < W::NR; ++r) dp[r] *= __builtin_amdgcn_exp2f(fmaf(s[r], c2, neg_l2));
             weighted_rows(rd, kt, hh * HALF, k0, dp, acc);
@@ -473,6 +478,7 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
         const float* extra = g.add_dq ? g.add_dq + (bh_idx * g.n_blocks + i) * D : nullptr;
         store_column<D>(dq + base + q_tok * D, acc, g.scale, extra, inv_b, part);
     }
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -483,7 +489,7 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
 // them, and walked whenever it is full or the map is exhausted.
 constexpr int kConnCap = 2048;
 
-template <typename T, int D, int NL, int SPLIT>
+template <typename T, int D, int NL, int SPLIT, bool MIXED = false>
 __global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL
                              : NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
                              SPLIT > 1 ? (D == 32 || (D == 64 && sizeof(T) == 2) || (D == 64 && NL * SPLIT == 4 && SPLIT == 2) ? 2 : 1)
@@ -512,8 +518,6 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     const int lane = threadIdx.x & 63;
     const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = SPLIT == 1 ? 0 : wg_wave / NL, wave = wg_wave - group * NL;
-    using W = WaveTile<T>;
-    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int m = g.n_blocks, b = g.block_tokens;
     const int words = (m + 31) >> 5;                  // of a key block's row of the reverse map
 
@@ -540,26 +544,32 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                 d_rsrc = buffer_desc(db, (uint32_t)(group_rows * 4));
 
     fill_position_table(g, pos_s);
-    TileReader<T, D> rd;
+    const int first_row = row0 + WaveTile<T>::ROWS * wave, end_row = min(b, row0 + chunk_rows);
+
+    with_rows<T, MIXED>(end_row - first_row, [&](auto piece_key) {
+    using K = typename decltype(piece_key)::type;
+    using W = WaveTile<K>;
+    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
+    TileReader<K, D> rd;
     rd.init(lane);
 
     // this wavefront's key rows.  V enters negated: the accumulator that starts
     // from delta then ends as delta - dP without an instruction per element, and
     // dK is stored with the sign turned.
-    const int tau_k = row0 + W::ROWS * wave + col;
-    const bool valid = tau_k < min(b, row0 + chunk_rows);
+    const int tau_k = first_row + col;
+    const bool valid = tau_k < end_row;
     const int64_t k_tok = token_of(g, j, valid ? tau_k : 0);
-    typename RowPieces<T, D>::type kf[RowPieces<T, D>::N], vf[RowPieces<T, D>::N];
+    typename RowPieces<K, D>::type kf[RowPieces<K, D>::N], vf[RowPieces<K, D>::N];
 #pragma unroll
-    for (int s = 0; s < RowPieces<T, D>::N; ++s) {
-        load_row(k + base + k_tok * D, kf[s], s, part);
-        load_row(v + base + k_tok * D, vf[s], s, part);
+    for (int s = 0; s < RowPieces<K, D>::N; ++s) {
+        load_row<K>(k + base + k_tok * D, kf[s], s, part);
+        load_row<K>(v + base + k_tok * D, vf[s], s, part);
         vf[s] = negated(vf[s]);
     }
     const float c2 = g.scale * kLog2e;
-    Column<T, D> acck, accv;
-    clear_column<T, D>(acck);
-    clear_column<T, D>(accv);
+    Column<K, D> acck, accv;
+    clear_column<K, D>(acck);
+    clear_column<K, D>(accv);
 
     const uint32_t q_dst = lds_address(q_lds), g_dst = lds_address(g_lds);
     const uint32_t l_dst = lds_address(l_lds), d_dst = lds_address(d_lds);
@@ -674,20 +684,20 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
                 const uint32_t qt = q_dst + first, gt = g_dst + first;
                 const int row = 32 * (group * PIECES + hh), left = total - (KT * c + row);
                 if (left <= 0) break;
-                typename W::vec p = constant_tile<T>(0.0f), dp;
+                typename W::vec p = constant_tile<K>(0.0f), dp;
 #pragma unroll
                 for (int r4 = 0; r4 < W::NR / 4; ++r4) {
                     const float4 d4 = *(const float4*)(d_lds[buf] + row + W::STEP * r4 + 4 * part);
                     dp[4 * r4] = d4.x; dp[4 * r4 + 1] = d4.y;
                     dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
                 }
-                dot_tiles<true, T, D>(rd, qt, gt, hh * HALF, kf, vf, p, dp);
-                ColumnPieces<T, D> c0;
+                dot_tiles<true, K, D>(rd, qt, gt, hh * HALF, kf, vf, p, dp);
+                ColumnPieces<K, D> c0;
                 read_columns(rd, gt, hh * HALF, 0, c0);
                 if (left < 32)
 #pragma unroll
                     for (int r = 0; r < W::NR; ++r)
-                        if (past_end<T>(r, part, left)) p[r] = -INFINITY;
+                        if (past_end<K>(r, part, left)) p[r] = -INFINITY;
 #pragma unroll
                 for (int r4 = 0; r4 < W::NR / 4; ++r4) {
                     const float4 l4 = *(const float4*)(l_lds[buf] + row + W::STEP * r4 + 4 * part);
@@ -731,6 +741,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
         store_column<D>(dv + base + k_tok * D, accv, 1.0f,
                            g.add_dv ? g.add_dv + pooled_row : nullptr, inv_b, part);
     }
+    });
 }
 
 // Row wavefronts of a workgroup at most, and groups that share its list, by the row
@@ -790,7 +801,7 @@ static BwdSplit dq_split(const Geom& g, int64_t BH)
     if (waves <= FOUR && pieces >= 6) return {1, 4};
     return waves <= TWO && pieces >= 5 ? BwdSplit{2, 2} : BwdSplit{BwdLimits<T, D>::MAX_WAVES, 1};
 }
-template <typename T, int D, int SPLIT>
+template <typename T, int D, int SPLIT, bool MIXED = false>
 static auto dkdv_kernel(int waves)
 {
     if constexpr (SPLIT == 4) {                       // (fp32, head dim 128: not chosen)
@@ -798,11 +809,12 @@ static auto dkdv_kernel(int waves)
     } else if constexpr (SPLIT == 2) {
         return waves >= 2 ? bwd_generic_dkdv<T, D, 2, 2> : bwd_generic_dkdv<T, D, 1, 2>;
     } else {
-        return waves >= 4 ? bwd_generic_dkdv<T, D, 4, 1>
-               : waves >= 2 ? bwd_generic_dkdv<T, D, 2, 1> : bwd_generic_dkdv<T, D, 1, 1>;
+        return waves >= 4 ? bwd_generic_dkdv<T, D, 4, 1, MIXED>
+               : waves >= 2 ? bwd_generic_dkdv<T, D, 2, 1, MIXED>
+                            : bwd_generic_dkdv<T, D, 1, 1, MIXED>;
     }
 }
-template <typename T, int D, int SPLIT>
+template <typename T, int D, int SPLIT, bool MIXED = false>
 static auto dq_kernel(int waves)
 {
     if constexpr (SPLIT == 4) {                       // (head dim 128: not chosen)
@@ -810,8 +822,13 @@ static auto dq_kernel(int waves)
     } else if constexpr (SPLIT == 2) {
         return waves >= 2 ? bwd_generic_dq<T, D, 2, 2> : bwd_generic_dq<T, D, 1, 2>;
     } else {
-        return waves >= 4 ? bwd_generic_dq<T, D, 4, 1>
-               : waves >= 2 ? bwd_generic_dq<T, D, 2, 1> : bwd_generic_dq<T, D, 1, 1>;
+        // three wavefronts at head dim 128: two workgroups fit a CU, and 256 registers let
+        // their six wavefronts share its SIMDs (dQ of 8 x 10 tiles -25 %; 2 x 2 wavefronts have
+        // a SIMD each and take as many as they want)
+        return waves >= 4 ? bwd_generic_dq<T, D, 4, 1, MIXED>
+               : waves == 3 && D == 128 ? bwd_generic_dq<T, D, D == 128 ? 3 : 2, 1, MIXED>
+               : waves >= 2 ? bwd_generic_dq<T, D, 2, 1, MIXED>
+                            : bwd_generic_dq<T, D, 1, 1, MIXED>;
     }
 }
 
@@ -830,6 +847,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
         const int nw = rows.waves * split.groups;
         auto kernel = split.groups == 4 ? dkdv_kernel<T, D, 4>(rows.waves)
                       : split.groups == 2 ? dkdv_kernel<T, D, 2>(rows.waves)
+                      : rows.narrow       ? dkdv_kernel<T, D, 1, sizeof(T) == 2>(rows.waves)
                                           : dkdv_kernel<T, D, 1>(rows.waves);
         const dim3 block(64 * nw);
         return launch_slices(BKV, wgs * 64 * nw, [&](int64_t first, int64_t slices) {
@@ -853,6 +871,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
         const int nw = rows.waves * split.groups;
         auto kernel = split.groups == 4 ? dq_kernel<T, D, 4>(rows.waves)
                       : split.groups == 2 ? dq_kernel<T, D, 2>(rows.waves)
+                      : rows.narrow       ? dq_kernel<T, D, 1, sizeof(T) == 2>(rows.waves)
                                           : dq_kernel<T, D, 1>(rows.waves);
         const dim3 block(64 * nw);
         return launch_slices(BKV, g.kv_group * wgs * 64 * nw, [&](int64_t first, int64_t slices) {

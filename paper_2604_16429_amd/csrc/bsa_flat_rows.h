@@ -13,6 +13,8 @@
 #include "bsa_device.h"
 #include "bsa_mfma_common.h"
 
+#include <type_traits>
+
 namespace bsa {
 
 constexpr int kListTable = 1024;           // listed blocks the LDS table holds
@@ -139,7 +141,16 @@ __device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint3
 //         and SIMD) with half the registers, so that twice as many wavefronts share a
 //         block: a chain of products that depend on each other is half as long, and four
 //         (backward three) wavefronts per SIMD instead of two cover it.
+//   Rows16: bf16 with 16, v_mfma_f32_16x16x32_bf16 (the same rate), for the last wavefront of
+//         a block when it has no more rows than that: half the vector work and matrix
+//         instructions, where 32 columns would be mostly idle.  Tiles of 10 x 10, whose
+//         fourth wavefront has four rows, work 112 rows instead of 128.
+struct Rows16 {};
 template <typename T> struct WaveTile;
+template <> struct WaveTile<Rows16> {
+    static constexpr int ROWS = 16, NR = 8, STEP = 16;
+    typedef __attribute__((ext_vector_type(8))) float vec;
+};
 template <> struct WaveTile<uint16_t> {
     static constexpr int ROWS = 32, NR = 16, STEP = 8;
     typedef f32x16 vec;
@@ -171,6 +182,7 @@ template <typename T> __device__ __forceinline__ float column_sum(float x)
 template <typename T, int D> struct Column;
 template <int D> struct Column<uint16_t, D> { f32x16 a[D / 32]; };
 template <int D> struct Column<float, D> { f32x4 a[D / 16]; };
+template <int D> struct Column<Rows16, D> { f32x4 a[D / 16]; };
 template <typename T, int D>
 __device__ __forceinline__ void scale_column(Column<T, D>& c, float f)
 {
@@ -230,6 +242,27 @@ template <int D> struct TileReader<float, D> {
         }
     }
 };
+template <int D> struct TileReader<Rows16, D> {
+    using Tile = FlatTile<uint16_t, D>;
+    static constexpr int BASES = D == 32 ? 1 : 2, WBASES = D == 32 ? 2 : 4;
+    uint32_t row[BASES];        // chunk 4 s + part of row col, s < BASES
+    uint32_t trans[WBASES];     // transposing read of channels 16 ct, ct < WBASES
+    __device__ __forceinline__ void init(int lane)
+    {
+        const int c16 = lane & 15, part = lane >> 4;
+#pragma unroll
+        for (int s = 0; s < BASES; ++s)
+            row[s] = (uint32_t)(c16 * Tile::ROW_BYTES + Tile::swz(c16, 4 * s + part) * 16);
+        // source lane c16 of 16-lane group `part` supplies 8 bytes of row 4 part + c16/4
+        // (+ 16), channel 4 (c16%4) + 16 ct
+        const int r = 4 * part + (c16 >> 2);
+#pragma unroll
+        for (int ct = 0; ct < WBASES; ++ct) {
+            const int at = 4 * (c16 & 3) + 16 * ct;
+            trans[ct] = (uint32_t)(r * Tile::ROW_BYTES + Tile::swz(r, at >> 3) * 16 + (at & 7) * 2);
+        }
+    }
+};
 
 // Products of a 32-row tile.  LDS reads are issued a group ahead of the matrix
 // instructions that use them, and held there (sched_barrier): the compiler would
@@ -246,6 +279,16 @@ template <int D> struct RowPieces<uint16_t, D> {
 };
 struct RowFrag16 {
     f32x4 t[2];
+};
+// (Rows16: a piece is 32 channels, 32 s + 8 part + 0..7 of each lane, one instruction for
+// each of the two 16-row halves)
+struct RowFragBf16 {
+    bf16x8 t[2];
+};
+template <int D> struct RowPieces<Rows16, D> {
+    typedef bf16x8 type;
+    typedef RowFragBf16 frag;
+    static constexpr int N = D / 32, GROUP = N;
 };
 template <int D> struct RowPieces<float, D> {
     typedef f32x4 type;
@@ -276,6 +319,17 @@ __device__ __forceinline__ void read_rows(const TileReader<float, D>& rd, uint32
                                         imm + (s / rd.BASES) * 128 + 16 * t * FlatTile<float, D>::ROW_BYTES);
     }
 }
+template <int D>
+__device__ __forceinline__ void read_rows(const TileReader<Rows16, D>& rd, uint32_t tile, int imm,
+                                          int, RowFragBf16 (&x)[RowPieces<Rows16, D>::GROUP])
+{
+#pragma unroll
+    for (int s = 0; s < RowPieces<Rows16, D>::GROUP; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            x[s].t[t] = lds_read<bf16x8>(rd.row[s % rd.BASES] + tile,
+                                         imm + (s / rd.BASES) * 128 + 16 * t * 2 * D);
+}
 typedef WaveTile<float>::vec f32x8;
 __device__ __forceinline__ f32x4 half_tile(const f32x8& v, int t)
 {
@@ -293,6 +347,12 @@ __device__ __forceinline__ f32x8 mul_piece(const RowFrag16& x, f32x4 y, f32x8 ac
         a = __builtin_amdgcn_mfma_f32_16x16x4f32(x.t[0][c], y[c], a, 0, 0, 0);
         b = __builtin_amdgcn_mfma_f32_16x16x4f32(x.t[1][c], y[c], b, 0, 0, 0);
     }
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+__device__ __forceinline__ f32x8 mul_piece(const RowFragBf16& x, bf16x8 y, f32x8 acc)
+{
+    const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.t[0], y, half_tile(acc, 0), 0, 0, 0);
+    const f32x4 b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.t[1], y, half_tile(acc, 1), 0, 0, 0);
     return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
@@ -364,6 +424,10 @@ template <int D> struct ColumnPieces<uint16_t, D> {
     static constexpr int GROUPS = 2;
     bf16x8 x[D / 32];                       // A operand: channels 32 dt .. x 16 rows
 };
+template <int D> struct ColumnPieces<Rows16, D> {
+    static constexpr int GROUPS = 1;
+    bf16x8 x[D / 16];                       // A operand: channels 16 ct .. x 32 rows
+};
 template <int D> struct ColumnPieces<float, D> {
     static constexpr int VEC = TileReader<float, D>::VEC;
     typedef __attribute__((ext_vector_type(VEC))) float vec;
@@ -385,6 +449,23 @@ __device__ __forceinline__ void read_columns(const TileReader<uint16_t, D>& rd, 
                     rd.trans[dt % rd.WBASES] + tile +
                     (uint32_t)(imm + (16 * group + 8 * r) * ROW + (dt / rd.WBASES) * 128)));
         c.x[dt] = __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+}
+// (rows 4 part + 0..3 and 16 + 4 part + 0..3: the order in which a lane holds its weights)
+template <int D>
+__device__ __forceinline__ void read_columns(const TileReader<Rows16, D>& rd, uint32_t tile, int imm,
+                                             int, ColumnPieces<Rows16, D>& c)
+{
+#pragma unroll
+    for (int ct = 0; ct < D / 16; ++ct) {
+        bf16x4 part[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+            part[r] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                (__attribute__((address_space(3))) bf16x4*)(uintptr_t)(
+                    rd.trans[ct % rd.WBASES] + tile +
+                    (uint32_t)(imm + 16 * r * 2 * D + (ct / rd.WBASES) * 128)));
+        c.x[ct] = __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
     }
 }
 template <int D>
@@ -418,6 +499,21 @@ __device__ __forceinline__ void add_columns(const ColumnPieces<uint16_t, D>& c, 
     }
 }
 template <int D>
+__device__ __forceinline__ void add_columns(const ColumnPieces<Rows16, D>& c, const f32x8& w, int,
+                                            Column<Rows16, D>& acc)
+{
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) split_bf16(w[2 * e], w[2 * e + 1], hi[e], lo[e]);
+    const bf16x8 w_hi = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+    const bf16x8 w_lo = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+#pragma unroll
+    for (int ct = 0; ct < D / 16; ++ct) {
+        acc.a[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.x[ct], w_hi, acc.a[ct], 0, 0, 0);
+        acc.a[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.x[ct], w_lo, acc.a[ct], 0, 0, 0);
+    }
+}
+template <int D>
 __device__ __forceinline__ void add_columns(const ColumnPieces<float, D>& c, const f32x8& w, int group,
                                             Column<float, D>& acc)
 {
@@ -445,10 +541,13 @@ __device__ __forceinline__ void weighted_rows(const TileReader<T, D>& rd, uint32
     }
 }
 
+// Piece `step` of a stationary row.  K: the key of the row pieces (element type or Rows16).
+template <typename K>
 __device__ __forceinline__ void load_row(const uint16_t* row, bf16x8& f, int step, int part)
 {
-    f = *(const bf16x8*)(row + 16 * step + 8 * part);
+    f = *(const bf16x8*)(row + (std::is_same<K, Rows16>::value ? 32 : 16) * step + 8 * part);
 }
+template <typename K>
 __device__ __forceinline__ void load_row(const float* row, f32x4& f, int step, int part)
 {
     f = *(const f32x4*)(row + 16 * step + 4 * part);
@@ -483,6 +582,18 @@ __device__ __forceinline__ void store_column(uint16_t* row, const Column<uint16_
                                       a[4 * r4 + 3] * f),
                           extra ? extra + d : nullptr, inv_b);
         }
+}
+template <int D>
+__device__ __forceinline__ void store_column(uint16_t* row, const Column<Rows16, D>& acc, float f,
+                                             const float* extra, float inv_b, int part)
+{
+#pragma unroll
+    for (int ct = 0; ct < D / 16; ++ct) {
+        const int d = 16 * ct + 4 * part;
+        const f32x4& a = acc.a[ct];
+        store4_or_add(row + d, make_float4(a[0] * f, a[1] * f, a[2] * f, a[3] * f),
+                      extra ? extra + d : nullptr, inv_b);
+    }
 }
 // (value r of output tile c is channel VEC (4 part + r) + c % VEC, + 64 for c >= 4)
 template <int D>
@@ -642,15 +753,34 @@ private:
     const Geom* geom;
 };
 
+// Runs body(key) with the row pieces that a wavefront of `rows` rows takes.  MIXED: the
+// kernel has the narrow form too (a kernel of its own: both forms in one took up to 3.5 %
+// longer where no wavefront is narrow).
+template <typename K> struct PieceKey {
+    typedef K type;
+};
+template <typename T, bool MIXED, class F> __device__ __forceinline__ void with_rows(int rows, F body)
+{
+    if constexpr (MIXED && sizeof(T) == 2) {
+        if (rows <= 16) {
+            body(PieceKey<Rows16>{});
+            return;
+        }
+    }
+    body(PieceKey<T>{});
+}
+
 // Rows of a block over workgroups of at most `max_waves` wavefronts of `rows` rows
 // each: as few workgroups as hold them, as even as possible.
 struct RowSplit {
     int chunks, waves;
+    bool narrow;                // bf16: a wavefront has at most 16 of its 32 rows
     RowSplit(int block_tokens, int max_waves, int rows)
     {
         const int row_tiles = (block_tokens + rows - 1) / rows;
         chunks = (row_tiles + max_waves - 1) / max_waves;
         waves = (row_tiles + chunks - 1) / chunks;
+        narrow = rows == 32 && chunks * waves * 32 - block_tokens >= 16;
     }
 };
 

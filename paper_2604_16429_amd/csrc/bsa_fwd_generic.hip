@@ -24,7 +24,11 @@
 //         grid 18.2 -> 12.7 us.
 //   bf16: v_mfma_f32_32x32x16_bf16.  The weights enter the second product as two
 //         bf16 terms (16 significant bits): these shapes have always had their
-//         weights multiplied in fp32, and keep that precision.
+//         weights multiplied in fp32, and keep that precision.  The last wavefront of a
+//         block with at most 16 rows left takes the 16-wide form (Rows16): 12 x 24 tiles, 16
+//         slices, 9 blocks, forward in us, head dim 32 tiles of 10 x 10 147 -> 137, 6 x 8
+//         51 -> 45, 10 x 13 (five wavefronts) 321 -> 272; 64: 221 -> 217, 81 -> 75, 529 ->
+//         475; backward at 64: 736 -> 721, 255 -> 243, 1,573 -> 1,386.
 // Measured against the vector-ALU kernel that it replaces (one lane per query
 // row, keys broadcast from LDS), select + forward: 131,072 tokens, 16 heads, head
 // dim 32, bf16, 17 blocks of 128: 9.77 -> 1.25 ms; the 32 x 64 grid in fp32: 121
@@ -54,7 +58,7 @@ constexpr float kPlainRef = 1048576.0f;
 // SPLIT > 1: as many groups of one or two (NL) wavefronts own the same rows and take
 // the key tiles in turn, with tiles and a softmax of their own; the first group merges them
 // at the end.  For launches that leave the chip idle; see key_split.
-template <typename T, int D, int NL, int SPLIT>
+template <typename T, int D, int NL, int SPLIT, bool MIXED = false>
 __global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL : NL == 4 ? 512 : NL == 2 ? 192 : 64,
                              SPLIT > 1 || NL == 1 || (NL == 2 && D == 128) ? 1
                              : D == 32 || (sizeof(T) == 4 && D == 128) ? 4 : 2)
@@ -79,8 +83,6 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     const int waves = SPLIT == 1 ? 0 : (int)(blockDim.x >> 6) / SPLIT;       // of a group
     const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = SPLIT == 1 ? 0 : wg_wave / waves, wave = wg_wave - group * waves;
-    using W = WaveTile<T>;
-    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
     const int b = g.block_tokens;
 
     int item;
@@ -90,18 +92,23 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     const int row0 = (item - i * row_chunks) * chunk_rows;
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
-    TileReader<T, D> rd;
-    rd.init(lane);
     AttendedKeys<T, D, NL, SPLIT> keys;
     keys.init(g, sel_idx, bh_idx, i, tables_s, lane, wave, group);
+    const int first_row = row0 + WaveTile<T>::ROWS * wave, end_row = min(b, row0 + chunk_rows);
 
+    with_rows<T, MIXED>(end_row - first_row, [&](auto piece_key) {
+    using K = typename decltype(piece_key)::type;
+    using W = WaveTile<K>;
+    const int col = lane & (W::ROWS - 1), part = lane / W::ROWS;
+    TileReader<K, D> rd;
+    rd.init(lane);
     // this wavefront's query rows
-    const int tau_q = row0 + W::ROWS * wave + col;
-    const bool valid = tau_q < min(b, row0 + chunk_rows);
+    const int tau_q = first_row + col;
+    const bool valid = tau_q < end_row;
     const int64_t q_tok = token_of(g, i, valid ? tau_q : 0);
-    typename RowPieces<T, D>::type qf[RowPieces<T, D>::N];
+    typename RowPieces<K, D>::type qf[RowPieces<K, D>::N];
 #pragma unroll
-    for (int s = 0; s < RowPieces<T, D>::N; ++s) load_row(q + base + q_tok * D, qf[s], s, part);
+    for (int s = 0; s < RowPieces<K, D>::N; ++s) load_row<K>(q + base + q_tok * D, qf[s], s, part);
     __syncthreads();                                 // tables
 
     const int64_t slice_bytes = g.n_tokens * Tile::ROW_BYTES;
@@ -113,8 +120,8 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
     }
 
     const float c2 = g.scale * 1.4426950408889634f;
-    Column<T, D> oacc;
-    clear_column<T, D>(oacc);
+    Column<K, D> oacc;
+    clear_column<K, D>(oacc);
     float m_ref = -INFINITY, m_rest = 0.0f, l_run = 0.0f;
     uint64_t rests = 0;                              // lanes whose m_rest is not 0
 
@@ -129,15 +136,15 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
         const uint32_t at = (uint32_t)buf * Tile::TILE_BYTES;
 #pragma unroll
         for (int hh = 0; hh < KT / 32; ++hh) {
-            typename W::vec s = dot_tile(rd, k_dst + at, 32 * hh * Tile::ROW_BYTES, qf, constant_tile<T>(0.0f));
+            typename W::vec s = dot_tile<K, D>(rd, k_dst + at, 32 * hh * Tile::ROW_BYTES, qf, constant_tile<K>(0.0f));
             const int left = keys.total - (KT * c + 32 * hh);     // keys from this half tile on
             if (left < 32) {
                 if (left <= 0) break;
 #pragma unroll
                 for (int r = 0; r < W::NR; ++r)
-                    if (past_end<T>(r, part, left)) s[r] = -INFINITY;
+                    if (past_end<K>(r, part, left)) s[r] = -INFINITY;
             }
-            ColumnPieces<T, D> v0;
+            ColumnPieces<K, D> v0;
             read_columns(rd, v_dst + at, 32 * hh * Tile::ROW_BYTES, 0, v0);
             typename W::vec p;
             float rs0 = 0.0f, rs1 = 0.0f;
@@ -155,7 +162,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 float mx = s[0];
 #pragma unroll
                 for (int r = 1; r < W::NR; ++r) mx = fmaxf(mx, s[r]);
-                mx = column_max<T>(mx);
+                mx = column_max<K>(mx);
                 const bool up = fmaf(mx, c2, -m_ref) > m_rest;
                 const float m_new = up ? mx * c2 : m_ref;
                 // no reference yet: all scores so far are below the range of fp32 once
@@ -171,7 +178,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
                 m_rest = rest_new;
                 rests = __builtin_amdgcn_ballot_w64(rest_new != 0.0f);
                 l_run *= alpha;
-                scale_column<T, D>(oacc, alpha);
+                scale_column<K, D>(oacc, alpha);
                 rs = 0.0f;
 #pragma unroll
                 for (int r = 0; r < W::NR; ++r) {
@@ -186,7 +193,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 
     if constexpr (SPLIT > 1) {
         // groups 1 .. hand over what they have, lane by lane; the first group adds it up
-        constexpr int VALUES = (int)sizeof(Column<T, D>) / 4 + 3;
+        constexpr int VALUES = (int)sizeof(Column<K, D>) / 4 + 3;
         static_assert((SPLIT - 1) * NL * VALUES * 256 <= SPLIT * 2 * Tile::TILE_BYTES * 2,
                       "fits the tiles");
         constexpr int HALF = SPLIT * 2 * Tile::TILE_BYTES / 256;       // values per array and lane
@@ -225,7 +232,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
         }
     }
 
-    const float l_tot = column_sum<T>(l_run);
+    const float l_tot = column_sum<K>(l_run);
     if (valid) {
         const float inv_l = 1.0f / l_tot;
         store_column<D>(out + base + q_tok * D, oacc, inv_l, nullptr, 0.0f, part);
@@ -233,6 +240,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
             lse[bh_idx * g.n_tokens + q_tok] =
                 (m_ref + (m_rest + __builtin_amdgcn_logf(l_tot))) * 0.6931471805599453f;
     }
+    });
 }
 
 // Row wavefronts of a workgroup at most, and groups that share its keys, for a launch of
@@ -270,7 +278,7 @@ static KeySplit key_split(int64_t wavefronts, int64_t pairs, bool single, int64_
     return {most, 1};
 }
 
-template <typename T, int D, int SPLIT>
+template <typename T, int D, int SPLIT, bool MIXED = false>
 static auto kernel_of(int waves)
 {
     if constexpr (SPLIT == 4) {                       // (head dim 128: not chosen)
@@ -278,8 +286,9 @@ static auto kernel_of(int waves)
     } else if constexpr (SPLIT == 2) {
         return waves >= 2 ? fwd_generic_kernel<T, D, 2, 2> : fwd_generic_kernel<T, D, 1, 2>;
     } else {
-        return waves >= 4 ? fwd_generic_kernel<T, D, 4, 1>
-               : waves >= 2 ? fwd_generic_kernel<T, D, 2, 1> : fwd_generic_kernel<T, D, 1, 1>;
+        return waves >= 4 ? fwd_generic_kernel<T, D, 4, 1, MIXED>
+               : waves >= 2 ? fwd_generic_kernel<T, D, 2, 1, MIXED>
+                            : fwd_generic_kernel<T, D, 1, 1, MIXED>;
     }
 }
 
@@ -310,7 +319,8 @@ static hipError_t launch_t(const void* q, const void* k, const void* v, const Fw
     const int nw = rows.waves, split = ks.groups;
     const int64_t wgs = (int64_t)g.kv_group * g.n_blocks * rows.chunks;    // per key/value slice
     auto kernel = split == 4 ? kernel_of<T, D, 4>(nw)
-                  : split == 2 ? kernel_of<T, D, 2>(nw) : kernel_of<T, D, 1>(nw);
+                  : split == 2 ? kernel_of<T, D, 2>(nw)
+                  : rows.narrow ? kernel_of<T, D, 1, sizeof(T) == 2>(nw) : kernel_of<T, D, 1>(nw);
     return launch_slices(BH / g.kv_group, wgs * 64 * nw * split, [&](int64_t first, int64_t slices) {
         const int64_t row = first * g.kv_group * g.n_tokens, kv = first * g.n_tokens * D;
         FwdJob piece[2];

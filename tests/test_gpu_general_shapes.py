@@ -37,7 +37,10 @@ SHAPES = [
     (20, 26, 2, 2, 64, 64),      # 65: kept in the given order
     (16, 30, 16, 1, 64, 5),      # b = 16: one fp32 wavefront of 16 rows
     (34, 12, 17, 1, 128, 4),     # b = 17: one row in the second of them
-    (24, 36, 8, 6, 64, 7),       # b = 48: three, two of which gather
+    (24, 36, 8, 6, 64, 7),       # b = 48: three, two of which gather; bf16 two, the second
+                                 # 16 rows wide
+    (20, 50, 10, 10, 32, 5),     # b = 100: the fourth of four 16 rows wide
+    (28, 30, 7, 10, 128, 5),     # b = 70: the third of three
     (46, 48, 1, 2, 32, 959),     # list and its repeated last entry just fit the LDS table
     (46, 48, 1, 2, 32, 960),     # just not
     (46, 48, 1, 2, 32, 1030),    # more listed blocks than the LDS table holds
@@ -294,6 +297,9 @@ SPLIT_LIMITS = {("bf16", 32): (2048, 4096), ("bf16", 64): (2048, 4096), ("bf16",
     (1, 1, 32, 30, 8, 6, 9),     # b = 48: row wavefronts in pairs, bf16 one, fp32 two per block
     (2, 1, 44, 15, 11, 3, 9),    # b = 33; 330 rows and more to a list, the last piece not full
     (1, 1, 32, 32, 4, 4, 27),    # b = 16: one row wavefront, in two groups or four
+    (1, 1, 40, 40, 10, 10, 7),   # b = 100: bf16 unsplit, four, the last of them 16 rows wide
+    (1, 1, 28, 40, 7, 10, 7),    # b = 70: three
+    (1, 1, 40, 52, 10, 13, 7),   # b = 130: five; head dim 128 two workgroups of three, one empty
 ])
 def test_general_backward_split(G, oracle, dtype, D, heads, kv_heads, H, W, bh, bw, n):
     """One entry as often as it takes for launches whose lists are walked by four groups of
