@@ -74,15 +74,13 @@ __device__ __forceinline__ float dot16(const float* a_row, const float* b_row)
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(const T* __restrict__ out,
-                                                       const T* __restrict__ dout,
-                                                       const float* __restrict__ lse,
-                                                       float* __restrict__ delta,
-                                                       float* __restrict__ lse2, int64_t rows)
+__device__ __forceinline__ void prep_rows(const T* __restrict__ out, const T* __restrict__ dout,
+                                          const float* __restrict__ lse, float* __restrict__ delta,
+                                          float* __restrict__ lse2, int64_t rows, uint32_t wg)
 {
     constexpr int VEC = 16 / (int)sizeof(T), LPR = D / VEC;      // 4, 8, 16 or 32 lanes per row
     const int sub = threadIdx.x % LPR;
-    int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LPR;
+    int64_t row = ((int64_t)wg * blockDim.x + threadIdx.x) / LPR;
     const bool valid = row < rows;
     if (!valid) row = rows - 1;                     // keep the lane group whole for the sums
     float acc = dot16(out + row * D + VEC * sub, dout + row * D + VEC * sub);
@@ -98,33 +96,13 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const T* __restrict__ out
 }
 
 template <typename T, int D>
-static hipError_t launch_prep_t(const void* out, const void* dout, const float* lse, float* delta,
-                                float* lse2, int64_t rows, hipStream_t stream)
+__global__ __launch_bounds__(256) void bwd_prep_kernel(const T* __restrict__ out,
+                                                       const T* __restrict__ dout,
+                                                       const float* __restrict__ lse,
+                                                       float* __restrict__ delta,
+                                                       float* __restrict__ lse2, int64_t rows)
 {
-    constexpr int LPR = D * (int)sizeof(T) / 16, RPW = 256 / LPR;     // rows per workgroup
-    return launch_slices((rows + RPW - 1) / RPW, 256, [&](int64_t first, int64_t wgs) {
-        const int64_t row = first * RPW;
-        bwd_prep_kernel<T, D><<<dim3((unsigned)wgs), dim3(256), 0, stream>>>(
-            (const T*)out + row * D, (const T*)dout + row * D, lse + row, delta + row, lse2 + row,
-            rows - row < wgs * RPW ? rows - row : wgs * RPW);
-        return hipGetLastError();
-    });
-}
-
-hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
-                           float* delta, float* lse2, int64_t rows, int D, hipStream_t stream)
-{
-#define BSA_CASE(DD)                                                                              \
-    case DD:                                                                                      \
-        return is_bf16 ? launch_prep_t<uint16_t, DD>(out, dout, lse, delta, lse2, rows, stream)   \
-                       : launch_prep_t<float, DD>(out, dout, lse, delta, lse2, rows, stream);
-    switch (D) {
-        BSA_CASE(32)
-        BSA_CASE(64)
-        BSA_CASE(128)
-    }
-#undef BSA_CASE
-    return hipErrorInvalidValue;
+    prep_rows<T, D>(out, dout, lse, delta, lse2, rows, blockIdx.x);
 }
 
 // The reverse map of the selection ("the query blocks connected to a key/value
@@ -138,14 +116,14 @@ hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, cons
 // against one thread per row setting bits in global memory).
 constexpr int kMapCols = 8192;
 
-__global__ __launch_bounds__(256) void bwd_connect_kernel(const int32_t* __restrict__ sel_idx,
-                                                          uint32_t* __restrict__ conn, Geom g,
-                                                          int words)
+__device__ __forceinline__ void connect_words(const int32_t* __restrict__ sel_idx,
+                                              uint32_t* __restrict__ conn, const Geom& g, int words,
+                                              uint32_t wg)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t col_s[];   // [min(m, kMapCols)]
     const int m = g.n_blocks, n = g.n_select;
-    const int64_t bh_idx = blockIdx.x / (uint32_t)words;
-    const int w = (int)(blockIdx.x - (uint32_t)bh_idx * (uint32_t)words);
+    const int64_t bh_idx = wg / (uint32_t)words;
+    const int w = (int)(wg - (uint32_t)bh_idx * (uint32_t)words);
     const int rows = min(32, m - 32 * w);
     const int32_t* sel = sel_idx + (bh_idx * m + 32 * w) * n;
     uint32_t* dst = conn + (bh_idx * words + w) * m;
@@ -165,6 +143,28 @@ __global__ __launch_bounds__(256) void bwd_connect_kernel(const int32_t* __restr
         for (int c = threadIdx.x; c < cols; c += blockDim.x) dst[j0 + c] = col_s[c];
         __syncthreads();
     }
+}
+
+__global__ __launch_bounds__(256) void bwd_connect_kernel(const int32_t* __restrict__ sel_idx,
+                                                          uint32_t* __restrict__ conn, Geom g,
+                                                          int words)
+{
+    connect_words(sel_idx, conn, g, words, blockIdx.x);
+}
+
+// The map and delta in one launch, the map's workgroups first: both are short, read nothing
+// of each other, and a launch of its own costs a small backward 4.5 us.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void bwd_prep_connect_kernel(
+    const T* __restrict__ out, const T* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ delta, float* __restrict__ lse2, int64_t rows,
+    const int32_t* __restrict__ sel_idx, uint32_t* __restrict__ conn, Geom g, int words,
+    uint32_t n_connect)
+{
+    if (blockIdx.x < n_connect)
+        connect_words(sel_idx, conn, g, words, blockIdx.x);
+    else
+        prep_rows<T, D>(out, dout, lse, delta, lse2, rows, blockIdx.x - n_connect);
 }
 
 // The order in which the key blocks of a key/value slice are worked on: those with
@@ -206,7 +206,7 @@ __device__ __forceinline__ int64_t first_query_slice(const Geom& g, int64_t u)
 }
 
 // The classes of all key blocks by the whole chip, for maps that are too large to be
-// read by one workgroup per slice; see launch_bwd_connect.
+// read by one workgroup per slice; see launch_order.
 __global__ __launch_bounds__(256) void bwd_class_kernel(const uint32_t* __restrict__ conn,
                                                         uint8_t* __restrict__ classes, Geom g,
                                                         int words, uint32_t chunks)
@@ -286,19 +286,26 @@ __global__ __launch_bounds__(1024) void bwd_order_kernel(const uint32_t* __restr
     }
 }
 
-hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,
-                              int64_t BH, hipStream_t stream)
+static hipError_t launch_connect(const int32_t* sel_idx, uint32_t* conn, const Geom& g, int64_t BH,
+                                 hipStream_t stream)
 {
     const int m = g.n_blocks, words = (m + 31) >> 5;
     const int cols = m < kMapCols ? m : kMapCols;
     const int64_t map = (int64_t)words * m;          // words per query slice
-    hipError_t e = launch_slices(BH, 256 * (int64_t)words, [&](int64_t first, int64_t slices) {
+    return launch_slices(BH, 256 * (int64_t)words, [&](int64_t first, int64_t slices) {
         bwd_connect_kernel<<<dim3((unsigned)(slices * words)), dim3(256),
                              sizeof(uint32_t) * (size_t)cols, stream>>>(
             sel_idx + first * m * g.n_select, conn + first * map, g, words);
         return hipGetLastError();
     });
-    if (e != hipSuccess || !order) return e;
+}
+
+static hipError_t launch_order(const uint32_t* conn, int32_t* order, const Geom& g, int64_t BH,
+                               hipStream_t stream)
+{
+    const int m = g.n_blocks, words = (m + 31) >> 5;
+    const int64_t map = (int64_t)words * m;
+    hipError_t e = hipSuccess;
     // A slice's map of up to 1,024 blocks and 64 words each is read where the order is
     // made, a larger one by a launch of its own: 450 blocks with 60 words 9.9 us, in two
     // launches 6.9 + 4.9; 1,024 with 128 8.0 + 5.0 us, 4,050 with 127 9.7 + 10.8 us (one
@@ -323,6 +330,53 @@ hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* o
             order + first * m, g, words);
         return hipGetLastError();
     });
+}
+
+template <typename T, int D>
+static hipError_t launch_prep_t(const void* out, const void* dout, const float* lse, float* delta,
+                                float* lse2, int64_t rows, const int32_t* sel_idx, uint32_t* conn,
+                                const Geom& g, int64_t BH, hipStream_t stream)
+{
+    constexpr int LPR = D * (int)sizeof(T) / 16, RPW = 256 / LPR;     // rows per workgroup
+    const int64_t wgs = (rows + RPW - 1) / RPW;
+    // together with the map where its LDS leaves the rows' workgroups alone and one launch
+    // holds both
+    const int m = g.n_blocks, words = (m + 31) >> 5;
+    const int64_t n_connect = BH * words;
+    if (m <= 1024 && (wgs + n_connect) * 256 < (int64_t)1 << 32) {
+        bwd_prep_connect_kernel<T, D><<<dim3((unsigned)(wgs + n_connect)), dim3(256),
+                                        sizeof(uint32_t) * (size_t)m, stream>>>(
+            (const T*)out, (const T*)dout, lse, delta, lse2, rows, sel_idx, conn, g, words,
+            (uint32_t)n_connect);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_slices(wgs, 256, [&](int64_t first, int64_t count) {
+        const int64_t row = first * RPW;
+        bwd_prep_kernel<T, D><<<dim3((unsigned)count), dim3(256), 0, stream>>>(
+            (const T*)out + row * D, (const T*)dout + row * D, lse + row, delta + row, lse2 + row,
+            rows - row < count * RPW ? rows - row : count * RPW);
+        return hipGetLastError();
+    });
+    return e != hipSuccess ? e : launch_connect(sel_idx, conn, g, BH, stream);
+}
+
+hipError_t launch_bwd_prepare(bool is_bf16, const void* out, const void* dout, const float* lse,
+                              float* delta, float* lse2, const int32_t* sel_idx, uint32_t* conn,
+                              int32_t* order, const Geom& g, int D, int64_t BH, hipStream_t stream)
+{
+    hipError_t e = hipErrorInvalidValue;
+    if (!lse) e = launch_connect(sel_idx, conn, g, BH, stream);
+#define BSA_CASE(DD)                                                                              \
+    else if (D == DD)                                                                             \
+        e = is_bf16 ? launch_prep_t<uint16_t, DD>(out, dout, lse, delta, lse2, BH * g.n_tokens,   \
+                                                  sel_idx, conn, g, BH, stream)                   \
+                    : launch_prep_t<float, DD>(out, dout, lse, delta, lse2, BH * g.n_tokens,      \
+                                               sel_idx, conn, g, BH, stream);
+    BSA_CASE(32)
+    BSA_CASE(64)
+    BSA_CASE(128)
+#undef BSA_CASE
+    return e != hipSuccess || !order ? e : launch_order(conn, order, g, BH, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -833,15 +887,24 @@ static auto dq_kernel(int waves)
 }
 
 template <typename T, int D>
-static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void* dout,
-                               const int32_t* sel_idx, void* dq, void* dk, void* dv,
-                               const float* delta, const float* lse2, const uint32_t* conn,
-                               const int32_t* order, const Geom& g, int64_t BH, hipStream_t stream)
+static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void* out,
+                               const float* lse, const void* dout, const int32_t* sel_idx, void* dq,
+                               void* dk, void* dv, float* delta, float* lse2, uint32_t* conn,
+                               int32_t* order, const Geom& g, int64_t BH, hipStream_t stream)
 {
     const int m = g.n_blocks, words = (m + 31) >> 5;
     const int64_t BKV = BH / g.kv_group, N = g.n_tokens;
+    const BwdSplit split_kv = dkdv_split<T, D>(g, BKV);
+    const bool dkdv_first = order != nullptr;        // `order` may lie where dQ goes
+    {
+        const RowSplit rows(g.block_tokens, split_kv.max_waves, WaveTile<T>::ROWS);
+        if (BKV * m * rows.chunks * rows.waves * split_kv.groups <= kUnorderedWaves) order = nullptr;
+        const hipError_t e = launch_bwd_prepare(sizeof(T) == 2, out, dout, lse, delta, lse2, sel_idx,
+                                                conn, order, g, D, BH, stream);
+        if (e != hipSuccess) return e;
+    }
     auto run_dkdv = [&] {
-        const BwdSplit split = dkdv_split<T, D>(g, BKV);
+        const BwdSplit split = split_kv;
         const RowSplit rows(g.block_tokens, split.max_waves, WaveTile<T>::ROWS);
         const int64_t wgs = (int64_t)m * rows.chunks;             // per slice
         const int nw = rows.waves * split.groups;
@@ -886,10 +949,10 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
             return hipGetLastError();
         });
     };
-    // `order` may lie where dQ goes; without it dK and dV may lie where k and v are
-    const hipError_t e = order ? run_dkdv() : run_dq();
+    // without the memory for an order dK and dV may lie where k and v are
+    const hipError_t e = dkdv_first ? run_dkdv() : run_dq();
     if (e != hipSuccess) return e;
-    return order ? run_dq() : run_dkdv();
+    return dkdv_first ? run_dq() : run_dkdv();
 }
 
 hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v, const void* out,
@@ -897,17 +960,12 @@ hipError_t launch_bwd(bool is_bf16, const void* q, const void* k, const void* v,
                       void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
                       const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
-    hipError_t e = hipSuccess;
-    if (lse) e = launch_bwd_prep(is_bf16, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
-    if (e != hipSuccess) return e;
-    e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
-    if (e != hipSuccess) return e;
 #define BSA_CASE(DD)                                                                             \
     case DD:                                                                                     \
-        return is_bf16 ? launch_bwd_t<uint16_t, DD>(q, k, v, dout, sel_idx, dq, dk, dv, delta,   \
-                                                    lse2, conn, order, g, BH, stream)                   \
-                       : launch_bwd_t<float, DD>(q, k, v, dout, sel_idx, dq, dk, dv, delta,      \
-                                                 lse2, conn, order, g, BH, stream);
+        return is_bf16 ? launch_bwd_t<uint16_t, DD>(q, k, v, out, lse, dout, sel_idx, dq, dk,    \
+                                                    dv, delta, lse2, conn, order, g, BH, stream) \
+                       : launch_bwd_t<float, DD>(q, k, v, out, lse, dout, sel_idx, dq, dk, dv,   \
+                                                 delta, lse2, conn, order, g, BH, stream);
     switch (D) {
         BSA_CASE(32)
         BSA_CASE(64)

@@ -1228,15 +1228,15 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
                            void* dk, void* dv, float* delta, float* lse2, uint32_t* conn, int32_t* order,
                            const Geom& g, int D, int64_t BH, hipStream_t stream)
 {
-    hipError_t e = hipSuccess;
-    if (lse) e = launch_bwd_prep(true, out, dout, lse, delta, lse2, BH * g.n_tokens, D, stream);
-    if (e != hipSuccess) return e;
-    e = launch_bwd_connect(sel_idx, conn, order, g, BH, stream);
-    if (e != hipSuccess) return e;
     const int nw = g.block_tokens / 32;
     const uint32_t sx = (uint32_t)(BH / g.kv_group);           // key/value slices
     const dim3 grid((unsigned)(BH * g.n_blocks)), block(64 * nw);
     const DkdvSplit split = dkdv_split(g, D, sx);
+    const bool dkdv_first = order != nullptr;        // `order` may lie where dQ goes
+    if ((int64_t)sx * g.n_blocks * nw * split.groups <= kUnorderedWaves) order = nullptr;
+    hipError_t e = launch_bwd_prepare(true, out, dout, lse, delta, lse2, sel_idx, conn, order, g, D,
+                                      BH, stream);
+    if (e != hipSuccess) return e;
     auto run_dkdv = [&](auto kernel) {
         kernel<<<dim3(sx * (unsigned)(g.n_blocks * (nw / split.waves))),
                  dim3(64 * split.waves * split.groups), 0, stream>>>(
@@ -1250,16 +1250,16 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
                                            sel_idx, (uint16_t*)dq, g, sx);
         return hipGetLastError();
     };
-    // `order` may lie where dQ goes; without it dK and dV may lie where k and v are
+    // without the memory for an order dK and dV may lie where k and v are
 #define BSA_LAUNCH(D_, NW_, FOUR_GROUPS, FOUR_WAVES)                                              \
     if (D == D_ && nw == NW_) {                                                                   \
-        if (!order && (e = run_dq(bwd_mfma_dq_d##D_##_w##NW_)) != hipSuccess) return e;           \
+        if (!dkdv_first && (e = run_dq(bwd_mfma_dq_d##D_##_w##NW_)) != hipSuccess) return e;      \
         e = run_dkdv(split.groups == 1   ? bwd_mfma_dkdv_d##D_##_w##NW_                           \
                      : split.groups == 4 ? bwd_mfma_dkdv_d##D_##_##FOUR_GROUPS                    \
                      : split.waves == 4  ? bwd_mfma_dkdv_d##D_##_##FOUR_WAVES                     \
                                          : bwd_mfma_dkdv_d##D_##_w##NW_##_split2);                \
         if (e != hipSuccess) return e;                                                            \
-        return order ? run_dq(bwd_mfma_dq_d##D_##_w##NW_) : hipSuccess;                           \
+        return dkdv_first ? run_dq(bwd_mfma_dq_d##D_##_w##NW_) : hipSuccess;                      \
     }
     // (the last two columns: a kernel that the rule does not name there is not launched)
     BSA_LAUNCH(64, 2, w2_split4, w2_split2)

@@ -83,15 +83,21 @@ hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v, con
                                 int n_jobs, const Geom& g, int64_t BH, hipStream_t stream);
 
 // What both backward paths need first: delta_l = dO_l . O_l and lse_l * log2(e)
-// (fp32, `rows` of each), the reverse map of the selection in `conn` and, in
-// `order` (int32, key/value slices x m, followed by as many bytes of scratch), the
-// order in which the key blocks of each key/value slice are worked on.  It is read
-// before dQ is written: dq may serve; null: ascending.  The preparation comes first:
-// `order` may lie in the memory of `out`.
-hipError_t launch_bwd_prep(bool is_bf16, const void* out, const void* dout, const float* lse,
-                           float* delta, float* lse2, int64_t rows, int D, hipStream_t stream);
-hipError_t launch_bwd_connect(const int32_t* sel_idx, uint32_t* conn, int32_t* order, const Geom& g,
-                              int64_t BH, hipStream_t stream);
+// (fp32, B*heads*N of each; lse null: they are there already), the reverse map of the
+// selection in `conn` and, in `order` (int32, key/value slices x m, followed by as many bytes
+// of scratch), the order in which the key blocks of each key/value slice are worked on.  It
+// is read before dQ is written: dq may serve; null: none is made.  It comes last: `order` may
+// lie in the memory of `out`.
+hipError_t launch_bwd_prepare(bool is_bf16, const void* out, const void* dout, const float* lse,
+                              float* delta, float* lse2, const int32_t* sel_idx, uint32_t* conn,
+                              int32_t* order, const Geom& g, int D, int64_t BH, hipStream_t stream);
+// A dK/dV launch of up to so many wavefronts, two per SIMD, runs at once: no key block waits
+// for its turn, and the launch that orders them, 4 to 7 us, is left out.  Whole backward with
+// and without it: 32 blocks of 100 tokens, 4 slices, head dim 32 37.0 and 31.6 us, 64 46.0 and
+// 41.0; 72 of 64, 4 slices 38.5 and 36.6; 144 of 128 at head dim 128 102.6 and 100.2.  Beyond,
+// up to 4,096: 36 of 128, 4 slices 56.7 and 63.4, 288 of 64 in fp32 195 and 229, 72 of 64, 4
+// slices, 123 and 121.
+constexpr int64_t kUnorderedWaves = 2048;
 
 // Backward with the selection fixed, any tile shape / head dim in {32, 64, 128} /
 // dtype.  `delta` and `lse2` are fp32 scratch of B*heads*N floats each, `conn`
@@ -143,7 +149,7 @@ struct BranchGrads {
     const void* dout;
     void *do_fg, *do_l;                         // out: upstream gradients of the branches
     float *dgates, *dobar;                      // out
-    float *delta_fg, *delta_l, *lse2_fg, *lse2_l;    // out: see launch_bwd_prep
+    float *delta_fg, *delta_l, *lse2_fg, *lse2_l;    // out: see launch_bwd_prepare
 };
 hipError_t launch_branch_grads(bool is_bf16, const BranchGrads& x, const Geom& g, int D, int64_t BH,
                                hipStream_t stream);

@@ -357,6 +357,32 @@ def test_backward_order_of_popular_blocks(G, oracle, heads, kv_heads, H, W, bh, 
         assert err <= 1e-4 * np.abs(r).max(), f"{name}: max error {err}"
 
 
+@pytest.mark.parametrize("dtype,H,W,bh,bw,D,n,batch", [
+    ("fp32", 32, 32, 8, 8, 32, 3, 16),     # 16 blocks x 4 row wavefronts x 2 groups per slice
+    ("bf16", 32, 64, 8, 8, 64, 15, 8),     # 32 x 2 x 4, matrix-core kernels
+    ("bf16", 32, 64, 8, 16, 128, 7, 16),   # 16 x 4 x 2
+])
+def test_backward_without_an_order(G, oracle, dtype, H, W, bh, bw, D, n, batch):
+    """2,048 wavefronts of dK/dV take the key blocks as they lie, one slice more has them
+    ordered: the same lists, sums and bits (dQ, which knows no order, may be split otherwise
+    there).  Bounds of test_general_backward."""
+    cfg = shape_ns(1, 1, H, W, bh, bw, D, n, dtype)
+    q, k, v = rand_qkv(cfg, 31)
+    dout = rand_qkv(cfg, 32)[0]
+    if dtype == "bf16":
+        q, k, v, dout = (round_to_bf16(x) for x in (q, k, v, dout))
+    idx = random_selection(cfg, 33)
+    ref = oracle.bwd(oracle.shape_of(cfg), q, k, v, dout, idx)
+    grads = []
+    for cfg.batch in (batch, batch + 1):
+        got = G.gpu_bwd(cfg, *(np.repeat(x, cfg.batch, axis=0) for x in (q, k, v, dout, idx)))
+        assert all((x == x[:1]).all() for x in got)
+        grads.append([x[0] for x in got])
+    for name, x, y, r in zip(("dq", "dk", "dv"), *grads, ref):
+        assert name == "dq" or np.array_equal(x, y), name
+        assert max(np.abs(x - r[0]).max(), np.abs(y - r[0]).max()) <= (1e-4 if dtype == "fp32" else 1e-2) * np.abs(r).max()
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_backward_fp32_score_rounding(G, oracle, D):
     """Scores whose terms all have one sign, mean s (22 and 31 here): a chain of c
