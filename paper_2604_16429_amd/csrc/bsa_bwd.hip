@@ -575,10 +575,10 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     const int m = g.n_blocks, b = g.block_tokens;
     const int words = (m + 31) >> 5;                  // of a key block's row of the reverse map
 
-    // workgroup -> (key/value slice, key block, row chunk), slices dealt to the 8
-    // XCDs whole; the query slices that share the key/value slice are consecutive
+    // workgroup -> (key/value slice, key block, row chunk); the query slices that share the
+    // key/value slice are consecutive
     uint32_t unit, item;
-    map_unit(blockIdx.x, (uint32_t)(m * row_chunks), n_units, unit, item);
+    map_key_block(g, blockIdx.x, (uint32_t)(m * row_chunks), n_units, unit, item);
     const int place = (int)item / row_chunks;
     const int row0 = ((int)item - place * row_chunks) * chunk_rows;
     const int j = order ? order[(int64_t)unit * m + place] : place;

@@ -179,8 +179,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
     const int l32 = lane & 31, half = lane >> 5;
     const int subs = g.block_tokens / 64;
 
-    // workgroup -> (query slice, query block), key/value slices dealt to the 8
-    // XCDs whole
+    // workgroup -> (query slice, query block)
     int i;
     int64_t bh_idx;
     map_workgroup(g, blockIdx.x, (uint32_t)g.n_blocks, n_units, bh_idx, i);
@@ -636,10 +635,10 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
     const int l32 = lane & 31, half = lane >> 5;
     const int m = g.n_blocks;
 
-    // workgroup -> (key/value slice, key block), slices dealt to the 8 XCDs
-    // whole; the query slices that share the key/value slice are consecutive
+    // workgroup -> (key/value slice, key block); the query slices that share the
+    // key/value slice are consecutive
     uint32_t unit, r_unit;
-    map_unit(blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
+    map_key_block(g, blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
     const int place = (int)r_unit / CHUNKS, row0 = 32 * (NW * ((int)r_unit % CHUNKS) + wave);
     const int j = order ? order[(int64_t)unit * m + place] : place;
     const int64_t base = (int64_t)unit * g.n_tokens * D;
@@ -894,7 +893,7 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
 
     // workgroup -> (key/value slice, key block), see dkdv_d64_body
     uint32_t unit, r_unit;
-    map_unit(blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
+    map_key_block(g, blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
     const int place = (int)r_unit / CHUNKS, row0 = 32 * (NW * ((int)r_unit % CHUNKS) + wave);
     const int j = order ? order[(int64_t)unit * m + place] : place;
     const int64_t base = (int64_t)unit * g.n_tokens * D;

@@ -274,9 +274,8 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
     const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
 
-    // Work item -> (query slice, query block); key/value slices are dealt to
-    // the XCDs whole (map_workgroup).  A work item is NW consecutive
-    // sub-blocks of 64 queries of one query block (NW divides subs):
+    // Work item -> (query slice, query block), see map_workgroup.  A work item is NW
+    // consecutive sub-blocks of 64 queries of one query block (NW divides subs):
     // item = block * (subs / NW) + group.
     int i, qsub;
     int64_t bh_idx;

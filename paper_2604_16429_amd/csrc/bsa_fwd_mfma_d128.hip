@@ -100,8 +100,7 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
     const int l32 = lane & 31, half = lane >> 5;
     const int subs = g.block_tokens / 64;          // 64-key sub-tiles per attended block
 
-    // Workgroup -> (query slice, query block); key/value slices are dealt to
-    // the XCDs whole (map_workgroup).
+    // workgroup -> (query slice, query block)
     int i;
     int64_t bh_idx;
     map_workgroup(g, wg, (uint32_t)g.n_blocks, n_units, bh_idx, i);

@@ -383,6 +383,42 @@ def test_backward_without_an_order(G, oracle, dtype, H, W, bh, bw, D, n, batch):
         assert max(np.abs(x - r[0]).max(), np.abs(y - r[0]).max()) <= (1e-4 if dtype == "fp32" else 1e-2) * np.abs(r).max()
 
 
+@pytest.mark.parametrize("dtype,H,W,bh,bw,D,slices", [
+    ("bf16", 272, 512, 16, 16, 64, 9),     # m = 544: eight runs of 64 blocks and 32 more per slice
+    ("bf16", 512, 132, 8, 12, 128, 8),     # general kernels, m = 704: runs of 128
+    ("bf16", 264, 256, 8, 16, 128, 8),     # m = 528: runs of 128, 8 slices in 33 rounds
+    ("fp32", 330, 410, 10, 10, 32, 9),     # m = 1,353
+])
+def test_large_slices_in_runs(G, dtype, H, W, bh, bw, D, slices):
+    """Slices of more than 32 MB of keys and values, which all XCDs share in runs of blocks:
+    every row is written, with the bits that a launch of its slice alone gives it (launches
+    of so many rows are not split, whatever the number of slices)."""
+    import paper_2604_16429_amd as bsa
+    from paper_2604_16429_amd import binding
+    element = torch.bfloat16 if dtype == "bf16" else torch.float32
+    one, many = (shape_ns(e, 1, H, W, bh, bw, D, 3, dtype) for e in (1, slices))
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v, dout = (torch.randn((slices, 1, H * W, D), generator=gen, device="cuda").to(element)
+                     for _ in range(4))
+    idx = torch.from_numpy(random_selection(many, 4)).cuda()
+
+    def run(cfg, q, k, v, dout, idx):
+        p = G.params_of(cfg)
+        out, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+        lse = torch.full(q.shape[:3], float("nan"), device="cuda")
+        ws = torch.empty(bsa.mosaic_bsa_workspace_bytes(p, binding.OP_BWD), dtype=torch.uint8,
+                         device="cuda")
+        bsa.mosaic_bsa_fwd(p, q, k, v, idx, out, lse)
+        bsa.mosaic_bsa_bwd(p, q, k, v, out, lse, dout, idx, dq, dk, dv, ws)
+        return out, lse, dq, dk, dv
+
+    got = run(many, q, k, v, dout, idx)
+    assert all(bool(torch.isfinite(x).all()) for x in got)
+    for e in (0, slices - 1):
+        for x, y in zip(got, run(one, *(t[e:e + 1] for t in (q, k, v, dout, idx)))):
+            assert torch.equal(x[e:e + 1], y)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_backward_fp32_score_rounding(G, oracle, D):
     """Scores whose terms all have one sign, mean s (22 and 31 here): a chain of c
