@@ -72,7 +72,8 @@ int check_params(const mosaic_bsa_params* p, Checked* out, bool own_is_candidate
     g.list_only = 0;
     g.add_dq = g.add_dk = g.add_dv = nullptr;
     g.own_is_candidate = own_is_candidate ? 1 : 0;
-    bsa::set_xcd_runs(g, p->head_dim * (out->is_bf16 ? 2 : 4));
+    g.deal = bsa::xcd_deal(2 * g.n_tokens * p->head_dim * (out->is_bf16 ? 2 : 4),
+                           g.block_tokens);
     return MOSAIC_BSA_OK;
 }
 

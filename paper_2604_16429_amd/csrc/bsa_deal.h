@@ -1,0 +1,81 @@
+// Which workgroup works on what (host and device; tested on the CPU).  Workgroup ids go
+// round-robin over the 8 XCDs, each with its own L2; what the workgroups of an XCD that run
+// at the same time gather in common is fetched into that L2 once.
+//   * Slices whose K and V take up to 32 MB: dealt to XCDs whole, key/value slice u to
+//     XCD u % 8, the items of the query heads that share it back to back.  Eight of them
+//     fit the 256 MB of cache behind the L2s.
+//   * Larger ones, and the last (number of key/value slices % 8): all XCDs share a slice,
+//     in runs of consecutive blocks dealt to them in turn.  Near query blocks attend to the
+//     same blocks, so that a run finds them in its L2, and the runs that are worked on
+//     at the same time keep to one region of one slice, which the cache behind holds.  A run
+//     takes the same blocks of all query heads that share the slice: head after head, the
+//     part of the slice that an XCD needs was fetched by as many XCDs as there are heads, and
+//     small launches were slower than item by item.
+// Forward us, dealt item by item before (small numbers of slices) | in runs: 6 slices of 2,276
+// blocks of 64, 31 attended, head dim 128, 24 heads 7,040 | 3,960; 4 of 450 blocks of 64 57 |
+// 45; 15 of 450 106 | 97; 2 of 1,800, 6 heads 321 | 280; 3 of 384 of 128, 12 heads 517 | 493; 4 of
+// 4,050 of 256 4,670 | 4,710.  One run per XCD: the last 4,920 (the eight regions do not
+// fit the cache, and the slowest one is waited for).
+// Heads that share a slice, item by item | in runs head after head | in runs of all heads, head
+// dim 64, blocks of 64, slices x blocks, query heads: 1 x 128, 8 17.6 | 19.3 | 17.7; 2 x 128, 8
+// 18.2 | 19.3 | 17.6; 3 x 288, 12 52.7 | 53.6 | 50.3; 3 x 450, 12 87.4 | 81.8 | 76.4; 7 x 450, 14
+// 107 | 97 | 92; head dim 128: 4 x 4,050, 16 2,565 | 1,902 | 1,765.
+// 16 slices, dealt whole | in runs: 4,050 of 256 (265 MB) 20,440 | 19,190, at head dim 128
+// 22,980 | 22,330; 2,025 of 128 (66 MB) 1,528 | 1,458; 3,422 (112 MB) 2,429 | 2,376; 1,800 of 64
+// at head dim 128 (59 MB) 1,853 | 1,872; 32 slices of 450 of 64 (7 MB) 1,257 | 1,287; 72 of 384 of
+// 128 (13 MB) 11,700 | 11,930.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace bsa {
+
+struct Deal {
+    int32_t whole_slices;      // slices are dealt to XCDs whole while there are eight
+    int32_t run_log2;          // items of a run
+};
+
+// Workgroup w of a launch over n_units key/value slices -> slice, query head (of the `heads`
+// that share it) and item of that head, of per_head.
+__host__ __device__ __forceinline__ void map_unit(Deal deal, uint32_t w, uint32_t per_head,
+                                                  uint32_t heads, uint32_t n_units,
+                                                  uint32_t& unit, uint32_t& head, uint32_t& item)
+{
+    const uint32_t per_unit = per_head * heads;
+    const uint32_t units_dealt = deal.whole_slices ? n_units & ~7u : 0;
+    const uint32_t dealt = units_dealt * per_unit;
+    if (w < dealt) {
+        const uint32_t seq = w >> 3, round = seq / per_unit, r = seq - round * per_unit;
+        unit = round * 8 + (w & 7);
+        head = heads == 1 ? 0 : r / per_head;
+        item = r - head * per_head;
+        return;
+    }
+    // runs for all XCDs while there are, then an eighth of what is left to each
+    const int log2 = deal.run_log2;
+    const uint32_t rest = (n_units - units_dealt) * per_unit;
+    const uint32_t even = rest >> (log2 + 3) << (log2 + 3), tail = rest - even;
+    const uint32_t xcd = (w - dealt) & 7, seq = (w - dealt) >> 3;
+    const uint32_t at =
+        w - dealt < even
+            ? (((seq >> log2 << 3) + xcd) << log2) + (seq & ((1u << log2) - 1))
+            : even + (seq - (even >> 3)) + xcd * (tail >> 3) + (xcd < (tail & 7u) ? xcd : tail & 7u);
+    const uint32_t u = at / per_unit, r = at - u * per_unit;
+    unit = units_dealt + u;
+    item = heads == 1 ? r : r / heads;               // the heads of an item side by side
+    head = r - item * heads;
+}
+
+// Runs of about 16,384 tokens, 64 to 256 blocks: 2 slices of 1,800 blocks of 64 in runs of
+// 4,096 300 us, of 8,192 283, of 16,384 280, of 65,536 283.
+inline Deal xcd_deal(int64_t slice_bytes, int block_tokens)
+{
+    Deal d;
+    d.whole_slices = slice_bytes <= (int64_t)32 << 20;
+    d.run_log2 = 14;
+    for (int rows = block_tokens - 1; rows > 0; rows >>= 1) --d.run_log2;
+    return d;
+}
+
+}  // namespace bsa

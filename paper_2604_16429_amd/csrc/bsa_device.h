@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bsa_deal.h"
+
 namespace bsa {
 
 // Geometry of one call, passed by value to every kernel.
@@ -24,7 +26,7 @@ struct Geom {
     int32_t list_only;    // forward: 1 = attend exactly the n listed blocks (n >= 1), 0 = block i
                           // itself, then the n listed blocks
     int32_t own_is_candidate;  // selection: 1 = rank all m key blocks, 0 = all but block i
-    int32_t whole_slices, run_log2;    // see map_unit
+    Deal deal;            // see map_unit
     // Backward: when not null, a gradient is ADDED to what dq / dk / dv hold,
     // together with row [slice, block of the token] of these fp32 [slices, m, D]
     // tensors divided by b (the three-branch form: the local branch adds to the
@@ -70,66 +72,15 @@ __device__ __forceinline__ int64_t kv_slice_of(const Geom& g, int64_t bh)
     return e * (g.heads / g.kv_group) + a / g.kv_group;
 }
 
-// Workgroup id -> (query slice, item).  Workgroup ids go round-robin over the
-// 8 XCDs, each with its own L2; what the workgroups of an XCD that run at the same
-// time gather in common is fetched into that L2 once.
-//   * Slices whose K and V take up to 32 MB: dealt to XCDs whole, key/value slice u to
-//     XCD u % 8, the items of the query heads that share it back to back.  Eight of them
-//     fit the 256 MB of cache behind the L2s.
-//   * Larger ones, and the last (number of key/value slices % 8): all XCDs share a slice,
-//     in runs of consecutive items dealt to them in turn.  Near query blocks attend to the
-//     same blocks, so that a run finds them in its L2, and the runs that are worked on
-//     at the same time keep to one region of one slice, which the cache behind holds.
-// Forward us, dealt item by item before (small numbers of slices) | in runs: 6 slices of 2,276
-// blocks of 64, 31 attended, head dim 128, 24 heads 7,040 | 3,960; 4 of 450 blocks of 64 57 |
-// 45; 15 of 450 106 | 97; 2 of 1,800, 6 heads 321 | 280; 3 of 384 of 128, 12 heads 517 | 493; 4 of
-// 4,050 of 256 4,670 | 4,710.  One run per XCD: the last 4,920 (the eight regions do not
-// fit the cache, and the slowest one is waited for).
-// 16 slices, dealt whole | in runs: 4,050 of 256 (265 MB) 20,440 | 19,190, at head dim 128
-// 22,980 | 22,330; 2,025 of 128 (66 MB) 1,528 | 1,458; 3,422 (112 MB) 2,429 | 2,376; 1,800 of 64
-// at head dim 128 (59 MB) 1,853 | 1,872; 32 slices of 450 of 64 (7 MB) 1,257 | 1,287; 72 of 384 of
-// 128 (13 MB) 11,700 | 11,930.
-// per_unit: items per key/value slice; n_units: number of key/value slices.  whole_slices
-// and run_log2 (items of a run) are the host's: see set_xcd_runs.
-__device__ __forceinline__ void map_unit(const Geom& g, uint32_t w, uint32_t per_unit,
-                                         uint32_t n_units, int run_log2, uint32_t& unit,
-                                         uint32_t& r)
-{
-    const uint32_t units_dealt = g.whole_slices ? n_units & ~7u : 0, dealt = units_dealt * per_unit;
-    if (w < dealt) {
-        const uint32_t seq = w >> 3, round = seq / per_unit;
-        unit = round * 8 + (w & 7);
-        r = seq - round * per_unit;
-        return;
-    }
-    // runs for all XCDs while there are, then an eighth of what is left to each
-    const uint32_t rest = (n_units - units_dealt) * per_unit;
-    const uint32_t even = rest >> (run_log2 + 3) << (run_log2 + 3), tail = rest - even;
-    const uint32_t xcd = (w - dealt) & 7, seq = (w - dealt) >> 3;
-    const uint32_t at =
-        w - dealt < even ? (((seq >> run_log2 << 3) + xcd) << run_log2) + (seq & ((1u << run_log2) - 1))
-                         : even + (seq - (even >> 3)) + xcd * (tail >> 3) + min(xcd, tail & 7u);
-    const uint32_t u = at / per_unit;
-    unit = units_dealt + u;
-    r = at - u * per_unit;
-}
-
-// Runs of about 16,384 tokens, 64 to 256 blocks: 2 slices of 1,800 blocks of 64 in runs of
-// 4,096 300 us, of 8,192 283, of 16,384 280, of 65,536 283.
-inline void set_xcd_runs(Geom& g, int row_bytes)
-{
-    g.whole_slices = 2 * g.n_tokens * row_bytes <= (int64_t)32 << 20;
-    g.run_log2 = 14;
-    for (int rows = g.block_tokens - 1; rows > 0; rows >>= 1) --g.run_log2;
-}
-
-// Key blocks: with their order (long lists first) runs would give one XCD all the long
-// lists; they are dealt item by item where slices are not dealt whole.  Whole backward, 16
-// slices of 4,050 blocks of 256 69.2 ms with whole slices, 67.8 so; 2,025 of 128 5,040 us and 4,910.
+// Key blocks, per_unit items of a key/value slice: with their order (long lists first) runs
+// would give one XCD all the long lists; they are dealt item by item where slices are not
+// dealt whole.  Whole backward, 16 slices of 4,050 blocks of 256 69.2 ms with whole slices,
+// 67.8 so; 2,025 of 128 5,040 us and 4,910.
 __device__ __forceinline__ void map_key_block(const Geom& g, uint32_t w, uint32_t per_unit,
                                               uint32_t n_units, uint32_t& unit, uint32_t& r)
 {
-    map_unit(g, w, per_unit, n_units, 0, unit, r);
+    uint32_t head;
+    map_unit(Deal{g.deal.whole_slices, 0}, w, per_unit, 1, n_units, unit, head, r);
 }
 
 // Query blocks, per_slice items of a slice.  The grid is n_units * kv_group * per_slice
@@ -137,18 +88,16 @@ __device__ __forceinline__ void map_key_block(const Geom& g, uint32_t w, uint32_
 __device__ __forceinline__ void map_workgroup(const Geom& g, uint32_t w, uint32_t per_slice,
                                               uint32_t n_units, int64_t& bh, int& item)
 {
-    uint32_t unit, r;
-    map_unit(g, w, per_slice * (uint32_t)g.kv_group, n_units, g.run_log2, unit, r);
+    uint32_t unit, head, r;
+    map_unit(g.deal, w, per_slice, (uint32_t)g.kv_group, n_units, unit, head, r);
+    item = (int)r;
     if (g.kv_group == 1) {
         bh = unit;
-        item = (int)r;
         return;
     }
-    const uint32_t head_in_group = r / per_slice;
-    item = (int)(r - head_in_group * per_slice);
     const uint32_t kv_heads = (uint32_t)(g.heads / g.kv_group);
     const uint32_t e = unit / kv_heads, a = unit - e * kv_heads;
-    bh = (int64_t)e * g.heads + a * g.kv_group + head_in_group;
+    bh = (int64_t)e * g.heads + a * g.kv_group + head;
 }
 
 // Token index (inside one [N, D] slice) of in-tile position tau of block beta:

@@ -1,0 +1,88 @@
+"""Which workgroup works on what (csrc/bsa_deal.h), compiled for the host: every item once,
+and what shares an L2 lies on one XCD.  Workgroup w runs on XCD w % 8."""
+import ctypes
+import os
+import random
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2604_16429_amd", "csrc")
+
+SOURCE = """
+#include "bsa_deal.h"
+using namespace bsa;
+extern "C" void deal_of(int64_t slice_bytes, int block_tokens, int32_t* out)
+{
+    const Deal d = xcd_deal(slice_bytes, block_tokens);
+    out[0] = d.whole_slices;
+    out[1] = d.run_log2;
+}
+extern "C" void map_all(int whole, int run_log2, uint32_t per_head, uint32_t heads,
+                        uint32_t n_units, uint32_t* out)
+{
+    const uint32_t all = n_units * heads * per_head;
+    for (uint32_t w = 0; w < all; ++w)
+        map_unit(Deal{whole, run_log2}, w, per_head, heads, n_units, out[3 * w],
+                 out[3 * w + 1], out[3 * w + 2]);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def deal(tmp_path_factory):
+    d = tmp_path_factory.mktemp("deal")
+    src, lib = d / "deal.hip", d / "deal.so"
+    src.write_text(SOURCE)
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950",
+                    "--offload-host-only", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC,
+                    "-I", os.path.join(ROOT, "include"), str(src), "-o", str(lib)], check=True)
+    return ctypes.CDLL(str(lib))
+
+
+def mapped(deal, whole, run_log2, per_head, heads, n_units):
+    """[workgroups, 3]: key/value slice, query head of the slice, item of the head."""
+    out = np.empty((n_units * heads * per_head, 3), dtype=np.uint32)
+    deal.map_all(whole, run_log2, per_head, heads, n_units, out.ctypes.data_as(ctypes.c_void_p))
+    return out.astype(np.int64)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_every_item_once(deal, seed):
+    rng = random.Random(seed)
+    for _ in range(300):
+        whole, run_log2 = rng.randint(0, 1), rng.randint(0, 7)
+        per_head, heads, n_units = rng.randint(1, 300), rng.choice([1, 1, 2, 3, 4, 7]), rng.randint(1, 20)
+        m = mapped(deal, whole, run_log2, per_head, heads, n_units)
+        assert m[:, 1].max() < heads and m[:, 2].max() < per_head
+        key = np.sort((m[:, 0] * heads + m[:, 1]) * per_head + m[:, 2])
+        assert np.array_equal(key, np.arange(len(m)))
+
+
+@pytest.mark.parametrize("heads,per_head,n_units,run_log2", [
+    (4, 128, 1, 8),      # an eighth to each XCD
+    (8, 450, 2, 8),
+    (4, 24, 5, 7),
+    (3, 2025, 1, 7),     # runs of 128 and a tail
+    (4, 4050, 3, 6),
+])
+def test_heads_of_a_slice_share_an_xcd(deal, heads, per_head, n_units, run_log2):
+    """Of the slices that all XCDs share, an XCD works on the same items of all query heads of a
+    slice, but for the ends of its runs."""
+    m = mapped(deal, 0, run_log2, per_head, heads, n_units)
+    xcds = {}
+    for w, (unit, _, item) in enumerate(m):
+        xcds.setdefault((unit, item), set()).add(w % 8)
+    spread = sum(len(x) > 1 for x in xcds.values())
+    runs = heads * per_head * n_units // (1 << run_log2) + 8
+    assert spread <= runs, f"{spread} of {len(xcds)} items on more than one XCD"
+
+
+def test_whole_slices(deal):
+    """Eight slices at a time, one to each XCD."""
+    m = mapped(deal, 1, 6, 50, 3, 19)
+    dealt = m[: 16 * 150]
+    assert np.array_equal(dealt[:, 0] % 8, np.arange(len(dealt)) % 8)
+    assert m[16 * 150 :, 0].min() == 16
