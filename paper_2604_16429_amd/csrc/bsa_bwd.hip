@@ -455,7 +455,7 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
 
     int item;
     int64_t bh_idx;
-    map_workgroup(g, blockIdx.x, (uint32_t)(g.n_blocks * row_chunks), n_units, bh_idx, item);
+    map_workgroup(g, blockIdx.x, (uint32_t)row_chunks, n_units, bh_idx, item);
     const int i = item / row_chunks;
     const int row0 = (item - i * row_chunks) * chunk_rows;
     const int64_t base = bh_idx * g.n_tokens * D;
@@ -578,7 +578,7 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
     // workgroup -> (key/value slice, key block, row chunk); the query slices that share the
     // key/value slice are consecutive
     uint32_t unit, item;
-    map_key_block(g, blockIdx.x, (uint32_t)(m * row_chunks), n_units, unit, item);
+    map_key_block(g, blockIdx.x, (uint32_t)row_chunks, n_units, unit, item);
     const int place = (int)item / row_chunks;
     const int row0 = ((int)item - place * row_chunks) * chunk_rows;
     const int j = order ? order[(int64_t)unit * m + place] : place;

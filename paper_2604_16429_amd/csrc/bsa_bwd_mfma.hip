@@ -182,7 +182,7 @@ __device__ __forceinline__ void dq_body(const uint16_t* __restrict__ q,
     // workgroup -> (query slice, query block)
     int i;
     int64_t bh_idx;
-    map_workgroup(g, blockIdx.x, (uint32_t)g.n_blocks, n_units, bh_idx, i);
+    map_workgroup(g, blockIdx.x, 1, n_units, bh_idx, i);
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
     // The attended blocks: block i itself followed by its selected blocks, or,
@@ -638,7 +638,7 @@ __device__ __forceinline__ void dkdv_d64_body(const uint16_t* __restrict__ q,
     // workgroup -> (key/value slice, key block); the query slices that share the
     // key/value slice are consecutive
     uint32_t unit, r_unit;
-    map_key_block(g, blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
+    map_key_block(g, blockIdx.x, CHUNKS, n_units, unit, r_unit);
     const int place = (int)r_unit / CHUNKS, row0 = 32 * (NW * ((int)r_unit % CHUNKS) + wave);
     const int j = order ? order[(int64_t)unit * m + place] : place;
     const int64_t base = (int64_t)unit * g.n_tokens * D;
@@ -893,7 +893,7 @@ __device__ __forceinline__ void dkdv_d128_body(const uint16_t* __restrict__ q,
 
     // workgroup -> (key/value slice, key block), see dkdv_d64_body
     uint32_t unit, r_unit;
-    map_key_block(g, blockIdx.x, (uint32_t)(m * CHUNKS), n_units, unit, r_unit);
+    map_key_block(g, blockIdx.x, CHUNKS, n_units, unit, r_unit);
     const int place = (int)r_unit / CHUNKS, row0 = 32 * (NW * ((int)r_unit % CHUNKS) + wave);
     const int j = order ? order[(int64_t)unit * m + place] : place;
     const int64_t base = (int64_t)unit * g.n_tokens * D;

@@ -11,6 +11,7 @@
 //     takes the same blocks of all query heads that share the slice: head after head, the
 //     part of the slice that an XCD needs was fetched by as many XCDs as there are heads, and
 //     small launches were slower than item by item.
+//   * The workgroups of one block (its row chunks) stay together: they gather the same tiles.
 // Forward us, dealt item by item before (small numbers of slices) | in runs: 6 slices of 2,276
 // blocks of 64, 31 attended, head dim 128, 24 heads 7,040 | 3,960; 4 of 450 blocks of 64 57 |
 // 45; 15 of 450 106 | 97; 2 of 1,800, 6 heads 321 | 280; 3 of 384 of 128, 12 heads 517 | 493; 4 of
@@ -33,16 +34,17 @@ namespace bsa {
 
 struct Deal {
     int32_t whole_slices;      // slices are dealt to XCDs whole while there are eight
-    int32_t run_log2;          // items of a run
+    int32_t run_log2;          // blocks of a run (of any head)
 };
 
 // Workgroup w of a launch over n_units key/value slices -> slice, query head (of the `heads`
-// that share it) and item of that head, of per_head.
-__host__ __device__ __forceinline__ void map_unit(Deal deal, uint32_t w, uint32_t per_head,
-                                                  uint32_t heads, uint32_t n_units,
-                                                  uint32_t& unit, uint32_t& head, uint32_t& item)
+// that share it) and item of that head: `chunks` items to each of `blocks` blocks.
+__host__ __device__ __forceinline__ void map_unit(Deal deal, uint32_t w, uint32_t blocks,
+                                                  uint32_t heads, uint32_t chunks,
+                                                  uint32_t n_units, uint32_t& unit,
+                                                  uint32_t& head, uint32_t& item)
 {
-    const uint32_t per_unit = per_head * heads;
+    const uint32_t per_head = blocks * chunks, per_unit = per_head * heads;
     const uint32_t units_dealt = deal.whole_slices ? n_units & ~7u : 0;
     const uint32_t dealt = units_dealt * per_unit;
     if (w < dealt) {
@@ -54,20 +56,30 @@ __host__ __device__ __forceinline__ void map_unit(Deal deal, uint32_t w, uint32_
     }
     // runs for all XCDs while there are, then an eighth of what is left to each
     const int log2 = deal.run_log2;
-    const uint32_t rest = (n_units - units_dealt) * per_unit;
-    const uint32_t even = rest >> (log2 + 3) << (log2 + 3), tail = rest - even;
+    const uint32_t rest = (n_units - units_dealt) * blocks * heads;
+    const uint32_t even = (rest >> (log2 + 3) << (log2 + 3)) * chunks, tail = rest * chunks - even;
     const uint32_t xcd = (w - dealt) & 7, seq = (w - dealt) >> 3;
-    const uint32_t at =
-        w - dealt < even
-            ? (((seq >> log2 << 3) + xcd) << log2) + (seq & ((1u << log2) - 1))
-            : even + (seq - (even >> 3)) + xcd * (tail >> 3) + (xcd < (tail & 7u) ? xcd : tail & 7u);
+    uint32_t at;
+    if (w - dealt < even) {
+        const uint32_t place = seq / chunks;
+        at = ((((place >> log2 << 3) + xcd) << log2) + (place & ((1u << log2) - 1))) * chunks +
+             (seq - place * chunks);
+    } else {
+        at = even + (seq - (even >> 3)) + xcd * (tail >> 3) + (xcd < (tail & 7u) ? xcd : tail & 7u);
+    }
     const uint32_t u = at / per_unit, r = at - u * per_unit;
     unit = units_dealt + u;
-    item = heads == 1 ? r : r / heads;               // the heads of an item side by side
-    head = r - item * heads;
+    head = 0;
+    item = r;
+    if (heads > 1) {                                 // the heads of a block side by side
+        const uint32_t of_block = heads * chunks, block = r / of_block, in_block = r - block * of_block;
+        head = in_block / chunks;
+        item = block * chunks + (in_block - head * chunks);
+    }
 }
 
-// Runs of about 16,384 tokens, 64 to 256 blocks: 2 slices of 1,800 blocks of 64 in runs of
+// Runs of about 16,384 tokens (of one head or another), from 16 blocks of 1,024 tokens to 16,384
+// of one: 2 slices of 1,800 blocks of 64 in runs of
 // 4,096 300 us, of 8,192 283, of 16,384 280, of 65,536 283.
 inline Deal xcd_deal(int64_t slice_bytes, int block_tokens)
 {

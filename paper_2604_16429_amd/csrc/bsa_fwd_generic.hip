@@ -87,7 +87,7 @@ void fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const 
 
     int item;
     int64_t bh_idx;
-    map_workgroup(g, wg, (uint32_t)(g.n_blocks * row_chunks), n_units, bh_idx, item);
+    map_workgroup(g, wg, (uint32_t)row_chunks, n_units, bh_idx, item);
     const int i = item / row_chunks;
     const int row0 = (item - i * row_chunks) * chunk_rows;
     const int64_t base = bh_idx * g.n_tokens * D;

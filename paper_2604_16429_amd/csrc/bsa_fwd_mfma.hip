@@ -282,7 +282,7 @@ __device__ __forceinline__ void fwd_mfma_d64_body(
     {
         const int groups = subs / NW;
         int item;
-        map_workgroup(g, wg, (uint32_t)(g.n_blocks * groups), n_units, bh_idx, item);
+        map_workgroup(g, wg, (uint32_t)groups, n_units, bh_idx, item);
         i = item / groups;
         qsub = (item - i * groups) * NW + wave;
     }

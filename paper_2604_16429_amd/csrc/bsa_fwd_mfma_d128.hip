@@ -103,7 +103,7 @@ __device__ __forceinline__ void fwd_mfma_q32_body(
     // workgroup -> (query slice, query block)
     int i;
     int64_t bh_idx;
-    map_workgroup(g, wg, (uint32_t)g.n_blocks, n_units, bh_idx, i);
+    map_workgroup(g, wg, 1, n_units, bh_idx, i);
     const int64_t base = bh_idx * g.n_tokens * D;
     const int64_t kv_base = kv_slice_of(g, bh_idx) * g.n_tokens * D;
     // The attended blocks: block i itself followed by its selected blocks, or,

@@ -20,13 +20,13 @@ extern "C" void deal_of(int64_t slice_bytes, int block_tokens, int32_t* out)
     out[0] = d.whole_slices;
     out[1] = d.run_log2;
 }
-extern "C" void map_all(int whole, int run_log2, uint32_t per_head, uint32_t heads,
-                        uint32_t n_units, uint32_t* out)
+extern "C" void map_all(int whole, int run_log2, uint32_t blocks, uint32_t heads,
+                        uint32_t chunks, uint32_t n_units, uint32_t* out)
 {
-    const uint32_t all = n_units * heads * per_head;
+    const uint32_t all = n_units * heads * blocks * chunks;
     for (uint32_t w = 0; w < all; ++w)
-        map_unit(Deal{whole, run_log2}, w, per_head, heads, n_units, out[3 * w],
-                 out[3 * w + 1], out[3 * w + 2]);
+        map_unit(Deal{whole, run_log2}, w, blocks, heads, chunks, n_units,
+                 out[3 * w], out[3 * w + 1], out[3 * w + 2]);
 }
 """
 
@@ -42,10 +42,10 @@ def deal(tmp_path_factory):
     return ctypes.CDLL(str(lib))
 
 
-def mapped(deal, whole, run_log2, per_head, heads, n_units):
+def mapped(deal, whole, run_log2, blocks, heads, chunks, n_units):
     """[workgroups, 3]: key/value slice, query head of the slice, item of the head."""
-    out = np.empty((n_units * heads * per_head, 3), dtype=np.uint32)
-    deal.map_all(whole, run_log2, per_head, heads, n_units, out.ctypes.data_as(ctypes.c_void_p))
+    out = np.empty((n_units * heads * blocks * chunks, 3), dtype=np.uint32)
+    deal.map_all(whole, run_log2, blocks, heads, chunks, n_units, out.ctypes.data_as(ctypes.c_void_p))
     return out.astype(np.int64)
 
 
@@ -54,35 +54,55 @@ def test_every_item_once(deal, seed):
     rng = random.Random(seed)
     for _ in range(300):
         whole, run_log2 = rng.randint(0, 1), rng.randint(0, 7)
-        per_head, heads, n_units = rng.randint(1, 300), rng.choice([1, 1, 2, 3, 4, 7]), rng.randint(1, 20)
-        m = mapped(deal, whole, run_log2, per_head, heads, n_units)
+        blocks, heads, n_units = rng.randint(1, 200), rng.choice([1, 1, 2, 3, 4, 7]), rng.randint(1, 20)
+        chunks = rng.choice([1, 1, 2, 3, 4, 5, 8])
+        m = mapped(deal, whole, run_log2, blocks, heads, chunks, n_units)
+        per_head = blocks * chunks
         assert m[:, 1].max() < heads and m[:, 2].max() < per_head
         key = np.sort((m[:, 0] * heads + m[:, 1]) * per_head + m[:, 2])
         assert np.array_equal(key, np.arange(len(m)))
 
 
-@pytest.mark.parametrize("heads,per_head,n_units,run_log2", [
-    (4, 128, 1, 8),      # an eighth to each XCD
-    (8, 450, 2, 8),
-    (4, 24, 5, 7),
-    (3, 2025, 1, 7),     # runs of 128 and a tail
-    (4, 4050, 3, 6),
+@pytest.mark.parametrize("heads,blocks,chunks,n_units,run_log2", [
+    (4, 128, 1, 1, 8),      # an eighth to each XCD
+    (8, 450, 1, 2, 8),
+    (4, 24, 2, 5, 7),
+    (3, 2025, 1, 1, 7),     # runs of 128 and a tail
+    (4, 4050, 3, 3, 6),
 ])
-def test_heads_of_a_slice_share_an_xcd(deal, heads, per_head, n_units, run_log2):
+def test_heads_of_a_slice_share_an_xcd(deal, heads, blocks, chunks, n_units, run_log2):
     """Of the slices that all XCDs share, an XCD works on the same items of all query heads of a
     slice, but for the ends of its runs."""
-    m = mapped(deal, 0, run_log2, per_head, heads, n_units)
+    m = mapped(deal, 0, run_log2, blocks, heads, chunks, n_units)
     xcds = {}
     for w, (unit, _, item) in enumerate(m):
         xcds.setdefault((unit, item), set()).add(w % 8)
     spread = sum(len(x) > 1 for x in xcds.values())
-    runs = heads * per_head * n_units // (1 << run_log2) + 8
-    assert spread <= runs, f"{spread} of {len(xcds)} items on more than one XCD"
+    runs = heads * blocks * n_units // (1 << run_log2) + 8
+    assert spread <= chunks * runs, f"{spread} of {len(xcds)} items on more than one XCD"
+
+
+@pytest.mark.parametrize("blocks,heads,chunks,n_units,run_log2", [
+    (128, 1, 4, 1, 0),     # key blocks, one by one
+    (225, 1, 2, 3, 0),
+    (96, 1, 3, 7, 0),
+    (1024, 1, 2, 1, 6),    # runs of 64
+    (700, 2, 5, 3, 5),
+])
+def test_chunks_of_a_block_share_an_xcd(deal, blocks, heads, chunks, n_units, run_log2):
+    """The workgroups of one block, which gather the same tiles, follow each other on one XCD, but
+    for the blocks that the eighths of the last round cut (seven)."""
+    m = mapped(deal, 0, run_log2, blocks, heads, chunks, n_units)
+    xcds = {}
+    for w, (unit, head, item) in enumerate(m):
+        xcds.setdefault((unit, head, item // chunks), []).append(w)
+    apart = sum(not np.array_equal(x, x[0] + 8 * np.arange(chunks)) for x in xcds.values())
+    assert apart <= 7, f"{apart} of {len(xcds)} blocks on more than one XCD"
 
 
 def test_whole_slices(deal):
     """Eight slices at a time, one to each XCD."""
-    m = mapped(deal, 1, 6, 50, 3, 19)
+    m = mapped(deal, 1, 6, 25, 3, 2, 19)
     dealt = m[: 16 * 150]
     assert np.array_equal(dealt[:, 0] % 8, np.arange(len(dealt)) % 8)
     assert m[16 * 150 :, 0].min() == 16
