@@ -916,6 +916,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
         return launch_slices(BKV, wgs * 64 * nw, [&](int64_t first, int64_t slices) {
             const int64_t bh = first * g.kv_group, row = bh * N, kv = first * N * D;
             Geom piece = g;
+            piece.deal = key_deal(g.deal, 2 * N * D * (int)sizeof(T), order != nullptr, g.add_dk != nullptr);
             if (g.add_dk) piece.add_dk += first * m * D;
             if (g.add_dv) piece.add_dv += first * m * D;
             kernel<<<dim3((unsigned)(slices * wgs)), block, sizeof(uint32_t) * (size_t)g.block_tokens,

@@ -1236,11 +1236,13 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
     hipError_t e = launch_bwd_prepare(true, out, dout, lse, delta, lse2, sel_idx, conn, order, g, D,
                                       BH, stream);
     if (e != hipSuccess) return e;
+    Geom g_kv = g;
+    g_kv.deal = key_deal(g.deal, 2 * g.n_tokens * D * 2, order != nullptr, g.add_dk != nullptr);
     auto run_dkdv = [&](auto kernel) {
         kernel<<<dim3(sx * (unsigned)(g.n_blocks * (nw / split.waves))),
                  dim3(64 * split.waves * split.groups), 0, stream>>>(
             (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2,
-            delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g, sx);
+            delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g_kv, sx);
         return hipGetLastError();
     };
     auto run_dq = [&](auto kernel) {

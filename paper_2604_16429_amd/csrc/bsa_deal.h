@@ -12,6 +12,9 @@
 //     part of the slice that an XCD needs was fetched by as many XCDs as there are heads, and
 //     small launches were slower than item by item.
 //   * The workgroups of one block (its row chunks) stay together: they gather the same tiles.
+//     Key blocks, whose chunks walk the same list, dealt workgroup by workgroup | block by
+//     block, backward us: 1 slice of 128 blocks of 256 in four chunks 129 | 122, 2 slices 183 | 178,
+//     3 with 6 heads 454 | 444, head dim 128 347 | 338; 1,024 tokens, 3 with 6 heads 5,190 | 4,961.
 // Forward us, dealt item by item before (small numbers of slices) | in runs: 6 slices of 2,276
 // blocks of 64, 31 attended, head dim 128, 24 heads 7,040 | 3,960; 4 of 450 blocks of 64 57 |
 // 45; 15 of 450 106 | 97; 2 of 1,800, 6 heads 321 | 280; 3 of 384 of 128, 12 heads 517 | 493; 4 of
@@ -87,6 +90,30 @@ inline Deal xcd_deal(int64_t slice_bytes, int block_tokens)
     d.whole_slices = slice_bytes <= (int64_t)32 << 20;
     d.run_log2 = 14;
     for (int rows = block_tokens - 1; rows > 0; rows >>= 1) --d.run_log2;
+    return d;
+}
+
+// Key blocks (dK and dV).  `ordered`: in the order of their lists, long ones first; `even`: all
+// lists are as long (local branch); neither: uneven lists as they lie.
+//   * Ordered or even, slices are dealt to XCDs whole whatever their size: an XCD then gathers
+//     the query tiles of its own slice, and the long lists of all slices start early.  Shared
+//     block by block, each tile was fetched into eight L2s and the long lists of the last slice
+//     came last.  Whole backward, us, slices above 32 MB shared | whole: fp32, 8 slices of
+//     1,200 blocks of 64 (38 MB) 2,928 | 2,665, of 1,024 of 128 (64 MB) 9,063 | 8,446; bf16, 8 of
+//     1,600 of 10 x 10 (39 MB) 2,278 | 2,116, of 1,200 of 64 at head dim 128 (38 MB) 1,479 | 1,356;
+//     local branch, 8 of 4,096 of 128 (128 MB) 15,500 | 15,020.  Many blocks in bf16 lose a little: 8
+//     of 2,048 of 128 2,497 | 2,504, 16 of 4,050 of 256 38,250 | 38,470, 16 selected 67,800 | 68,420,
+//     20 of 8,100 of 64 3,819 | 3,898.
+//   * Uneven lists as they lie balance best block by block over all XCDs: above 32 MB, gradients
+//     in place, head dim 128, 8 slices of 42 MB 1,572, whole 1,650, 64 MB 2,679 | 2,663, fp32
+//     9,087 | 9,150.  Below, 0.92 to 1.07 times either way.
+//   * What is left is shared block by block: runs would give one XCD all the long lists (1 slice
+//     of 225 blocks of 128 in runs 84 us, block by block 70).  Even lists: in runs as the query
+//     blocks are (6 slices of 450 blocks, backward of three branches 394 | 389).
+inline Deal key_deal(Deal d, int64_t slice_bytes, bool ordered, bool even)
+{
+    d.whole_slices = ordered || even || slice_bytes <= (int64_t)32 << 20;
+    if (!even) d.run_log2 = 0;
     return d;
 }
 

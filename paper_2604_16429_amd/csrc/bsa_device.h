@@ -72,18 +72,12 @@ __device__ __forceinline__ int64_t kv_slice_of(const Geom& g, int64_t bh)
     return e * (g.heads / g.kv_group) + a / g.kv_group;
 }
 
-// Key blocks, `chunks` workgroups to each: with their order (long lists first) runs would give
-// one XCD all the long lists; they are dealt block by block where slices are not dealt whole.
-// Whole backward, 16 slices of 4,050 blocks of 256 69.2 ms with whole slices, 67.8 so; 2,025 of
-// 128 5,040 us and 4,910.  Workgroup by workgroup, the chunks of a block, which walk the same
-// list, lay on different XCDs: 1 slice of 128 blocks of 256, four chunks, head dim 64 133 us,
-// together 126, 2 slices 194 and 187, 3 with 6 heads 488 and 469, head dim 128 369 and 363.
+// Key blocks, `chunks` workgroups to each (g.deal: key_deal).
 __device__ __forceinline__ void map_key_block(const Geom& g, uint32_t w, uint32_t chunks,
                                               uint32_t n_units, uint32_t& unit, uint32_t& item)
 {
     uint32_t head;
-    map_unit(Deal{g.deal.whole_slices, 0}, w, (uint32_t)g.n_blocks, 1, chunks, n_units, unit, head,
-             item);
+    map_unit(g.deal, w, (uint32_t)g.n_blocks, 1, chunks, n_units, unit, head, item);
 }
 
 // Query blocks, `chunks` workgroups to each.  The grid is n_units * kv_group * m * chunks

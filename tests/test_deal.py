@@ -20,6 +20,12 @@ extern "C" void deal_of(int64_t slice_bytes, int block_tokens, int32_t* out)
     out[0] = d.whole_slices;
     out[1] = d.run_log2;
 }
+extern "C" void key_deal_of(int64_t slice_bytes, int block_tokens, int ordered, int even, int32_t* out)
+{
+    const Deal d = key_deal(xcd_deal(slice_bytes, block_tokens), slice_bytes, ordered, even);
+    out[0] = d.whole_slices;
+    out[1] = d.run_log2;
+}
 extern "C" void map_all(int whole, int run_log2, uint32_t blocks, uint32_t heads,
                         uint32_t chunks, uint32_t n_units, uint32_t* out)
 {
@@ -39,7 +45,10 @@ def deal(tmp_path_factory):
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950",
                     "--offload-host-only", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC,
                     "-I", os.path.join(ROOT, "include"), str(src), "-o", str(lib)], check=True)
-    return ctypes.CDLL(str(lib))
+    lib = ctypes.CDLL(str(lib))
+    lib.deal_of.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
+    lib.key_deal_of.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3 + [ctypes.c_void_p]
+    return lib
 
 
 def mapped(deal, whole, run_log2, blocks, heads, chunks, n_units):
@@ -98,6 +107,20 @@ def test_chunks_of_a_block_share_an_xcd(deal, blocks, heads, chunks, n_units, ru
         xcds.setdefault((unit, head, item // chunks), []).append(w)
     apart = sum(not np.array_equal(x, x[0] + 8 * np.arange(chunks)) for x in xcds.values())
     assert apart <= 7, f"{apart} of {len(xcds)} blocks on more than one XCD"
+
+
+@pytest.mark.parametrize("megabytes", [1, 31, 33, 64, 265, 2048])
+@pytest.mark.parametrize("block_tokens", [64, 100, 256])
+def test_deal_of_key_blocks(deal, megabytes, block_tokens):
+    """Slices whose key blocks are ordered, or have lists of one length, go to one XCD whatever
+    their size; only lists of one length go in runs, those of the query blocks."""
+    d = np.empty((4, 2), dtype=np.int32)
+    deal.deal_of(megabytes << 20, block_tokens, d[0].ctypes.data)
+    for row, (ordered, even) in zip(d[1:], ((1, 0), (0, 1), (0, 0))):
+        deal.key_deal_of(megabytes << 20, block_tokens, ordered, even, row.ctypes.data)
+    assert d[1].tolist() == [1, 0]
+    assert d[2].tolist() == [1, d[0, 1]]
+    assert d[3].tolist() == [int(megabytes <= 32), 0]
 
 
 def test_whole_slices(deal):
