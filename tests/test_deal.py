@@ -109,6 +109,15 @@ def test_chunks_of_a_block_share_an_xcd(deal, blocks, heads, chunks, n_units, ru
     assert apart <= 7, f"{apart} of {len(xcds)} blocks on more than one XCD"
 
 
+@pytest.mark.parametrize("megabytes,whole", [(1, 1), (32, 1), (33, 0), (265, 0)])
+def test_deal_of_query_blocks(deal, megabytes, whole):
+    """Slices up to 32 MB whole, larger ones in runs of about 16,384 tokens."""
+    d = np.empty(2, dtype=np.int32)
+    for block_tokens, run in ((1, 16384), (60, 256), (64, 256), (100, 128), (256, 64), (1024, 16)):
+        deal.deal_of(megabytes << 20, block_tokens, d.ctypes.data)
+        assert d.tolist() == [whole, run.bit_length() - 1]
+
+
 @pytest.mark.parametrize("megabytes", [1, 31, 33, 64, 265, 2048])
 @pytest.mark.parametrize("block_tokens", [64, 100, 256])
 def test_deal_of_key_blocks(deal, megabytes, block_tokens):
