@@ -894,37 +894,32 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
 {
     const int m = g.n_blocks, words = (m + 31) >> 5;
     const int64_t BKV = BH / g.kv_group, N = g.n_tokens;
-    const BwdSplit split_kv = dkdv_split<T, D>(g, BKV);
     const bool dkdv_first = order != nullptr;        // `order` may lie where dQ goes
-    {
-        const RowSplit rows(g.block_tokens, split_kv.max_waves, WaveTile<T>::ROWS);
-        if (BKV * m * rows.chunks * rows.waves * split_kv.groups <= kUnorderedWaves) order = nullptr;
-        const hipError_t e = launch_bwd_prepare(sizeof(T) == 2, out, dout, lse, delta, lse2, sel_idx,
-                                                conn, order, g, D, BH, stream);
-        if (e != hipSuccess) return e;
-    }
+    const BwdSplit split_kv = dkdv_split<T, D>(g, BKV);
+    const RowSplit rows_kv(g.block_tokens, split_kv.max_waves, WaveTile<T>::ROWS);
+    const int waves_kv = rows_kv.waves * split_kv.groups;
+    const int64_t wgs_kv = (int64_t)m * rows_kv.chunks;           // per slice
+    const size_t lds_kv = sizeof(uint32_t) * (size_t)g.block_tokens;
+    auto kernel_kv = split_kv.groups == 4   ? dkdv_kernel<T, D, 4>(rows_kv.waves)
+                     : split_kv.groups == 2 ? dkdv_kernel<T, D, 2>(rows_kv.waves)
+                     : rows_kv.narrow       ? dkdv_kernel<T, D, 1, sizeof(T) == 2>(rows_kv.waves)
+                                            : dkdv_kernel<T, D, 1>(rows_kv.waves);
+    if (order && needs_no_order(kernel_kv, BKV * wgs_kv, waves_kv, lds_kv)) order = nullptr;
+    hipError_t e = launch_bwd_prepare(sizeof(T) == 2, out, dout, lse, delta, lse2, sel_idx, conn,
+                                      order, g, D, BH, stream);
+    if (e != hipSuccess) return e;
     auto run_dkdv = [&] {
-        const BwdSplit split = split_kv;
-        const RowSplit rows(g.block_tokens, split.max_waves, WaveTile<T>::ROWS);
-        const int64_t wgs = (int64_t)m * rows.chunks;             // per slice
-        const int nw = rows.waves * split.groups;
-        auto kernel = split.groups == 4 ? dkdv_kernel<T, D, 4>(rows.waves)
-                      : split.groups == 2 ? dkdv_kernel<T, D, 2>(rows.waves)
-                      : rows.narrow       ? dkdv_kernel<T, D, 1, sizeof(T) == 2>(rows.waves)
-                                          : dkdv_kernel<T, D, 1>(rows.waves);
-        const dim3 block(64 * nw);
-        return launch_slices(BKV, wgs * 64 * nw, [&](int64_t first, int64_t slices) {
+        return launch_slices(BKV, wgs_kv * 64 * waves_kv, [&](int64_t first, int64_t slices) {
             const int64_t bh = first * g.kv_group, row = bh * N, kv = first * N * D;
             Geom piece = g;
             piece.deal = key_deal(g.deal, 2 * N * D * (int)sizeof(T), order != nullptr, g.add_dk != nullptr);
             if (g.add_dk) piece.add_dk += first * m * D;
             if (g.add_dv) piece.add_dv += first * m * D;
-            kernel<<<dim3((unsigned)(slices * wgs)), block, sizeof(uint32_t) * (size_t)g.block_tokens,
-                     stream>>>((const T*)q + row * D, (const T*)k + kv, (const T*)v + kv,
-                               (const T*)dout + row * D, lse2 + row, delta + row,
-                               conn + bh * words * m, order ? order + first * m : nullptr,
-                               (T*)dk + kv, (T*)dv + kv, piece, (uint32_t)slices, rows.chunks,
-                               WaveTile<T>::ROWS * rows.waves);
+            kernel_kv<<<dim3((unsigned)(slices * wgs_kv)), dim3(64 * waves_kv), lds_kv, stream>>>(
+                (const T*)q + row * D, (const T*)k + kv, (const T*)v + kv, (const T*)dout + row * D,
+                lse2 + row, delta + row, conn + bh * words * m, order ? order + first * m : nullptr,
+                (T*)dk + kv, (T*)dv + kv, piece, (uint32_t)slices, rows_kv.chunks,
+                WaveTile<T>::ROWS * rows_kv.waves);
             return hipGetLastError();
         });
     };
@@ -951,7 +946,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
         });
     };
     // without the memory for an order dK and dV may lie where k and v are
-    const hipError_t e = dkdv_first ? run_dkdv() : run_dq();
+    e = dkdv_first ? run_dkdv() : run_dq();
     if (e != hipSuccess) return e;
     return dkdv_first ? run_dq() : run_dkdv();
 }

@@ -1229,39 +1229,41 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
 {
     const int nw = g.block_tokens / 32;
     const uint32_t sx = (uint32_t)(BH / g.kv_group);           // key/value slices
-    const dim3 grid((unsigned)(BH * g.n_blocks)), block(64 * nw);
     const DkdvSplit split = dkdv_split(g, D, sx);
-    const bool dkdv_first = order != nullptr;        // `order` may lie where dQ goes
-    if ((int64_t)sx * g.n_blocks * nw * split.groups <= kUnorderedWaves) order = nullptr;
-    hipError_t e = launch_bwd_prepare(true, out, dout, lse, delta, lse2, sel_idx, conn, order, g, D,
-                                      BH, stream);
-    if (e != hipSuccess) return e;
-    Geom g_kv = g;
-    g_kv.deal = key_deal(g.deal, 2 * g.n_tokens * D * 2, order != nullptr, g.add_dk != nullptr);
-    auto run_dkdv = [&](auto kernel) {
-        kernel<<<dim3(sx * (unsigned)(g.n_blocks * (nw / split.waves))),
-                 dim3(64 * split.waves * split.groups), 0, stream>>>(
-            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2,
-            delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, g_kv, sx);
-        return hipGetLastError();
+    auto run = [&](auto dq_kernel, auto dkdv_kernel) {
+        const bool dkdv_first = order != nullptr;    // `order` may lie where dQ goes
+        const int waves = split.waves * split.groups;
+        const uint32_t wgs = sx * (unsigned)(g.n_blocks * (nw / split.waves));
+        if (order && needs_no_order(dkdv_kernel, wgs, waves, 0)) order = nullptr;
+        hipError_t e = launch_bwd_prepare(true, out, dout, lse, delta, lse2, sel_idx, conn, order, g,
+                                          D, BH, stream);
+        if (e != hipSuccess) return e;
+        auto run_dkdv = [&] {
+            Geom gk = g;
+            gk.deal = key_deal(g.deal, 2 * g.n_tokens * D * 2, order != nullptr, g.add_dk != nullptr);
+            dkdv_kernel<<<dim3(wgs), dim3(64 * waves), 0, stream>>>(
+                (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
+                lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, gk, sx);
+            return hipGetLastError();
+        };
+        auto run_dq = [&] {
+            dq_kernel<<<dim3((unsigned)(BH * g.n_blocks)), dim3(64 * nw), 0, stream>>>(
+                (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
+                lse2, delta, sel_idx, (uint16_t*)dq, g, sx);
+            return hipGetLastError();
+        };
+        // without the memory for an order dK and dV may lie where k and v are
+        e = dkdv_first ? run_dkdv() : run_dq();
+        if (e != hipSuccess) return e;
+        return dkdv_first ? run_dq() : run_dkdv();
     };
-    auto run_dq = [&](auto kernel) {
-        kernel<<<grid, block, 0, stream>>>((const uint16_t*)q, (const uint16_t*)k,
-                                           (const uint16_t*)v, (const uint16_t*)dout, lse2, delta,
-                                           sel_idx, (uint16_t*)dq, g, sx);
-        return hipGetLastError();
-    };
-    // without the memory for an order dK and dV may lie where k and v are
 #define BSA_LAUNCH(D_, NW_, FOUR_GROUPS, FOUR_WAVES)                                              \
-    if (D == D_ && nw == NW_) {                                                                   \
-        if (!dkdv_first && (e = run_dq(bwd_mfma_dq_d##D_##_w##NW_)) != hipSuccess) return e;      \
-        e = run_dkdv(split.groups == 1   ? bwd_mfma_dkdv_d##D_##_w##NW_                           \
-                     : split.groups == 4 ? bwd_mfma_dkdv_d##D_##_##FOUR_GROUPS                    \
-                     : split.waves == 4  ? bwd_mfma_dkdv_d##D_##_##FOUR_WAVES                     \
-                                         : bwd_mfma_dkdv_d##D_##_w##NW_##_split2);                \
-        if (e != hipSuccess) return e;                                                            \
-        return dkdv_first ? run_dq(bwd_mfma_dq_d##D_##_w##NW_) : hipSuccess;                      \
-    }
+    if (D == D_ && nw == NW_)                                                                     \
+        return run(bwd_mfma_dq_d##D_##_w##NW_,                                                    \
+                   split.groups == 1   ? bwd_mfma_dkdv_d##D_##_w##NW_                             \
+                   : split.groups == 4 ? bwd_mfma_dkdv_d##D_##_##FOUR_GROUPS                      \
+                   : split.waves == 4  ? bwd_mfma_dkdv_d##D_##_##FOUR_WAVES                       \
+                                       : bwd_mfma_dkdv_d##D_##_w##NW_##_split2);
     // (the last two columns: a kernel that the rule does not name there is not launched)
     BSA_LAUNCH(64, 2, w2_split4, w2_split2)
     BSA_LAUNCH(64, 4, w4_split4, w4_split2)

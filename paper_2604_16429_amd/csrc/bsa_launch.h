@@ -91,13 +91,38 @@ hipError_t launch_fwd_mfma_d128(const void* q, const void* k, const void* v, con
 hipError_t launch_bwd_prepare(bool is_bf16, const void* out, const void* dout, const float* lse,
                               float* delta, float* lse2, const int32_t* sel_idx, uint32_t* conn,
                               int32_t* order, const Geom& g, int D, int64_t BH, hipStream_t stream);
-// A dK/dV launch of up to so many wavefronts, two per SIMD, runs at once: no key block waits
-// for its turn, and the launch that orders them, 4 to 7 us, is left out.  Whole backward with
-// and without it: 32 blocks of 100 tokens, 4 slices, head dim 32 37.0 and 31.6 us, 64 46.0 and
-// 41.0; 72 of 64, 4 slices 38.5 and 36.6; 144 of 128 at head dim 128 102.6 and 100.2.  Beyond,
-// up to 4,096: 36 of 128, 4 slices 56.7 and 63.4, 288 of 64 in fp32 195 and 229, 72 of 64, 4
-// slices, 123 and 121.
+// A dK/dV launch that runs at once, or nearly, with up to two wavefronts per SIMD needs no
+// order of its key blocks: that takes a launch of 4 to 7 us.  How many workgroups run at once
+// is the kernel's matter: LDS or registers leave several forms one wavefront per SIMD or half
+// of one (the runtime answers in 0.13 us).  With a third more the last ones start where short
+// lists have ended.  Whole backward, us, ordered | not (wavefronts, room):
+//   * all at once: 32 blocks of 100 tokens, 4 slices, head dim 32 37.0 | 31.6, 64 46.0 | 41.0; 72
+//     of 64, 4 slices 38.5 | 36.6; 128 of 64, 4 slices 73.1 | 61.7; head dim 128, 128 of 128 (1,024)
+//     122 | 118; fp32, 128 of 16, 2 slices (512) 95 | 91.
+//   * up to a third more: head dim 32, 128 of 24, 16 slices (2,048, 1,536) 58.4 | 55.2, fp32 128 of
+//     16 92 | 82; head dim 64, 256 of 48, 4 slices 116 | 107, fp32 128 of 16, 7 slices (896, 768)
+//     70.7 | 66.2, 8 slices (1,024) 102 | 105.
+//   * half as many more and beyond: head dim 128, 192 of 128 (1,536, 1,024) 155 | 168, 4 heads on 1
+//     400 | 458, 192 of 64 117 | 139, 128 of 64, 8 slices (2,048) 226 | 265; fp32 128 of 64, 2 slices
+//     323 | 389, 192 of 16, 8 slices (1,536, 512) 300 | 386; head dim 64, fp32 128 of 64 (2,048,
+//     1,024) 122 | 137.  Short lists, 4 selected, gain less than it takes: 128 of 48, 6 slices
+//     (1,536, 1,024) 110 | 107, of 24 (768, 512) 74 | 71.
+//   * more than two wavefronts per SIMD, up to 4,096: 36 of 128, 4 slices 56.7 | 63.4, 288 of 64 in
+//     fp32 195 | 229, 72 of 64, 4 slices, 123 | 121.
 constexpr int64_t kUnorderedWaves = 2048;
+inline bool needs_no_order(int64_t workgroups, int waves, int per_cu)
+{
+    return workgroups * waves <= kUnorderedWaves && 3 * workgroups <= (int64_t)4 * 256 * per_cu;
+}
+template <class K>
+inline bool needs_no_order(K kernel, int64_t workgroups, int waves, size_t dynamic_lds)
+{
+    int per_cu = 0;
+    return needs_no_order(workgroups, waves, 8) &&
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, 64 * waves,
+                                                        dynamic_lds) == hipSuccess &&
+           needs_no_order(workgroups, waves, per_cu);
+}
 
 // Backward with the selection fixed, any tile shape / head dim in {32, 64, 128} /
 // dtype.  `delta` and `lse2` are fp32 scratch of B*heads*N floats each, `conn`

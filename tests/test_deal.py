@@ -12,7 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2604_16429_amd", "csrc")
 
 SOURCE = """
-#include "bsa_deal.h"
+#include "bsa_launch.h"
 using namespace bsa;
 extern "C" void deal_of(int64_t slice_bytes, int block_tokens, int32_t* out)
 {
@@ -25,6 +25,10 @@ extern "C" void key_deal_of(int64_t slice_bytes, int block_tokens, int ordered, 
     const Deal d = key_deal(xcd_deal(slice_bytes, block_tokens), slice_bytes, ordered, even);
     out[0] = d.whole_slices;
     out[1] = d.run_log2;
+}
+extern "C" int no_order(int64_t workgroups, int waves, int per_cu)
+{
+    return needs_no_order(workgroups, waves, per_cu);
 }
 extern "C" void map_all(int whole, int run_log2, uint32_t blocks, uint32_t heads,
                         uint32_t chunks, uint32_t n_units, uint32_t* out)
@@ -46,6 +50,7 @@ def deal(tmp_path_factory):
                     "--offload-host-only", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC,
                     "-I", os.path.join(ROOT, "include"), str(src), "-o", str(lib)], check=True)
     lib = ctypes.CDLL(str(lib))
+    lib.no_order.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     lib.deal_of.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
     lib.key_deal_of.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3 + [ctypes.c_void_p]
     return lib
@@ -130,6 +135,14 @@ def test_deal_of_key_blocks(deal, megabytes, block_tokens):
     assert d[1].tolist() == [1, 0]
     assert d[2].tolist() == [1, d[0, 1]]
     assert d[3].tolist() == [int(megabytes <= 32), 0]
+
+
+@pytest.mark.parametrize("waves,per_cu", [(1, 2), (2, 1), (4, 1), (2, 3), (4, 2), (8, 1), (3, 1), (2, 8)])
+def test_launches_without_an_order(deal, waves, per_cu):
+    """dK/dV goes without an order only where 256 CUs that hold per_cu workgroups each take all but a
+    quarter of the launch at once, and at two wavefronts per SIMD at most."""
+    most = min(256 * per_cu * 4 // 3, 2048 // waves)
+    assert deal.no_order(most, waves, per_cu) and not deal.no_order(most + 1, waves, per_cu)
 
 
 def test_whole_slices(deal):
