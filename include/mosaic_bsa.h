@@ -198,7 +198,12 @@ int mosaic_bsa_fwd(const mosaic_bsa_params *params, const void *q, const void *k
  * Memory that gradients may share with an input, whole tensors only: dq with out
  * (which then is lost), dk with k and dv with v.  Everything else must not overlap.
  * dk/dv of a key block are reduced over the query blocks that attend to it in
- * a fixed order (no floating-point atomics): results are run-to-run identical.
+ * a fixed order (no floating-point atomics): the same call gives the same bits from run
+ * to run.  They may differ between calls that hold different numbers of slices (batch
+ * or heads): in small calls two or four groups of wavefronts each sum a part of that
+ * order (dk and dv in every type; dq where the general kernels run), and the parts are
+ * added in the order of the groups.  Results are within the rounding of fp32 sums of
+ * each other.
  */
 int mosaic_bsa_bwd(const mosaic_bsa_params *params, const void *q, const void *k,
                    const void *v, const void *out, const float *lse, const void *dout,
@@ -238,7 +243,8 @@ int mosaic_bsa_bwd(const mosaic_bsa_params *params, const void *q, const void *k
  *                      log-sum-exps); on return it holds what
  *                      mosaic_bsa_bwd_three_branch needs from the forward.
  * The branch outputs are rounded to the element type of q before the gated
- * sum, which runs in fp32.  Errors as for the other entry points; a local
+ * sum, which runs in fp32.  Bits may differ between calls that hold different numbers
+ * of slices, as in mosaic_bsa_fwd.  Errors as for the other entry points; a local
  * group that does not divide the grid of tiles is MOSAIC_BSA_ERR_SHAPE.
  * mosaic_bsa_three_branch_workspace_bytes returns 0 for invalid arguments.
  */
@@ -266,7 +272,8 @@ int mosaic_bsa_fwd_three_branch(const mosaic_bsa_params *params, int32_t local_h
  *                         mosaic_bsa_three_branch_bwd_workspace_bytes(..) bytes
  * The upstream gradients of the two attention branches (gate * dout) and the
  * branches' partial gradients are rounded to the element type of q; every sum
- * runs in a fixed order (no floating-point atomics).
+ * runs in a fixed order (no floating-point atomics).  Bits may differ between calls
+ * that hold different numbers of slices, as in mosaic_bsa_bwd.
  */
 size_t mosaic_bsa_three_branch_bwd_workspace_bytes(const mosaic_bsa_params *params,
                                                    int32_t local_h, int32_t local_w);
