@@ -394,6 +394,26 @@ template <typename T, int D> struct BwdLimits {
     static constexpr int MAX_WAVES = WIDE || sizeof(T) == 4 ? 4 : 8;
     static constexpr int PER_SIMD = WIDE ? 1 : sizeof(T) == 4 && D < 128 ? 3 : 2;
 };
+// The bounds of one form: SPLIT groups of NL wavefronts; unsplit (SPLIT 1) NL wavefronts that
+// gather: 1 of 1, 2 of up to 3 (3: dQ of head dim 128 has a form for exactly three), 4 of up to
+// MAX_WAVES.  Wavefronts per SIMD that the registers must leave room for:
+//   * unsplit: what BwdLimits says from four wavefronts on.  A lone wavefront may take them all: its
+//     workgroups fill a CU's LDS before its SIMDs.  Two or three in dQ as from four on, at head dim
+//     128 dQ of three and more 2 (two workgroups of three fit a CU and share its SIMDs); in dK/dV,
+//     with twice the accumulators, 2 below head dim 128 and 1 there.
+//   * split: as many workgroups as LDS holds.  dQ 1 (it is split only where they are few); dK/dV 2
+//     where LDS holds eight wavefronts: head dim 32, bf16 of 64 (four single wavefronts spill 4
+//     registers outside of the tile loop) and fp32 of 64 in pairs, else 1.
+template <typename T, int D, int NL, int SPLIT> struct BwdBounds {
+    using L = BwdLimits<T, D>;
+    static constexpr bool F32 = sizeof(T) == 4;
+    static constexpr int THREADS = SPLIT > 1 ? 64 * SPLIT * NL
+                                   : NL == 4 ? 64 * L::MAX_WAVES : NL == 1 ? 64 : 192;
+    static constexpr int DQ = SPLIT > 1 || NL == 1 ? 1 : D == 128 && NL > 2 ? 2 : L::PER_SIMD;
+    static constexpr int SPLIT_DKDV = D == 32 || (D == 64 && (!F32 || (NL == 2 && SPLIT == 2))) ? 2 : 1;
+    static constexpr int DKDV = SPLIT > 1 ? SPLIT_DKDV
+                                : NL == 4 ? L::PER_SIMD : NL == 2 && D < 128 ? 2 : 1;
+};
 
 // Launches that leave most of the chip idle, or wait for the longest list of a few key
 // blocks: SPLIT groups of NL wavefronts own the same rows, and each takes 32 rows (bf16 in
@@ -432,10 +452,7 @@ __device__ __forceinline__ bool add_groups(unsigned char* lds_a, unsigned char* 
 }
 
 template <typename T, int D, int NL, int SPLIT, bool MIXED = false>
-__global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL
-                             : NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL >= 2 ? 192 : 64,
-                             SPLIT > 1 || NL == 1 ? 1
-                             : D == 128 && NL > 2 ? 2 : (BwdLimits<T, D>::PER_SIMD))
+__global__ __launch_bounds__((BwdBounds<T, D, NL, SPLIT>::THREADS), (BwdBounds<T, D, NL, SPLIT>::DQ))
 void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                     const T* __restrict__ dout, const float* __restrict__ lse2,
                     const float* __restrict__ delta, const int32_t* __restrict__ sel_idx,
@@ -544,10 +561,7 @@ void bwd_generic_dq(const T* __restrict__ q, const T* __restrict__ k, const T* _
 constexpr int kConnCap = 2048;
 
 template <typename T, int D, int NL, int SPLIT, bool MIXED = false>
-__global__ __launch_bounds__(SPLIT > 1 ? 64 * SPLIT * NL
-                             : NL == 4 ? 64 * (BwdLimits<T, D>::MAX_WAVES) : NL == 2 ? 192 : 64,
-                             SPLIT > 1 ? (D == 32 || (D == 64 && sizeof(T) == 2) || (D == 64 && NL * SPLIT == 4 && SPLIT == 2) ? 2 : 1)
-                             : NL == 4 ? (BwdLimits<T, D>::PER_SIMD) : NL == 2 && D < 128 ? 2 : 1)
+__global__ __launch_bounds__((BwdBounds<T, D, NL, SPLIT>::THREADS), (BwdBounds<T, D, NL, SPLIT>::DKDV))
 void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                       const T* __restrict__ dout, const float* __restrict__ lse2,
                       const float* __restrict__ delta, const uint32_t* __restrict__ conn,
@@ -904,7 +918,8 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
                      : split_kv.groups == 2 ? dkdv_kernel<T, D, 2>(rows_kv.waves)
                      : rows_kv.narrow       ? dkdv_kernel<T, D, 1, sizeof(T) == 2>(rows_kv.waves)
                                             : dkdv_kernel<T, D, 1>(rows_kv.waves);
-    if (order && needs_no_order(kernel_kv, BKV * wgs_kv, waves_kv, lds_kv)) order = nullptr;
+    const bool even = even_lists(g);
+    if (even || (order && needs_no_order(kernel_kv, BKV * wgs_kv, waves_kv, lds_kv))) order = nullptr;
     hipError_t e = launch_bwd_prepare(sizeof(T) == 2, out, dout, lse, delta, lse2, sel_idx, conn,
                                       order, g, D, BH, stream);
     if (e != hipSuccess) return e;
@@ -912,7 +927,7 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
         return launch_slices(BKV, wgs_kv * 64 * waves_kv, [&](int64_t first, int64_t slices) {
             const int64_t bh = first * g.kv_group, row = bh * N, kv = first * N * D;
             Geom piece = g;
-            piece.deal = key_deal(g.deal, 2 * N * D * (int)sizeof(T), order != nullptr, g.add_dk != nullptr);
+            piece.deal = key_deal(g.deal, 2 * N * D * (int)sizeof(T), order != nullptr, even);
             if (g.add_dk) piece.add_dk += first * m * D;
             if (g.add_dv) piece.add_dv += first * m * D;
             kernel_kv<<<dim3((unsigned)(slices * wgs_kv)), dim3(64 * waves_kv), lds_kv, stream>>>(

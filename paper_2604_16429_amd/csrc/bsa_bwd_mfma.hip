@@ -1198,7 +1198,8 @@ bool bwd_mfma_supported(bool is_bf16, const Geom& g, int D)
 //   head dim 128:  1 x 96 x 128, 13:  185 | 132 | -       4 x 96 x 128, 13:   249 | 221 | -
 //                  16 x 96 x 128, 13: 580 | 690 | -       4 x 96 x 256, 13:   727 | 720 | 655
 //                  1 x 448 x 256, 4:  340 | 309 | 277     16 x 96 x 256, 13: 2,256 | 2,480 | 2,234
-// (four groups do not fit beside V at head dim 128).  Lists of equal length (see there) are
+// (four groups at head dim 128 take 155 KB of LDS beside V; built, they spilled and were no faster
+// than two).  Lists of equal length (see there) are
 // split while SIMDs are idle.  367 launches of 48 to 12,288 row wavefronts, smooth fields,
 // noise, n = 0 and all blocks: 1.18 (head dim 64) and 1.20 times as fast on average, three
 // of them slower by 2 to 5 %.
@@ -1234,13 +1235,14 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
         const bool dkdv_first = order != nullptr;    // `order` may lie where dQ goes
         const int waves = split.waves * split.groups;
         const uint32_t wgs = sx * (unsigned)(g.n_blocks * (nw / split.waves));
-        if (order && needs_no_order(dkdv_kernel, wgs, waves, 0)) order = nullptr;
+        const bool even = even_lists(g);
+        if (even || (order && needs_no_order(dkdv_kernel, wgs, waves, 0))) order = nullptr;
         hipError_t e = launch_bwd_prepare(true, out, dout, lse, delta, lse2, sel_idx, conn, order, g,
                                           D, BH, stream);
         if (e != hipSuccess) return e;
         auto run_dkdv = [&] {
             Geom gk = g;
-            gk.deal = key_deal(g.deal, 2 * g.n_tokens * D * 2, order != nullptr, g.add_dk != nullptr);
+            gk.deal = key_deal(g.deal, 2 * g.n_tokens * D * 2, order != nullptr, even);
             dkdv_kernel<<<dim3(wgs), dim3(64 * waves), 0, stream>>>(
                 (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
                 lse2, delta, conn, order, (uint16_t*)dk, (uint16_t*)dv, gk, sx);

@@ -756,6 +756,11 @@ private:
 // Runs body(key) with the row pieces that a wavefront of `rows` rows takes.  MIXED: the
 // kernel has the narrow form too (a kernel of its own: both forms in one took up to 3.5 %
 // longer where no wavefront is narrow).
+// `rows` is the same for all lanes of a wavefront, but not for all wavefronts of a workgroup: the
+// narrow one runs its own copy of the body, workgroup barriers included.  That is sound on this
+// hardware only, whose s_barrier counts the wavefronts that arrive, wherever they do, and only as
+// long as both copies pass the same barriers in the same order: the body must not have a barrier,
+// a return before one, or a trip count of a loop with one that depends on the key or on the rows.
 template <typename K> struct PieceKey {
     typedef K type;
 };
