@@ -857,6 +857,18 @@ static BwdSplit dkdv_split(const Geom& g, int64_t BKV)
         return {2, 2};
     return {BwdLimits<T, D>::MAX_WAVES, 1};
 }
+// dQ: its lists are all as long, so that it is split only while wavefronts have a SIMD to
+// themselves.  Whole backward, us, dQ unsplit | in two groups of pairs | in four groups
+// (blocks x tokens, attended blocks; one slice, white noise):
+//   bf16, head dim 32:  476 x 30, 13: 30.1 | 29.0 | 27.7      864 x 30, 13:  48.5 | 46.5 | 46.5
+//   bf16, head dim 64:  120 x 100, 13: 71.2 | 62.0 | 60.7     240 x 100, 17: 123 | 118 | 127
+//   bf16, head dim 128: 476 x 30, 13: 66.4 | 61.4 | -         1,000 x 30, 17: 137 | 120 | -
+//   fp32, head dim 32:  120 x 64, 13: 67.5 | 56.7 | 57.3      240 x 64, 17:  115 | 113 | 120
+//   fp32, head dim 64:  120 x 64, 13: 122 | 104 | 113         240 x 64, 17:  217 | 214 | 249
+// Blocks of one fp32 wavefront, up to 16 tokens, form no pairs, and rounds of 64 keys are too
+// long for few keys: 864 blocks of 16, head dim 32, 13 attended 62.2 | 76.4, 15 attended 7 % faster
+// in two groups; head dim 128, 480 blocks, 13 attended 124 | 133, 280, 15 attended 112 | 119, 17
+// attended as fast.
 template <typename T, int D>
 static BwdSplit dq_split(const Geom& g, int64_t BH)
 {
@@ -867,7 +879,9 @@ static BwdSplit dq_split(const Geom& g, int64_t BH)
     const int64_t waves = BH * g.n_blocks * single.chunks;
     const int64_t pieces = (g.n_select + 1 - g.list_only) * (int64_t)g.block_tokens / 32;
     if (waves <= FOUR && pieces >= 6) return {1, 4};
-    return waves <= TWO && pieces >= 5 ? BwdSplit{2, 2} : BwdSplit{BwdLimits<T, D>::MAX_WAVES, 1};
+    const bool lone = F32 && single.chunks == 1;
+    const int least = lone && D == 128 ? 8 : lone && D == 32 && waves > 512 ? 7 : 5;
+    return waves <= TWO && pieces >= least ? BwdSplit{2, 2} : BwdSplit{BwdLimits<T, D>::MAX_WAVES, 1};
 }
 template <typename T, int D, int SPLIT, bool MIXED = false>
 static auto dkdv_kernel(int waves)
