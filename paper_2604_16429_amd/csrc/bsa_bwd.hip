@@ -832,7 +832,9 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
 // (four groups of fp32 at head dim 128 do not fit LDS).  Lists of equal length, of the
 // local branch, n = 0 or most blocks selected, have no popular block to wait for and pay
 // only while SIMDs are idle: 4 x 24 x 128, all 24 attended, fp32, head dim 64 unsplit 598,
-// pairs 560; 16 x 24 x 128 1,060 and 1,099.  1,750 launches of 24 to 14,000 row
+// pairs 560; 16 x 24 x 128 1,060 and 1,099; 8 x 18 x 100, all, 1,152 row wavefronts in pairs, 406 and
+// 376, 16 x 40 x 30, 25 attended, 1,280 of them, 229 and 251; head dim 32, 16 x 12 x 128, 9 attended,
+// 1,536, 1.17 times as fast in pairs, 16 x 15 x 100, 13 attended, 1,920, 194 and 206.  1,750 launches of 24 to 14,000 row
 // wavefronts, smooth fields, noise, n = 0 and all blocks: 1.09 to 1.28 times as fast on
 // average by type and head dim, 5 of them slower by 2.5 to 5 %.
 struct BwdSplit {
@@ -845,15 +847,17 @@ static BwdSplit dkdv_split(const Geom& g, int64_t BKV)
     constexpr bool F32 = sizeof(T) == 4, WIDE = !F32 && D == 128;
     constexpr int64_t FOUR = WIDE ? 512 : !F32 ? 2048 : D < 128 ? 1408 : 0;
     constexpr int64_t TWO = WIDE ? 1024 : !F32 ? 4096 : D < 128 ? 8192 : 2048;
+    // the same for lists of equal length
+    constexpr int64_t EVEN_FOUR = FOUR / 3, EVEN_TWO = F32 && D == 32 ? 1700 : F32 && D == 64 ? 1200 : TWO / 4;
     const RowSplit single(g.block_tokens, 1, WaveTile<T>::ROWS);
     const RowSplit pairs(g.block_tokens, 2, WaveTile<T>::ROWS);
     const int64_t blocks = BKV * g.n_blocks, attended = g.n_select + 1 - g.list_only;
     const int64_t one = blocks * single.chunks, two = blocks * pairs.chunks * pairs.waves;
     const int64_t pieces = g.kv_group * attended * g.block_tokens / 32;
     const bool even = g.add_dk || attended == 1 || 2 * attended > g.n_blocks;
-    if (one <= (even ? FOUR / 3 : FOUR) && pieces >= (WIDE ? 12 + one / 64 : 6 + one / 128))
+    if (one <= (even ? EVEN_FOUR : FOUR) && pieces >= (WIDE ? 12 + one / 64 : 6 + one / 128))
         return {1, 4};
-    if (two <= (even ? TWO / 4 : TWO) && pieces >= (WIDE ? 8 + two / 128 : 6 + two / 512))
+    if (two <= (even ? EVEN_TWO : TWO) && pieces >= (WIDE ? 8 + two / 128 : 6 + two / 512))
         return {2, 2};
     return {BwdLimits<T, D>::MAX_WAVES, 1};
 }
