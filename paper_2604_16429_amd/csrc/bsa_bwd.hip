@@ -870,9 +870,10 @@ static BwdSplit dkdv_split(const Geom& g, int64_t BKV)
 //   fp32, head dim 32:  120 x 64, 13: 67.5 | 56.7 | 57.3      240 x 64, 17:  115 | 113 | 120
 //   fp32, head dim 64:  120 x 64, 13: 122 | 104 | 113         240 x 64, 17:  217 | 214 | 249
 // Blocks of one fp32 wavefront, up to 16 tokens, form no pairs, and rounds of 64 keys are too
-// long for few keys: 864 blocks of 16, head dim 32, 13 attended 62.2 | 76.4, 15 attended 7 % faster
-// in two groups; head dim 128, 480 blocks, 13 attended 124 | 133, 280, 15 attended 112 | 119, 17
-// attended as fast.
+// long for few keys once CUs have to take several workgroups (head dim 128: their LDS holds one):
+// 864 blocks of 16, head dim 32, 13 attended 62.2 | 76.4, 15 attended 7 % faster in two groups;
+// head dim 128, 480 blocks, 13 attended 124 | 133, 280, 15 attended 112 | 119, 17 attended as fast,
+// 240, 13 attended 86 | 78.
 template <typename T, int D>
 static BwdSplit dq_split(const Geom& g, int64_t BH)
 {
@@ -884,7 +885,7 @@ static BwdSplit dq_split(const Geom& g, int64_t BH)
     const int64_t pieces = (g.n_select + 1 - g.list_only) * (int64_t)g.block_tokens / 32;
     if (waves <= FOUR && pieces >= 6) return {1, 4};
     const bool lone = F32 && single.chunks == 1;
-    const int least = lone && D == 128 ? 8 : lone && D == 32 && waves > 512 ? 7 : 5;
+    const int least = lone && D == 128 && waves > 256 ? 8 : lone && D == 32 && waves > 512 ? 7 : 5;
     return waves <= TWO && pieces >= least ? BwdSplit{2, 2} : BwdSplit{BwdLimits<T, D>::MAX_WAVES, 1};
 }
 template <typename T, int D, int SPLIT, bool MIXED = false>
