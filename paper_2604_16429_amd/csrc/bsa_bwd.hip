@@ -829,14 +829,20 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
 //   fp32, head dim 64:   1 x 96 x 64, 13:    265 | 173 | 131    1 x 448 x 64, 13:  407 | 270 | 313
 //                        4 x 448 x 64, 13:   915 | 824 | 1,076
 //   fp32, head dim 128:  1 x 448 x 64, 13:   765 | 539 | -      4 x 448 x 64, 13: 1,788 | 1,770 | -
-// (four groups of fp32 at head dim 128 do not fit LDS).  Lists of equal length, of the
-// local branch, n = 0 or most blocks selected, have no popular block to wait for and pay
-// only while SIMDs are idle: 4 x 24 x 128, all 24 attended, fp32, head dim 64 unsplit 598,
-// pairs 560; 16 x 24 x 128 1,060 and 1,099; 8 x 18 x 100, all, 1,152 row wavefronts in pairs, 406 and
-// 376, 16 x 40 x 30, 25 attended, 1,280 of them, 229 and 251; head dim 32, 16 x 12 x 128, 9 attended,
-// 1,536, 1.17 times as fast in pairs, 16 x 15 x 100, 13 attended, 1,920, 194 and 206.  1,750 launches of 24 to 14,000 row
-// wavefronts, smooth fields, noise, n = 0 and all blocks: 1.09 to 1.28 times as fast on
-// average by type and head dim, 5 of them slower by 2.5 to 5 %.
+// (four groups of fp32 at head dim 128 do not fit LDS).  Lists of nearly equal length, of the
+// local branch, n = 0 or half of the blocks selected and more, have hardly a popular block to wait
+// for and pay only while SIMDs are idle: 4 x 24 x 128, all 24 attended, fp32, head dim 64 unsplit
+// 598, pairs 560; 16 x 24 x 128 1,060 and 1,099.  With three quarters attended and more the bound
+// of fp32 is lower still: head dim 64, 8 x 18 x 100, all attended, 1,152 row wavefronts in pairs, 438
+// and 376, 16 x 15 x 100, 13 attended, 1,920 of them, 342 and 354 (8 attended 275 and 244); head dim
+// 32, 16 x 12 x 128, 9 attended, 1,536, 1.17 times as fast in pairs, 16 x 15 x 100, 13 attended, 191
+// and 206; head dim 128, where a workgroup takes the LDS of a CU, blocks of one wavefront: 8 x 32
+// x 16, 256, 165 and 97, 12 x 28 x 16, 336, 152 and 165 (12 x 24 x 16, 48 heads, 17 attended, 365
+// and 330).
+// 1,750 launches of 24 to 14,000 row wavefronts, smooth fields, noise, n = 0 and all blocks: 1.09
+// to 1.28 times as fast on average by type and head dim.  Of 560 others, up to 9,000, 14 were
+// slower than unsplit by 2 to 10 %; the two groups and four that the rule leaves out gain up to
+// twice in single cases, 3 to 10 % on average (profiles/backward_splits.md).
 struct BwdSplit {
     int max_waves, groups;
 };
@@ -847,17 +853,19 @@ static BwdSplit dkdv_split(const Geom& g, int64_t BKV)
     constexpr bool F32 = sizeof(T) == 4, WIDE = !F32 && D == 128;
     constexpr int64_t FOUR = WIDE ? 512 : !F32 ? 2048 : D < 128 ? 1408 : 0;
     constexpr int64_t TWO = WIDE ? 1024 : !F32 ? 4096 : D < 128 ? 8192 : 2048;
-    // the same for lists of equal length
-    constexpr int64_t EVEN_FOUR = FOUR / 3, EVEN_TWO = F32 && D == 32 ? 1700 : F32 && D == 64 ? 1200 : TWO / 4;
+    // two groups, lists of equal length (fp32, head dim 128: a workgroup to each CU)
+    constexpr int64_t EQUAL_TWO = !F32 ? TWO / 4 : D == 32 ? 1700 : 1200;
     const RowSplit single(g.block_tokens, 1, WaveTile<T>::ROWS);
     const RowSplit pairs(g.block_tokens, 2, WaveTile<T>::ROWS);
     const int64_t blocks = BKV * g.n_blocks, attended = g.n_select + 1 - g.list_only;
     const int64_t one = blocks * single.chunks, two = blocks * pairs.chunks * pairs.waves;
     const int64_t pieces = g.kv_group * attended * g.block_tokens / 32;
     const bool even = g.add_dk || attended == 1 || 2 * attended > g.n_blocks;
-    if (one <= (even ? EVEN_FOUR : FOUR) && pieces >= (WIDE ? 12 + one / 64 : 6 + one / 128))
+    const bool equal = g.add_dk || attended == 1 || 4 * attended > 3 * g.n_blocks;
+    const int64_t equal_two = F32 && D == 128 ? 256 * pairs.waves : EQUAL_TWO;
+    if (one <= (even ? FOUR / 3 : FOUR) && pieces >= (WIDE ? 12 + one / 64 : 6 + one / 128))
         return {1, 4};
-    if (two <= (even ? EVEN_TWO : TWO) && pieces >= (WIDE ? 8 + two / 128 : 6 + two / 512))
+    if (two <= (equal ? equal_two : even ? TWO / 4 : TWO) && pieces >= (WIDE ? 8 + two / 128 : 6 + two / 512))
         return {2, 2};
     return {BwdLimits<T, D>::MAX_WAVES, 1};
 }
