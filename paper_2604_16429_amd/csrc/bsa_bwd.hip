@@ -946,7 +946,8 @@ static hipError_t launch_bwd_t(const void* q, const void* k, const void* v, cons
                      : rows_kv.narrow       ? dkdv_kernel<T, D, 1, sizeof(T) == 2>(rows_kv.waves)
                                             : dkdv_kernel<T, D, 1>(rows_kv.waves);
     const bool even = even_lists(g);
-    if (even || (order && needs_no_order(kernel_kv, BKV * wgs_kv, waves_kv, lds_kv))) order = nullptr;
+    if (even || (order && needs_no_order(kernel_kv, BKV * wgs_kv, waves_kv, lds_kv,
+                                         short_lists(g, D, sizeof(T) == 4)))) order = nullptr;
     hipError_t e = launch_bwd_prepare(sizeof(T) == 2, out, dout, lse, delta, lse2, sel_idx, conn,
                                       order, g, D, BH, stream);
     if (e != hipSuccess) return e;

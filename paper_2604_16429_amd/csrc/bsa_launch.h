@@ -95,13 +95,16 @@ hipError_t launch_bwd_prepare(bool is_bf16, const void* out, const void* dout, c
 // order of its key blocks: that takes a launch of 4 to 7 us.  How many workgroups run at once
 // is the kernel's matter: LDS or registers leave several forms one wavefront per SIMD or half
 // of one (the runtime answers in 0.13 us).  With a third more the last ones start where short
-// lists have ended.  Whole backward, us, ordered | not (wavefronts, room):
+// lists have ended, which is soon where all lists are short.  Whole backward, us, ordered | not
+// (wavefronts, room):
 //   * all at once: 32 blocks of 100 tokens, 4 slices, head dim 32 37.0 | 31.6, 64 46.0 | 41.0; 72
 //     of 64, 4 slices 38.5 | 36.6; 128 of 64, 4 slices 73.1 | 61.7; head dim 128, 128 of 128 (1,024)
 //     122 | 118; fp32, 128 of 16, 2 slices (512) 95 | 91.
-//   * up to a third more: head dim 32, 128 of 24, 16 slices (2,048, 1,536) 58.4 | 55.2, fp32 128 of
-//     16 92 | 82; head dim 64, 256 of 48, 4 slices 116 | 107, fp32 128 of 16, 7 slices (896, 768)
-//     70.7 | 66.2, 8 slices (1,024) 102 | 105.
+//   * up to a third more, short lists: head dim 32, 128 of 24, 16 slices (2,048, 1,536) 58.4 | 55.2,
+//     fp32 128 of 16 92 | 82; head dim 64, 256 of 48, 4 slices 116 | 107, fp32 128 of 16, 7 slices,
+//     5 attended (896, 768) 70.7 | 66.2.  Longer ones: fp32 128 of 16, 8 slices, 13 attended (1,024,
+//     768) 102 | 105, 128 of 32, 7 attended (2,048, 1,536) 144 | 154; head dim 128, dK/dV of 50 of 240,
+//     3 slices, 17 attended (1,200, 1,024) 235 | 255.
 //   * half as many more and beyond: head dim 128, 192 of 128 (1,536, 1,024) 155 | 168, 4 heads on 1
 //     400 | 458, 192 of 64 117 | 139, 128 of 64, 8 slices (2,048) 226 | 265; fp32 128 of 64, 2 slices
 //     323 | 389, 192 of 16, 8 slices (1,536, 512) 300 | 386; head dim 64, fp32 128 of 64 (2,048,
@@ -110,21 +113,29 @@ hipError_t launch_bwd_prepare(bool is_bf16, const void* out, const void* dout, c
 //   * more than two wavefronts per SIMD, up to 4,096: 36 of 128, 4 slices 56.7 | 63.4, 288 of 64 in
 //     fp32 195 | 229, 72 of 64, 4 slices, 123 | 121.
 constexpr int64_t kUnorderedWaves = 2048;
-inline bool needs_no_order(int64_t workgroups, int waves, int per_cu)
+inline bool needs_no_order(int64_t workgroups, int waves, int per_cu, bool short_lists)
 {
-    return workgroups * waves <= kUnorderedWaves && 3 * workgroups <= (int64_t)4 * 256 * per_cu;
+    return workgroups * waves <= kUnorderedWaves &&
+           (short_lists ? 3 * workgroups <= (int64_t)4 * 256 * per_cu : workgroups <= (int64_t)256 * per_cu);
+}
+// In pieces of 32 rows, which take twice as long in fp32 and in proportion to the head dim.
+inline bool short_lists(const Geom& g, int D, bool is_f32)
+{
+    return (int64_t)g.kv_group * (g.n_select + 1 - g.list_only) * g.block_tokens * D * (is_f32 ? 2 : 1) <=
+           24 * 32 * 32;
 }
 // Lists of one length need none at all: the local branch's, and without selected blocks (fp32, 180
 // blocks of 30, 4 slices, head dim 128 59.9 | 54.7).
 inline bool even_lists(const Geom& g) { return g.add_dk || g.n_select == 0; }
 template <class K>
-inline bool needs_no_order(K kernel, int64_t workgroups, int waves, size_t dynamic_lds)
+inline bool needs_no_order(K kernel, int64_t workgroups, int waves, size_t dynamic_lds,
+                           bool short_lists)
 {
     int per_cu = 0;
-    return needs_no_order(workgroups, waves, 8) &&
+    return needs_no_order(workgroups, waves, 8, short_lists) &&
            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, 64 * waves,
                                                         dynamic_lds) == hipSuccess &&
-           needs_no_order(workgroups, waves, per_cu);
+           needs_no_order(workgroups, waves, per_cu, short_lists);
 }
 
 // Backward with the selection fixed, any tile shape / head dim in {32, 64, 128} /

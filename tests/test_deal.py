@@ -26,9 +26,9 @@ extern "C" void key_deal_of(int64_t slice_bytes, int block_tokens, int ordered, 
     out[0] = d.whole_slices;
     out[1] = d.run_log2;
 }
-extern "C" int no_order(int64_t workgroups, int waves, int per_cu)
+extern "C" int no_order(int64_t workgroups, int waves, int per_cu, int short_lists)
 {
-    return needs_no_order(workgroups, waves, per_cu);
+    return needs_no_order(workgroups, waves, per_cu, short_lists);
 }
 extern "C" void map_all(int whole, int run_log2, uint32_t blocks, uint32_t heads,
                         uint32_t chunks, uint32_t n_units, uint32_t* out)
@@ -50,7 +50,7 @@ def deal(tmp_path_factory):
                     "--offload-host-only", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC,
                     "-I", os.path.join(ROOT, "include"), str(src), "-o", str(lib)], check=True)
     lib = ctypes.CDLL(str(lib))
-    lib.no_order.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    lib.no_order.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     lib.deal_of.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
     lib.key_deal_of.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3 + [ctypes.c_void_p]
     return lib
@@ -139,10 +139,12 @@ def test_deal_of_key_blocks(deal, megabytes, block_tokens):
 
 @pytest.mark.parametrize("waves,per_cu", [(1, 2), (2, 1), (4, 1), (2, 3), (4, 2), (8, 1), (3, 1), (2, 8)])
 def test_launches_without_an_order(deal, waves, per_cu):
-    """dK/dV goes without an order only where 256 CUs that hold per_cu workgroups each take all but a
-    quarter of the launch at once, and at two wavefronts per SIMD at most."""
-    most = min(256 * per_cu * 4 // 3, 2048 // waves)
-    assert deal.no_order(most, waves, per_cu) and not deal.no_order(most + 1, waves, per_cu)
+    """dK/dV goes without an order only where 256 CUs that hold per_cu workgroups each take the launch
+    at once, or all but a quarter of it where lists are short, and at two wavefronts per SIMD at most."""
+    for short, room in ((0, 256 * per_cu), (1, 256 * per_cu * 4 // 3)):
+        most = min(room, 2048 // waves)
+        assert deal.no_order(most, waves, per_cu, short)
+        assert not deal.no_order(most + 1, waves, per_cu, short)
 
 
 def test_whole_slices(deal):
