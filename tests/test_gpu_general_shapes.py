@@ -383,28 +383,64 @@ def test_backward_without_an_order(G, oracle, dtype, H, W, bh, bw, D, n, batch):
         assert max(np.abs(x - r[0]).max(), np.abs(y - r[0]).max()) <= (1e-4 if dtype == "fp32" else 1e-2) * np.abs(r).max()
 
 
-@pytest.mark.parametrize("dtype,H,W,bh,bw,D,slices", [
-    ("bf16", 272, 512, 16, 16, 64, 9),     # m = 544: eight runs of 64 blocks and 32 more per slice
-    ("bf16", 512, 132, 8, 12, 128, 8),     # general kernels, m = 704: runs of 128
-    ("bf16", 264, 256, 8, 16, 128, 8),     # m = 528: runs of 128, 8 slices in 33 rounds
-    ("fp32", 330, 410, 10, 10, 32, 9),     # m = 1,353
+def tokens_of_blocks(cfg):
+    """int64 [m, b]: the tokens of every block."""
+    i = torch.arange(cfg.n_tokens, device="cuda")
+    i = i.view(cfg.grid_h // cfg.block_h, cfg.block_h, cfg.grid_w // cfg.block_w, cfg.block_w)
+    return i.permute(0, 2, 1, 3).reshape(cfg.n_blocks, cfg.block_tokens)
+
+
+def block_by_block(cfg, q, k, v, dout, blocks, i):
+    """Attention of query block i of one slice (q [N, D] and so on) over the given blocks in 64
+    bits: out, log-sum-exp, dq and the block's share of dk and dv, [len(blocks), b, D] each."""
+    tok = tokens_of_blocks(cfg)
+    rows, keys = tok[i], tok[blocks].reshape(-1)
+    qd, kd, vd, gd = (x.double() for x in (q[rows], k[keys], v[keys], dout[rows]))
+    scale = cfg.head_dim ** -0.5
+    s = qd @ kd.T * scale
+    lse = torch.logsumexp(s, dim=1)
+    p = torch.exp(s - lse[:, None])
+    out = p @ vd
+    ds = p * (gd @ vd.T - (gd * out).sum(1, keepdim=True)) * scale
+    shape = (len(blocks), cfg.block_tokens, cfg.head_dim)
+    return out, lse, ds @ kd, (ds.T @ qd).reshape(shape), (p.T @ gd).reshape(shape)
+
+
+def close(name, x, ref, dtype, fp32_tol):
+    big = float(ref.abs().max())
+    tol = fp32_tol * big if dtype == "fp32" else 1e-2 * max(1.0, big)
+    err = float((x.double() - ref).abs().max())
+    assert err <= tol, f"{name}: max error {err} > {tol}"
+
+
+@pytest.mark.parametrize("dtype,H,W,bh,bw,D,heads,kv_heads", [
+    ("bf16", 272, 512, 16, 16, 64, 9, 9),     # m = 544: eight runs of 64 blocks and 32 more per slice
+    ("bf16", 272, 512, 16, 16, 64, 6, 2),     # runs over three heads, the tail 192 blocks
+    ("bf16", 512, 132, 8, 12, 128, 8, 8),     # general kernels, m = 704: runs of 128
+    ("bf16", 264, 256, 8, 16, 128, 8, 8),     # m = 528: runs of 128, 8 slices in 33 rounds
+    ("bf16", 264, 256, 8, 16, 128, 20, 10),   # two slices more than are dealt whole
+    ("fp32", 330, 410, 10, 10, 32, 9, 9),     # m = 1,353
+    ("fp32", 330, 410, 10, 10, 32, 6, 3),     # and row chunks, 4,059 blocks of two heads each
 ])
-def test_large_slices_in_runs(G, dtype, H, W, bh, bw, D, slices):
-    """Slices of more than 32 MB of keys and values, which all XCDs share in runs of blocks:
-    every row is written, with the bits that a launch of its slice alone gives it (launches
-    of so many rows are not split, whatever the number of slices)."""
+def test_large_slices_in_runs(G, dtype, H, W, bh, bw, D, heads, kv_heads):
+    """Slices of more than 32 MB of keys and values, whose query blocks all XCDs share in runs (and
+    the key blocks of what is no multiple of eight slices): every row is written, with the bits
+    that a launch of its slice alone gives it (launches of so many rows are not split, whatever
+    the number of slices), and some blocks of the first and the last slice against 64 bits."""
     import paper_2604_16429_amd as bsa
     from paper_2604_16429_amd import binding
     element = torch.bfloat16 if dtype == "bf16" else torch.float32
-    one, many = (shape_ns(e, 1, H, W, bh, bw, D, 3, dtype) for e in (1, slices))
+    group = heads // kv_heads
+    one = shape_ns(1, group, H, W, bh, bw, D, 3, dtype, 1)
+    many = shape_ns(1, heads, H, W, bh, bw, D, 3, dtype, kv_heads)
     gen = torch.Generator(device="cuda").manual_seed(D)
-    q, k, v, dout = (torch.randn((slices, 1, H * W, D), generator=gen, device="cuda").to(element)
-                     for _ in range(4))
+    q, k, v, dout = (torch.randn((1, h, H * W, D), generator=gen, device="cuda").to(element)
+                     for h in (heads, kv_heads, kv_heads, heads))
     idx = torch.from_numpy(random_selection(many, 4)).cuda()
 
     def run(cfg, q, k, v, dout, idx):
         p = G.params_of(cfg)
-        out, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+        out, dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, q, k, v))
         lse = torch.full(q.shape[:3], float("nan"), device="cuda")
         ws = torch.empty(bsa.mosaic_bsa_workspace_bytes(p, binding.OP_BWD), dtype=torch.uint8,
                          device="cuda")
@@ -414,9 +450,82 @@ def test_large_slices_in_runs(G, dtype, H, W, bh, bw, D, slices):
 
     got = run(many, q, k, v, dout, idx)
     assert all(bool(torch.isfinite(x).all()) for x in got)
-    for e in (0, slices - 1):
-        for x, y in zip(got, run(one, *(t[e:e + 1] for t in (q, k, v, dout, idx)))):
-            assert torch.equal(x[e:e + 1], y)
+    out, lse, dq, dk, dv = got
+    tok = tokens_of_blocks(many)
+    for u in (0, kv_heads - 1):
+        of_q, of_kv = slice(u * group, (u + 1) * group), slice(u, u + 1)
+        alone = run(one, *(x[:, s].contiguous() for x, s in
+                           ((q, of_q), (k, of_kv), (v, of_kv), (dout, of_q), (idx, of_q))))
+        for x, y, s in zip(got, alone, (of_q, of_q, of_q, of_kv, of_kv)):
+            assert torch.equal(x[:, s], y)
+        for j in (0, many.n_blocks // 2, many.n_blocks - 1):
+            sum_k = sum_v = 0.0
+            for a in range(u * group, (u + 1) * group):
+                connected = torch.nonzero((idx[0, a] == j).any(1)).flatten().tolist() + [j]
+                for i in connected:
+                    blocks = [i] + idx[0, a, i].tolist()
+                    o, l, g_q, g_k, g_v = block_by_block(many, q[0, a], k[0, u], v[0, u], dout[0, a],
+                                                         blocks, i)
+                    sum_k, sum_v = sum_k + g_k[blocks.index(j)], sum_v + g_v[blocks.index(j)]
+                    close("out", out[0, a, tok[i]], o, dtype, 1e-5)
+                    close("lse", lse[0, a, tok[i]], l, "fp32", 1e-5 if dtype == "fp32" else 1e-3)
+                    close("dq", dq[0, a, tok[i]], g_q, dtype, 1e-4)
+            close("dk", dk[0, u, tok[j]], sum_k, dtype, 1e-4)
+            close("dv", dv[0, u, tok[j]], sum_v, dtype, 1e-4)
+
+
+@pytest.mark.parametrize("dtype,H,W,bh,bw,D,heads,kv_heads", [
+    ("bf16", 272, 512, 16, 16, 64, 9, 9),
+    ("bf16", 272, 512, 16, 16, 64, 4, 2),     # two jobs in runs over two heads
+    ("fp32", 330, 410, 10, 10, 32, 9, 9),
+])
+def test_large_slices_three_branch(G, dtype, H, W, bh, bw, D, heads, kv_heads):
+    """The same for the three branches, forward and backward: both attention branches of a launch
+    in runs, the local branch's key blocks as well."""
+    import paper_2604_16429_amd as bsa
+    element = torch.bfloat16 if dtype == "bf16" else torch.float32
+    group, lh, lw, n = heads // kv_heads, 1, 2 if W // bw % 2 == 0 else 1, 3
+    one = shape_ns(1, group, H, W, bh, bw, D, n, dtype, 1)
+    many = shape_ns(1, heads, H, W, bh, bw, D, n, dtype, kv_heads)
+    gen = torch.Generator(device="cuda").manual_seed(D + 1)
+    q, k, v, dout = (torch.randn((1, h, H * W, D), generator=gen, device="cuda").to(element)
+                     for h in (heads, kv_heads, kv_heads, heads))
+    gates = torch.rand((1, heads, H * W, 3), generator=gen, device="cuda")
+
+    def run(cfg, q, k, v, gates, dout):
+        p = G.params_of(cfg)
+        out, dq, dk, dv, dgates = (torch.full_like(x, float("nan")) for x in (q, q, k, v, gates))
+        idx = torch.empty((1, cfg.heads, cfg.n_blocks, n), dtype=torch.int32, device="cuda")
+        ws, ws_b = (torch.empty(size(p, lh, lw), dtype=torch.uint8, device="cuda") for size in (
+            bsa.mosaic_bsa_three_branch_workspace_bytes,
+            bsa.mosaic_bsa_three_branch_bwd_workspace_bytes))
+        bsa.mosaic_bsa_fwd_three_branch(p, lh, lw, q, k, v, gates, out, idx, ws)
+        bsa.mosaic_bsa_bwd_three_branch(p, lh, lw, q, k, v, gates, dout, idx, ws, dq, dk, dv,
+                                        dgates, ws_b)
+        return idx, out, dq, dk, dv, dgates
+
+    got = run(many, q, k, v, gates, dout)
+    idx, out = got[:2]
+    assert all(bool(torch.isfinite(x).all()) for x in got[1:])
+    tok = tokens_of_blocks(many)
+    for u in (0, kv_heads - 1):
+        of_q, of_kv = slice(u * group, (u + 1) * group), slice(u, u + 1)
+        alone = run(one, *(x[:, s].contiguous() for x, s in
+                           ((q, of_q), (k, of_kv), (v, of_kv), (gates, of_q), (dout, of_q))))
+        for x, y, s in zip(got, alone, (of_q, of_q, of_q, of_kv, of_kv, of_q)):
+            assert torch.equal(x[:, s], y)
+        kbar, vbar = (x[0, u][tok].double().mean(1) for x in (k, v))
+        for a in range(u * group, (u + 1) * group):
+            for i in (0, many.n_blocks // 3, many.n_blocks - 1):
+                w = torch.softmax(kbar @ q[0, a, tok[i]].double().mean(0) * D ** -0.5, dim=0)
+                fg = block_by_block(many, q[0, a], k[0, u], v[0, u], dout[0, a], idx[0, a, i].tolist(), i)
+                local = block_by_block(many, q[0, a], k[0, u], v[0, u], dout[0, a],
+                                       [i // lw * lw + x for x in range(lw)], i)
+                parts = torch.stack([(w @ vbar).expand_as(fg[0]), fg[0], local[0]], dim=2)
+                ref = (parts * gates[0, a, tok[i]].double()[:, None]).sum(2)
+                close("out", out[0, a, tok[i]], ref, dtype, 1e-5)
+                close("dgates", got[5][0, a, tok[i]],
+                      (parts * dout[0, a, tok[i]].double()[:, :, None]).sum(1), dtype, 1e-4)
 
 
 @pytest.mark.parametrize("D", [64, 128])
