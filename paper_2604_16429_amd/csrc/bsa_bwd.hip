@@ -840,9 +840,10 @@ void bwd_generic_dkdv(const T* __restrict__ q, const T* __restrict__ k, const T*
 // x 16, 256, 165 and 97, 12 x 28 x 16, 336, 152 and 165 (12 x 24 x 16, 48 heads, 17 attended, 365
 // and 330).
 // 1,750 launches of 24 to 14,000 row wavefronts, smooth fields, noise, n = 0 and all blocks: 1.09
-// to 1.28 times as fast on average by type and head dim.  Of 560 others, up to 9,000, 14 were
-// slower than unsplit by 2 to 10 %; the two groups and four that the rule leaves out gain up to
-// twice in single cases, 3 to 10 % on average (profiles/backward_splits.md).
+// to 1.28 times as fast on average by type and head dim.  Of 600 others, up to 9,000, five were
+// slower than unsplit by 2 to 11 %; what the rule leaves out gains up to twice in single cases, 4 to
+// 10 % on average.  The terms a + w / c are straight lines between the launches that gain and
+// those that lose: few wavefronts gain from short lists already, a full chip from long ones only.
 struct BwdSplit {
     int max_waves, groups;
 };

@@ -1201,8 +1201,8 @@ bool bwd_mfma_supported(bool is_bf16, const Geom& g, int D)
 // (four groups at head dim 128 take 155 KB of LDS beside V; built, they spilled and were no faster
 // than two).  Lists of equal length (see there) are
 // split while SIMDs are idle.  367 launches of 48 to 12,288 row wavefronts, smooth fields,
-// noise, n = 0 and all blocks: 1.18 (head dim 64) and 1.20 times as fast on average, three
-// of them slower by 2 to 5 %.
+// noise, n = 0 and all blocks: 1.18 (head dim 64) and 1.20 times as fast on average; of 200
+// others, up to 9,000, five were slower than unsplit by 2 to 9 %.  The terms a + w / c: see there.
 struct DkdvSplit {
     int waves, groups;
 };

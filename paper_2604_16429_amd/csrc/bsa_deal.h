@@ -25,11 +25,12 @@
 // 18.2 | 19.3 | 17.6; 3 x 288, 12 52.7 | 53.6 | 50.3; 3 x 450, 12 87.4 | 81.8 | 76.4; 7 x 450, 14
 // 107 | 97 | 92; head dim 128: 4 x 4,050, 16 2,565 | 1,902 | 1,765.
 // 16 slices, dealt whole | in runs: 4,050 of 256 (265 MB) 20,440 | 19,190, at head dim 128
-// 22,980 | 22,330; 2,025 of 128 (66 MB) 1,528 | 1,458; 3,422 (112 MB) 2,429 | 2,376; 1,800 of 64
-// at head dim 128 (59 MB) 1,853 | 1,872; 32 slices of 450 of 64 (7 MB) 1,257 | 1,287; 72 of 384 of
-// 128 (13 MB) 11,700 | 11,930.  Just above 32 MB it is 2 % either way: 8 of 1,056 of 128 (35 MB) 364 | 368; 16 of 1,152 (38 MB) 797 | 797, 32 heads on 8
-// 1,586 | 1,549; 16 of 600 of 256 (39 MB) 1,467 | 1,458; at head dim 128 16 of 1,200 of 64 (39 MB) 583 |
-// 594, of 600 of 128 835 | 823.
+// 22,980 | 22,330; 2,025 of 128 (66 MB) 1,528 | 1,458; 3,422 (112 MB) 2,429 | 2,376; 1,800 of
+// 64 at head dim 128 (59 MB) 1,853 | 1,872; 32 slices of 450 of 64 (7 MB) 1,257 | 1,287; 72 of
+// 384 of 128 (13 MB) 11,700 | 11,930.  Just above 32 MB it is 2 % either way: 8 of 1,056 of
+// 128 (35 MB) 364 | 368; 16 of 1,152 (38 MB) 797 | 797, 32 heads on 8 1,586 | 1,549; 16 of 600
+// of 256 (39 MB) 1,467 | 1,458; at head dim 128 16 of 1,200 of 64 (39 MB) 583 | 594, of 600 of
+// 128 835 | 823.
 #pragma once
 
 #include <hip/hip_runtime.h>
