@@ -410,7 +410,8 @@ template <typename T, int D, int NL, int SPLIT> struct BwdBounds {
     static constexpr int THREADS = SPLIT > 1 ? 64 * SPLIT * NL
                                    : NL == 4 ? 64 * L::MAX_WAVES : NL == 1 ? 64 : 192;
     static constexpr int DQ = SPLIT > 1 || NL == 1 ? 1 : D == 128 && NL > 2 ? 2 : L::PER_SIMD;
-    static constexpr int SPLIT_DKDV = D == 32 || (D == 64 && (!F32 || (NL == 2 && SPLIT == 2))) ? 2 : 1;
+    static constexpr int SPLIT_DKDV =
+        D == 32 || (D == 64 && (!F32 || (NL == 2 && SPLIT == 2))) ? 2 : 1;
     static constexpr int DKDV = SPLIT > 1 ? SPLIT_DKDV
                                 : NL == 4 ? L::PER_SIMD : NL == 2 && D < 128 ? 2 : 1;
 };
@@ -866,7 +867,8 @@ static BwdSplit dkdv_split(const Geom& g, int64_t BKV)
     const int64_t equal_two = F32 && D == 128 ? 256 * pairs.waves : EQUAL_TWO;
     if (one <= (even ? FOUR / 3 : FOUR) && pieces >= (WIDE ? 12 + one / 64 : 6 + one / 128))
         return {1, 4};
-    if (two <= (equal ? equal_two : even ? TWO / 4 : TWO) && pieces >= (WIDE ? 8 + two / 128 : 6 + two / 512))
+    if (two <= (equal ? equal_two : even ? TWO / 4 : TWO) &&
+        pieces >= (WIDE ? 8 + two / 128 : 6 + two / 512))
         return {2, 2};
     return {BwdLimits<T, D>::MAX_WAVES, 1};
 }

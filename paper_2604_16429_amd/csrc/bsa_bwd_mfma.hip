@@ -1236,7 +1236,8 @@ hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const vo
         const int waves = split.waves * split.groups;
         const uint32_t wgs = sx * (unsigned)(g.n_blocks * (nw / split.waves));
         const bool even = even_lists(g);
-        if (even || (order && needs_no_order(dkdv_kernel, wgs, waves, 0, short_lists(g, D, false)))) order = nullptr;
+        if (even || (order && needs_no_order(dkdv_kernel, wgs, waves, 0, short_lists(g, D, false))))
+            order = nullptr;
         hipError_t e = launch_bwd_prepare(true, out, dout, lse, delta, lse2, sel_idx, conn, order, g,
                                           D, BH, stream);
         if (e != hipSuccess) return e;

@@ -78,7 +78,8 @@ __host__ __device__ __forceinline__ void map_unit(Deal deal, uint32_t w, uint32_
     head = 0;
     item = r;
     if (heads > 1) {                                 // the heads of a block side by side
-        const uint32_t of_block = heads * chunks, block = r / of_block, in_block = r - block * of_block;
+        const uint32_t of_block = heads * chunks, block = r / of_block;
+        const uint32_t in_block = r - block * of_block;
         head = in_block / chunks;
         item = block * chunks + (in_block - head * chunks);
     }

@@ -103,8 +103,8 @@ hipError_t launch_bwd_prepare(bool is_bf16, const void* out, const void* dout, c
 //   * up to a third more, short lists: head dim 32, 128 of 24, 16 slices (2,048, 1,536) 58.4 | 55.2,
 //     fp32 128 of 16 92 | 82; head dim 64, 256 of 48, 4 slices 116 | 107, fp32 128 of 16, 7 slices,
 //     5 attended (896, 768) 70.7 | 66.2.  Longer ones: fp32 128 of 16, 8 slices, 13 attended (1,024,
-//     768) 102 | 105, 128 of 32, 7 attended (2,048, 1,536) 144 | 154; head dim 128, dK/dV of 50 of 240,
-//     3 slices, 17 attended (1,200, 1,024) 235 | 255.
+//     768) 102 | 105, 128 of 32, 7 attended (2,048, 1,536) 144 | 154; head dim 128, dK/dV of 50
+//     of 240, 3 slices, 17 attended (1,200, 1,024) 235 | 255.
 //   * half as many more and beyond: head dim 128, 192 of 128 (1,536, 1,024) 155 | 168, 4 heads on 1
 //     400 | 458, 192 of 64 117 | 139, 128 of 64, 8 slices (2,048) 226 | 265; fp32 128 of 64, 2 slices
 //     323 | 389, 192 of 16, 8 slices (1,536, 512) 300 | 386; head dim 64, fp32 128 of 64 (2,048,
@@ -115,14 +115,15 @@ hipError_t launch_bwd_prepare(bool is_bf16, const void* out, const void* dout, c
 constexpr int64_t kUnorderedWaves = 2048;
 inline bool needs_no_order(int64_t workgroups, int waves, int per_cu, bool short_lists)
 {
+    const int64_t room = (int64_t)256 * per_cu;
     return workgroups * waves <= kUnorderedWaves &&
-           (short_lists ? 3 * workgroups <= (int64_t)4 * 256 * per_cu : workgroups <= (int64_t)256 * per_cu);
+           (short_lists ? 3 * workgroups <= 4 * room : workgroups <= room);
 }
 // In pieces of 32 rows, which take twice as long in fp32 and in proportion to the head dim.
 inline bool short_lists(const Geom& g, int D, bool is_f32)
 {
-    return (int64_t)g.kv_group * (g.n_select + 1 - g.list_only) * g.block_tokens * D * (is_f32 ? 2 : 1) <=
-           24 * 32 * 32;
+    const int64_t rows = (int64_t)g.kv_group * (g.n_select + 1 - g.list_only) * g.block_tokens;
+    return rows * D * (is_f32 ? 2 : 1) <= 24 * 32 * 32;
 }
 // Lists of one length need none at all: the local branch's, and without selected blocks (fp32, 180
 // blocks of 30, 4 slices, head dim 128 59.9 | 54.7).
@@ -132,10 +133,13 @@ inline bool needs_no_order(K kernel, int64_t workgroups, int waves, size_t dynam
                            bool short_lists)
 {
     int per_cu = 0;
-    return needs_no_order(workgroups, waves, 8, short_lists) &&
-           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, 64 * waves,
-                                                        dynamic_lds) == hipSuccess &&
-           needs_no_order(workgroups, waves, per_cu, short_lists);
+    if (!needs_no_order(workgroups, waves, 8, short_lists)) return false;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, 64 * waves,
+                                                     dynamic_lds) != hipSuccess) {
+        (void)hipGetLastError();                      // (not the launch's)
+        return false;
+    }
+    return needs_no_order(workgroups, waves, per_cu, short_lists);
 }
 
 // Backward with the selection fixed, any tile shape / head dim in {32, 64, 128} /

@@ -20,7 +20,8 @@ extern "C" void deal_of(int64_t slice_bytes, int block_tokens, int32_t* out)
     out[0] = d.whole_slices;
     out[1] = d.run_log2;
 }
-extern "C" void key_deal_of(int64_t slice_bytes, int block_tokens, int ordered, int even, int32_t* out)
+extern "C" void key_deal_of(int64_t slice_bytes, int block_tokens, int ordered, int even,
+                            int32_t* out)
 {
     const Deal d = key_deal(xcd_deal(slice_bytes, block_tokens), slice_bytes, ordered, even);
     out[0] = d.whole_slices;
@@ -68,8 +69,8 @@ def test_every_item_once(deal, seed):
     rng = random.Random(seed)
     for _ in range(300):
         whole, run_log2 = rng.randint(0, 1), rng.randint(0, 7)
-        blocks, heads, n_units = rng.randint(1, 200), rng.choice([1, 1, 2, 3, 4, 7]), rng.randint(1, 20)
-        chunks = rng.choice([1, 1, 2, 3, 4, 5, 8])
+        blocks, n_units = rng.randint(1, 200), rng.randint(1, 20)
+        heads, chunks = rng.choice([1, 1, 2, 3, 4, 7]), rng.choice([1, 1, 2, 3, 4, 5, 8])
         m = mapped(deal, whole, run_log2, blocks, heads, chunks, n_units)
         per_head = blocks * chunks
         assert m[:, 1].max() < heads and m[:, 2].max() < per_head
@@ -137,10 +138,12 @@ def test_deal_of_key_blocks(deal, megabytes, block_tokens):
     assert d[3].tolist() == [int(megabytes <= 32), 0]
 
 
-@pytest.mark.parametrize("waves,per_cu", [(1, 2), (2, 1), (4, 1), (2, 3), (4, 2), (8, 1), (3, 1), (2, 8)])
+@pytest.mark.parametrize("waves,per_cu", [
+    (1, 2), (2, 1), (4, 1), (2, 3), (4, 2), (8, 1), (3, 1), (2, 8)])
 def test_launches_without_an_order(deal, waves, per_cu):
     """dK/dV goes without an order only where 256 CUs that hold per_cu workgroups each take the launch
-    at once, or all but a quarter of it where lists are short, and at two wavefronts per SIMD at most."""
+    at once, or all but a quarter of it where lists are short, and at two wavefronts per SIMD at
+    most."""
     for short, room in ((0, 256 * per_cu), (1, 256 * per_cu * 4 // 3)):
         most = min(room, 2048 // waves)
         assert deal.no_order(most, waves, per_cu, short)
